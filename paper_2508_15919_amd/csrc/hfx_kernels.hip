@@ -32,14 +32,10 @@ struct KArgs {
 
 template <int D>
 struct Smem {
-  // prefill: two stage buffers of 32 keys (two pages) each, the halves of a 64-key tile.  A stage holds the keys in
-  // operand order ([D/16][2 dimension halves][32 keys][8 dims], 1 KB per 16-dimension group) followed by
-  // the two pages' V blocks as they lie in the pool ([D dims][16 slots] each).
-  static constexpr int kKBytes = HFX_STAGE_KEYS * D * 2;
-  static constexpr int kPageVBytes = HFX_PAGE * D * 2;
-  static constexpr int kStageBytes = kKBytes + 2 * kPageVBytes;
-  static constexpr int kStages = 2;
-  static constexpr int kCopies = D / 32;         // 16-byte pieces per lane that a wavefront moves per stage
+  // prefill: a ring of stage slots of 32 keys (two pages) each: the two pages' K blocks, then their V blocks
+  static constexpr int kBlockBytes = HFX_PAGE * D * 2;
+  static constexpr int kStageBytes = 4 * kBlockBytes;
+  static constexpr int kStages = 4;
   // decode: per-wavefront partial rows [4][16][D + 4] floats (same memory; an item is one or the other)
   static constexpr int kPartStride = D + 4;
   static constexpr int kPartBytes = 4 * 16 * kPartStride * 4;
@@ -57,8 +53,6 @@ __device__ __forceinline__ float keep_or_neg_inf(float x, bool keep) {
   const unsigned u = keep ? __builtin_bit_cast(unsigned, x) : 0xff800000u;
   return __builtin_bit_cast(float, u);
 }
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Exchange between lane n and lane n ^ 32 with the swap instruction gfx950 has for it (the upper half
 // of one register against the lower half of another); a shuffle would go through LDS and put
@@ -92,11 +86,12 @@ __device__ __forceinline__ float sum_xor32(float x) {
 
 // zero the elements e >= nv of an 8-element bf16 vector (nv may be <= 0 or >= 8)
 __device__ __forceinline__ bf16x8 keep_first(bf16x8 v, int nv) {
+  const unsigned bits = (1u << min(max(nv, 0), 8)) - 1u;
   u32x4 u = __builtin_bit_cast(u32x4, v);
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    uint32_t m = (2 * w < nv ? 0x0000ffffu : 0u) | (2 * w + 1 < nv ? 0xffff0000u : 0u);
-    u[w] &= m;
+    const int lo = (int)(bits << (31 - 2 * w)) >> 31, hi = (int)(bits << (30 - 2 * w)) >> 31;   // all ones where kept
+    u[w] &= __builtin_amdgcn_perm((unsigned)hi, (unsigned)lo, 0x05040100u);
   }
   return __builtin_bit_cast(bf16x8, u);
 }
@@ -235,7 +230,6 @@ __global__ __launch_bounds__(HFX_WG_THREADS) void merge_kernel(const HfxUnit* __
 constexpr int kDealtTickets = 2;
 struct Tickets {
   int cur, nxt;
-  int pending;   // meaningful in thread 0 only: the counter's reply, an offset from the dealt tickets
   int parity;
 };
 
@@ -246,14 +240,11 @@ struct Tickets {
 // one die, and the planner puts items that read the same keys into one class: they then share
 // that die's L2.
 //
-// Thread 0 asks its class's counter for one more ticket (when `ask`); the reply is first touched by
-// tickets_publish.  The other lanes, and a call with ask == false, set the field to zero rather
-// than keep what it held: keeping it reads the register the previous request wrote, and for that
-// the compiler puts a wait for everything in flight in front of this request.
-__device__ __forceinline__ void tickets_reserve(Tickets& t, int* ctrl, int nc, bool ask = true) {
-  int r = 0;
-  if (ask && threadIdx.x == 0) r = atomicAdd(ctrl + ((int)blockIdx.x & (nc - 1)), 1);
-  t.pending = r;
+// Thread 0 asks its class's counter for one more ticket; the reply, an offset from the dealt
+// tickets, goes to tickets_publish.  The other lanes keep what `pending` held: a select on it would
+// wait for the reply, and with it for everything in flight, wherever the compiler places it.
+__device__ __forceinline__ void tickets_reserve(int& pending, int* ctrl, int nc) {
+  if (threadIdx.x == 0) pending = atomicAdd(ctrl + ((int)blockIdx.x & (nc - 1)), 1);
 }
 // Thread 0 puts the reserved ticket into LDS (two slots alternate, so one barrier per hand-over is
 // enough).  A reply past the end of the queue means the workgroup's class is empty.  It then reads
@@ -262,10 +253,10 @@ __device__ __forceinline__ void tickets_reserve(Tickets& t, int* ctrl, int nc, b
 // reply is past the end again) it looks again, a few times.  Giving up early costs balance, not
 // correctness: every class is drained by its own workgroups whether or not others help.
 constexpr int kStealAttempts = 4;
-__device__ __forceinline__ void tickets_publish(const Tickets& t, int* s_tk, int* ctrl, int n_items, int nc) {
+__device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, int* s_tk, int* ctrl, int n_items, int nc) {
   if (threadIdx.x == 0) {
     const int base = kDealtTickets * (int)gridDim.x;
-    int pos = base + t.pending * nc + ((int)blockIdx.x & (nc - 1));
+    int pos = base + pending * nc + ((int)blockIdx.x & (nc - 1));
     if (nc > 1) {
       for (int attempt = 0; attempt < kStealAttempts && pos >= n_items; ++attempt) {
         int best = 0, best_left = 0;
@@ -394,7 +385,8 @@ template <int D>
 __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __restrict__ items, int n_items,
                            Tickets& t, int* s_tk, int* ctrl, char* smem) {
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  int lane = tid & 63;
+  asm volatile("" : "+v"(lane));     // what follows from it is formed per run, not kept in registers through prefill runs
   const int wave = uniform(tid >> 6);
   const int Hq = H->num_q_heads, Hkv = H->num_kv_heads;
   const int G = Hq / Hkv;
@@ -439,10 +431,11 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     int pp = d.pp;
     int a0 = d.a0, a1 = d.a1, b0 = d.b0, b1 = d.b1;
     bool reserved = false;
+    int pending = 0;
     // page ids are fetched one pair ahead of the KV loads that need them
     while (pp < pe) {
       if (!reserved && pp + 4 * step >= pe) {   // a few pairs before the end (thread 0 sits in the first wavefront, which always has pairs)
-        tickets_reserve(t, ctrl, (int)H->queue_classes);
+        tickets_reserve(pending, ctrl, (int)H->queue_classes);
         reserved = true;
       }
       if (pp + step < pe) decode_load<D>(r1, a.pool, b0, b1, Hkv, g, k_sel, k_off, v_sel, v_off);
@@ -472,7 +465,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     // The reply to the ticket request has come back in front of the last pairs' loads (returns
     // are in order), so publishing it here waits for nothing; after the requests below it would
     // wait for them.  The barriers of the epilogue stand between this write and its readers.
-    tickets_publish(t, s_tk, ctrl, n_items, (int)H->queue_classes);
+    tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
     // both register sets and the Q operand are free now: start on the next item
     if (carry_on) {
       if (dn.pp < dn.pe) decode_load<D>(r0, a.pool, dn.a0, dn.a1, Hkv, dn.g, k_sel, k_off, v_sel, v_off);
@@ -537,187 +530,158 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
   }
 }
 
+// s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, the other counters left at their maxima)
+#define HFX_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
+
 // ----------------------------------------------------------------------------------------------
 // Prefill item.  Four wavefronts, each owning 32 chunk rows of one q-head; all four share the
-// kv-head.  Both contractions take their streamed operand from LDS, which on CDNA4 delivers 16-byte
-// reads at about 256 bytes per clock and CU, four times what the vector-memory path gives a wavefront
-// (about 64 bytes per clock and CU, measured): with 32 rows per wavefront every MFMA 32x32x16 needs a
-// fresh 1 KB operand, 128 bytes per clock and CU at full matrix rate.
-//   S^T[key][row]  = K[key][:] . Q[row][:]        A = K rows out of the stage buffer, B = Q^T in registers;
-//   O^T[d][row]   += V^T[d][key] . P^T[key][row]  A = V^T rows out of the stage buffer (a dimension-major
+// kv-head.  Both contractions take their streamed operand from LDS:
+//   S^T[key][row]  = K[key][:] . Q[row][:]        A = K rows out of the ring, B = Q^T in registers;
+//   O^T[d][row]   += V^T[d][key] . P^T[key][row]  A = V^T rows out of the ring (a dimension-major
 //                                                 V block is the operand layout), B = P^T from the
 //                                                 score registers.
-// The workgroup fills a stage (32 keys: two pages' K and V blocks, 16 KB at D = 128) once with
-// direct-to-LDS loads, two stages ahead of the one being multiplied; the global-to-LDS traffic is a
-// quarter of what four wavefronts loading their own fragments would move.
-// Each lane owns one query row (a column of S^T and O^T), so the running maximum, sum and rescale
+// Each lane owns one query row (a column of S^T and O^T), so the running sum and rescale
 // are lane-local up to one exchange with lane ^ 32.  The K rows of a score tile are taken in the
 // order that leaves every lane with 8 consecutive keys of one page per 16-key MFMA step.
+//
+// Keys arrive in stages of 32 (two pages' K and V blocks, 16 KB at D = 128) in a ring of four stage
+// slots, filled by direct-to-LDS loads about four stages ahead of their use: they take no registers and no
+// vector instructions (54 bytes per clock and CU out of the L2, measured; a stage pair needs 32 KB in
+// about 3500 clocks).
+//
+// What bounds it: the chip's power.  On 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens
+// (0.96 TFLOP) the matrix cores are busy 55 % of the cycles and the clock settles at 1.87 GHz; the form
+// before this one, which staged through registers, synchronised every stage and multiplied and
+// exponentiated one after the other, was at 44 % and 2.09 GHz.  The cycles fell by a fifth (2.10 M to
+// 1.67 M), the time by an eighth (1.02 to 0.89 ms; 1.18 to 1.03 ms on a 4096-row chunk at 64 k context,
+// 24.0 to 18.3 us on a single prompt of 777 tokens).  Leaving out the copies (data wrong) takes 9 % less, the
+// exponentials 5 %; the order of the instructions inside a phase and wavefront priorities change 1 %.
 // ----------------------------------------------------------------------------------------------
-struct StagePages {     // the two pages of a 32-key stage
-  int pg0, pg1;
-};
 
-// What a lane contributes to every stage copy; fixed for the lifetime of the kernel.  Wavefronts 0
-// and 1 copy the keys (D/32 groups of 16 dimensions each: 1 KB per instruction, the 32-byte pieces of
-// 32 keys, lanes 16-31 and 48-63 taking the second page), wavefronts 2 and 3 copy the V block of the
-// first and of the second page (1 KB per instruction, as it lies).
-struct CopyLane {
-  unsigned src_off;    // byte offset of the lane's first piece inside the (page, kv-head) K|V block pair
-  unsigned lds_off;    // where the lane's pieces start inside a stage buffer
-  bool second;         // the lane reads the stage's second page
-};
-
-template <int D>
-__device__ __forceinline__ CopyLane copy_lane(int wave, int lane) {
-  CopyLane c;
-  if (wave < 2) {
-    const int kk0 = wave * Smem<D>::kCopies;
-    // lane l fills LDS slot l of a 1 KB group: slot = 32 * (dimension half) + key, so that the 16
-    // lanes the LDS serves together later read 16 different bank groups
-    c.src_off = (unsigned)(((kk0 * 16 + (lane & 15)) * 16 + (lane >> 5) * 8) * 2);
-    c.lds_off = (unsigned)(kk0 * 1024 + lane * 16);
-    c.second = (lane >> 4) & 1;
-  } else {
-    c.src_off = (unsigned)(HFX_PAGE * D * 2 + lane * 16);
-    // A lane holds one half (8 slots, 16 bytes) of one dimension's 32-byte V row; the halves of rows
-    // 8-15 and 24-31 of a 1 KB group change places in LDS, so that the 16 lanes the LDS serves together
-    // hit 16 different bank groups both when the pieces are written (8 rows, both halves) and when the
-    // MFMA fragments are read (16 rows, one half); laid out as in the pool the reads collide in pairs.
-    const int row = lane >> 1, half = lane & 1;
-    c.lds_off = (unsigned)(Smem<D>::kKBytes + (wave - 2) * Smem<D>::kPageVBytes + (2 * row + (half ^ ((row >> 3) & 1))) * 16);
-    c.second = wave == 3;
-  }
-  return c;
+// One stage slot: [page 0 K][page 1 K][page 0 V][page 1 V], a block of 32 D bytes each, and
+// wavefront w copies block w, 1 KB (64 lanes of 16 bytes) per instruction.  An instruction puts lane
+// l's 16 bytes at 16 l, so the order inside a 1 KB chunk is chosen by the address each lane reads from:
+//   keys  : two 16-dimension groups of 16 slots x 32 bytes; LDS order (group, half, slot), so that
+//           the 16 lanes that the LDS serves together (16 slots, same half) hit 16 bank groups;
+//   values: 32 dimension rows of two 16-byte halves; the halves of rows 8-15 and 24-31 change places,
+//           so that 16 rows read at the same half hit 16 bank groups instead of colliding in pairs.
+__device__ __forceinline__ unsigned copy_lane_offset(int wave, int lane) {
+  if (wave < 2) return (unsigned)((lane >> 5) * 512 + (lane & 15) * 32 + ((lane >> 4) & 1) * 16);
+  return (unsigned)((lane >> 1) * 32 + ((lane & 1) ^ ((lane >> 4) & 1)) * 16);
 }
 
-// A wavefront's share of one 32-key stage on its way from the pool to LDS: D/32 pieces of 16 bytes per lane.
+// Direct-to-LDS copy of one block: base (scalar) + voff (lane) in memory, lds + 16 * lane in LDS.  The
+// instruction has no destination register; the compiler does not know of the load, so its own
+// vector-memory waits only become stricter by it, and the ring's waits are the explicit ones below.
 template <int D>
-struct StageRegs {
-  u32x4 r[Smem<D>::kCopies];
-};
-
-// Requests this wavefront's pieces of the stage made of pages pg0, pg1 of kv-head g.
-template <int D>
-__device__ __forceinline__ void stage_load(StageRegs<D>& sr, const __bf16* pool, const StagePages& sp, int Hkv, int g,
-                                           const CopyLane& cl, int wave) {
-  constexpr long kPairBytes = 2L * HFX_PAGE * D * 2;   // K block + V block of one (page, kv-head)
-  // the block addresses of the two pages are formed in scalar registers; a lane only picks its page
-  const uintptr_t b0 = reinterpret_cast<uintptr_t>(pool) + ((long)sp.pg0 * Hkv + g) * kPairBytes;
-  const uintptr_t b1 = reinterpret_cast<uintptr_t>(pool) + ((long)sp.pg1 * Hkv + g) * kPairBytes;
-  // (an address formed from integers has to be told that it is a global one, or the loads come out as flat loads)
-  typedef const __attribute__((address_space(1))) char* gptr;
-  gptr src = reinterpret_cast<gptr>((cl.second ? b1 : b0) + cl.src_off);
-  const int step = wave < 2 ? 512 : 1024;   // keys: the next 16-dimension group is 512 bytes on in the page; values: 1 KB
-#pragma unroll
-  for (int i = 0; i < Smem<D>::kCopies; ++i)
-    sr.r[i] = *reinterpret_cast<const __attribute__((address_space(1))) u32x4*>(src + i * step);
+__device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
+  if (D == 128)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %1\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:3072"
+                 :: "v"(voff), "s"(base), "s"(lds) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %1\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:1024"
+                 :: "v"(voff), "s"(base), "s"(lds) : "memory");
 }
 
-// ... and puts them into the stage buffer `buf` (1 KB per instruction, lane l at 16 l).
-template <int D>
-__device__ __forceinline__ void stage_write(char* buf, const StageRegs<D>& sr, const CopyLane& cl, int lane) {
-  char* dst = buf + cl.lds_off;
-#pragma unroll
-  for (int i = 0; i < Smem<D>::kCopies; ++i) *reinterpret_cast<u32x4*>(dst + i * 1024) = sr.r[i];
+// Workgroup barrier of the ring: this wavefront's LDS reads are done.  The compiler may move loads across
+// the barrier builtin, which claims no memory effect, so the empty asm on both sides holds them.
+__device__ __forceinline__ void ring_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-// Per-wavefront state of a prefill item that lives across key tiles.
+// Per-wavefront state of a prefill item that lives across stages.
 template <int D>
 struct PrefillWave {
   f32x16 o[D / 32];        // O^T accumulators per 32-dimension block
   bf16x8 qf[D / 16];       // Q^T operand fragments
   float m, l;              // reference exponent (base-2 domain) and running sum
-  int pos;                 // last key this lane's row may see
 };
 
-// Softmax of 32 scores (one MFMA result tile) of this lane's row.  `m` is the reference exponent
-// of the running sums; it is only raised -- and O, l rescaled -- when some row's maximum has
-// grown by more than 2^8 over it, which keeps every weight below 2^8 and makes the rescale rare.
-// s[v] is key key0 + (v>>3)*16 + (v&7)   (key0 already includes the lane's 8j).
-template <int D>
-__device__ __forceinline__ void softmax_block(f32x16& s, PrefillWave<D>& w, bf16x8* pb, float sl2, bool masked,
-                                              int key0) {
-  if (masked) {                // wave-uniform; the empty asm keeps the compiler from turning the rare
-    asm volatile("" ::: );     // masking into selects executed on every tile
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int key = key0 + (v >> 3) * 16 + (v & 7);
-      s[v] = keep_or_neg_inf(s[v], key <= w.pos);
-    }
-  }
-  float mx = fmaxf(s[0], s[1]);
-#pragma unroll
-  for (int v = 2; v < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);   // v_max3_f32
-  mx = max_xor32(mx) * sl2;
-  if (__any(mx > w.m + 8.0f)) {
-    const float mn = fmaxf(w.m, mx);
-    const float alpha = fast_exp2(w.m - (mn == NEG_INF ? 0.f : mn));
-    w.l *= alpha;
-#pragma unroll
-    for (int b = 0; b < D / 32; ++b) w.o[b] *= alpha;
-    w.m = mn;
-  }
-  const float mneg = w.m == NEG_INF ? 0.f : -w.m;
-  // The weights are summed in fp32 with plain adds, four partial sums.  (The two-element dot-product
-  // instruction would sum the rounded weights in half as many instructions, but it does not issue
-  // while a matrix instruction executes -- measured: 28 of them interleaved with 4 MFMA 32x32x16
-  // take the sum of both times, every other instruction of this function the maximum -- and so
-  // serialises the softmax of one wavefront with the MFMAs of both wavefronts of its SIMD.)
-  float ps[4] = {0.f, 0.f, 0.f, 0.f};
+#define HFX_M_NONE (-3.402823466e38f)   // reference exponent before the first stage: lower than any score
+
+// Weights of 16 scores against reference exponent m, and their sum (fp32, four partial sums; plain
+// adds, because the two-element dot-product instruction does not issue while a matrix instruction
+// executes).
+__device__ __forceinline__ float weights(const f32x16& s, float sl2, float m, bf16x8* pb) {
+  float ps[4];
 #pragma unroll
   for (int v = 0; v < 16; v += 2) {
-    const float p0 = fast_exp2(__builtin_fmaf(s[v], sl2, mneg));
-    const float p1 = fast_exp2(__builtin_fmaf(s[v + 1], sl2, mneg));
-    ps[(v >> 1) & 3] += p0 + p1;
+    const float p0 = fast_exp2(__builtin_fmaf(s[v], sl2, -m));
+    const float p1 = fast_exp2(__builtin_fmaf(s[v + 1], sl2, -m));
+    if (v < 8) ps[v >> 1] = p0 + p1;
+    else ps[(v >> 1) & 3] += p0 + p1;
     pb[v >> 3][v & 7] = (__bf16)p0;
     pb[v >> 3][(v & 7) + 1] = (__bf16)p1;
   }
-  w.l += (ps[0] + ps[1]) + (ps[2] + ps[3]);
+  return (ps[0] + ps[1]) + (ps[2] + ps[3]);
 }
 
-// One 32-key stage out of the LDS buffer `buf` against the wavefront's 32 rows; key0 is the stage's
-// first key.  k_lane / v_lane: byte offsets of this lane's K row and V^T fragment inside the buffer.
+// Masks the scores of keys that this lane's row must not see (those past `pos`): s[v] is key
+// key0 + (v>>3)*16 + (v&7)   (key0 already includes the lane's 8j).  The visible ones are the first few
+// of the 16, so one bit mask says which; selects on compares would hold 16 condition masks at once.  Masked
+// scores may be NaN (unused slots hold anything), hence integer operations.
+__device__ __forceinline__ void mask_scores(f32x16& s, int pos, int key0) {
+  const int d = pos - key0;
+  const int visible = min(max(d + 1, 0), 8) + min(max(d - 15, 0), 8);
+  const int bits = (1 << visible) - 1;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const unsigned keep = (unsigned)((int)((unsigned)bits << (31 - v)) >> 31);     // all ones where visible
+    const float x = s[v];            // (a bit cast of the vector element itself would read element 0)
+    s[v] = __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, x) & keep) | (0xff800000u & ~keep));
+  }
+}
+
+// Maximum over the 32 scores of this lane's row (16 here, 16 in lane ^ 32), in the base-2 domain.
+__device__ __forceinline__ float row_max(const f32x16& s, float sl2) {
+  float mx = fmaxf(s[0], s[1]);
+#pragma unroll
+  for (int v = 2; v < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);   // v_max3_f32
+  return max_xor32(mx) * sl2;
+}
+
+// m is the reference exponent of an item's running sums: the maximum of its first stage to begin
+// with.  A stage's weights are taken against the m at hand; only when some lane's 16 weights sum to
+// more than 2^8 -- its maximum has grown well over m -- is m raised to the maximum, O and l rescaled,
+// and the weights taken again.  So the common stage needs neither the maximum nor the exchange
+// between the lanes of a row, and no weight exceeds 2^8.
 template <int D>
-__device__ __forceinline__ void prefill_stage(PrefillWave<D>& w, const char* buf, int k_lane, int v_lane, bool masked,
-                                              bool past_ctx, int key0, int ctx_len, int j, float sl2, char* fill,
-                                              const StageRegs<D>& sr, const CopyLane& cl, int lane) {
-  bf16x8 kf[D / 16];
-  bf16x8 vf[2][D / 32];
+__device__ __forceinline__ void settle_weights(PrefillWave<D>& w, const f32x16& s, bf16x8* pb, float sum, float sl2) {
+  if (__builtin_expect(__any(sum > 256.0f), 0)) {
+    const float mx = fmaxf(w.m, row_max(s, sl2));
+    const float alpha = fast_exp2(w.m - mx);
+    w.l *= alpha;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(buf + kk * 1024 + k_lane);
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int b = 0; b < D / 32; ++b)
-      vf[sp][b] = *reinterpret_cast<const bf16x8*>(buf + Smem<D>::kKBytes + sp * Smem<D>::kPageVBytes + b * 1024 + v_lane);
-  // keep all the reads in front of the MFMA chain that consumes them: left alone, the scheduler
-  // sinks each read next to its MFMA to save registers and exposes the LDS latency every time
-  __builtin_amdgcn_sched_barrier(0);
+    for (int b = 0; b < D / 32; ++b) w.o[b] *= alpha;
+    w.m = mx;
+    sum = weights(s, sl2, w.m, pb);
+  }
+  w.l += sum;
+}
+
+// Scores of one stage: S^T = K . Q^T out of K fragments in registers.
+template <int D>
+__device__ __forceinline__ f32x16 score_mfma(const PrefillWave<D>& w, const bf16x8* kf) {
   f32x16 s;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    if (kk == 0) {
-      f32x16 z;
+  for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) z[v] = 0.f;
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], z, 0, 0, 0);
-    } else {
-      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], s, 0, 0, 0);
-    }
-  }
-  // the pieces of the stage after next go to the other buffer while the score MFMAs run
-  stage_write<D>(fill, sr, cl, lane);
-  __builtin_amdgcn_sched_barrier(0);
-  if (past_ctx) {              // the stage runs past the context: unused V slots may hold anything
-    asm volatile("" ::: );
-#pragma unroll
-    for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-      for (int b = 0; b < D / 32; ++b) vf[sp][b] = keep_first(vf[sp][b], ctx_len - (key0 + sp * 16 + j * 8));
-  }
-  bf16x8 pb[2];
-  softmax_block<D>(s, w, pb, sl2, masked, key0 + j * 8);
+  for (int kk = 0; kk < D / 16; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], s, 0, 0, 0);
+  return s;
+}
+
+// O^T += V^T . P^T of one stage.
+template <int D>
+__device__ __forceinline__ void value_mfma(PrefillWave<D>& w, bf16x8 (*vf)[D / 32], const bf16x8* pb) {
 #pragma unroll
   for (int sp = 0; sp < 2; ++sp)
 #pragma unroll
@@ -725,120 +689,143 @@ __device__ __forceinline__ void prefill_stage(PrefillWave<D>& w, const char* buf
       w.o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sp][b], pb[sp], w.o[b], 0, 0, 0);
 }
 
-// s_waitcnt vmcnt(N) alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14, the other counters left at their maxima)
-#define HFX_WAIT_VMCNT(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
+template <int D>
+__device__ __forceinline__ void read_keys(bf16x8* kf, const char* slot, int k_lane) {
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(slot + kk * 512 + k_lane);
+}
 
-// Wave-uniform description of where the workgroup's tile stream goes: the current prefill item
-// and, when the next item of this workgroup is a prefill item too, that one.
-struct TileStream {
-  int bt0;            // start of the current item's request in the stored block table
-  int g;              // kv-head
-  int end;            // first key past the current item's last (whole) 64-key tile
-  bool next_ok;
-  int bt0_n, g_n, kb_n, len_n;   // the same for the next item, its first key and its length in whole tiles' keys
-};
+template <int D>
+__device__ __forceinline__ void read_values(bf16x8 (*vf)[D / 32], const char* slot, int v_lane) {
+#pragma unroll
+  for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+      vf[sp][b] = *reinterpret_cast<const bf16x8*>(slot + (2 + sp) * Smem<D>::kBlockBytes + b * 1024 + v_lane);
+}
 
-// Page ids of the 64-key tile that starts `kt` keys into a request (kt a multiple of 64): one aligned
-// quad out of the step's stored block table.  The stored table repeats a request's last page for
-// HFX_BT_PAD entries behind it, so the quad needs no clamping a tile past the end.
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-struct TilePages {
-  StagePages half[2];
-};
+// Scores of the next stage (K fragments kf) and the weights of the present one (scores cur) in one
+// instruction stream, with the reads of the present stage's value fragments between them: a matrix
+// instruction is followed by about as many vector instructions as issue while it executes -- the two
+// exponentials of a pair of scores, and the sum and rounding of the pair before.  Left to itself the
+// compiler puts the matrix instructions in one block and the exponentials in another.
+template <int D>
+__device__ __forceinline__ float scores_and_weights(const PrefillWave<D>& w, const bf16x8* kf, const f32x16& cur,
+                                                    f32x16& next, bf16x8* pb, float sl2, bf16x8 (*vf)[D / 32],
+                                                    const char* v_slot, int v_lane) {
+  constexpr int kPairs = 8, kPer = kPairs / (D / 16);      // pairs of scores per matrix instruction
+  constexpr int B = D / 32;
+  float ps[4], p0 = 0.f, p1 = 0.f;
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  auto finish = [&](int i) {       // sum and rounding of pair i
+    if (i < 4) ps[i] = p0 + p1;
+    else ps[i & 3] += p0 + p1;
+    pb[i >> 2][(2 * i) & 7] = (__bf16)p0;
+    pb[i >> 2][((2 * i) & 7) + 1] = (__bf16)p1;
+  };
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], acc, 0, 0, 0);
+    vf[kk / B][kk % B] = *reinterpret_cast<const bf16x8*>(v_slot + (2 + kk / B) * Smem<D>::kBlockBytes + (kk % B) * 1024 + v_lane);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int i = kk * kPer + u;
+      const float x0 = __builtin_fmaf(cur[2 * i], sl2, -w.m), x1 = __builtin_fmaf(cur[2 * i + 1], sl2, -w.m);
+      if (i > 0) finish(i - 1);
+      p0 = fast_exp2(x0);
+      p1 = fast_exp2(x1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  finish(kPairs - 1);
+  asm volatile("" : "+v"(pb[0]), "+v"(pb[1]));   // the roundings belong here, not behind the branch that follows
+  next = acc;
+  return (ps[0] + ps[1]) + (ps[2] + ps[3]);
+}
 
-// Pages and kv-head of the tile that starts `kt` keys into the stream.  The tile after an item's
-// last is the first tile of the workgroup's next item (key ranges of items start at multiples of
-// 64).  `known` says whether the position lies in the current or in the next item; past those (the
-// item after next has no ticket yet), and with no next prefill item at all, the stored table is read
-// on into its padding, which repeats a request's last page: readable pages whose data is never used.
-__device__ __forceinline__ TilePages stream_pages(const int* __restrict__ bt, const TileStream& ts, int kt,
-                                                  int& g_out, bool& known) {
-  const bool into_next = kt >= ts.end && ts.next_ok;
-  const int off = kt - ts.end;
-  known = kt < ts.end || (ts.next_ok && off < ts.len_n);
-  const int bt0 = into_next ? ts.bt0_n : ts.bt0;
-  const int k = into_next ? ts.kb_n + off : kt;
-  g_out = into_next ? ts.g_n : ts.g;
-  const i32x4 v = *reinterpret_cast<const i32x4*>(bt + bt0 + k / HFX_PAGE);
-  TilePages t;
-  t.half[0].pg0 = v[0];
-  t.half[0].pg1 = v[1];
-  t.half[1].pg0 = v[2];
-  t.half[1].pg1 = v[3];
-  return t;
+// Weighted values of the present stage, with the reads of the key fragments of the stage after next between them.
+template <int D>
+__device__ __forceinline__ void values_and_reads(PrefillWave<D>& w, bf16x8 (*vf)[D / 32], const bf16x8* pb, bf16x8* kf,
+                                                 const char* k_slot, int k_lane) {
+  constexpr int B = D / 32;
+#pragma unroll
+  for (int i = 0; i < 2 * B; ++i) {
+    w.o[i % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i / B][i % B], pb[i / B], w.o[i % B], 0, 0, 0);
+    if (i < B) {
+#pragma unroll
+      for (int k = 2 * i; k < 2 * i + 2; ++k) kf[k] = *reinterpret_cast<const bf16x8*>(k_slot + k * 512 + k_lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // What a wavefront derives from a prefill item: its q-head and rows, and the key ranges that
-// decide whether a tile is worked on and whether it needs masks.
+// decide whether a stage is worked on and whether it needs masks.
 struct WaveRows {
-  int head, qrow, wave_kend, wave_pmin;
-  bool store;    // qrow is a real row of the chunk
+  int head, row0;             // q-head and first chunk row
+  int wave_kend, wave_pmin;
 };
 
-template <int D>
-__device__ __forceinline__ WaveRows wave_rows(const HfxItem& it, int wave, int n) {
+__device__ __forceinline__ WaveRows wave_rows(const HfxItem& it, int wave) {
   WaveRows r;
   r.head = it.h0 + wave % it.hn;
-  const int r0 = it.row0 + (wave / it.hn) * HFX_WAVE_ROWS;
+  r.row0 = it.row0 + (wave / it.hn) * HFX_WAVE_ROWS;
   const int p = it.rq.ctx_len - it.rq.q_len;
-  r.wave_kend = r0 < it.rq.q_len ? p + min(r0 + HFX_WAVE_ROWS, it.rq.q_len) : 0;   // keys >= this: nothing to do
-  r.wave_pmin = p + r0;                                                            // keys <= this are visible to every row
-  r.qrow = r0 + n;
-  r.store = r.qrow < it.rq.q_len;
+  r.wave_kend = r.row0 < it.rq.q_len ? min(it.ke, p + min(r.row0 + HFX_WAVE_ROWS, it.rq.q_len)) : 0;   // keys >= this: nothing to do
+  r.wave_pmin = p + r.row0;                                                            // keys <= this are visible to every row
   return r;
 }
 
 // Q^T operand fragments of this lane's row (rows past the chunk read the last row and are never stored)
 template <int D>
-__device__ __forceinline__ void q_load(PrefillWave<D>& w, const KArgs& a, const HfxItem& it, const WaveRows& r, int Hq,
-                                       int j) {
-  const int qc = r.store ? r.qrow : it.rq.q_len - 1;
-  w.pos = it.rq.ctx_len - it.rq.q_len + qc;
+__device__ __forceinline__ void q_load(bf16x8* qf, const KArgs& a, const HfxItem& it, const WaveRows& r, int Hq, int n, int j) {
+  const int qc = min(r.row0 + n, it.rq.q_len - 1);
   const __bf16* qp = a.q + (((long)it.rq.q_start + qc) * Hq + r.head) * D + j * 8;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) w.qf[kk] = ld16(qp + kk * 16);
+  for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld16(qp + kk * 16);
 }
 
 // Result of a finished item: normalised bf16 rows, or (m, l, acc) partial rows when the item is one split of a group.
 // A lane holds 4-dimension pieces of its own row, so stored straight from the registers every
 // instruction would touch 32 rows with 16 bytes each, and the write path takes one request per
-// (instruction, line): measured, the 16 stores of an item took longer to issue than two of its
-// tiles took to compute.  The bf16 rows therefore go through `stage` (4 KB of LDS owned by this
-// wavefront, 64 dimensions of its 32 rows at a time) and leave as whole 128-byte lines, 8 rows per
-// instruction.  The 8-byte pieces of a row are swizzled by the row number to spread the LDS banks.
+// (instruction, line).  The bf16 rows therefore go through `stage` (2 KB of LDS owned by this
+// wavefront, 32 dimensions of its 32 rows at a time) and leave in 64-byte pieces, 16 rows per
+// instruction.  The 16-byte units of a row are permuted by the row number, and the two 8-byte halves of a unit
+// change places in rows 16-31, so that writes and reads spread over all LDS banks.
 template <int D>
 __device__ __forceinline__ void prefill_store(const KArgs& a, const HfxHeader* H, const HfxItem& it, const WaveRows& r,
                                               const PrefillWave<D>& w, int Hq, int wave, int lane, char* stage) {
-  // o[b][v] is dimension 32b + (v>>2)*8 + 4j + (v&3) of chunk row `qrow`
+  // o[b][v] is dimension 32b + (v>>2)*8 + 4j + (v&3) of chunk row row0 + (lane & 31)
   const float lsum = sum_xor32(w.l);
   // The lane's parts of the destination addresses are formed here, per call: left visible, the
   // compiler hoists them out of the item loop, runs out of registers and parks them in scratch
-  // memory, and the reload at every hand-over waits for every load the tile stream has in flight.
+  // memory, and the reload at every hand-over waits for every load the stage ring has in flight.
   asm volatile("" : "+v"(lane));
   const int n = lane & 31, j = lane >> 5;
   if (it.group < 0) {
     const float inv = 1.0f / lsum;
-    const int row0 = r.qrow - n;                 // first chunk row of this wavefront
-    const int rr = lane >> 3, u = lane & 7;      // read-back: row rr + 8i, 16-byte piece u
+    const int row0 = r.row0;
+    const int rr = lane >> 2, u = lane & 3;      // read-back: row rr + 16i, 16-byte unit u
     __bf16* dst = a.out + (((long)it.rq.q_start + row0 + rr) * Hq + r.head) * D + u * 8;
+    char* wr = stage + n * 64 + (j ^ (n >> 4)) * 8;
+    const char* rd = stage + rr * 64 + ((u ^ ((rr >> 2) & 3)) * 16);
 #pragma unroll
-    for (int p = 0; p < D / 64; ++p) {
+    for (int b = 0; b < D / 32; ++b) {
 #pragma unroll
-      for (int bb = 0; bb < 2; ++bb)
+      for (int q4 = 0; q4 < 4; ++q4) {
+        bf16x4 ob;
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          bf16x4 ob;
+        for (int e = 0; e < 4; ++e) ob[e] = (__bf16)(w.o[b][q4 * 4 + e] * inv);
+        *reinterpret_cast<bf16x4*>(wr + ((q4 ^ ((n >> 2) & 3)) * 16)) = ob;
+      }
 #pragma unroll
-          for (int e = 0; e < 4; ++e) ob[e] = (__bf16)(w.o[2 * p + bb][q4 * 4 + e] * inv);
-          const int c = 8 * bb + 2 * q4 + j;     // 8-byte piece of the 128-byte half row
-          *reinterpret_cast<bf16x4*>(stage + n * 128 + ((c ^ ((n & 7) << 1)) * 8)) = ob;
-        }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = rr + 8 * i;
-        const bf16x8 line = *reinterpret_cast<const bf16x8*>(stage + row * 128 + ((u ^ (row & 7)) * 16));
-        if (row0 + row < it.rq.q_len)
-          *reinterpret_cast<bf16x8*>(dst + (long)i * 8 * Hq * D + p * 64) = line;
+      for (int i = 0; i < 2; ++i) {
+        u32x4 line = *reinterpret_cast<const u32x4*>(rd + i * 1024);
+        if (i == 1) line = u32x4{line[2], line[3], line[0], line[1]};
+        if (row0 + rr + 16 * i < it.rq.q_len)
+          *reinterpret_cast<u32x4*>(dst + (long)i * 16 * Hq * D + b * 32) = line;
       }
     }
   } else {
@@ -860,163 +847,243 @@ __device__ __forceinline__ void prefill_store(const KArgs& a, const HfxHeader* H
   }
 }
 
+// The workgroup's stream of stage copies: the stages of the current item and then those of the next
+// item, if that is a prefill item too (the item after next has no ticket yet).  Wave-uniform.
+struct CopyStream {
+  int count;          // stages copied so far, over all items of the run
+  int left;           // stages of the item being copied that are still to come
+  int bt;             // stored block-table entry of the next stage's page that this wavefront copies
+  int limit;          // stages that may be copied without overwriting one still to be read
+  const char* base;   // block of page 0: the item's kv-head, keys or values
+  int in_next;        // the item being copied is the next one, not the current one
+};
+
+__device__ __forceinline__ int item_stages(const HfxItem& it) { return (it.ke - it.kb + HFX_STAGE_KEYS - 1) / HFX_STAGE_KEYS; }
+
 // Runs the prefill item t.cur and, for as long as the workgroup's next item is a prefill item as
-// well, carries straight on into it: the K/V pipeline does not drain between items, only the
+// well, carries straight on into it: the stage ring does not drain between items, only the
 // per-row state (Q, O, m, l) is swapped.  Returns with t.cur at the first item it did not process.
 //
-// The pipeline, per 64-key tile (two stages, buffers 0 and 1):
-//   first stage  : request the next tile's first half from the pool into register set A; multiply
-//                  buffer 0; put register set B (this tile's second half, requested a tile ago) into
-//                  buffer 1; barrier.
-//   second stage : request the next tile's second half into register set B; multiply buffer 1; put
-//                  register set A into buffer 0; barrier.
-// Every piece therefore has two stages between its request and its use, and ordinary loads are
-// used on purpose: the direct-to-LDS form of the load moved about 16 bytes per clock and CU here,
-// a quarter of the ordinary path, and bounded the loop.  "Next tile" is a position in the
-// workgroup's tile stream: past the end of the item it is the first tile of the next prefill item.
+// A wavefront's work on stage s, in two phases:
+//   first  : scores of stage s + 1 (matrix cores, K fragments in registers) between the instructions of the softmax
+//            of stage s (vector unit) and the reads of its value fragments;
+//   second : weighted values of stage s between the reads of the key fragments of stage s + 2.
+// Two stages make a step of the loop, so that the scores change places without being moved, and there
+// is one synchronisation point per step, between the phases of its first stage g: the keys up to stage
+// g + 3 and the values up to stage g + 2 have landed, every wavefront has taken the fragments of keys up to
+// g + 1 and values up to g, and their slots are copied into next.  (One point per stage: 1.75 M cycles instead
+// of 1.67 M.)
 template <int D>
 __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* __restrict__ items, int n_items,
                             Tickets& t, int* s_tk, int* ctrl, char* smem, char* o_stage) {
   constexpr int SK = HFX_STAGE_KEYS;
-  constexpr int SB = Smem<D>::kStageBytes;
+  constexpr int RING = Smem<D>::kStages;
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
+  int lane = tid & 63;
+  asm volatile("" : "+v"(lane));     // what follows from it is formed per run, not kept in registers through decode runs
   const int wave = uniform(tid >> 6);
   const int Hq = H->num_q_heads, Hkv = H->num_kv_heads;
   const int G = Hq / Hkv;
   const int n = lane & 31, j = lane >> 5;
-  // The result rows are staged in buffer 1 at the hand-over: its stage has been multiplied, and the
-  // slice a wavefront stages its rows in is the slice that only its own next pieces go to.
-  char* stage = D == 128 ? smem + SB + wave * 4096 : o_stage + wave * 4096;
+  char* stage = o_stage + wave * 2048;
   const float sl2 = H->softmax_scale * 1.4426950408889634f;
-  const int* bt_all = reinterpret_cast<const int*>(a.desc + H->off_bt);
+  const int* __restrict__ bt = reinterpret_cast<const int*>(a.desc + H->off_bt);
   // row of this lane's key inside the stage's 32 keys
   const int krow = (n >> 4) * 16 + ((n >> 2) & 1) * 8 + ((n >> 3) & 1) * 4 + (n & 3);
-  const int k_lane = (j * 32 + krow) * 16;
-  const int v_lane = (n * 2 + (j ^ ((n >> 3) & 1))) * 16;   // V^T rows 32b + n, keys 8j.. of a page, at their swizzled place (copy_lane)
-  const CopyLane cl = copy_lane<D>(wave, lane);
+  const int k_lane = (krow >> 4) * Smem<D>::kBlockBytes + j * 256 + (krow & 15) * 16;
+  const int v_lane = (n * 2 + (j ^ ((n >> 3) & 1))) * 16;   // V^T rows 32b + n, keys 8j.. of a page
+  const unsigned voff = copy_lane_offset(wave, lane);
+  const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * Smem<D>::kBlockBytes;
+  const char* pool = reinterpret_cast<const char*>(a.pool) + (wave >> 1) * Smem<D>::kBlockBytes;
+  const unsigned long page_bytes = (unsigned long)(unsigned)Hkv * (2 * Smem<D>::kBlockBytes);
+  const int key_wave = 1 - (wave >> 1);   // 1: this wavefront copies keys, which are read a stage before the values
 
   HfxItem it = items[t.cur];
   HfxItem nx = items[t.nxt < n_items ? t.nxt : t.cur];
-  TileStream ts;
-  auto set_stream = [&]() {
-    ts.bt0 = it.rq.bt_start;
-    ts.g = it.h0 / G;
-    ts.end = it.kb + (it.ke - it.kb + HFX_KEY_TILE - 1) / HFX_KEY_TILE * HFX_KEY_TILE;
-    ts.next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
-    ts.bt0_n = nx.rq.bt_start;
-    ts.g_n = nx.h0 / G;
-    ts.kb_n = nx.kb;
-    ts.len_n = (nx.ke - nx.kb + HFX_KEY_TILE - 1) / HFX_KEY_TILE * HFX_KEY_TILE;
+  bool next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
+  CopyStream cs;
+  auto stream_start = [&](const HfxItem& item) {
+    cs.left = item_stages(item);
+    cs.base = pool + (long)(item.h0 / G) * (2 * Smem<D>::kBlockBytes);
+    cs.bt = item.rq.bt_start + item.kb / HFX_PAGE + (wave & 1);
   };
-  set_stream();
-  // Tiles (by first key) at whose start the next ticket is published and asked for: published at
-  // the last tile but one, asked for a tile earlier.  Items of one or two tiles ask at the
-  // hand-over and publish at their first tile.
-  int publish_kt, reserve_kt;
+  auto copy_page = [&](int page) {     // slots are handed out round-robin over the whole run
+    block_copy<D>(cs.base + (unsigned long)(unsigned)page * page_bytes, voff,
+                  lds_ring + (cs.count & (RING - 1)) * Smem<D>::kStageBytes);
+    ++cs.count;
+    --cs.left;
+    cs.bt += 2;
+  };
+  // copies what there is room for, as far as the items to come are known
+  auto stream_catch_up = [&]() {
+#pragma unroll 1
+    while (cs.left > 0 && cs.count < cs.limit) {
+      copy_page(bt[cs.bt]);
+      if (cs.left == 0 && !cs.in_next && next_ok) {
+        cs.in_next = 1;
+        stream_start(nx);
+      }
+    }
+  };
+  cs.count = 0;
+  cs.in_next = 0;
+  stream_start(it);
+
+  // The stage in which the next ticket is asked for and published (the workgroup waits for the reply there:
+  // a reply in flight through the stage loop would make the compiler wait for it, and with it for every copy
+  // in flight, wherever it touches the register).  Short items ask at the hand-over, where the reply comes
+  // back with Q, and have no such stage.
+  int n_st, publish_st;
   auto set_ticket_points = [&]() {
-    const int n_tiles = (it.ke - it.kb + HFX_KEY_TILE - 1) / HFX_KEY_TILE;
-    const int ip = n_tiles > 2 ? n_tiles - 2 : 0;
-    publish_kt = it.kb + ip * HFX_KEY_TILE;
-    reserve_kt = ip > 0 ? publish_kt - HFX_KEY_TILE : -1;
-    tickets_reserve(t, ctrl, (int)H->queue_classes, ip == 0);   // the field is dead here: the last publish has read it
+    n_st = item_stages(it);
+    publish_st = n_st > 6 ? n_st - 3 : -(1 << 30);
   };
   set_ticket_points();
+  int pending = 0;
+  if (n_st <= 6) tickets_reserve(pending, ctrl, (int)H->queue_classes);
 
   PrefillWave<D> w;
-  WaveRows wr = wave_rows<D>(it, wave, n);
-  int wave_end = min(wr.wave_kend, it.ke);   // keys from here on: nothing to do for this wavefront
-  q_load<D>(w, a, it, wr, Hq, j);
-#pragma unroll
-  for (int b = 0; b < D / 32; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) w.o[b][v] = 0.f;
-  w.m = NEG_INF;
-  w.l = 0.f;
+  WaveRows wr = wave_rows(it, wave);
+  q_load<D>(w.qf, a, it, wr, Hq, n, j);
+  int g_st = 0;      // stages multiplied so far, over all items of the run: the ring position
+  cs.limit = RING;
+  stream_catch_up();
+  if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
 
-  // cold start: the first tile's first half goes to buffer 0, its second half is requested; the
-  // page ids of the tile after it are looked up (they are always asked for a tile before the loads
-  // that need them, so that no tile starts by waiting for a scalar load)
-  int kt = it.kb;
-  StageRegs<D> ra, rb;
-  TilePages tn;
-  int gn;
-  bool tn_known;
-  {
-    int gq;
-    bool known;
-    const TilePages tp = stream_pages(bt_all, ts, kt, gq, known);
-    stage_load<D>(ra, a.pool, tp.half[0], Hkv, gq, cl, wave);
-    stage_load<D>(rb, a.pool, tp.half[1], Hkv, gq, cl, wave);
-    tn = stream_pages(bt_all, ts, kt + HFX_KEY_TILE, gn, tn_known);
-    stage_write<D>(smem, ra, cl, lane);
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wavefront's pieces are in LDS
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  }
-  for (;;) {
-    if (kt == publish_kt) {
-      // The ticket asked for earlier is published ahead of this tile's barriers, so that the
-      // hand-over at the end of the item needs no barrier of its own.  Reading the counter's reply
-      // makes the wavefront wait for what it had in flight when it asked.
-      tickets_publish(t, s_tk, ctrl, n_items, (int)H->queue_classes);
+  // Synchronisation point of the ring: what has been copied so far has landed, everyone's fragment reads
+  // so far are done, and copies may go on up to `limit`.  In the general form the next ticket is asked
+  // for and published and the copy stream catches up or changes items; it also says up to which stage
+  // (event_st) nothing of that kind will happen, so that the short form, two copies, does.
+  int event_st = 0;
+  auto sync_general = [&](int limit) {
+    if (g_st == publish_st || g_st + 1 == publish_st) {
+      int reply = 0;
+      tickets_reserve(reply, ctrl, (int)H->queue_classes);
+      tickets_publish(t, reply, s_tk, ctrl, n_items, (int)H->queue_classes);
     }
-    if (kt == reserve_kt) tickets_reserve(t, ctrl, (int)H->queue_classes);   // never in the publishing tile
-    // ---- first stage: keys kt .. kt + 31 out of buffer 0
-    stage_load<D>(ra, a.pool, tn.half[0], Hkv, gn, cl, wave);
-    if (kt < wave_end) {
-      prefill_stage<D>(w, smem, k_lane, v_lane, kt + SK - 1 > wr.wave_pmin, kt + SK > it.rq.ctx_len, kt,
-                       it.rq.ctx_len, j, sl2, smem + SB, rb, cl, lane);
-    } else {
-      stage_write<D>(smem + SB, rb, cl, lane);
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();   // bare barrier: LDS is only written by the pieces ordered above
-    asm volatile("" ::: "memory");  // keep the next stage's LDS reads below the barrier
-    // ---- second stage: keys kt + 32 .. kt + 63 out of buffer 1
-    stage_load<D>(rb, a.pool, tn.half[1], Hkv, gn, cl, wave);
-    // the tile after next, for the next tile's loads
-    tn = stream_pages(bt_all, ts, kt + 2 * HFX_KEY_TILE, gn, tn_known);
-    if (kt + SK < wave_end) {
-      prefill_stage<D>(w, smem + SB, k_lane, v_lane, kt + 2 * SK - 1 > wr.wave_pmin, kt + 2 * SK > it.rq.ctx_len,
-                       kt + SK, it.rq.ctx_len, j, sl2, smem, ra, cl, lane);
-    } else {
-      stage_write<D>(smem, ra, cl, lane);
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    kt += HFX_KEY_TILE;
-    if (kt < it.ke) continue;
-
-    // hand-over: the item is finished; its successor's first tile is in buffer 0 and on its way
-    const bool carry_on = ts.next_ok;
-    prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
-    tickets_take(t, s_tk);
-    if (!carry_on) break;
-    it = nx;
-    nx = items[t.nxt < n_items ? t.nxt : t.cur];   // asked for here, first looked at behind the wait for Q
-    set_ticket_points();
-    wr = wave_rows<D>(it, wave, n);
-    wave_end = min(wr.wave_kend, it.ke);
-    q_load<D>(w, a, it, wr, Hq, j);
-    // Q is needed by the very next MFMA.  Waiting for it here, in so many words, also tells the
-    // compiler that nothing is in flight when the tile loop is re-entered; left to itself it
-    // carries the Q loads into the loop as pending and drains the queue down to them on every tile.
     HFX_WAIT_VMCNT(0);
-    set_stream();
-    // the page ids for the tile after this item's first were asked for while the item after this one
-    // had no ticket yet, if this item is one tile long: asked for again, now that it has
-    if (!tn_known) tn = stream_pages(bt_all, ts, it.kb + HFX_KEY_TILE, gn, tn_known);
+    ring_barrier();
+    cs.limit = limit;
+    stream_catch_up();
+    // the short form copies two stages at stage g if count is g + 3 (values) or g + 4 (keys) there, and must
+    // leave one for the general form to notice the item's end by
+    event_st = cs.count == limit ? g_st + (cs.left > 0 ? (cs.left - 1) / 2 * 2 : 0) + 1 : g_st;
+    if (publish_st > g_st) event_st = min(event_st, publish_st - 1);
+  };
+  for (;;) {
+    w.l = 0.f;
 #pragma unroll
     for (int b = 0; b < D / 32; ++b)
 #pragma unroll
       for (int v = 0; v < 16; ++v) w.o[b][v] = 0.f;
-    w.m = NEG_INF;
-    w.l = 0.f;
-    kt = it.kb;
+    const int wave_end = wr.wave_kend, unmasked_upto = wr.wave_pmin, ctx_len = it.rq.ctx_len;
+    const int end_st = g_st + n_st - 1;      // the item's last stage
+    publish_st += g_st;
+    int kt = it.kb;
+    auto mask_stage = [&](f32x16& s) {     // keys past this lane's row's horizon (rows past the chunk: its last row's)
+      mask_scores(s, min(wr.wave_pmin + n, ctx_len - 1), kt + j * 8);
+    };
+    bf16x8 kf[D / 16];
+    f32x16 s0, s1;
+    // the first stage: its scores, and their maximum as the reference exponent
+    sync_general(g_st + RING);
+    event_st = g_st - 1;
+    read_keys<D>(kf, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
+    s0 = score_mfma<D>(w, kf);
+    read_keys<D>(kf, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
+    if (kt + SK - 1 > unmasked_upto) mask_stage(s0);
+    w.m = fmaxf(HFX_M_NONE, row_max(s0, sl2));
+    auto slot = [&](int st) { return smem + (st & (RING - 1)) * Smem<D>::kStageBytes; };
+    auto mask_values = [&](bf16x8 (*vf)[D / 32]) {   // unused V slots may hold anything
+#pragma unroll
+      for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b) vf[sp][b] = keep_first(vf[sp][b], ctx_len - (kt + sp * 16 + j * 8));
+    };
+    // One stage: `cur` holds its scores, `next` receives those of the stage after it.  Every other stage
+    // synchronises between its two phases.
+    auto stage_step = [&](f32x16& cur, f32x16& next, bool sync) {
+      const bool busy = kt < wave_end;
+      bf16x8 vf[2][D / 32], pb[2];
+      int page0 = 0, page1 = 0;
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the key fragments
+      if (sync) {
+        page0 = bt[cs.bt];
+        page1 = bt[cs.bt + 2];
+      }
+      if (busy) {
+        if (kt + SK - 1 > unmasked_upto) mask_stage(cur);
+        __builtin_amdgcn_sched_barrier(0);
+        const float sum = scores_and_weights<D>(w, kf, cur, next, pb, sl2, vf, slot(g_st), v_lane);
+        settle_weights<D>(w, cur, pb, sum, sl2);
+      }
+      if (sync) {
+        if (g_st < event_st) {
+          HFX_WAIT_VMCNT(0);
+          ring_barrier();
+          copy_page(page0);
+          copy_page(page1);
+        } else {
+          sync_general(g_st + RING + 1 + key_wave);
+        }
+      }
+      if (busy) {
+        if (kt + SK > ctx_len) mask_values(vf);
+        __builtin_amdgcn_sched_barrier(0);
+        values_and_reads<D>(w, vf, pb, kf, slot(g_st + 2), k_lane);
+      }
+      ++g_st;
+      kt += SK;
+    };
+    for (;;) {
+      if (g_st == end_st) break;
+      stage_step(s0, s1, true);
+      if (g_st == end_st) {
+        s0 = s1;
+        break;
+      }
+      stage_step(s1, s0, false);
+    }
+    // the item's last stage: Q is not needed any more, and the next item's is asked for
+    WaveRows wr_n = wr;
+    if (next_ok) {
+      wr_n = wave_rows(nx, wave);
+      q_load<D>(w.qf, a, nx, wr_n, Hq, n, j);
+    }
+    if (kt < wave_end) {
+      bf16x8 vf[2][D / 32], pb[2];
+      if (kt + SK - 1 > unmasked_upto) mask_stage(s0);
+      read_values<D>(vf, slot(g_st), v_lane);
+      const float sum = weights(s0, sl2, w.m, pb);
+      settle_weights<D>(w, s0, pb, sum, sl2);
+      if (kt + SK > ctx_len) mask_values(vf);
+      value_mfma<D>(w, vf, pb);
+    }
+    ++g_st;
+    // hand-over: the item is finished; its successor's first stages are in the ring or on their way
+    prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
+    tickets_take(t, s_tk);
+    if (!next_ok) break;
+    it = nx;
+    wr = wr_n;
+    nx = items[t.nxt < n_items ? t.nxt : t.cur];
+    next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
+    set_ticket_points();
+    pending = 0;
+    if (n_st <= 6) tickets_reserve(pending, ctrl, (int)H->queue_classes);
+    cs.in_next = 0;
+    if (cs.left <= 0 && next_ok) {     // the new current item is wholly copied already
+      cs.in_next = 1;
+      stream_start(nx);
+    }
+    stream_catch_up();
+    // Q is needed by the next MFMA; waiting for it in so many words also tells the compiler that
+    // nothing is in flight when the stage loop is re-entered
+    if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
+    HFX_WAIT_VMCNT(0);
   }
-  __syncthreads();     // every wavefront is done with the stage buffers before the LDS is used for anything else
+  __syncthreads();     // every wavefront is done with the ring before the LDS is used for anything else
 }
 
 // ----------------------------------------------------------------------------------------------
@@ -1041,15 +1108,14 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   a.out = out;
   __shared__ __attribute__((aligned(1024))) char smem[Smem<D>::kBytes];
   __shared__ int s_tk[2];
-  // result rows on their way out (prefill_store): at D = 128 they go through a free stage buffer
-  __shared__ __attribute__((aligned(128))) char s_ostage[D == 128 ? 128 : 4 * 4096];
+  // result rows on their way out (prefill_store)
+  __shared__ __attribute__((aligned(128))) char s_ostage[4 * 2048];
   const HfxHeader* H = &hdr;
   const HfxItem* items = reinterpret_cast<const HfxItem*>(a.desc + H->off_items);
   const int n_items = H->n_items;
   Tickets t;
   t.cur = (int)blockIdx.x;
   t.nxt = (int)(blockIdx.x + gridDim.x);
-  t.pending = 0;
   t.parity = 0;
   while (t.cur < n_items) {
     if (items[t.cur].type == HFX_ITEM_DECODE) {

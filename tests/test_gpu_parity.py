@@ -202,6 +202,36 @@ def test_items_of_one_to_six_tiles_and_pairs(hb, oracle):
     check_full(hb, oracle, synth.make_batch(32, 8, 128, kinds, ql, cl, 92, name="ticket-points"))
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 8, 64), (12, 4, 128)])
+def test_prefill_items_of_one_to_fifteen_stages(hb, oracle, Hq, Hkv, D):
+    """The prefill loop takes 32-key stages in pairs out of a ring of four: items of every small stage count
+    (odd and even, with whole and partly filled last stages) follow each other, several per workgroup."""
+    rng = np.random.default_rng(96)
+    kinds, ql, cl = [], [], []
+    for rep in range(20):
+        for stages in range(1, 16):
+            q = int(rng.integers(1, 33)) if rep % 2 else 32
+            kinds.append(PREFILL); ql.append(q); cl.append(max(q, 32 * stages - (int(rng.integers(0, 32)) if rep % 3 else 0)))
+    check_full(hb, oracle, synth.make_batch(Hq, Hkv, D, kinds, ql, cl, 97, name=f"stages-{D}"))
+
+
+@pytest.mark.parametrize("step", [0.02, 0.3, 40.0, -0.3])
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (4, 4, 64)])
+def test_scores_that_grow_along_the_context(hb, oracle, Hq, Hkv, D, step):
+    """The softmax keeps a reference exponent that is raised only when weights outgrow it: scores that rise by
+    `step` per token (slowly, past 2^8 within a few stages, by thousands per stage) or fall, on chunks whose
+    first stage is masked, whole, or in another split of the context."""
+    b = synth.make_batch(Hq, Hkv, D, [PREFILL, PREFILL, DECODE, PREFILL], [70, 200, 1, 33], [70, 1500, 900, 3000], 98)
+    u = np.where(np.arange(D) % 3 == 0, 1.0, -1.0).astype(np.float32)          # |u|^2 = D; scale * D = sqrt(D)
+    for r in range(b.num_requests):
+        for t in range(int(b.ctx_len[r])):
+            page = b.bt_pages[b.bt_indptr[r] + t // 16]
+            k = b.pool[page, :, 0].reshape(Hkv, D // 16, 16, 16)
+            k[:, :, t % 16, :] = synth.f32_to_bf16_bits(u * np.float32(step * t / np.sqrt(D))).reshape(D // 16, 16)
+    b.q[...] = synth.f32_to_bf16_bits(u)
+    check_full(hb, oracle, b)
+
+
 def test_merge_of_two_to_sixty_splits(hb, oracle):
     """The merge launch has one body per slot count (2, 4, 8) and a wide form above 8 splits: decode
     contexts cut into 2, 3, 4, 5, 8, 9, 16, about 40 and about 60 pieces, and a prompt chunk on a
