@@ -303,7 +303,8 @@ class DescHeader(ctypes.Structure):
                 ("total_bytes", ctypes.c_uint64), ("workspace_bytes", ctypes.c_uint64),
                 ("ws_off_ml", ctypes.c_uint64), ("max_group_rows", ctypes.c_int32),
                 ("n_units", ctypes.c_int32), ("off_units", ctypes.c_uint32), ("n_runs", ctypes.c_int32),
-                ("off_runs", ctypes.c_uint32), ("queue_classes", ctypes.c_uint32), ("reserved", ctypes.c_uint32 * 2)]
+                ("off_runs", ctypes.c_uint32), ("queue_classes", ctypes.c_uint32),
+                ("deal_balanced", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
 
 
 ITEM_DTYPE = np.dtype([(n, np.int32) for n in ("type", "req", "group", "slot_row", "h0", "hn", "row0", "nrows",

@@ -4,7 +4,7 @@
 #include <stdint.h>
 
 #define HFX_DESC_MAGIC 0x31584648u /* "HFX1" */
-#define HFX_DESC_VERSION 15u
+#define HFX_DESC_VERSION 16u
 #define HFX_PAGE 16
 #define HFX_WG_THREADS 256
 #define HFX_PLAN_WGS 512         /* planning width: 256 compute units x 2 resident workgroups */
@@ -39,7 +39,8 @@ struct HfxHeader {
   int32_t n_runs;               /* append runs: the new tokens of the step, cut at page boundaries */
   uint32_t off_runs;
   uint32_t queue_classes;       /* 1 or HFX_QUEUE_CLASSES: how many classes the queue positions past the dealt ones fall into */
-  uint32_t reserved[2];
+  uint32_t deal_balanced;       /* the two dealt rounds pair large items with small ones (see the kernel) instead of running straight */
+  uint32_t reserved;
 };
 
 struct HfxReq {

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 
 namespace hfx {
 
@@ -15,19 +16,25 @@ namespace hfx {
 // order the queue and size the splits.
 static const double kDecodeBytesPerNs = 12.0;
 static const double kPrefillFlopsPerNs = 2000.0;
+static const double kPrefillFlopsPerNs64 = 1400.0;   // 64-wide heads, in the decisions about cuts: twice the exponentials per MFMA
 static const double kMinItemNs = 32000.0;
 static const int kMinDecodeTokens = 128;
 static const int kMinPrefillKeys = 256;
 static const int kMaxSplits = 64;
 static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of D + 2 floats per q-head)
 // Which prefill-dominated steps get a queue per die (see the queue order in plan_step), by items per
-// workgroup of the planning width.  Steps of many short items gain nothing from it (their time
-// goes into item hand-overs, not into key traffic).  In the first rounds all workgroups of a die
-// start together, and those that read the same keys then move in step: every cache line is a
-// first touch for all of them at once, its full memory latency shows in each, and a tile takes up
-// to twice as long as when neighbours run a little ahead and leave the lines in the L2.  Later
-// rounds start staggered.  Steps of fewer than three rounds therefore keep the plain order.
-static const int kClassRoundsMin = 3;
+// workgroup of the planning width; besides, the items have to be long on average (kMinItemNs).  Steps
+// of many short items gain nothing from it: their time goes into item hand-overs, not into key traffic, and
+// the dies end at different times (six tasks' short prompts, 17 each: 219 us with classes, about
+// 131 without).  In the first rounds all workgroups of a die start together, and those that read the same keys
+// then move in step: every cache line is a first touch for all of them at once.  Later
+// rounds start staggered.  What it buys is HBM traffic (0.6 instead of 1.06 GB on the prefill-heavy
+// mixed step), at a time within 1 % either way from four rounds on; below that the dies' unequal ends show
+// (4096 tokens, three rounds: 223 us with classes, 155 without).
+static const int kClassRoundsMin = 4;
+static const double kLongStepNs = 400000.0; // steps of less time than this are cut by trying what the cut leads to ...
+static const double kLoneShare = 0.575;      // time of an item alone on its CU, over its time beside another
+static const int64_t kCutMaxTiles = 8192;   // ... if they have no more row tiles (the host time of the trial)
 static const int kClassRoundsMax = 8;
 static const int kFitRounds = 6;           // steps with fewer rounds of prefill items than this get whole rounds
 static const int kPrefillItemsPerWg = 2;   // prefill partials are 128 rows: split only where balance needs it
@@ -60,25 +67,127 @@ static int64_t pairs_in(int64_t p, int64_t r0, int64_t r1, int64_t kb, int64_t k
   return n * (p + 1 - kb) + (i_lo + i_hi - 1) * n / 2 + (r1 - i_hi) * (ke - kb);
 }
 
-// How the keys a row tile (chunk rows [r0, r1) behind p earlier tokens) sees are cut into items
-// of at most about cap_ns each: nsplit pieces of tiles_per key tiles (the last may be shorter).
-static void prefill_splits(int64_t p, int64_t r0, int64_t r1, int D, int hpw, double cap_ns, int64_t* nsplit_out,
-                           int64_t* tiles_per_out) {
+// How the keys a row tile (chunk rows up to r1 behind p earlier tokens) sees are cut into items of at
+// most about cap_ns each: nsplit pieces of tiles_per key tiles (the last may be shorter).  What counts
+// is the time a workgroup spends, which is that of four full wavefronts however few rows the tile has.
+// Returns the time of the whole tile.
+static double prefill_splits(int64_t p, int64_t r1, int D, double cap_ns, int64_t* nsplit_out, int64_t* tiles_per_out) {
   const int64_t kmax = p + r1;
   const int64_t ntiles = (kmax + HFX_KEY_TILE - 1) / HFX_KEY_TILE;
-  const double ns_all = 4.0 * D * hpw * (double)pairs_in(p, r0, r1, 0, kmax) / kPrefillFlopsPerNs;
-  int64_t nsplit = (int64_t)std::ceil(ns_all / cap_ns);
-  nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, kMaxSplits));
+  const double ns_all = 4.0 * D * 4 * HFX_WAVE_ROWS * (double)kmax / (D == 64 ? kPrefillFlopsPerNs64 : kPrefillFlopsPerNs);
+  int64_t nsplit = (int64_t)std::min(std::ceil(ns_all / cap_ns), (double)kMaxSplits);
+  nsplit = std::max<int64_t>(1, nsplit);
   int64_t tiles_per = (ntiles + nsplit - 1) / nsplit;
   tiles_per = std::max<int64_t>(tiles_per, kMinPrefillKeys / HFX_KEY_TILE);
   *nsplit_out = (ntiles + tiles_per - 1) / tiles_per;
   *tiles_per_out = tiles_per;
+  return ns_all;
 }
 
 static int32_t clamp_cost(double ns) {
   if (ns < 1.0) return 1;
   if (ns > 2.0e9) return 2000000000;
   return (int32_t)ns;
+}
+
+// The cap on an item's time by which the row tiles of a step are cut along the keys.  Tiles come `mult` at
+// a time, one per head block, all alike.  `share` is the step's time when perfectly spread; no cap is
+// smaller than about half of it, which bounds the partials (about two pieces of 64 KB per workgroup).
+//
+// In a decode-dominated step the prefill items run beside the decode stream on CUs of their own (see the
+// queue order in plan_step) and only have to be done when it is: pieces of up to 0.75 of a share save
+// partials and merge work (64 decodes and two chunks of 512: 109 us at 0.6, where the later chunk's tiles
+// are cut in two, 102 at 0.75 to 1.2, where they are not).
+//
+// Prefill-dominated steps:
+// In short steps the cap is chosen by what it leads to: largest first, items go to where there is the least
+// work, an item alone on its CU runs at 1.74 times its rate, and every cut adds partials (64 KB a piece,
+// written and read: 26 ns) and the merge launch (4 us).  Not cutting at all is the common answer: whole tiles
+// fill the CUs (1500 tokens: 35 us cut, 32 whole; 4096 tokens 222 and 135; 1000 behind 3000 beside 16
+// decodes 126 and 85).  Cuts pay where there are fewer tiles than CUs (128 tokens behind 8000: 8 pieces
+// 33 us, 9 pieces 44, 4 pieces 51) or few more equal ones (2000 behind 3000 on 24 heads: 129 whole, 114 cut).
+// Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
+// expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
+// raising the cap by up to a half.
+static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
+                                    int rows_wg, double dec_ns, bool decode_dominated, Plan* P) {
+  std::vector<float>& cost = P->cut_cost;
+  double longest = 0.0, sum = 0.0;
+  int64_t pieces = 0;          // of tiles that are cut
+  auto cut = [&](double cap, bool list) {      // returns the number of items
+    int64_t count = 0;
+    cost.clear();
+    sum = 0.0;
+    pieces = 0;
+    for (int r = 0; r < R; ++r) {
+      if (kind[r] != HFX_PREFILL) continue;
+      const int64_t p = ctx_len[r] - q_len[r];
+      const int n_rt = (q_len[r] + rows_wg - 1) / rows_wg;
+      for (int rt = 0; rt < n_rt; ++rt) {
+        const int64_t r1 = std::min<int64_t>(q_len[r], (int64_t)(rt + 1) * rows_wg);
+        int64_t nsplit, tiles_per;
+        const double ns = prefill_splits(p, r1, D, cap, &nsplit, &tiles_per);
+        longest = std::max(longest, ns);
+        sum += ns * mult;
+        count += nsplit * mult;
+        if (nsplit > 1) pieces += nsplit * mult;
+        if (list) cost.insert(cost.end(), (size_t)nsplit, (float)(ns / (double)nsplit + 3000.0));
+      }
+    }
+    return count;
+  };
+  const int64_t whole_tiles = cut(1e18, false);
+  const double share = (sum + dec_ns) / HFX_PLAN_WGS;
+  double cap = std::max(share / kPrefillItemsPerWg, kMinItemNs);
+  if (decode_dominated) return std::max(cap, 0.75 * share);
+  if (longest <= cap || whole_tiles > kCutMaxTiles) return cap;
+  // The time a cap leads to.  Workgroups and CUs are taken in sets that get the same items: as many as the
+  // common divisor of their number and `mult`.
+  int set = 1;
+  while (mult % (2 * set) == 0 && 2 * set <= HFX_PLAN_WGS / 2) set *= 2;
+  std::vector<float>& load = P->cut_load;
+  auto time_of = [&](double cap) {
+    const bool queue = cut(cap, true) > HFX_PLAN_WGS;
+    std::sort(cost.begin(), cost.end(), std::greater<float>());
+    // up to one round: a CU's workgroups get items that fit; more: workgroups come back for the next item
+    load.assign((size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set), 0.f);        // a heap, least loaded first
+    for (size_t i = 0; i < cost.size(); ++i)
+      for (int k = 0; k < mult / set; ++k) {
+        std::pop_heap(load.begin(), load.end(), std::greater<float>());
+        load.back() += queue ? cost[i] : 0.5f * cost[i];
+        std::push_heap(load.begin(), load.end(), std::greater<float>());
+      }
+    double t = std::max((double)*std::max_element(load.begin(), load.end()), share);
+    if (queue) t = share + kLoneShare * (t - share);       // what is left at the end has its CU to itself
+    else t = std::max(t, kLoneShare * (double)cost[0]);
+    return pieces > 0 ? t + 4000.0 + 26.0 * (D / 128.0) * (double)pieces : t;
+  };
+  double best_cap = 1e18, best = time_of(best_cap);
+  if (share < kLongStepNs) {
+    for (const double f : {2.1, 1.45, 1.0, 0.7, 0.52}) {
+      const double c = std::max(f * share, 0.5 * kMinItemNs);
+      if (c >= longest) continue;
+      const double t = time_of(c);
+      // a cut has to promise a tenth, which is about what the estimate is worth, and costs workspace
+      // (the fixed workspace keeps room for the partials, and a quarter of it for those of decodes)
+      if (t < 0.9 * best && (double)pieces * 4 * HFX_WAVE_ROWS * (4.0 * D + 8.0) <= 0.75 * HFX_STATIC_WS_BYTES) {
+        best = t;
+        best_cap = c;
+      }
+      if (c <= 0.5 * kMinItemNs) break;
+    }
+    return best_cap;
+  }
+  const int64_t n0 = cut(cap, false), whole = n0 / HFX_PLAN_WGS * HFX_PLAN_WGS;
+  if (whole >= HFX_PLAN_WGS && n0 > whole && n0 < (int64_t)kFitRounds * HFX_PLAN_WGS && cut(1.5 * cap, false) <= whole) {
+    double lo = cap, hi = 1.5 * cap;
+    for (int it = 0; it < 12; ++it) {
+      const double mid = 0.5 * (lo + hi);
+      (cut(mid, false) <= whole ? hi : lo) = mid;
+    }
+    cap = hi;
+  }
+  return best <= time_of(cap) ? best_cap : cap;
 }
 
 hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
@@ -135,49 +244,11 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   double rounds = std::floor(dec_ns / (HFX_PLAN_WGS * kMinItemNs));
   rounds = std::min<double>(std::max(rounds, 1.0), kDecodeItemsPerWg);
   const double cap_ns = std::max(dec_ns / (HFX_PLAN_WGS * rounds), kMinItemNs);
-  double cap_prefill_ns = std::max(total_ns / (HFX_PLAN_WGS * kPrefillItemsPerWg), kMinItemNs);
-  // In a decode-dominated step the prefill items run beside the decode stream on CUs of their own
-  // (see the queue order below) and only have to be done when it is: pieces of up to 0.6 of the
-  // step's expected duration save partials and merge work (1 % on the Llama-8B-shaped mixed step;
-  // at 0.75, unsplit there, the longest item starts to decide the step).
-  if (dec_ns > pre_ns) cap_prefill_ns = std::max(cap_prefill_ns, 0.6 * total_ns / HFX_PLAN_WGS);
-
   const int ngc = kv_heads_per_item(Hkv);
   const int hpw = q_heads_per_item(G);
   const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
-  // A prefill-dominated step of few, about equally expensive items per workgroup lasts a whole
-  // number of items: 2.25 items per workgroup take as long as 3.  Where the cut above leaves a
-  // partly filled last round, the cap is raised (by up to a half) to the smallest value at which
-  // the prefill items fill whole rounds of the planning width.
-  if (pre_ns > dec_ns) {
-    auto count_items = [&](double cap) {
-      int64_t count = 0;
-      for (int r = 0; r < R; ++r) {
-        if (kind[r] != HFX_PREFILL) continue;
-        const int64_t p = ctx_len[r] - q_len[r];
-        const int n_rt = (q_len[r] + rows_wg - 1) / rows_wg;
-        for (int rt = 0; rt < n_rt; ++rt) {
-          const int64_t r0 = (int64_t)rt * rows_wg, r1 = std::min<int64_t>(q_len[r], r0 + rows_wg);
-          int64_t nsplit, tiles_per;
-          prefill_splits(p, r0, r1, D, hpw, cap, &nsplit, &tiles_per);
-          count += nsplit * Hkv * (G / hpw);
-        }
-      }
-      return count;
-    };
-    const int64_t n0 = count_items(cap_prefill_ns);
-    const int64_t whole = n0 / HFX_PLAN_WGS * HFX_PLAN_WGS;
-    if (whole >= HFX_PLAN_WGS && n0 > whole && n0 < (int64_t)kFitRounds * HFX_PLAN_WGS) {
-      double lo = cap_prefill_ns, hi = 1.5 * cap_prefill_ns;   // count(lo) > whole; is count(hi) <= whole?
-      if (count_items(hi) <= whole) {
-        for (int it = 0; it < 12; ++it) {
-          const double mid = 0.5 * (lo + hi);
-          (count_items(mid) <= whole ? hi : lo) = mid;
-        }
-        cap_prefill_ns = hi;
-      }
-    }
-  }
+  const double cap_prefill_ns =
+      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, rows_wg, dec_ns, dec_ns > pre_ns, &P) : kMinItemNs;
 
   int64_t rows = 0;
   std::vector<int32_t>& split_cost = P.split_cost;
@@ -232,7 +303,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         const int64_t r0 = (int64_t)rt * rows_wg, r1 = std::min<int64_t>(q.q_len, r0 + rows_wg);
         const int64_t kmax = p + r1;
         int64_t nsplit, tiles_per;
-        prefill_splits(p, r0, r1, D, hpw, cap_prefill_ns, &nsplit, &tiles_per);
+        prefill_splits(p, r1, D, cap_prefill_ns, &nsplit, &tiles_per);
         split_cost.resize((size_t)nsplit);
         for (int64_t s = 0; s < nsplit; ++s) {
           const int64_t kb = s * tiles_per * HFX_KEY_TILE, ke = std::min<int64_t>(kmax, (s + 1) * tiles_per * HFX_KEY_TILE);
@@ -311,6 +382,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     std::vector<uint32_t>& order = P.order;
     order.resize(n);
     P.queue_classes = 1;
+    P.deal_balanced = !(dec_ns > pre_ns && pre_ns > 0.0);   // the layout below is by workgroup
     if (dec_ns > pre_ns && pre_ns > 0.0) {
       // A step whose decode work outweighs its prefill work.  The first two items of workgroup b
       // are queue positions b and b + HFX_PLAN_WGS, and workgroups b and b + HFX_PLAN_WGS/2 share a
@@ -346,6 +418,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         for (size_t k = 0; k < kBlockItems && pi < pre.size(); ++k) order[o++] = pre[pi++];
       }
     } else if (pre_ns > 0.0 && n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
+               total_ns >= kMinItemNs * (double)n &&
                pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {
       // A step whose prefill work outweighs its decode work.  Many prefill items read the same
       // keys: all row tiles (and q-head blocks) of one request and kv-head that hold the same
@@ -483,6 +556,7 @@ void layout_blob(const hfx_shape* shape, const Plan& P, HfxHeader* h) {
   h->n_bt = P.n_bt;
   h->n_ctrl = 16;
   h->queue_classes = (uint32_t)P.queue_classes;
+  h->deal_balanced = (uint32_t)P.deal_balanced;
   h->max_group_rows = 0;
   for (const HfxGroup& g : P.groups) h->max_group_rows = std::max(h->max_group_rows, g.rows_per_split);
   uint64_t off = align_up(sizeof(HfxHeader), 256);

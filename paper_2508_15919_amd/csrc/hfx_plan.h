@@ -16,6 +16,7 @@ struct Plan {
   std::vector<HfxUnit> units;
   int32_t total_q = 0, n_bt = 0, n_partial_rows = 0, n_decode_items = 0, n_prefill_items = 0, n_runs = 0;
   int32_t queue_classes = 1;            // 1: plain queue; HFX_QUEUE_CLASSES: one list per die, interleaved by position
+  int32_t deal_balanced = 0;            // see HfxHeader
   // scratch of plan_step, kept so that a reused Plan allocates nothing once it has grown
   std::vector<uint64_t> sort_keys;
   std::vector<uint32_t> order;          // queue position -> index into items
@@ -26,6 +27,7 @@ struct Plan {
   std::vector<int64_t> unit_cost;
   std::vector<uint32_t> unit_fill, unit_start;
   std::vector<uint64_t> unit_keys;
+  std::vector<float> cut_cost, cut_load;   // trial of a cut: item times, CU loads
 };
 
 hfx_status check_shape(const hfx_shape* shape);

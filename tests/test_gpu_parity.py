@@ -215,6 +215,19 @@ def test_prefill_items_of_one_to_fifteen_stages(hb, oracle, Hq, Hkv, D):
     check_full(hb, oracle, synth.make_batch(Hq, Hkv, D, kinds, ql, cl, 97, name=f"stages-{D}"))
 
 
+@pytest.mark.parametrize("n_items", [255, 256, 257, 300, 511, 512, 513, 770, 1023, 1024, 1025, 1300])
+def test_every_item_is_dealt_once(hb, oracle, n_items):
+    """The first two tickets of a workgroup are a permutation of the queue's first positions that depends on
+    the number of items: one item per request (one kv-head, at most 32 rows), around the widths where it changes."""
+    rng = np.random.default_rng(n_items)
+    ql = rng.integers(1, 33, n_items)
+    cl = ql + rng.integers(0, 100, n_items)
+    b = synth.make_batch(4, 1, 64, [PREFILL] * n_items, ql, cl, 99, name=f"deal-{n_items}")
+    d = hb.parse_desc(hb.DeviceStep(b).host_desc.numpy())["header"]
+    assert d.n_items == n_items and d.deal_balanced == 1
+    check_full(hb, oracle, b)
+
+
 @pytest.mark.parametrize("step", [0.02, 0.3, 40.0, -0.3])
 @pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (4, 4, 64)])
 def test_scores_that_grow_along_the_context(hb, oracle, Hq, Hkv, D, step):

@@ -256,6 +256,40 @@ def test_queue_per_die_and_whole_rounds(lib):
     assert fill(b)["header"].queue_classes == 1
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 1, 128), (24, 8, 128), (32, 4, 64), (16, 16, 128)])
+@pytest.mark.parametrize("q,prior", [(5, 20000), (100, 8000), (777, 0), (500, 3000), (1500, 0), (992, 2000), (4096, 0)])
+def test_cut_of_a_single_prompt(lib, Hq, Hkv, D, q, prior):
+    """The cut of a prompt's row tiles along the keys (whole where tiles fill the CUs, pieces where there are
+    fewer): every pair covered once, and bounded partials."""
+    b = lengths_only(Hq, Hkv, D, [PREFILL, PREFILL], [q, 40], [q + prior, 40])
+    d = fill(b)
+    check_coverage(b, d)
+    assert d["header"].deal_balanced == 1 and d["header"].workspace_bytes <= 48 << 20
+
+
+def test_partials_stay_bounded_where_tiles_are_nearly_empty(lib):
+    """Chunks of one row behind long contexts take the time of full tiles: the caps follow that time, or such
+    a step would be cut into pieces without number."""
+    for decodes in (0, 400):
+        b = lengths_only(32, 8, 128, [PREFILL] * 200 + [DECODE] * decodes, [1] * (200 + decodes), [30000] * 200 + [9000] * decodes)
+        d = fill(b)
+        assert d["header"].n_prefill_items <= 200 * 8 + 2048
+
+
+@pytest.mark.parametrize("rows", [1, 8, 32])
+def test_cut_goes_by_the_time_of_a_tile_not_by_its_rows(lib, rows):
+    """A tile of few rows takes as long as a full one: it is cut into as many pieces."""
+    b = lengths_only(32, 8, 128, [PREFILL], [rows], [rows + 12968])
+    assert fill(b)["header"].n_prefill_items == fill(lengths_only(32, 8, 128, [PREFILL], [32], [13000]))["header"].n_prefill_items
+
+
+def test_dealing_is_straight_where_the_layout_is_by_workgroup(lib):
+    b = lengths_only(32, 8, 128, [DECODE] * 64 + [PREFILL], [1] * 64 + [256], [3000] * 64 + [256])
+    assert fill(b)["header"].deal_balanced == 0
+    b = lengths_only(32, 8, 128, [DECODE] * 64, [1] * 64, [3000] * 64)
+    assert fill(b)["header"].deal_balanced == 1
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(4, 4, 64), (2, 2, 128), (16, 1, 64), (12, 4, 128), (6, 2, 64)])
 def test_planner_head_layouts_and_ragged_chunks(lib, Hq, Hkv, D):
     b = lengths_only(Hq, Hkv, D, [PREFILL, DECODE, PREFILL, DECODE, PREFILL], [1, 1, 33, 1, 130],
