@@ -183,8 +183,7 @@ hfx_status hfx_gather_kv(const hfx_shape* shape, const void* kv_pool, const void
   if (st != HFX_OK) return st;
   if (request < 0 || request >= h.num_requests) return HFX_ERR_LEN;
   const HfxReq* reqs = reinterpret_cast<const HfxReq*>(static_cast<const char*>(host_desc) + h.off_req);
-  const long elements = (long)reqs[request].ctx_len * h.num_kv_heads * h.head_dim;
-  if (hfx::launch_gather_kv(device_desc, kv_pool, request, elements, k_out, v_out,
+  if (hfx::launch_gather_kv(h, reqs[request].ctx_len, device_desc, kv_pool, request, k_out, v_out,
                             static_cast<hipStream_t>(stream)) != hipSuccess)
     return HFX_ERR_DEVICE;
   return HFX_OK;

@@ -12,8 +12,8 @@ hipError_t launch_mixed_attention(const HfxHeader& header, int grid, void* desc,
 // Device address, on the current device, of the library's fixed workspace of HFX_STATIC_WS_BYTES
 // (looked up once per device, then cached).
 hipError_t static_workspace(void** ptr);
-hipError_t launch_gather_kv(const void* desc, const void* pool, int request, long elements, void* k_out,
-                            void* v_out, hipStream_t stream);
+hipError_t launch_gather_kv(const HfxHeader& h, int n_tokens, const void* desc, const void* pool, int request,
+                            void* k_out, void* v_out, hipStream_t stream);
 
 hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_new, const void* v_new, void* pool,
                             hipStream_t stream);

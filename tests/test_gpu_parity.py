@@ -113,6 +113,28 @@ def test_gather_is_bit_exact(hb, oracle):
             assert np.array_equal(k, ok) and np.array_equal(v, ov), (b.name, r)
 
 
+@pytest.mark.parametrize("Hkv,D,ctx", [(8, 128, [1, 15, 16, 17, 300]), (1, 128, [33, 16]), (2, 64, [1, 47, 64]),
+                                       (4, 64, [31, 129]), (8, 64, [16384 + 17])])
+@pytest.mark.parametrize("offset", [0, 8, 1])
+def test_gather_at_page_edges_and_alignments(hb, oracle, Hkv, D, ctx, offset):
+    """Part pages, more (page, head) pairs than workgroups, outputs that start 16 bytes or one element into
+    their buffer (the latter take the element-wise kernel); what surrounds the output stays as it was."""
+    import torch
+    b = synth.make_batch(8, Hkv, D, [DECODE] * len(ctx), [1] * len(ctx), ctx, 31)
+    step = hb.DeviceStep(b)
+    for r, c in enumerate(ctx):
+        n = c * Hkv * D
+        out = [torch.full((n + 64,), 0x5a5a, dtype=torch.int16, device=step.device) for _ in range(2)]
+        k, v = (o[offset:offset + n] for o in out)
+        hb.hfx_gather_kv(step.shape, step.pool, step.host_desc, step.device_desc, r, k, v)
+        torch.cuda.synchronize()
+        ref = oracle.gather_kv(Hkv, D, b.num_pages, b.ctx_len, b.bt_indptr, b.bt_pages, b.pool, r)
+        for o, e in zip(out, ref):
+            o = o.cpu().numpy().view(np.uint16)
+            assert np.array_equal(o[offset:offset + n], e.reshape(-1)), (r, c)
+            assert (o[:offset] == 0x5a5a).all() and (o[offset + n:] == 0x5a5a).all(), (r, c)
+
+
 def test_descriptor_serves_repeated_launches(hb):
     import torch
     b = synth.config(4, 0.12)
