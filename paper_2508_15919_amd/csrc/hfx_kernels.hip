@@ -1249,74 +1249,59 @@ __global__ void gather_kv_unaligned_kernel(const char* desc, const uint16_t* poo
   }
 }
 
-// KV append: one workgroup per (run, kv-head), a run being the new tokens of one request that fall
-// into one page (at most 16 consecutive slots).  The tokens' K and V rows for the head are read in
-// whole rows into LDS and leave in the pool's block order: a K piece of 16 dimensions is 32
-// contiguous bytes per slot, and a V row (one dimension) gets its run of slots as one contiguous
-// piece -- stored token by token, the dimension-major V block took one 2-byte request per
-// (token, dimension), which was most of the launch.  D threads; rows are padded by one word in LDS
-// so that a column walk does not stay on one bank.
+// KV append: one workgroup of 2 D threads per (run, kv-head), a run being the new tokens of one request that
+// fall into one page (at most 16 consecutive slots).  A thread takes one 16-byte piece of a token's key
+// row and one of its value row, both loads at once.  Keys go straight to the pool's block order (four
+// slots are 128 contiguous bytes there); values are dimension-major in the pool and turn round in LDS, so that
+// a row of the block (one dimension) gets its run of slots as one contiguous piece -- stored token by token,
+// it took one 2-byte request per (token, dimension), which was most of the launch.  Bound: HBM, 4 D bytes a
+// token and head each way.  (8224 tokens of long chunks, 8 kv-heads, 67 MB: 11.4 us a call, 5.9 TB/s; with 4-byte
+// loads in a loop and both halves through LDS, 12.7.  36940 tokens of short prompts, 303 MB: 68.7 and 72.4 us.)
 template <int D>
-__global__ __launch_bounds__(D) void append_kv_kernel(const HfxRun* __restrict__ runs, int Hkv,
-                                                      const uint16_t* __restrict__ k_new,
-                                                      const uint16_t* __restrict__ v_new,
-                                                      uint16_t* __restrict__ pool) {
-  constexpr int LD = D + 2;                       // LDS row stride in elements
-  __shared__ uint16_t sk[HFX_PAGE * LD];
-  __shared__ uint16_t sv[HFX_PAGE * LD];
-  const HfxRun run = runs[blockIdx.x];
-  const int g = blockIdx.y;
-  const int tid = threadIdx.x;
-  // rows in: thread t takes 2 elements of each token's row (4-byte loads, a row is D*2 bytes contiguous)
-  for (int i = tid; i < run.n * (D / 2); i += D) {
-    const int tok = i / (D / 2), e2 = i % (D / 2);
-    const long src = ((long)(run.row0 + tok) * Hkv + g) * D + e2 * 2;
-    *reinterpret_cast<uint32_t*>(&sk[tok * LD + e2 * 2]) = *reinterpret_cast<const uint32_t*>(k_new + src);
-    *reinterpret_cast<uint32_t*>(&sv[tok * LD + e2 * 2]) = *reinterpret_cast<const uint32_t*>(v_new + src);
+__global__ __launch_bounds__(2 * D) void append_kv_kernel(const HfxRun* __restrict__ runs, int n_runs,
+                                                          const uint16_t* __restrict__ k_new,
+                                                          const uint16_t* __restrict__ v_new,
+                                                          uint16_t* __restrict__ pool) {
+  constexpr int LD = D + 8;                       // LDS row stride in elements
+  __shared__ __attribute__((aligned(16))) uint16_t sv[HFX_PAGE * LD];
+  const int index = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+  if (index >= n_runs) return;
+  const HfxRun run = runs[index];
+  const int Hkv = (int)gridDim.x, g = (int)blockIdx.x, tid = threadIdx.x;
+  uint16_t* kblk = pool + (((long)run.page * Hkv + g) * 2) * (16L * D);
+  const int tok = tid / (D / 8), piece = tid % (D / 8);
+  if (tok < run.n) {
+    const long src = ((long)(run.row0 + tok) * Hkv + g) * D + piece * 8;
+    const u32x4 kv = *reinterpret_cast<const u32x4*>(k_new + src);
+    const u32x4 vv = *reinterpret_cast<const u32x4*>(v_new + src);
+    // K block [D/16][16 slots][16]
+    *reinterpret_cast<u32x4*>(kblk + ((piece >> 1) * HFX_PAGE + run.slot0 + tok) * 16 + (piece & 1) * 8) = kv;
+    *reinterpret_cast<u32x4*>(sv + (run.slot0 + tok) * LD + piece * 8) = vv;
   }
   __syncthreads();
-  uint16_t* kblk = pool + (((long)run.page * Hkv + g) * 2) * (16L * D);
-  uint16_t* vblk = kblk + 16L * D;
-  // K block [D/16][16 slots][16]: 2 D pieces of 16 bytes, piece u = (dimension group u / 32, slot
-  // (u % 32) / 2, half u % 2); consecutive threads write consecutive pieces
+  // V block [D][16 slots]: this thread has 8 slots of dimension tid / 2; slots outside the run hold what was in
+  // LDS and are not stored
+  const int d = tid >> 1, s0 = (tid & 1) * 8;
+  uint16_t* dst = kblk + 16L * D + tid * 8;
+  const int lo = run.slot0 - s0, hi = lo + run.n;     // the run, relative to the thread's slots
+  if (lo >= 8 || hi <= 0) return;
+  uint16_t x[8];
 #pragma unroll
-  for (int u = tid; u < 2 * D; u += D) {
-    const int slot = (u % 32) / 2;
-    if (slot >= run.slot0 && slot < run.slot0 + run.n) {
-      const uint16_t* src = &sk[(slot - run.slot0) * LD + (u / 32) * 16 + (u % 2) * 8];
-      u32x4 v;
+  for (int e = 0; e < 8; ++e) x[e] = sv[(s0 + e) * LD + d];
+  if (lo <= 0 && hi >= 8) {
+    u32x4 v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const uint32_t*>(src + 2 * e);
-      *reinterpret_cast<u32x4*>(kblk + u * 8) = v;
-    }
-  }
-  // V block [D][16 slots]: a row (one dimension) is 32 bytes
-  if (run.slot0 == 0 && run.n == HFX_PAGE) {
-    // a whole page: 2 D pieces of 16 bytes, piece u = (dimension u / 2, slots 8 (u % 2) ..)
-#pragma unroll
-    for (int u = tid; u < 2 * D; u += D) {
-      const int d = u >> 1, s0 = (u & 1) * 8;
-      u32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        v[e] = (uint32_t)sv[(s0 + 2 * e) * LD + d] | ((uint32_t)sv[(s0 + 2 * e + 1) * LD + d] << 16);
-      *reinterpret_cast<u32x4*>(vblk + u * 8) = v;
-    }
+    for (int e = 0; e < 4; ++e) v[e] = (uint32_t)x[2 * e] | ((uint32_t)x[2 * e + 1] << 16);
+    *reinterpret_cast<u32x4*>(dst) = v;
   } else {
-    // part of a page: thread d writes its row's slots, two at a time where both belong to the run
-    const int d = tid;
-    uint16_t* dst = vblk + (long)d * HFX_PAGE;
-    const int lo = run.slot0, hi = run.slot0 + run.n;
+    // part of them: two at a time where both belong to the run
 #pragma unroll
-    for (int w = 0; w < HFX_PAGE / 2; ++w) {
+    for (int w = 0; w < 4; ++w) {
       const int a = 2 * w, b = 2 * w + 1;
       const bool in_a = a >= lo && a < hi, in_b = b >= lo && b < hi;
-      if (in_a && in_b)
-        *reinterpret_cast<uint32_t*>(dst + a) = (uint32_t)sv[(a - lo) * LD + d] | ((uint32_t)sv[(b - lo) * LD + d] << 16);
-      else if (in_a)
-        dst[a] = sv[(a - lo) * LD + d];
-      else if (in_b)
-        dst[b] = sv[(b - lo) * LD + d];
+      if (in_a && in_b) *reinterpret_cast<uint32_t*>(dst + a) = (uint32_t)x[a] | ((uint32_t)x[b] << 16);
+      else if (in_a) dst[a] = x[a];
+      else if (in_b) dst[b] = x[b];
     }
   }
 }
@@ -1423,13 +1408,17 @@ hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_
                             hipStream_t stream) {
   if (h.n_runs <= 0) return hipSuccess;
   const HfxRun* runs = reinterpret_cast<const HfxRun*>(static_cast<const char*>(desc) + h.off_runs);
-  const dim3 grid((unsigned)h.n_runs, (unsigned)h.num_kv_heads);
+  // the heads of a run follow each other, so that what runs at the same time reads whole token rows (11.4 us on 8224
+  // tokens, 11.7 with the runs of a head in a row); the runs fill the two slower dimensions, the first of
+  // which holds at most 65535
+  const unsigned per_z = (unsigned)std::min(h.n_runs, 32768);
+  const dim3 grid((unsigned)h.num_kv_heads, per_z, ((unsigned)h.n_runs + per_z - 1) / per_z);
   if (h.head_dim == 128)
-    hipLaunchKernelGGL(append_kv_kernel<128>, grid, dim3(128), 0, stream, runs, h.num_kv_heads,
+    hipLaunchKernelGGL(append_kv_kernel<128>, grid, dim3(256), 0, stream, runs, h.n_runs,
                        static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                        static_cast<uint16_t*>(pool));
   else
-    hipLaunchKernelGGL(append_kv_kernel<64>, grid, dim3(64), 0, stream, runs, h.num_kv_heads,
+    hipLaunchKernelGGL(append_kv_kernel<64>, grid, dim3(128), 0, stream, runs, h.n_runs,
                        static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
                        static_cast<uint16_t*>(pool));
   return hipGetLastError();

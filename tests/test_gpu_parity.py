@@ -348,6 +348,19 @@ def test_append_kv_runs_that_start_and_end_inside_pages(hb, oracle, Hq, Hkv, D):
     assert np.array_equal(step.pool.cpu().numpy().view(np.uint16), b.pool), "pool after append must match bit for bit"
 
 
+def test_append_kv_of_more_runs_than_one_grid_dimension_holds(hb, oracle):
+    import torch
+    b = synth.make_batch(1, 1, 64, [DECODE, PREFILL], [1, 16 * 32768 + 21], [37, 16 * 32768 + 30], 96, name="append-many-runs")
+    rng = np.random.default_rng(96)
+    k_new, v_new = (rng.integers(0, 1 << 16, (b.total_q, 1, 64), dtype=np.uint16) for _ in range(2))
+    step = hb.DeviceStep(b)
+    hb.hfx_append_kv(step.shape, torch.from_numpy(k_new.view(np.int16)).cuda(), torch.from_numpy(v_new.view(np.int16)).cuda(),
+                     step.pool, step.host_desc, step.device_desc, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    oracle.append_kv(1, 64, b.num_pages, b.q_len, b.ctx_len, b.bt_indptr, b.bt_pages, k_new, v_new, b.pool)
+    assert np.array_equal(step.pool.cpu().numpy().view(np.uint16), b.pool)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 1, 64), (12, 12, 128)])
 def test_copy_pages_is_bit_exact_and_attention_follows_the_pages(hb, oracle, Hq, Hkv, D):
     """A request's pages move to another pool (bit for bit, nothing else touched); attention through the
