@@ -146,8 +146,11 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
   int set = 1;
   while (mult % (2 * set) == 0 && 2 * set <= HFX_PLAN_WGS / 2) set *= 2;
   std::vector<float>& load = P->cut_load;
-  auto time_of = [&](double cap) {
+  const double merge_ns = 4000.0, piece_ns = 26.0 * (D / 128.0);
+  auto time_of = [&](double cap, double limit) {      // ... or `limit`, if it is no less
     const bool queue = cut(cap, true) > HFX_PLAN_WGS;
+    const double extra = pieces > 0 ? merge_ns + piece_ns * (double)pieces : 0.0;
+    if (share + extra >= limit) return limit;
     std::sort(cost.begin(), cost.end(), std::greater<float>());
     // up to one round: a CU's workgroups get items that fit; more: workgroups come back for the next item
     load.assign((size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set), 0.f);        // a heap, least loaded first
@@ -160,17 +163,19 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
     double t = std::max((double)*std::max_element(load.begin(), load.end()), share);
     if (queue) t = share + kLoneShare * (t - share);       // what is left at the end has its CU to itself
     else t = std::max(t, kLoneShare * (double)cost[0]);
-    return pieces > 0 ? t + 4000.0 + 26.0 * (D / 128.0) * (double)pieces : t;
+    return std::min(t + extra, limit);
   };
-  double best_cap = 1e18, best = time_of(best_cap);
+  double best_cap = 1e18, best = time_of(best_cap, 1e18);
   if (share < kLongStepNs) {
     for (const double f : {2.1, 1.45, 1.0, 0.7, 0.52}) {
       const double c = std::max(f * share, 0.5 * kMinItemNs);
       if (c >= longest) continue;
-      const double t = time_of(c);
+      const double limit = 0.9 * best;
+      if (share + merge_ns >= limit) break;
+      const double t = time_of(c, limit);
       // a cut has to promise a tenth, which is about what the estimate is worth, and costs workspace
       // (the fixed workspace keeps room for the partials, and a quarter of it for those of decodes)
-      if (t < 0.9 * best && (double)pieces * 4 * HFX_WAVE_ROWS * (4.0 * D + 8.0) <= 0.75 * HFX_STATIC_WS_BYTES) {
+      if (t < limit && (double)pieces * 4 * HFX_WAVE_ROWS * (4.0 * D + 8.0) <= 0.75 * HFX_STATIC_WS_BYTES) {
         best = t;
         best_cap = c;
       }
@@ -187,7 +192,7 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
     }
     cap = hi;
   }
-  return best <= time_of(cap) ? best_cap : cap;
+  return best <= time_of(cap, best) ? best_cap : cap;
 }
 
 hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
