@@ -594,7 +594,8 @@ __device__ __forceinline__ unsigned copy_lane_offset(int wave, int lane) {
 
 // Direct-to-LDS copy of one block: base (scalar) + voff (lane) in memory, lds + 16 * lane in LDS.  The
 // instruction has no destination register; the compiler does not know of the load, so its own
-// vector-memory waits only become stricter by it, and the ring's waits are the explicit ones below.
+// vector-memory waits only become stricter by it, and the ring's waits are the explicit ones below.  The LDS
+// address travels in m0, which the compiler may want for something of its own: hence the clobber.
 template <int D>
 __device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
   if (D == 128)
@@ -603,12 +604,12 @@ __device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsi
                  "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:2048\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:3072"
-                 :: "v"(voff), "s"(base), "s"(lds) : "memory");
+                 :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
   else
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
                  "global_load_lds_dwordx4 %0, %1\n\t"
                  "global_load_lds_dwordx4 %0, %1 offset:1024"
-                 :: "v"(voff), "s"(base), "s"(lds) : "memory");
+                 :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
 }
 
 // Workgroup barrier of the ring: this wavefront's LDS reads are done.  The compiler may move loads across

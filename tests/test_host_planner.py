@@ -412,3 +412,15 @@ def test_header_is_plain_c_and_cpp(tmp_path):
         src = tmp_path / f"use.{ext}"
         src.write_text('#include "hfxattn.h"\nint main(void) { hfx_shape s; hfx_decision d; (void)s; (void)d; return HFX_OK; }\n')
         subprocess.run([compiler, *flags, "-fsyntax-only", "-I", os.path.dirname(hdr), str(src)], check=True)
+
+
+def test_inline_assembly_declares_the_registers_it_writes():
+    """An asm statement that writes m0 says so: the compiler keeps values of its own there otherwise."""
+    src = open(os.path.join(ROOT, "paper_2508_15919_amd", "csrc", "hfx_kernels.hip")).read()
+    writes = 0
+    for stmt in re.findall(r"\basm\s+volatile\s*\((.*?)\)\s*;", src, re.S):
+        if not re.search(r"\bs_mov_b32 m0\b", stmt):
+            continue
+        writes += 1
+        assert '"m0"' in stmt.rsplit(":", 1)[1], stmt
+    assert writes == 2           # one per head dimension
