@@ -595,7 +595,11 @@ __device__ __forceinline__ unsigned copy_lane_offset(int wave, int lane) {
 // Direct-to-LDS copy of one block: base (scalar) + voff (lane) in memory, lds + 16 * lane in LDS.  The
 // instruction has no destination register; the compiler does not know of the load, so its own
 // vector-memory waits only become stricter by it, and the ring's waits are the explicit ones below.  The LDS
-// address travels in m0, which the compiler may want for something of its own: hence the clobber.
+// address travels in m0: the compiler reserves that register but merges its own settings of it where it sees no
+// other write between them, so the write is declared.  (Its warning that a clobber does not save a
+// reserved register is switched off: nothing lives in m0 across a statement.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int D>
 __device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
   if (D == 128)
@@ -611,6 +615,7 @@ __device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsi
                  "global_load_lds_dwordx4 %0, %1 offset:1024"
                  :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // Workgroup barrier of the ring: this wavefront's LDS reads are done.  The compiler may move loads across
 // the barrier builtin, which claims no memory effect, so the empty asm on both sides holds them.
