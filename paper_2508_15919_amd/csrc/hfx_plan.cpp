@@ -67,21 +67,22 @@ static int64_t pairs_in(int64_t p, int64_t r0, int64_t r1, int64_t kb, int64_t k
   return n * (p + 1 - kb) + (i_lo + i_hi - 1) * n / 2 + (r1 - i_hi) * (ke - kb);
 }
 
-// How the keys a row tile (chunk rows up to r1 behind p earlier tokens) sees are cut into items of at
-// most about cap_ns each: nsplit pieces of tiles_per key tiles (the last may be shorter).  What counts
-// is the time a workgroup spends, which is that of four full wavefronts however few rows the tile has.
-// Returns the time of the whole tile.
-static double prefill_splits(int64_t p, int64_t r1, int D, double cap_ns, int64_t* nsplit_out, int64_t* tiles_per_out) {
-  const int64_t kmax = p + r1;
+// Time of a row tile that sees `keys` keys.  What counts is the time a workgroup spends, which is that of
+// four full wavefronts however few rows the tile has.
+static double tile_ns(int D, int64_t keys) {
+  return 4.0 * D * 4 * HFX_WAVE_ROWS * (double)keys / (D == 64 ? kPrefillFlopsPerNs64 : kPrefillFlopsPerNs);
+}
+
+// How the kmax keys a row tile of ns_all sees are cut into items of at most about cap_ns each: nsplit pieces
+// of tiles_per key tiles (the last may be shorter).
+static void prefill_splits(int64_t kmax, double ns_all, double cap_ns, int64_t* nsplit_out, int64_t* tiles_per_out) {
   const int64_t ntiles = (kmax + HFX_KEY_TILE - 1) / HFX_KEY_TILE;
-  const double ns_all = 4.0 * D * 4 * HFX_WAVE_ROWS * (double)kmax / (D == 64 ? kPrefillFlopsPerNs64 : kPrefillFlopsPerNs);
   int64_t nsplit = (int64_t)std::min(std::ceil(ns_all / cap_ns), (double)kMaxSplits);
   nsplit = std::max<int64_t>(1, nsplit);
   int64_t tiles_per = (ntiles + nsplit - 1) / nsplit;
   tiles_per = std::max<int64_t>(tiles_per, kMinPrefillKeys / HFX_KEY_TILE);
   *nsplit_out = (ntiles + tiles_per - 1) / tiles_per;
   *tiles_per_out = tiles_per;
-  return ns_all;
 }
 
 static int32_t clamp_cost(double ns) {
@@ -92,7 +93,7 @@ static int32_t clamp_cost(double ns) {
 
 // The cap on an item's time by which the row tiles of a step are cut along the keys.  Tiles come `mult` at
 // a time, one per head block, all alike.  `share` is the step's time when perfectly spread; no cap is
-// smaller than about half of it, which bounds the partials (about two pieces of 64 KB per workgroup).
+// smaller than about half of it.  What the cut needs of workspace is bounded afterwards (cap_within_workspace).
 //
 // In a decode-dominated step the prefill items run beside the decode stream on CUs of their own (see the
 // queue order in plan_step) and only have to be done when it is: pieces of up to 0.75 of a share save
@@ -126,7 +127,8 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
       for (int rt = 0; rt < n_rt; ++rt) {
         const int64_t r1 = std::min<int64_t>(q_len[r], (int64_t)(rt + 1) * rows_wg);
         int64_t nsplit, tiles_per;
-        const double ns = prefill_splits(p, r1, D, cap, &nsplit, &tiles_per);
+        const double ns = tile_ns(D, p + r1);
+        prefill_splits(p + r1, ns, cap, &nsplit, &tiles_per);
         longest = std::max(longest, ns);
         sum += ns * mult;
         count += nsplit * mult;
@@ -195,67 +197,85 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
   return best <= time_of(cap, best) ? best_cap : cap;
 }
 
-hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
-                     const int32_t* ctx_len, Plan* out) {
-  hfx_status st = check_shape(shape);
-  if (st != HFX_OK) return st;
-  if (!kind || !q_len || !ctx_len || !out) return HFX_ERR_NULL;
-  if (R < 1) return HFX_ERR_SHAPE;
-  const int Hq = shape->num_q_heads, Hkv = shape->num_kv_heads, D = shape->head_dim;
-  const int G = Hq / Hkv;
+// Partial rows of a cut of the step's row tiles by cap: 4 * HFX_WAVE_ROWS for every piece of a tile that is cut.
+// tile_time(p, r0, r1) is the time of the tile of chunk rows [r0, r1) behind p earlier tokens.
+template <typename F>
+static int64_t cut_rows(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int rows_wg,
+                        double cap, F tile_time, int64_t* n_items = nullptr) {
+  int64_t pieces = 0, count = 0;
+  for (int r = 0; r < R; ++r) {
+    if (kind[r] != HFX_PREFILL) continue;
+    const int64_t p = ctx_len[r] - q_len[r];
+    for (int64_t r0 = 0; r0 < q_len[r]; r0 += rows_wg) {
+      const int64_t r1 = std::min<int64_t>(q_len[r], r0 + rows_wg);
+      int64_t nsplit, tiles_per;
+      prefill_splits(p + r1, tile_time(p, r0, r1), cap, &nsplit, &tiles_per);
+      count += nsplit * mult;
+      if (nsplit > 1) pieces += nsplit * mult;
+    }
+  }
+  if (n_items) *n_items = count;
+  return pieces * 4 * HFX_WAVE_ROWS;
+}
 
+// A cap >= `cap` whose partial rows, with the dec_rows of the decode items, stay inside the fixed workspace
+// (HFX_STATIC_WS_BYTES): a caller that has no other must not be refused because tiles of few rows, which take the time of
+// full ones, are cut like full ones and write as many partial rows.  More than the fixed workspace is taken only
+// where the work itself asks for it: as many rows as half a share of the step, counted in visible
+// (row, key) pairs, cuts the tiles into, in whole rounds.  (A 4096-token chunk behind 61440 on one kv-head: 72 MB,
+// two rounds of equal pieces.  32 chunks of one row behind 64000: 68 MB by time, 34 by pairs, 51 so bounded.)
+static double cap_within_workspace(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
+                                   int hpw, int rows_wg, double dec_ns, double pre_ns, int64_t dec_rows, double cap) {
+  auto by_pairs = [&](int64_t p, int64_t r0, int64_t r1) {
+    return 4.0 * D * hpw * (double)pairs_in(p, r0, r1, 0, p + r1) / kPrefillFlopsPerNs;
+  };
+  auto by_time = [&](int64_t p, int64_t, int64_t r1) { return tile_ns(D, p + r1); };
+  const double total = dec_ns + pre_ns;
+  double pair_cap = std::max(total / (HFX_PLAN_WGS * kPrefillItemsPerWg), kMinItemNs);
+  if (dec_ns > pre_ns) pair_cap = std::max(pair_cap, 0.6 * total / HFX_PLAN_WGS);
+  int64_t n = 0;
+  int64_t pair_rows = cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, pair_cap, by_pairs, &n);
+  const int64_t whole = n / HFX_PLAN_WGS * HFX_PLAN_WGS;
+  if (pre_ns > dec_ns && whole >= HFX_PLAN_WGS && n > whole && n < (int64_t)kFitRounds * HFX_PLAN_WGS) {
+    double lo = pair_cap, hi = 1.5 * pair_cap;
+    cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, hi, by_pairs, &n);
+    for (int it = 0; it < 12 && n <= whole; ++it) {
+      const double mid = 0.5 * (lo + hi);
+      int64_t n_mid = 0;
+      cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, mid, by_pairs, &n_mid);
+      (n_mid <= whole ? hi : lo) = mid;
+    }
+    if (n <= whole) pair_rows = cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, hi, by_pairs);
+  }
+  const int64_t fixed_rows = (int64_t)((HFX_STATIC_WS_BYTES - 512) / (4 * D + 8));     // 512: both parts start on 256 bytes
+  const int64_t allowed = std::max(fixed_rows - dec_rows, pair_rows);
+  double longest = 0.0;
+  for (int r = 0; r < R; ++r)
+    if (kind[r] == HFX_PREFILL) longest = std::max(longest, tile_ns(D, ctx_len[r]));
+  double lo = cap, hi = std::max(cap, longest);        // uncut tiles need no partials
+  if (cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, cap, by_time) <= allowed) return cap;
+  for (int it = 0; it < 20; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    (cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, mid, by_time) <= allowed ? hi : lo) = mid;
+  }
+  return hi;
+}
+
+// The work items of the step's requests (P.reqs), decode pieces of at most about cap_ns and prefill tiles cut
+// by cap_prefill_ns, with their merge groups; *rows: partial rows of all of them, *dec_rows: those of decode items,
+// *pre_ord: prefill requests.
+static hfx_status make_items(const hfx_shape* shape, int32_t R, double cap_ns, double cap_prefill_ns, Plan* out,
+                             int64_t* rows_out, int64_t* dec_rows_out, int64_t* pre_ord_out) {
+  const int Hkv = shape->num_kv_heads, D = shape->head_dim, G = shape->num_q_heads / Hkv;
+  const int ngc = kv_heads_per_item(Hkv);
+  const int hpw = q_heads_per_item(G);
+  const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
   Plan& P = *out;
-  P.reqs.assign((size_t)R, HfxReq());
   P.items.clear();
   P.groups.clear();
   P.item_unit.clear();
   P.item_frac.clear();
-  int64_t T = 0, nbt = 0;
-  double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work
-  for (int r = 0; r < R; ++r) {
-    if (kind[r] != HFX_DECODE && kind[r] != HFX_PREFILL) return HFX_ERR_KIND;
-    if (q_len[r] < 1 || ctx_len[r] < q_len[r]) return HFX_ERR_LEN;
-    if (kind[r] == HFX_DECODE && q_len[r] != 1) return HFX_ERR_LEN;
-    HfxReq& q = P.reqs[(size_t)r];
-    q.kind = kind[r];
-    q.q_len = q_len[r];
-    q.ctx_len = ctx_len[r];
-    q.n_pages = (int32_t)(((int64_t)ctx_len[r] + HFX_PAGE - 1) / HFX_PAGE);
-    q.bt_len = ((q.n_pages + 3) & ~3) + HFX_BT_PAD;
-    if (T > 0x7fffffff - q_len[r] || nbt > 0x7fffffff - q.bt_len) return HFX_ERR_LEN;
-    q.q_start = (int32_t)T;
-    q.bt_start = (int32_t)nbt;
-    T += q_len[r];
-    nbt += q.bt_len;
-    if (kind[r] == HFX_DECODE) {
-      dec_ns += (double)ctx_len[r] * Hkv * D * 4.0 / kDecodeBytesPerNs;
-    } else {
-      double ql = q_len[r], p = ctx_len[r] - q_len[r];
-      pre_ns += 4.0 * D * Hq * (ql * p + ql * (ql + 1) / 2) / kPrefillFlopsPerNs;
-    }
-  }
-  P.total_q = (int32_t)T;
-  P.n_bt = (int32_t)nbt;
-  int64_t n_runs = 0;   // pages touched by each request's new tokens
-  for (int r = 0; r < R; ++r)
-    n_runs += (ctx_len[r] - 1) / HFX_PAGE - (ctx_len[r] - q_len[r]) / HFX_PAGE + 1;
-  P.n_runs = (int32_t)n_runs;
-  const double total_ns = dec_ns + pre_ns;
-  // Decode pieces are sized against the decode work alone (in a step dominated by prefill they stay
-  // small and fill the gaps between the large prefill items), for a whole number of rounds of the
-  // planning width: as many rounds as fit pieces of at least the minimum size, at most
-  // kDecodeItemsPerWg.  A step with work for 2.4 rounds of minimum-size pieces is better served by
-  // two rounds of larger ones than by a third, half-empty round.
-  double rounds = std::floor(dec_ns / (HFX_PLAN_WGS * kMinItemNs));
-  rounds = std::min<double>(std::max(rounds, 1.0), kDecodeItemsPerWg);
-  const double cap_ns = std::max(dec_ns / (HFX_PLAN_WGS * rounds), kMinItemNs);
-  const int ngc = kv_heads_per_item(Hkv);
-  const int hpw = q_heads_per_item(G);
-  const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
-  const double cap_prefill_ns =
-      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, rows_wg, dec_ns, dec_ns > pre_ns, &P) : kMinItemNs;
-
-  int64_t rows = 0;
+  int64_t rows = 0, dec_rows = 0;
   std::vector<int32_t>& split_cost = P.split_cost;
   int64_t pre_ord = 0;              // prefill requests seen so far
   for (int r = 0; r < R; ++r) {
@@ -299,7 +319,10 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
           P.item_unit.push_back(kNoUnit);
           P.item_frac.push_back(0.f);
         }
-        if (nsplit > 1) rows += (int64_t)nsplit * ngc * G;
+        if (nsplit > 1) {
+          rows += (int64_t)nsplit * ngc * G;
+          dec_rows += (int64_t)nsplit * ngc * G;
+        }
       }
     } else {
       const int64_t p = q.ctx_len - q.q_len;
@@ -308,7 +331,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         const int64_t r0 = (int64_t)rt * rows_wg, r1 = std::min<int64_t>(q.q_len, r0 + rows_wg);
         const int64_t kmax = p + r1;
         int64_t nsplit, tiles_per;
-        prefill_splits(p, r1, D, cap_prefill_ns, &nsplit, &tiles_per);
+        prefill_splits(kmax, tile_ns(D, kmax), cap_prefill_ns, &nsplit, &tiles_per);
         split_cost.resize((size_t)nsplit);
         for (int64_t s = 0; s < nsplit; ++s) {
           const int64_t kb = s * tiles_per * HFX_KEY_TILE, ke = std::min<int64_t>(kmax, (s + 1) * tiles_per * HFX_KEY_TILE);
@@ -351,6 +374,77 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       ++pre_ord;
     }
     if (rows > 0x7fffffff / 2 || P.items.size() > 0x3fffffffu) return HFX_ERR_LEN;
+  }
+  *rows_out = rows;
+  *dec_rows_out = dec_rows;
+  *pre_ord_out = pre_ord;
+  return HFX_OK;
+}
+
+hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
+                     const int32_t* ctx_len, Plan* out) {
+  hfx_status st = check_shape(shape);
+  if (st != HFX_OK) return st;
+  if (!kind || !q_len || !ctx_len || !out) return HFX_ERR_NULL;
+  if (R < 1) return HFX_ERR_SHAPE;
+  const int Hq = shape->num_q_heads, Hkv = shape->num_kv_heads, D = shape->head_dim;
+  const int G = Hq / Hkv;
+
+  Plan& P = *out;
+  P.reqs.assign((size_t)R, HfxReq());
+  int64_t T = 0, nbt = 0;
+  double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work
+  for (int r = 0; r < R; ++r) {
+    if (kind[r] != HFX_DECODE && kind[r] != HFX_PREFILL) return HFX_ERR_KIND;
+    if (q_len[r] < 1 || ctx_len[r] < q_len[r]) return HFX_ERR_LEN;
+    if (kind[r] == HFX_DECODE && q_len[r] != 1) return HFX_ERR_LEN;
+    HfxReq& q = P.reqs[(size_t)r];
+    q.kind = kind[r];
+    q.q_len = q_len[r];
+    q.ctx_len = ctx_len[r];
+    q.n_pages = (int32_t)(((int64_t)ctx_len[r] + HFX_PAGE - 1) / HFX_PAGE);
+    q.bt_len = ((q.n_pages + 3) & ~3) + HFX_BT_PAD;
+    if (T > 0x7fffffff - q_len[r] || nbt > 0x7fffffff - q.bt_len) return HFX_ERR_LEN;
+    q.q_start = (int32_t)T;
+    q.bt_start = (int32_t)nbt;
+    T += q_len[r];
+    nbt += q.bt_len;
+    if (kind[r] == HFX_DECODE) {
+      dec_ns += (double)ctx_len[r] * Hkv * D * 4.0 / kDecodeBytesPerNs;
+    } else {
+      double ql = q_len[r], p = ctx_len[r] - q_len[r];
+      pre_ns += 4.0 * D * Hq * (ql * p + ql * (ql + 1) / 2) / kPrefillFlopsPerNs;
+    }
+  }
+  P.total_q = (int32_t)T;
+  P.n_bt = (int32_t)nbt;
+  int64_t n_runs = 0;   // pages touched by each request's new tokens
+  for (int r = 0; r < R; ++r)
+    n_runs += (ctx_len[r] - 1) / HFX_PAGE - (ctx_len[r] - q_len[r]) / HFX_PAGE + 1;
+  P.n_runs = (int32_t)n_runs;
+  const double total_ns = dec_ns + pre_ns;
+  // Decode pieces are sized against the decode work alone (in a step dominated by prefill they stay
+  // small and fill the gaps between the large prefill items), for a whole number of rounds of the
+  // planning width: as many rounds as fit pieces of at least the minimum size, at most
+  // kDecodeItemsPerWg.  A step with work for 2.4 rounds of minimum-size pieces is better served by
+  // two rounds of larger ones than by a third, half-empty round.
+  double rounds = std::floor(dec_ns / (HFX_PLAN_WGS * kMinItemNs));
+  rounds = std::min<double>(std::max(rounds, 1.0), kDecodeItemsPerWg);
+  const double cap_ns = std::max(dec_ns / (HFX_PLAN_WGS * rounds), kMinItemNs);
+  const int hpw = q_heads_per_item(G);
+  const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
+  const double cap_prefill_ns =
+      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, rows_wg, dec_ns, dec_ns > pre_ns, &P) : kMinItemNs;
+
+  int64_t rows = 0, dec_rows = 0, pre_ord = 0;
+  st = make_items(shape, R, cap_ns, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
+  if (st != HFX_OK) return st;
+  if (rows * (4ll * D + 8) + 512 > (int64_t)HFX_STATIC_WS_BYTES && rows > dec_rows) {
+    const double c = cap_within_workspace(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, hpw, rows_wg, dec_ns, pre_ns, dec_rows, cap_prefill_ns);
+    if (c > cap_prefill_ns) {
+      st = make_items(shape, R, cap_ns, c, &P, &rows, &dec_rows, &pre_ord);
+      if (st != HFX_OK) return st;
+    }
   }
   P.n_partial_rows = (int32_t)rows;
   // queue order: descending cost, ties in creation order: a stable radix sort (11-bit digits) of

@@ -267,6 +267,105 @@ def test_cut_of_a_single_prompt(lib, Hq, Hkv, D, q, prior):
     assert d["header"].deal_balanced == 1 and d["header"].workspace_bytes <= 48 << 20
 
 
+def workspace_of_cut_by_pairs(Hq, Hkv, D, kind, q_len, ctx_len, decode_rows):
+    """Workspace of a step whose prefill tiles are cut by the (row, key) pairs they work on: pieces of half a workgroup's
+    share of the step (0.6 of one where decodes outweigh prefills), at least 32 us, in whole rounds of 512."""
+    G = Hq // Hkv
+    hpw = 4 if G % 4 == 0 else 2 if G % 2 == 0 else 1
+    rows_wg, mult = 128 // hpw, Hkv * (G // hpw)
+    pre = kind == PREFILL
+    q, c = q_len[pre].astype(np.int64), ctx_len[pre].astype(np.int64)
+    dec_ns = float(ctx_len[~pre].sum()) * Hkv * D * 4 / 12.0
+    pre_ns = 4.0 * D * Hq * float((q * (c - q) + q * (q + 1) // 2).sum()) / 2000.0
+    n_rt = -(-q // rows_wg)
+    p = np.repeat(c - q, n_rt)
+    r0 = (np.arange(n_rt.sum()) - np.repeat(np.cumsum(n_rt) - n_rt, n_rt)) * rows_wg
+    r1 = np.minimum(np.repeat(q, n_rt), r0 + rows_wg)
+    ns = 4.0 * D * hpw * ((r1 - r0) * (p + 1) + (r0 + r1 - 1) * (r1 - r0) // 2) / 2000.0
+
+    def pieces(cap):
+        tiles = (p + r1 + 63) // 64
+        n = np.clip(np.ceil(ns / cap), 1, 64).astype(np.int64)
+        n = -(-tiles // np.maximum(-(-tiles // n), 4))
+        return int(n.sum()) * mult, int(n[n > 1].sum()) * mult
+
+    cap = max((dec_ns + pre_ns) / 1024, 32000.0)
+    if dec_ns > pre_ns:
+        cap = max(cap, 0.6 * (dec_ns + pre_ns) / 512)
+    whole = pieces(cap)[0] // 512 * 512
+    if pre_ns > dec_ns and 512 <= whole < pieces(cap)[0] < 6 * 512 and pieces(1.5 * cap)[0] <= whole:
+        lo, cap = cap, 1.5 * cap
+        for _ in range(12):
+            mid = 0.5 * (lo + cap)
+            if pieces(mid)[0] <= whole:
+                cap = mid
+            else:
+                lo = mid
+    rows = decode_rows + 128 * pieces(cap)[1]
+    return -(-rows * D * 4 // 256) * 256 + -(-rows * 8 // 256) * 256
+
+
+def check_workspace(Hq, Hkv, D, kind, q_len, ctx_len):
+    kind, q_len, ctx_len = (np.asarray(a, np.int32) for a in (kind, q_len, ctx_len))
+    shape = hb.make_shape(Hq, Hkv, D, 1 << 30)
+    ws = hb.hfx_batch_desc_sizes(shape, kind, q_len, ctx_len)[2]
+    if ws <= FIXED_WORKSPACE:
+        return ws
+    d = fill(lengths_only(Hq, Hkv, D, kind, q_len, ctx_len))
+    decode_rows = int(sum(g["nsplit"] * g["rows_per_split"] for g in d["groups"] if g["type"] == 0))
+    assert ws <= workspace_of_cut_by_pairs(Hq, Hkv, D, kind, q_len, ctx_len, decode_rows)
+    return ws
+
+
+FIXED_WORKSPACE = 64 << 20
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunks", [
+    (32, 8, 128, [(32, 1, 64000)]), (8, 1, 128, [(64, 2, 64000)]), (32, 8, 128, [(40, 40, 20000), (4, 2048, 2048)]),
+    (8, 8, 128, [(77, 2, 13424)]), (2, 2, 128, [(272, 2, 9000)]), (12, 4, 128, [(17, 300, 40000)]), (24, 8, 128, [(89, 4, 6000)])])
+def test_steps_of_few_row_chunks_fit_the_fixed_workspace(lib, Hq, Hkv, D, chunks):
+    """Tiles of few rows are cut like full ones, each piece with as many partial rows: a caller of the entry point with the
+    fixed workspace must not be refused for it."""
+    q = [n_q for n, n_q, _ in chunks for _ in range(n)]
+    c = [n_c for n, _, n_c in chunks for _ in range(n)]
+    assert check_workspace(Hq, Hkv, D, [PREFILL] * len(q), q, c) <= FIXED_WORKSPACE
+    check_coverage_of_groups(fill(lengths_only(Hq, Hkv, D, [PREFILL] * len(q), q, c)))
+
+
+def check_coverage_of_groups(d):
+    """What check_coverage says of partial rows, for steps whose (row, key) pairs are too many to list."""
+    rows = np.zeros(d["header"].n_partial_rows, np.int32)
+    for it in d["items"][d["items"]["group"] >= 0]:
+        rows[it["slot_row"]:it["slot_row"] + d["groups"][it["group"]]["rows_per_split"]] += 1
+    assert np.all(rows == 1)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_workspace_beyond_the_fixed_one_only_where_the_work_asks_for_it(lib, seed):
+    """Random steps: workspace above the fixed 64 MiB is no more than cutting by visible pairs takes, so that whatever
+    that cut lets the entry point with the fixed workspace accept, it accepts."""
+    rng = np.random.default_rng(seed)
+
+    def log_int(lo, hi):
+        return int(np.rint(np.exp(rng.uniform(np.log(lo), np.log(hi)))))
+
+    largest = 0
+    for _ in range(150):
+        Hq, Hkv, D = [(32, 8, 128), (8, 1, 128), (8, 2, 128), (24, 8, 128), (8, 8, 128), (12, 4, 128), (2, 2, 128),
+                      (16, 1, 64), (32, 8, 64)][rng.integers(9)]
+        kind, q, c = [], [], []
+        for _ in range(rng.integers(1, 4)):
+            rows, ctx, same = [(1, 8), (1, 64), (20, 500), (500, 5000)][rng.integers(4)], log_int(1000, 70000), rng.random() < 0.5
+            for _ in range(log_int(1, 100) if rows[1] < 5000 else rng.integers(1, 6)):
+                n = rows[1] // 3 if same else log_int(*rows)
+                kind.append(PREFILL); q.append(n); c.append(n + (ctx if same else log_int(1, ctx)))
+        if rng.random() < 0.5:
+            for _ in range(log_int(1, 200)):
+                kind.append(DECODE); q.append(1); c.append(log_int(20, 50000))
+        largest = max(largest, check_workspace(Hq, Hkv, D, kind, q, c))
+    assert largest > FIXED_WORKSPACE // 2
+
+
 def test_partials_stay_bounded_where_tiles_are_nearly_empty(lib):
     """Chunks of one row behind long contexts take the time of full tiles: the caps follow that time, or such
     a step would be cut into pieces without number."""
@@ -274,6 +373,7 @@ def test_partials_stay_bounded_where_tiles_are_nearly_empty(lib):
         b = lengths_only(32, 8, 128, [PREFILL] * 200 + [DECODE] * decodes, [1] * (200 + decodes), [30000] * 200 + [9000] * decodes)
         d = fill(b)
         assert d["header"].n_prefill_items <= 200 * 8 + 2048
+        assert d["header"].workspace_bytes <= FIXED_WORKSPACE
 
 
 @pytest.mark.parametrize("rows", [1, 8, 32])
