@@ -173,11 +173,12 @@ def check_coverage(b, d):
                 assert it["hn"] in (1, 2, 4) and it["nrows"] == 32 * 4 // it["hn"] and it["kb"] % 64 == 0
                 assert it["h0"] // G == (it["h0"] + it["hn"] - 1) // G, "an item stays inside one kv group"
                 r1 = min(ql, it["row0"] + it["nrows"])
+                assert it["ke"] <= p + r1
                 cover[it["h0"]:it["h0"] + it["hn"], it["row0"]:r1, it["kb"]:it["ke"]] += 1
-                # modelled cost: 4*D flops per visible pair per q-head at 2000 flops/ns, plus a fixed 3000 ns
-                rows_i = np.arange(it["row0"], r1)
-                pairs = int(np.clip(np.minimum(it["ke"], p + rows_i + 1) - it["kb"], 0, None).sum())
-                assert it["cost"] == int(4.0 * b.head_dim * it["hn"] * pairs / 2000.0 + 3000.0)
+                # modelled cost: a workgroup's time, 4*D flops per key for each of its 128 rows at 2000 flops/ns (1400
+                # where heads are 64 wide) however many of the rows exist, plus a fixed 3000 ns
+                rate = 1400.0 if b.head_dim == 64 else 2000.0
+                assert it["cost"] == int(4.0 * b.head_dim * 128 * int(it["ke"] - it["kb"]) / rate + 3000.0)
             visible = (np.arange(c)[None, :] <= (p + np.arange(ql))[:, None])
             assert np.all(cover[:, visible] == 1), "every visible pair exactly once"
         for f in ("kind", "q_len", "ctx_len", "q_start", "bt_start", "n_pages", "bt_len"):
@@ -374,6 +375,16 @@ def test_partials_stay_bounded_where_tiles_are_nearly_empty(lib):
         d = fill(b)
         assert d["header"].n_prefill_items <= 200 * 8 + 2048
         assert d["header"].workspace_bytes <= FIXED_WORKSPACE
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunks", [
+    (32, 8, 128, [(2500, 0)]), (32, 8, 128, [(4097, 0)]), (32, 8, 128, [(2049, 0)]), (32, 8, 128, [(777, 0)]), (24, 8, 128, [(1025, 0)]),
+    (32, 8, 64, [(301, 0), (1029, 700), (130, 63)]), (8, 1, 128, [(33, 900), (65, 300)])])
+def test_longest_items_come_first(lib, Hq, Hkv, D, chunks):
+    """The last tile of a prompt of 32 k + 1 tokens holds one row and sees the most keys: it takes longest, so it may not be
+    queued behind tiles that see fewer."""
+    items = fill(lengths_only(Hq, Hkv, D, [PREFILL] * len(chunks), [q for q, _ in chunks], [q + p for q, p in chunks]))["items"]
+    assert np.all(np.diff(items["ke"] - items["kb"]) <= 0)
 
 
 @pytest.mark.parametrize("rows", [1, 8, 32])
