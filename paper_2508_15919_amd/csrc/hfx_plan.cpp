@@ -75,6 +75,12 @@ static double tile_ns(int D, int64_t keys) {
   return 4.0 * D * 4 * HFX_WAVE_ROWS * (double)keys / (D == 64 ? kPrefillFlopsPerNs64 : kPrefillFlopsPerNs);
 }
 
+// Share of a row tile's four wavefronts that have rows to work on: `rows` chunk rows of hpw q-heads, a wavefront 32 rows
+// of one head.
+static double tile_busy(int hpw, int64_t rows) {
+  return 0.25 * hpw * (double)((rows + HFX_WAVE_ROWS - 1) / HFX_WAVE_ROWS);
+}
+
 // How the kmax keys a row tile of ns_all sees are cut into items of at most about cap_ns each: nsplit pieces
 // of tiles_per key tiles (the last may be shorter).
 static void prefill_splits(int64_t kmax, double ns_all, double cap_ns, int64_t* nsplit_out, int64_t* tiles_per_out) {
@@ -109,18 +115,24 @@ static int32_t clamp_cost(double ns) {
 // fill the CUs (1500 tokens: 35 us cut, 32 whole; 4096 tokens 222 and 135; 1000 behind 3000 beside 16
 // decodes 126 and 85).  Cuts pay where there are fewer tiles than CUs (128 tokens behind 8000: 8 pieces
 // 33 us, 9 pieces 44, 4 pieces 51) or few more equal ones (2000 behind 3000 on 24 heads: 129 whole, 114 cut).
+// Tiles of few rows in layouts of few q-heads per kv-head leave wavefronts without rows.  Where all such tiles start at
+// once, whole, they slow their neighbours on the CU the less; and no cut makes a step shorter than its keys take to
+// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 455 us whole, 528 in
+// two pieces each; 23 behind 8015 on 12/4 heads: 186 and 225.
 // Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
+static const double kWhole = 1e18;
 static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
-                                    int rows_wg, double dec_ns, bool decode_dominated, Plan* P) {
+                          int hpw, int rows_wg, double dec_ns, double stream_ns, bool decode_dominated, Plan* P) {
   std::vector<float>& cost = P->cut_cost;
-  double longest = 0.0, sum = 0.0;
+  double longest = 0.0, sum = 0.0, piece = 0.0;     // of the tiles; time of the longest item
   int64_t pieces = 0;          // of tiles that are cut
+  bool idle_waves = false;     // count the wavefronts that have rows
   auto cut = [&](double cap, bool list) {      // returns the number of items
     int64_t count = 0;
     cost.clear();
-    sum = 0.0;
+    sum = piece = 0.0;
     pieces = 0;
     for (int r = 0; r < R; ++r) {
       if (kind[r] != HFX_PREFILL) continue;
@@ -135,13 +147,19 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
         sum += ns * mult;
         count += nsplit * mult;
         if (nsplit > 1) pieces += nsplit * mult;
-        if (list) cost.insert(cost.end(), (size_t)nsplit, (float)(ns / (double)nsplit + 3000.0));
+        if (list) {
+          const double one = ns / (double)nsplit + 3000.0;
+          const double busy = idle_waves ? tile_busy(hpw, r1 - (int64_t)rt * rows_wg) : 1.0;
+          piece = std::max(piece, one);
+          cost.insert(cost.end(), (size_t)nsplit, (float)(one * (kLoneShare + (1.0 - kLoneShare) * busy)));
+        }
       }
     }
     return count;
   };
-  const int64_t whole_tiles = cut(1e18, false);
+  const int64_t whole_tiles = cut(kWhole, false);
   const double share = (sum + dec_ns) / HFX_PLAN_WGS;
+  const double least = std::max(share, (dec_ns + stream_ns) / HFX_PLAN_WGS);
   double cap = std::max(share / kPrefillItemsPerWg, kMinItemNs);
   if (decode_dominated) return std::max(cap, 0.75 * share);
   if (longest <= cap || whole_tiles > kCutMaxTiles) return cap;
@@ -154,7 +172,7 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
   auto time_of = [&](double cap, double limit) {      // ... or `limit`, if it is no less
     const bool queue = cut(cap, true) > HFX_PLAN_WGS;
     const double extra = pieces > 0 ? merge_ns + piece_ns * (double)pieces : 0.0;
-    if (share + extra >= limit) return limit;
+    if (least + extra >= limit) return limit;
     std::sort(cost.begin(), cost.end(), std::greater<float>());
     // up to one round: a CU's workgroups get items that fit; more: workgroups come back for the next item
     load.assign((size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set), 0.f);        // a heap, least loaded first
@@ -164,18 +182,20 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
         load.back() += queue ? cost[i] : 0.5f * cost[i];
         std::push_heap(load.begin(), load.end(), std::greater<float>());
       }
-    double t = std::max((double)*std::max_element(load.begin(), load.end()), share);
-    if (queue) t = share + kLoneShare * (t - share);       // what is left at the end has its CU to itself
-    else t = std::max(t, kLoneShare * (double)cost[0]);
+    double t = std::max((double)*std::max_element(load.begin(), load.end()), least);
+    if (queue) t = least + kLoneShare * (t - least);       // what is left at the end has its CU to itself
+    else t = std::max(t, kLoneShare * piece);
     return std::min(t + extra, limit);
   };
-  double best_cap = 1e18, best = time_of(best_cap, 1e18);
+  idle_waves = whole_tiles <= HFX_PLAN_WGS;
+  double best_cap = kWhole, best = time_of(best_cap, kWhole);
+  idle_waves = false;
   if (share < kLongStepNs) {
     for (const double f : {2.1, 1.45, 1.0, 0.7, 0.52}) {
       const double c = std::max(f * share, 0.5 * kMinItemNs);
       if (c >= longest) continue;
       const double limit = 0.9 * best;
-      if (share + merge_ns >= limit) break;
+      if (least + merge_ns >= limit) break;
       const double t = time_of(c, limit);
       // a cut has to promise a tenth, which is about what the estimate is worth, and costs workspace
       // (the fixed workspace keeps room for the partials, and a quarter of it for those of decodes)
@@ -391,11 +411,15 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   if (R < 1) return HFX_ERR_SHAPE;
   const int Hq = shape->num_q_heads, Hkv = shape->num_kv_heads, D = shape->head_dim;
   const int G = Hq / Hkv;
+  const int hpw = q_heads_per_item(G);
+  const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
+  const int mult = Hkv * (G / hpw);      // prefill items of a row tile, when it is not cut
 
   Plan& P = *out;
   P.reqs.assign((size_t)R, HfxReq());
   int64_t T = 0, nbt = 0;
-  double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work
+  double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work, prefill by (row, key) pairs
+  double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes
   for (int r = 0; r < R; ++r) {
     if (kind[r] != HFX_DECODE && kind[r] != HFX_PREFILL) return HFX_ERR_KIND;
     if (q_len[r] < 1 || ctx_len[r] < q_len[r]) return HFX_ERR_LEN;
@@ -416,6 +440,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     } else {
       double ql = q_len[r], p = ctx_len[r] - q_len[r];
       pre_ns += 4.0 * D * Hq * (ql * p + ql * (ql + 1) / 2) / kPrefillFlopsPerNs;
+      stream_ns += (double)ctx_len[r] * Hkv * D * 4.0 / kDecodeBytesPerNs;
     }
   }
   P.total_q = (int32_t)T;
@@ -433,16 +458,14 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   double rounds = std::floor(dec_ns / (HFX_PLAN_WGS * kMinItemNs));
   rounds = std::min<double>(std::max(rounds, 1.0), kDecodeItemsPerWg);
   const double cap_ns = std::max(dec_ns / (HFX_PLAN_WGS * rounds), kMinItemNs);
-  const int hpw = q_heads_per_item(G);
-  const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
   const double cap_prefill_ns =
-      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, rows_wg, dec_ns, dec_ns > pre_ns, &P) : kMinItemNs;
+      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, stream_ns, dec_ns > pre_ns, &P) : kMinItemNs;
 
   int64_t rows = 0, dec_rows = 0, pre_ord = 0;
   st = make_items(shape, R, cap_ns, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
   if (st != HFX_OK) return st;
   if (rows * (4ll * D + 8) + 512 > (int64_t)HFX_STATIC_WS_BYTES && rows > dec_rows) {
-    const double c = cap_within_workspace(kind, q_len, ctx_len, R, Hkv * (G / hpw), D, hpw, rows_wg, dec_ns, pre_ns, dec_rows, cap_prefill_ns);
+    const double c = cap_within_workspace(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, pre_ns, dec_rows, cap_prefill_ns);
     if (c > cap_prefill_ns) {
       st = make_items(shape, R, cap_ns, c, &P, &rows, &dec_rows, &pre_ord);
       if (st != HFX_OK) return st;

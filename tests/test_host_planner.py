@@ -387,6 +387,16 @@ def test_longest_items_come_first(lib, Hq, Hkv, D, chunks):
     assert np.all(np.diff(items["ke"] - items["kb"]) <= 0)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,q,prior,whole", [
+    (8, 8, 128, 36, 4, 17273, True), (12, 4, 128, 23, 4, 8015, True), (16, 16, 128, 27, 4, 18490, True), (8, 8, 64, 42, 4, 5321, True),
+    (16, 8, 128, 33, 1, 12028, True), (8, 8, 128, 2, 4, 18671, False), (24, 8, 128, 3, 3, 20051, False)])
+def test_tiles_with_idle_wavefronts_stay_whole_where_they_all_start_at_once(lib, Hq, Hkv, D, n, q, prior, whole):
+    """Between 256 and 512 tiles of a few rows, one to a workgroup, do not slow each other like full ones and last as long as
+    their keys take to stream: cutting them only adds partials.  Fewer tiles than CUs are cut."""
+    h = fill(lengths_only(Hq, Hkv, D, [PREFILL] * n, [q] * n, [q + prior] * n))["header"]
+    assert (h.n_groups == 0) == whole, (h.n_items, h.n_groups)
+
+
 @pytest.mark.parametrize("rows", [1, 8, 32])
 def test_cut_goes_by_the_time_of_a_tile_not_by_its_rows(lib, rows):
     """A tile of few rows takes as long as a full one: it is cut into as many pieces."""
