@@ -23,15 +23,25 @@ static const int kMinPrefillKeys = 256;
 static const int kMaxSplits = 64;
 static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of D + 2 floats per q-head)
 // Which prefill-dominated steps get a queue per die (see the queue order in plan_step), by items per
-// workgroup of the planning width; besides, the items have to be long on average (kMinItemNs).  Steps
-// of many short items gain nothing from it: their time goes into item hand-overs, not into key traffic, and
-// the dies end at different times (six tasks' short prompts, 17 each: 219 us with classes, about
-// 131 without).  In the first rounds all workgroups of a die start together, and those that read the same keys
+// workgroup of the planning width; besides, the items have to be long on average (kMinItemNs, by the (row, key) pairs
+// they work on).  Steps of many short items gain nothing from it: their time goes into item hand-overs, not into key
+// traffic, and the dies end at different times (six tasks' short prompts, 17 each: 219 us with classes, about
+// 131 without; by the time of full tiles, 180 chunks of 33 rows on 1800 tokens of 32/4 heads would count as long: 260
+// with, 199 without).  In the first rounds all workgroups of a die start together, and those that read the same keys
 // then move in step: every cache line is a first touch for all of them at once.  Later
 // rounds start staggered.  What it buys is HBM traffic (0.6 instead of 1.06 GB on the prefill-heavy
 // mixed step), at a time within 1 % either way from four rounds on; below that the dies' unequal ends show
 // (4096 tokens, three rounds: 223 us with classes, 155 without).
 static const int kClassRoundsMin = 4;
+// Steps of requests with one row tile of few rows behind long contexts are another matter.  Where several head
+// blocks read the same keys, each on a die of its own, the step lasts as long as the blocks take to stream them apart
+// (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 22937 on
+// 24/8 heads 2473 us without classes, 1626 with; 97 of one row, half as long, 1665 and 1110.  The ratio is 1.9 with one
+// busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in the
+// cache; the gain holds from three rounds and about 3000 keys an item (99 chunks of 4 rows behind 2091: 180 without, 202 with).
+static const int kClassRoundsMinApart = 3;
+static const double kClassApart = 1.5;
+static const double kClassItemNsApart = 96000.0;
 static const double kLongStepNs = 400000.0; // steps of less time than this are cut by trying what the cut leads to ...
 static const double kLoneShare = 0.575;      // time of an item alone on its CU, over its time beside another
 static const int64_t kCutMaxTiles = 8192;   // ... if they have no more row tiles (the host time of the trial)
@@ -419,7 +429,9 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   P.reqs.assign((size_t)R, HfxReq());
   int64_t T = 0, nbt = 0;
   double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work, prefill by (row, key) pairs
-  double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes
+  double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes ...
+  double apart_ns = 0.0;               // ... or by every row tile and head block of a request that has one row tile
+  double tiles_ns = 0.0, beside_ns = 0.0;   // the row tiles: time of full ones, and counting the wavefronts that have rows
   for (int r = 0; r < R; ++r) {
     if (kind[r] != HFX_DECODE && kind[r] != HFX_PREFILL) return HFX_ERR_KIND;
     if (q_len[r] < 1 || ctx_len[r] < q_len[r]) return HFX_ERR_LEN;
@@ -440,7 +452,15 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     } else {
       double ql = q_len[r], p = ctx_len[r] - q_len[r];
       pre_ns += 4.0 * D * Hq * (ql * p + ql * (ql + 1) / 2) / kPrefillFlopsPerNs;
-      stream_ns += (double)ctx_len[r] * Hkv * D * 4.0 / kDecodeBytesPerNs;
+      const double keys_ns = (double)ctx_len[r] * D * 4.0 / kDecodeBytesPerNs;
+      stream_ns += keys_ns * Hkv;
+      apart_ns += keys_ns * (q_len[r] <= rows_wg ? mult : Hkv);
+      // full row tiles see p + rows_wg, p + 2 rows_wg, ... keys; a last one that is not full sees all
+      const int64_t full = q_len[r] / rows_wg, rest = q_len[r] % rows_wg;
+      const double full_ns = tile_ns(D, 1) * mult * ((double)full * p + 0.5 * rows_wg * (double)full * (double)(full + 1));
+      const double rest_ns = rest ? tile_ns(D, ctx_len[r]) * mult : 0.0;
+      tiles_ns += full_ns + rest_ns;
+      beside_ns += full_ns + rest_ns * (kLoneShare + (1.0 - kLoneShare) * tile_busy(hpw, rest));
     }
   }
   P.total_q = (int32_t)T;
@@ -541,8 +561,10 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         for (size_t k = 0; k < kBlockItems && di < dec.size(); ++k) order[o++] = dec[di++];
         for (size_t k = 0; k < kBlockItems && pi < pre.size(); ++k) order[o++] = pre[pi++];
       }
-    } else if (pre_ns > 0.0 && n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
-               total_ns >= kMinItemNs * (double)n &&
+    } else if (pre_ns > 0.0 && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
+               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && total_ns >= kMinItemNs * (double)n) ||
+                (n >= (size_t)kClassRoundsMinApart * HFX_PLAN_WGS && dec_ns + tiles_ns >= kClassItemNsApart * (double)n &&
+                 mult > Hkv && apart_ns >= kClassApart * beside_ns)) &&
                pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {
       // A step whose prefill work outweighs its decode work.  Many prefill items read the same
       // keys: all row tiles (and q-head blocks) of one request and kv-head that hold the same

@@ -257,6 +257,19 @@ def test_queue_per_die_and_whole_rounds(lib):
     assert fill(b)["header"].queue_classes == 1
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,q,prior,classes", [
+    (24, 8, 128, 134, 2, 22937, 8), (24, 8, 128, 97, 1, 12208, 8), (12, 4, 128, 273, 4, 5267, 8), (24, 8, 128, 60, 1, 30000, 1),
+    (24, 8, 128, 99, 4, 2091, 1), (32, 8, 128, 200, 1, 30000, 1), (32, 4, 128, 180, 33, 1785, 1), (24, 8, 64, 68, 4, 5198, 1)])
+def test_queue_per_die_where_few_row_tiles_read_the_same_keys(lib, Hq, Hkv, D, n, q, prior, classes):
+    """Chunks of a few rows behind long contexts, several head blocks to a kv-head: one die per kv-head's keys from three rounds
+    on.  Not with fewer or shorter items, where no two items share keys, or where the tiles are bound by the matrix cores."""
+    b = lengths_only(Hq, Hkv, D, [PREFILL] * n, [q] * n, [q + prior] * n)
+    d = fill(b)
+    assert d["header"].queue_classes == classes
+    if classes > 1:
+        check_class_order(b, d["items"])
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 1, 128), (24, 8, 128), (32, 4, 64), (16, 16, 128)])
 @pytest.mark.parametrize("q,prior", [(5, 20000), (100, 8000), (777, 0), (500, 3000), (1500, 0), (992, 2000), (4096, 0)])
 def test_cut_of_a_single_prompt(lib, Hq, Hkv, D, q, prior):
