@@ -470,6 +470,10 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     n_runs += (ctx_len[r] - 1) / HFX_PAGE - (ctx_len[r] - q_len[r]) / HFX_PAGE + 1;
   P.n_runs = (int32_t)n_runs;
   const double total_ns = dec_ns + pre_ns;
+  // Which kind of work outweighs the other goes by the time the items take, as cuts and queue do.  (By pairs, four decodes of
+  // 2000 tokens outweighed 48 chunks of one row behind 3269 that take twenty times as long: all tiles were cut for a decode
+  // stream that is not there, and the step took 82 us instead of 65.)
+  const bool decode_dominated = dec_ns > tiles_ns;
   // Decode pieces are sized against the decode work alone (in a step dominated by prefill they stay
   // small and fill the gaps between the large prefill items), for a whole number of rounds of the
   // planning width: as many rounds as fit pieces of at least the minimum size, at most
@@ -479,7 +483,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   rounds = std::min<double>(std::max(rounds, 1.0), kDecodeItemsPerWg);
   const double cap_ns = std::max(dec_ns / (HFX_PLAN_WGS * rounds), kMinItemNs);
   const double cap_prefill_ns =
-      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, stream_ns, dec_ns > pre_ns, &P) : kMinItemNs;
+      pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, stream_ns, decode_dominated, &P) : kMinItemNs;
 
   int64_t rows = 0, dec_rows = 0, pre_ord = 0;
   st = make_items(shape, R, cap_ns, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
@@ -526,8 +530,8 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     std::vector<uint32_t>& order = P.order;
     order.resize(n);
     P.queue_classes = 1;
-    P.deal_balanced = !(dec_ns > pre_ns && pre_ns > 0.0);   // the layout below is by workgroup
-    if (dec_ns > pre_ns && pre_ns > 0.0) {
+    P.deal_balanced = !(decode_dominated && pre_ns > 0.0);   // the layout below is by workgroup
+    if (decode_dominated && pre_ns > 0.0) {
       // A step whose decode work outweighs its prefill work.  The first two items of workgroup b
       // are queue positions b and b + HFX_PLAN_WGS, and workgroups b and b + HFX_PLAN_WGS/2 share a
       // CU.  Over those two rounds the prefill items (largest first) go to the workgroups of the

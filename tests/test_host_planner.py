@@ -424,6 +424,14 @@ def test_dealing_is_straight_where_the_layout_is_by_workgroup(lib):
     assert fill(b)["header"].deal_balanced == 1
 
 
+def test_decodes_outweigh_prefills_by_time(lib):
+    """48 chunks of one row take the time of full tiles: four decodes beside them do not make a decode step of it."""
+    h = fill(lengths_only(8, 8, 64, [DECODE] * 4 + [PREFILL] * 48, [1] * 52, [2000] * 4 + [3270] * 48))["header"]
+    assert h.deal_balanced == 1 and h.n_prefill_items == 48 * 8
+    h = fill(lengths_only(8, 8, 64, [DECODE] * 400 + [PREFILL] * 8, [1] * 408, [2000] * 400 + [3270] * 8))["header"]
+    assert h.deal_balanced == 0
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(4, 4, 64), (2, 2, 128), (16, 1, 64), (12, 4, 128), (6, 2, 64)])
 def test_planner_head_layouts_and_ragged_chunks(lib, Hq, Hkv, D):
     b = lengths_only(Hq, Hkv, D, [PREFILL, DECODE, PREFILL, DECODE, PREFILL], [1, 1, 33, 1, 130],
