@@ -6,7 +6,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
 
 namespace hfx {
 
@@ -95,6 +94,11 @@ static double tile_busy(int hpw, int64_t rows) {
 // of tiles_per key tiles (the last may be shorter).
 static void prefill_splits(int64_t kmax, double ns_all, double cap_ns, int64_t* nsplit_out, int64_t* tiles_per_out) {
   const int64_t ntiles = (kmax + HFX_KEY_TILE - 1) / HFX_KEY_TILE;
+  if (ns_all <= cap_ns) {             // most tiles, without a division
+    *nsplit_out = 1;
+    *tiles_per_out = std::max<int64_t>(ntiles, kMinPrefillKeys / HFX_KEY_TILE);
+    return;
+  }
   int64_t nsplit = (int64_t)std::min(std::ceil(ns_all / cap_ns), (double)kMaxSplits);
   nsplit = std::max<int64_t>(1, nsplit);
   int64_t tiles_per = (ntiles + nsplit - 1) / nsplit;
@@ -107,6 +111,76 @@ static int32_t clamp_cost(double ns) {
   if (ns < 1.0) return 1;
   if (ns > 2.0e9) return 2000000000;
   return (int32_t)ns;
+}
+
+// Sorts positive floats, largest first: their bit patterns order like the values.  Four passes of 8 bits.
+static void sort_descending(std::vector<float>& v, std::vector<float>& scratch) {
+  scratch.resize(v.size());
+  const size_t n = v.size();
+  float* a = v.data();
+  float* b = scratch.data();
+  uint32_t count[4][256];
+  std::memset(count, 0, sizeof count);
+  auto bits = [](float x) {
+    uint32_t u;
+    std::memcpy(&u, &x, sizeof u);
+    return ~u;
+  };
+  for (size_t i = 0; i < n; ++i) {
+    const uint32_t u = bits(a[i]);
+    for (int pass = 0; pass < 4; ++pass) ++count[pass][(u >> (8 * pass)) & 255u];
+  }
+  for (int pass = 0; pass < 4; ++pass) {
+    const int shift = 8 * pass;
+    uint32_t* c = count[pass];
+    if (n == 0 || c[(bits(a[0]) >> shift) & 255u] == n) continue;      // all alike in these bits
+    uint32_t at = 0;
+    for (int d = 0; d < 256; ++d) {
+      const uint32_t k = c[d];
+      c[d] = at;
+      at += k;
+    }
+    for (size_t i = 0; i < n; ++i) b[c[(bits(a[i]) >> shift) & 255u]++] = a[i];
+    std::swap(a, b);
+  }
+  if (a != v.data()) v.swap(scratch);
+}
+
+// When the last bin ends that items of `cost` * `scale` (sorted, largest first; each comes `copies` times) keep busy, if every
+// item goes to the least loaded bin.  Beyond two rounds the placing is left out for its bound: an item starts no later
+// than when the items before it, perfectly spread, are done.
+static double last_end(const std::vector<float>& cost, int copies, float scale, size_t bins, std::vector<float>& load) {
+  const size_t n = cost.size() * (size_t)copies;
+  double end = 0.0;
+  if (n > 2 * bins && n > 1024) {
+    double before = 0.0;
+    for (const float c : cost) {
+      end = std::max(end, before + (double)c * (double)(copies - 1) / (double)bins + c);
+      before += (double)c * copies / (double)bins;
+    }
+    return end * scale;
+  }
+  load.assign(bins, 0.f);         // from the point on where all bins have an item: a heap, least loaded on top
+  for (size_t i = 0; i < n; ++i) {
+    const float c = scale * cost[i / (size_t)copies];
+    if (i < bins) {               // the first of each bin; they descend, so the reverse order is a heap
+      load[bins - 1 - i] = c;
+      continue;
+    }
+    const float x = load[0] + c;
+    size_t at = 0;
+    for (;;) {
+      size_t child = 2 * at + 1;
+      if (child >= bins) break;
+      if (child + 1 < bins && load[child + 1] < load[child]) ++child;
+      if (load[child] >= x) break;
+      load[at] = load[child];
+      at = child;
+    }
+    load[at] = x;
+  }
+  for (const float x : load) end = std::max(end, (double)x);
+  return end;
 }
 
 // The cap on an item's time by which the row tiles of a step are cut along the keys.  Tiles come `mult` at
@@ -132,6 +206,10 @@ static int32_t clamp_cost(double ns) {
 // Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
+//
+// Planning has to stay short next to the step: a trial is a pass over the row tiles, a radix sort and, up to two rounds,
+// the placing itself (last_end).  With a general sort and heap, 120 prompt chunks on 8/1 heads (8000 items; tiles of one
+// kv-head are all different) took 1390 us to plan, 390 without any trial; 290 so.
 static const double kWhole = 1e18;
 static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
                           int hpw, int rows_wg, double dec_ns, double stream_ns, bool decode_dominated, Plan* P) {
@@ -177,22 +255,15 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
   // common divisor of their number and `mult`.
   int set = 1;
   while (mult % (2 * set) == 0 && 2 * set <= HFX_PLAN_WGS / 2) set *= 2;
-  std::vector<float>& load = P->cut_load;
   const double merge_ns = 4000.0, piece_ns = 26.0 * (D / 128.0);
   auto time_of = [&](double cap, double limit) {      // ... or `limit`, if it is no less
     const bool queue = cut(cap, true) > HFX_PLAN_WGS;
     const double extra = pieces > 0 ? merge_ns + piece_ns * (double)pieces : 0.0;
     if (least + extra >= limit) return limit;
-    std::sort(cost.begin(), cost.end(), std::greater<float>());
+    sort_descending(cost, P->cut_sort);
     // up to one round: a CU's workgroups get items that fit; more: workgroups come back for the next item
-    load.assign((size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set), 0.f);        // a heap, least loaded first
-    for (size_t i = 0; i < cost.size(); ++i)
-      for (int k = 0; k < mult / set; ++k) {
-        std::pop_heap(load.begin(), load.end(), std::greater<float>());
-        load.back() += queue ? cost[i] : 0.5f * cost[i];
-        std::push_heap(load.begin(), load.end(), std::greater<float>());
-      }
-    double t = std::max((double)*std::max_element(load.begin(), load.end()), least);
+    const size_t bins = (size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set);
+    double t = std::max(last_end(cost, mult / set, queue ? 1.f : 0.5f, bins, P->cut_load), least);
     if (queue) t = least + kLoneShare * (t - least);       // what is left at the end has its CU to itself
     else t = std::max(t, kLoneShare * piece);
     return std::min(t + extra, limit);

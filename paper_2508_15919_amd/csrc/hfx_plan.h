@@ -27,7 +27,7 @@ struct Plan {
   std::vector<int64_t> unit_cost;
   std::vector<uint32_t> unit_fill, unit_start;
   std::vector<uint64_t> unit_keys;
-  std::vector<float> cut_cost, cut_load;   // trial of a cut: item times, CU loads
+  std::vector<float> cut_cost, cut_sort, cut_load;   // trial of a cut: item times, sort scratch, CU loads
 };
 
 hfx_status check_shape(const hfx_shape* shape);

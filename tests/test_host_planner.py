@@ -417,6 +417,26 @@ def test_cut_goes_by_the_time_of_a_tile_not_by_its_rows(lib, rows):
     assert fill(b)["header"].n_prefill_items == fill(lengths_only(32, 8, 128, [PREFILL], [32], [13000]))["header"].n_prefill_items
 
 
+def test_planning_time_per_item_does_not_depend_on_the_head_layout(lib):
+    """The trial of cuts looks at every row tile that differs: one of eight items on 8 kv-heads, every one or two on a single
+    kv-head.  Time per descriptor byte of two steps of about 8000 items, best of ten."""
+    import time
+    g = np.random.default_rng(5)
+    q = np.rint(np.exp(g.uniform(np.log(100), np.log(3000), 120))).astype(np.int32)
+    c = q + np.rint(np.exp(g.uniform(0, np.log(40000), 120))).astype(np.int32)
+
+    def seconds_per_byte(Hq, Hkv, every):
+        args = hb.make_shape(Hq, Hkv, 128, 1 << 30), np.full(len(q[::every]), PREFILL, np.int32), q[::every], c[::every]
+        best = np.inf
+        for _ in range(10):
+            t = time.perf_counter()
+            size = hb.hfx_batch_desc_sizes(*args)[0]
+            best = min(best, time.perf_counter() - t)
+        return best / size
+
+    assert seconds_per_byte(8, 1, 1) < 3 * seconds_per_byte(32, 8, 4)
+
+
 def test_dealing_is_straight_where_the_layout_is_by_workgroup(lib):
     b = lengths_only(32, 8, 128, [DECODE] * 64 + [PREFILL], [1] * 64 + [256], [3000] * 64 + [256])
     assert fill(b)["header"].deal_balanced == 0
