@@ -22,22 +22,22 @@ static const int kMinPrefillKeys = 256;
 static const int kMaxSplits = 64;
 static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of D + 2 floats per q-head)
 // Which prefill-dominated steps get a queue per die (see the queue order in plan_step), by items per
-// workgroup of the planning width; besides, the items have to be long on average (kMinItemNs, by the (row, key) pairs
-// they work on).  Steps of many short items gain nothing from it: their time goes into item hand-overs, not into key
-// traffic, and the dies end at different times (six tasks' short prompts, 17 each: 219 us with classes, about
-// 131 without; by the time of full tiles, 180 chunks of 33 rows on 1800 tokens of 32/4 heads would count as long: 260
-// with, 199 without).  In the first rounds all workgroups of a die start together, and those that read the same keys
-// then move in step: every cache line is a first touch for all of them at once.  Later
-// rounds start staggered.  What it buys is HBM traffic (0.6 instead of 1.06 GB on the prefill-heavy
-// mixed step), at a time within 1 % either way from four rounds on; below that the dies' unequal ends show
-// (4096 tokens, three rounds: 223 us with classes, 155 without).
+// workgroup of the planning width and by the time of the step.  What it buys is HBM traffic: 0.6 instead of 1.06 GB on the
+// prefill-heavy mixed step.  What it costs is that the dies end at different times and that in the first rounds
+// all workgroups of a die start together, so that those that read the same keys move in step and every cache line is
+// a first touch for all of them at once: 40 to 80 us a step.  Prompts of 128-wide heads in four to eight rounds, with
+// classes over without: 1.2 to 1.4 at 250 us of modelled time, 1.05 to 1.15 at 500, 0.99 to 1.05 from 800 on; three
+// rounds (6144 tokens) 1.12, 17 short prompts of each of six tasks 1.8.  64-wide heads, with half the bytes a key and
+// less to save, lose more, 1.15 to 1.2 still at 1000 us, and never get it.
 static const int kClassRoundsMin = 4;
+static const double kClassStepNs = 800000.0;
 // Steps of requests with one row tile of few rows behind long contexts are another matter.  Where several head
 // blocks read the same keys, each on a die of its own, the step lasts as long as the blocks take to stream them apart
-// (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 22937 on
-// 24/8 heads 2473 us without classes, 1626 with; 97 of one row, half as long, 1665 and 1110.  The ratio is 1.9 with one
-// busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in the
-// cache; the gain holds from three rounds and about 3000 keys an item (99 chunks of 4 rows behind 2091: 180 without, 202 with).
+// (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
+// 22937 tokens on 24/8 heads 2467 us without classes, 1591 with; 97 of one row behind 12208, 1594 and 1107.  The ratio is
+// 1.9 with one busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in
+// the cache; the gain holds from three rounds and about 3000 keys an item (99 chunks of 4 rows behind 523 to 2091: 180
+// without, 202 with).
 static const int kClassRoundsMinApart = 3;
 static const double kClassApart = 1.5;
 static const double kClassItemNsApart = 96000.0;
@@ -637,7 +637,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         for (size_t k = 0; k < kBlockItems && pi < pre.size(); ++k) order[o++] = pre[pi++];
       }
     } else if (pre_ns > 0.0 && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
-               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && total_ns >= kMinItemNs * (double)n) ||
+               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && D == 128 && total_ns >= kClassStepNs * HFX_PLAN_WGS) ||
                 (n >= (size_t)kClassRoundsMinApart * HFX_PLAN_WGS && dec_ns + tiles_ns >= kClassItemNsApart * (double)n &&
                  mult > Hkv && apart_ns >= kClassApart * beside_ns)) &&
                pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {

@@ -152,14 +152,21 @@ def test_descriptor_serves_repeated_launches(hb):
 
 
 def test_queue_per_die_step_and_repeated_launches(hb, oracle):
-    """A prefill-dominated step of four items per workgroup: the planner lays the queue out in one class
+    """A prefill-dominated step of three items per workgroup: the planner lays the queue out in one class
     per die and the kernel keeps a ticket counter per class.  Compared with the oracle, launched again on
-    the same descriptor (all counters must have been put back), and with a decode request beside it."""
+    the same descriptor (all counters must have been put back), and with decode requests beside it.
+    (Chunks of a few rows behind long contexts, whose pages are drawn from a small pool; prompts get classes only in
+    steps as long as the prefill-heavy configuration, which is compared at full size.)"""
     import torch
-    kinds = [PREFILL] * 4 + [DECODE] * 6
-    ql = [2048, 2048, 2048, 2000] + [1] * 6
-    cl = [2048, 2304, 2560, 2100] + [700, 33, 1500, 257, 4096, 16]
-    b = synth.make_batch(32, 8, 128, kinds, ql, cl, 4242)
+    rng = np.random.default_rng(4242)
+    kind = np.array([PREFILL] * 130 + [DECODE] * 6, np.int32)
+    q_len = np.array([1 + i % 8 for i in range(130)] + [1] * 6, np.int32)
+    ctx_len = np.concatenate([rng.integers(3100, 3500, 130), [700, 33, 1500, 257, 4096, 16]]).astype(np.int32)
+    indptr = np.concatenate([[0], np.cumsum((ctx_len + 15) // 16)]).astype(np.int32)
+    n_pages = 700
+    b = synth.StepBatch(12, 4, 128, n_pages, kind, q_len, ctx_len, indptr, rng.integers(0, n_pages, indptr[-1]).astype(np.int32),
+                        synth.f32_to_bf16_bits(rng.standard_normal((int(q_len.sum()), 12, 128)).astype(np.float32)),
+                        synth.f32_to_bf16_bits(rng.standard_normal((n_pages, 4, 2, 16 * 128)).astype(np.float32)), name="queue-per-die")
     step, _ = check_full(hb, oracle, b)
     d = hb.parse_desc(step.host_desc.numpy())
     assert d["header"].queue_classes == 8 and np.all(d["items"]["home"] >= 0)

@@ -229,7 +229,7 @@ def test_planner_covers_full_size_lengths(lib):
 
 
 def test_queue_per_die_and_whole_rounds(lib):
-    """Prefill-dominated steps of three to eight items per workgroup get one queue class per die;
+    """Long prefill-dominated steps of four to eight items per workgroup get one queue class per die;
     steps of few prefill items per workgroup are cut so that the prefill items fill whole rounds of 512."""
     # four prompts' chunks of 2048 tokens at different depths plus 32 decodes (the prefill-heavy mixed shape)
     g = np.random.default_rng(1)
@@ -255,6 +255,15 @@ def test_queue_per_die_and_whole_rounds(lib):
     assert fill(b)["header"].queue_classes == 1
     b = lengths_only(32, 8, 128, [PREFILL] * 2, [512] * 2, [512, 2048])
     assert fill(b)["header"].queue_classes == 1
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,chunks", [
+    (32, 8, 128, [(9000, 0)]), (32, 8, 128, [(2048, 0), (2048, 256), (2048, 512), (2148, 100)]), (24, 8, 128, [(6000, 144), (5743, 3040)]),
+    (32, 8, 64, [(7993, 1035), (4771, 142), (706, 1961)]), (32, 4, 64, [(6336, 8000), (6214, 9000)])])
+def test_one_queue_where_the_dies_would_end_apart(lib, Hq, Hkv, D, chunks):
+    """Four to eight rounds of prompt tiles in less than 800 us, or of 64-wide heads, are done sooner from one queue."""
+    h = fill(lengths_only(Hq, Hkv, D, [PREFILL] * len(chunks), [q for q, _ in chunks], [q + p for q, p in chunks]))["header"]
+    assert 4 * 512 <= h.n_items <= 8 * 512 and h.queue_classes == 1
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,n,q,prior,classes", [
