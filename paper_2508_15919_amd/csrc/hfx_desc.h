@@ -48,9 +48,9 @@ struct HfxReq {
   int32_t q_start;              /* first packed query row */
   int32_t bt_start;             /* first entry in the stored block table; a multiple of 4 */
   int32_t n_pages;              /* ceil(ctx_len / 16) */
-  int32_t bt_len;               /* entries stored: n_pages rounded up to 4, plus HFX_BT_PAD; those past
-                                   n_pages repeat the last page, so that a tile's four ids can be fetched
-                                   as one aligned quad without clamping, a little way past the end */
+  int32_t bt_len;               /* entries stored: n_pages rounded up to 4 (requests start on 16 bytes), plus
+                                   HFX_BT_PAD; those past n_pages repeat the last page, so that the prefill loop may
+                                   read the ids of stages to come without clamping, a little way past the end */
   int32_t pad1;
 };
 

@@ -239,8 +239,8 @@ struct Tickets {
 // meet on another, and the second round gives the workgroups with the largest items one more.  Here the
 // first round runs up and then down the queue -- with fewer items than workgroups, the CUs that stay with
 // one workgroup get the largest -- and the second runs down, both within the positions that are equal
-// modulo the number of classes.  (4 to 8 % of a step of one to four rounds, more on a single prompt:
-// 2500 tokens 98 -> 85 us, 4096 tokens 155 -> 135 us; nothing on queues of many items.)
+// modulo the number of classes.  (2500 tokens on 32/8 heads 69 -> 59 us, 4096 tokens 152 -> 138 us; nothing on queues of
+// many items.)
 // `mode` is set by the launch: the grid is HFX_PLAN_WGS (1), or more than half of that, one item each (2).
 __device__ __forceinline__ void deal_balanced(Tickets& t, int mode, int n_items) {
   constexpr int kHalf = HFX_PLAN_WGS / 2, kLow = HFX_QUEUE_CLASSES - 1;
@@ -953,6 +953,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       }
     }
   };
+  // Block-table entries are read a little past the last page of a request: the second page of a partly filled last stage
+  // (1 entry), and at every synchronisation point the pages of the stream's next two stages, whether or not they are
+  // copied (up to the fifth entry behind the last page).  Those entries name the last page again.
+  static_assert(HFX_BT_PAD >= 5, "entries behind a request's last page that the copy stream may read");
   cs.count = 0;
   cs.in_next = 0;
   stream_start(it);
@@ -1200,9 +1204,10 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict_
 // 128 contiguous bytes of the source block), and one of values, which are dimension-major in the
 // pool and turn round in LDS: a piece is 8 slots of one dimension there and 8 dimensions of one
 // slot on the way out.  Rows in LDS are 16 bytes longer than the data, which spreads the 2-byte
-// writes of one piece and the 16-byte reads of one row over the banks.  Bound: HBM, 4 D Hkv bytes a
-// token each way.  (12345 tokens of 8 kv-heads, 101 MB: 16.9 us a call, 6.0 TB/s; one thread per
-// element with 64-bit divisions took 44.7 us.)
+// writes of one piece and the 16-byte reads of one row over the banks.  Bound: memory, 4 D Hkv bytes a
+// token each way.  (12345 tokens of 8 kv-heads, 101 MB: 16.4 us a call on the same buffers, which stay in the 256 MB
+// last-level cache, 6.1 TB/s; 20.9 us, 4.8 TB/s, rotating over eight sets of buffers, from HBM.  One thread per element with
+// 64-bit divisions took 44.7 us on the same buffers.)
 template <int D>
 __global__ __launch_bounds__(2 * D) void gather_kv_kernel(const char* __restrict__ desc, const uint16_t* __restrict__ pool,
                                                           int request, uint16_t* __restrict__ k_out,
@@ -1260,9 +1265,10 @@ __global__ void gather_kv_unaligned_kernel(const char* desc, const uint16_t* poo
 // row and one of its value row, both loads at once.  Keys go straight to the pool's block order (four
 // slots are 128 contiguous bytes there); values are dimension-major in the pool and turn round in LDS, so that
 // a row of the block (one dimension) gets its run of slots as one contiguous piece -- stored token by token,
-// it took one 2-byte request per (token, dimension), which was most of the launch.  Bound: HBM, 4 D bytes a
-// token and head each way.  (8224 tokens of long chunks, 8 kv-heads, 67 MB: 11.4 us a call, 5.9 TB/s; with 4-byte
-// loads in a loop and both halves through LDS, 12.7.  36940 tokens of short prompts, 303 MB: 68.7 and 72.4 us.)
+// it took one 2-byte request per (token, dimension), which was most of the launch.  Bound: memory, 4 D bytes a
+// token and head each way.  (8224 tokens of long chunks, 8 kv-heads, 67 MB: 11.3 us a call on the same buffers, in the
+// last-level cache, 6.0 TB/s, 12.7 with 4-byte loads in a loop and both halves through LDS; 17.1 us, 3.9 TB/s, rotating over
+// ten sets of buffers, from HBM.  36940 tokens of short prompts, 303 MB: 68.7 us, 4.4 TB/s, and 72.4.)
 template <int D>
 __global__ __launch_bounds__(2 * D) void append_kv_kernel(const HfxRun* __restrict__ runs, int n_runs,
                                                           const uint16_t* __restrict__ k_new,

@@ -189,20 +189,21 @@ static double last_end(const std::vector<float>& cost, int copies, float scale, 
 //
 // In a decode-dominated step the prefill items run beside the decode stream on CUs of their own (see the
 // queue order in plan_step) and only have to be done when it is: pieces of up to 0.75 of a share save
-// partials and merge work (64 decodes and two chunks of 512: 109 us at 0.6, where the later chunk's tiles
+// partials and merge work (64 decodes and two chunks of 512: 108 us at 0.6, where the later chunk's tiles
 // are cut in two, 102 at 0.75 to 1.2, where they are not).
 //
 // Prefill-dominated steps:
 // In short steps the cap is chosen by what it leads to: largest first, items go to where there is the least
 // work, an item alone on its CU runs at 1.74 times its rate, and every cut adds partials (64 KB a piece,
 // written and read: 26 ns) and the merge launch (4 us).  Not cutting at all is the common answer: whole tiles
-// fill the CUs (1500 tokens: 35 us cut, 32 whole; 4096 tokens 222 and 135; 1000 behind 3000 beside 16
-// decodes 126 and 85).  Cuts pay where there are fewer tiles than CUs (128 tokens behind 8000: 8 pieces
-// 33 us, 9 pieces 44, 4 pieces 51) or few more equal ones (2000 behind 3000 on 24 heads: 129 whole, 114 cut).
+// fill the CUs (1500 tokens on 32/8 heads: 37 us cut at half a share, 33 whole; 2500 tokens 81 and 59; 4096 tokens 164 and
+// 138; 1000 behind 3000 beside 16 decodes 101 and 89).  Cuts pay where there are fewer tiles than CUs (128 tokens behind
+// 8000: 122 us whole, 44 in 4 pieces, 34 in 8, 48 in 9; 8 chunks of one row behind 4000: 66 whole, 34 in 4; behind
+// 1000: 21.6 whole, 20.6 in 3) and where a few tiles outlast the rest (300 behind 5000 and 200 behind 6000: 96 and 67).
 // Tiles of few rows in layouts of few q-heads per kv-head leave wavefronts without rows.  Where all such tiles start at
 // once, whole, they slow their neighbours on the CU the less; and no cut makes a step shorter than its keys take to
-// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 455 us whole, 528 in
-// two pieces each; 23 behind 8015 on 12/4 heads: 186 and 225.
+// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 454 us whole, 530 in
+// two pieces each; 23 behind 8015 on 12/4 heads: 168 and 231.
 // Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
@@ -326,7 +327,8 @@ static int64_t cut_rows(const int32_t* kind, const int32_t* q_len, const int32_t
 // full ones, are cut like full ones and write as many partial rows.  More than the fixed workspace is taken only
 // where the work itself asks for it: as many rows as half a share of the step, counted in visible
 // (row, key) pairs, cuts the tiles into, in whole rounds.  (A 4096-token chunk behind 61440 on one kv-head: 72 MB,
-// two rounds of equal pieces.  32 chunks of one row behind 64000: 68 MB by time, 34 by pairs, 51 so bounded.)
+// two rounds of equal pieces.  40 chunks of 40 rows behind 19960 tokens beside four of 2048: 85 MB and 1349 us by time, 64 MB by
+// pairs, 43 MB and 1264 us so bounded.)
 static double cap_within_workspace(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
                                    int hpw, int rows_wg, double dec_ns, double pre_ns, int64_t dec_rows, double cap) {
   auto by_pairs = [&](int64_t p, int64_t r0, int64_t r1) {
@@ -543,7 +545,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   const double total_ns = dec_ns + pre_ns;
   // Which kind of work outweighs the other goes by the time the items take, as cuts and queue do.  (By pairs, four decodes of
   // 2000 tokens outweighed 48 chunks of one row behind 3269 that take twenty times as long: all tiles were cut for a decode
-  // stream that is not there, and the step took 82 us instead of 65.)
+  // stream that is not there, and the step took 84 us instead of 70.)
   const bool decode_dominated = dec_ns > tiles_ns;
   // Decode pieces are sized against the decode work alone (in a step dominated by prefill they stay
   // small and fill the gaps between the large prefill items), for a whole number of rounds of the
