@@ -36,11 +36,11 @@ static const double kClassStepNs = 800000.0;
 // (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
 // 22937 tokens on 24/8 heads 2467 us without classes, 1591 with; 97 of one row behind 12208, 1594 and 1107.  The ratio is
 // 1.9 with one busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in
-// the cache; the gain holds from three rounds and about 3000 keys an item (99 chunks of 4 rows behind 523 to 2091: 180
-// without, 202 with).
+// the cache.  The gain holds from three rounds and about 2100 keys an item on: 90 steps of 50 to 96 us an item took, with
+// classes over without, 0.89 to 1.14 below 64 us, 0.81 to 0.97 from 70 to 80, 0.76 to 0.96 above.
 static const int kClassRoundsMinApart = 3;
 static const double kClassApart = 1.5;
-static const double kClassItemNsApart = 96000.0;
+static const double kClassItemNsApart = 70000.0;
 static const double kLongStepNs = 400000.0; // steps of less time than this are cut by trying what the cut leads to ...
 static const double kLoneShare = 0.575;      // time of an item alone on its CU, over its time beside another
 static const int64_t kCutMaxTiles = 8192;   // ... if they have no more row tiles (the host time of the trial)
