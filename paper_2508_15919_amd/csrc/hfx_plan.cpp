@@ -28,9 +28,13 @@ static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of
 // a first touch for all of them at once: 40 to 80 us a step.  Prompts of 128-wide heads in four to eight rounds, with
 // classes over without: 1.2 to 1.4 at 250 us of modelled time, 1.05 to 1.15 at 500, 0.99 to 1.05 from 800 on; three
 // rounds (6144 tokens) 1.12, 17 short prompts of each of six tasks 1.8.  64-wide heads, with half the bytes a key and
-// less to save, lose more, 1.15 to 1.2 still at 1000 us, and never get it.
+// less to save, lose more, 1.15 to 1.2 still at 1000 us.  All of these have keys that fit the last-level cache (256 MB).
+// With far more keys than that, each read by two items or more, a queue per die is the better one again, as far as the items
+// are long (kMinItemNs, by the (row, key) pairs they work on): 20 steps of 85 to 260 chunks of 33 or 64 rows on 1.3 to
+// 6 GB of keys took 0.9 to 1.01 of the time.  (Not where no two items share keys: 15 steps, 1.0 to 1.09.)
 static const int kClassRoundsMin = 4;
 static const double kClassStepNs = 800000.0;
+static const double kClassStreamBytes = 1e9;
 // Steps of requests with one row tile of few rows behind long contexts are another matter.  Where several head
 // blocks read the same keys, each on a die of its own, the step lasts as long as the blocks take to stream them apart
 // (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
@@ -505,6 +509,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes ...
   double apart_ns = 0.0;               // ... or by every row tile and head block of a request that has one row tile
   double tiles_ns = 0.0, beside_ns = 0.0;   // the row tiles: time of full ones, and counting the wavefronts that have rows
+  int64_t streams = 0, readers = 0;    // (request, kv-head) pairs of prefills, and the uncut items that read their keys
   for (int r = 0; r < R; ++r) {
     if (kind[r] != HFX_DECODE && kind[r] != HFX_PREFILL) return HFX_ERR_KIND;
     if (q_len[r] < 1 || ctx_len[r] < q_len[r]) return HFX_ERR_LEN;
@@ -532,6 +537,8 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       const int64_t full = q_len[r] / rows_wg, rest = q_len[r] % rows_wg;
       const double full_ns = tile_ns(D, 1) * mult * ((double)full * p + 0.5 * rows_wg * (double)full * (double)(full + 1));
       const double rest_ns = rest ? tile_ns(D, ctx_len[r]) * mult : 0.0;
+      streams += Hkv;
+      readers += (full + (rest ? 1 : 0)) * mult;
       tiles_ns += full_ns + rest_ns;
       beside_ns += full_ns + rest_ns * (kLoneShare + (1.0 - kLoneShare) * tile_busy(hpw, rest));
     }
@@ -639,7 +646,9 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         for (size_t k = 0; k < kBlockItems && pi < pre.size(); ++k) order[o++] = pre[pi++];
       }
     } else if (pre_ns > 0.0 && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
-               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS && D == 128 && total_ns >= kClassStepNs * HFX_PLAN_WGS) ||
+               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS &&
+                 ((D == 128 && total_ns >= kClassStepNs * HFX_PLAN_WGS) ||
+                  (stream_ns >= kClassStreamBytes / kDecodeBytesPerNs && readers >= 2 * streams && total_ns >= kMinItemNs * (double)n))) ||
                 (n >= (size_t)kClassRoundsMinApart * HFX_PLAN_WGS && dec_ns + tiles_ns >= kClassItemNsApart * (double)n &&
                  mult > Hkv && apart_ns >= kClassApart * beside_ns)) &&
                pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {

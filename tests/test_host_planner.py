@@ -268,10 +268,12 @@ def test_one_queue_where_the_dies_would_end_apart(lib, Hq, Hkv, D, chunks):
 
 @pytest.mark.parametrize("Hq,Hkv,D,n,q,prior,classes", [
     (24, 8, 128, 134, 2, 22937, 8), (24, 8, 128, 97, 1, 12208, 8), (12, 4, 128, 273, 4, 5267, 8), (24, 8, 128, 68, 4, 2396, 8), (24, 8, 128, 60, 1, 30000, 1),
-    (24, 8, 128, 99, 4, 2091, 1), (32, 8, 128, 200, 1, 30000, 1), (32, 4, 128, 180, 33, 1785, 1), (24, 8, 64, 68, 4, 5198, 1)])
+    (24, 8, 128, 99, 4, 2091, 1), (32, 8, 128, 200, 1, 30000, 1), (32, 4, 128, 180, 33, 1785, 1), (24, 8, 64, 68, 4, 5198, 1),
+    (24, 8, 64, 105, 64, 16000, 8), (32, 4, 64, 200, 64, 12000, 8), (32, 8, 128, 260, 32, 5500, 1)])
 def test_queue_per_die_where_few_row_tiles_read_the_same_keys(lib, Hq, Hkv, D, n, q, prior, classes):
     """Chunks of a few rows behind long contexts, several head blocks to a kv-head: one die per kv-head's keys from three rounds
-    on.  Not with fewer or shorter items, where no two items share keys, or where the tiles are bound by the matrix cores."""
+    on.  Not with fewer or shorter items, where no two items share keys, or where the tiles are bound by the matrix cores, unless
+    there are a great many keys."""
     b = lengths_only(Hq, Hkv, D, [PREFILL] * n, [q] * n, [q + prior] * n)
     d = fill(b)
     assert d["header"].queue_classes == classes
