@@ -571,13 +571,15 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
 // vector instructions (54 bytes per clock and CU out of the L2, measured; a stage pair needs 32 KB in
 // about 3500 clocks).
 //
-// What bounds it: the chip's power.  On 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens
+// What bounds it: the matrix cores, at the clock the chip's power leaves them, and the copies.  On 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens
 // (0.96 TFLOP) the matrix cores are busy 55 % of the cycles and the clock settles at 1.87 GHz; the form
 // before this one, which staged through registers, synchronised every stage and multiplied and
 // exponentiated one after the other, was at 44 % and 2.09 GHz.  The cycles fell by a fifth (2.10 M to
 // 1.67 M), the time by an eighth (1.02 to 0.89 ms; 1.18 to 1.03 ms on a 4096-row chunk at 64 k context,
 // 24.0 to 18.3 us on a single prompt of 777 tokens).  Leaving out the copies (data wrong) takes 9 % less, the
-// exponentials 5 %; the order of the instructions inside a phase and wavefront priorities change 1 %.
+// exponentials 5 %; the order of the instructions inside a phase and wavefront priorities change 1 %.  Power is not all of it:
+// a loop of the same matrix and softmax work out of LDS, without copies, takes 2554 clocks a 64-key tile and wavefront
+// where this one takes about 3500, and at its lower clock still gives 1268 TFLOP/s where this one gives 1100.
 // ----------------------------------------------------------------------------------------------
 
 // One stage slot: [page 0 K][page 1 K][page 0 V][page 1 V], a block of 32 D bytes each, and
