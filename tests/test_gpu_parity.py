@@ -151,6 +151,35 @@ def test_descriptor_serves_repeated_launches(hb):
     assert d["header"].n_groups > 0
 
 
+def small_pool_batch(rng, Hq, Hkv, D, kind, q_len, ctx_len, name, n_pages=700):
+    """A step on long contexts whose pages are drawn, with repetitions, from a pool of a few hundred."""
+    kind, q_len, ctx_len = (np.asarray(a, np.int32) for a in (kind, q_len, ctx_len))
+    indptr = np.concatenate([[0], np.cumsum((ctx_len + 15) // 16)]).astype(np.int32)
+    return synth.StepBatch(Hq, Hkv, D, n_pages, kind, q_len, ctx_len, indptr, rng.integers(0, n_pages, indptr[-1]).astype(np.int32),
+                           synth.f32_to_bf16_bits(rng.standard_normal((int(q_len.sum()), Hq, D)).astype(np.float32)),
+                           synth.f32_to_bf16_bits(rng.standard_normal((n_pages, Hkv, 2, 16 * D)).astype(np.float32)), name=name)
+
+
+@pytest.mark.parametrize("decodes", [0, 3])
+@pytest.mark.parametrize("Hq,Hkv,D", [(24, 8, 128), (32, 4, 64), (8, 8, 128), (16, 1, 128)])
+def test_chunks_of_a_few_rows_in_pieces(hb, oracle, Hq, Hkv, D, decodes):
+    """Chunks of 1 to 40 rows behind thousands of tokens, cut along the keys: pieces with idle wavefronts, rows and last stages,
+    merged from partial rows of which most do not exist; through the fixed workspace as well, bit for bit."""
+    import torch
+    rng = np.random.default_rng(100 + Hq + D)
+    q = [1, 2, 5, 8, 33, 40]
+    c = [int(n) + int(rng.integers(2500, 6000)) for n in q]
+    b = small_pool_batch(rng, Hq, Hkv, D, [PREFILL] * len(q) + [DECODE] * decodes, q + [1] * decodes, c + [900, 33, 1700][:decodes],
+                         f"few-rows-{Hq}-{Hkv}-{D}-{decodes}")
+    step, bits = check_full(hb, oracle, b)
+    d = hb.parse_desc(step.host_desc.numpy())
+    assert np.any(d["groups"]["type"] == 1) and d["header"].workspace_bytes <= 64 << 20
+    step.out.zero_()
+    hb.hfx_mixed_paged_attention_static(step.shape, step.q, step.pool, step.host_desc, step.device_desc, step.out)
+    torch.cuda.synchronize()
+    assert np.array_equal(step.out_bits(), bits)
+
+
 def test_queue_per_die_step_and_repeated_launches(hb, oracle):
     """A prefill-dominated step of three items per workgroup: the planner lays the queue out in one class
     per die and the kernel keeps a ticket counter per class.  Compared with the oracle, launched again on
@@ -159,14 +188,8 @@ def test_queue_per_die_step_and_repeated_launches(hb, oracle):
     steps as long as the prefill-heavy configuration, which is compared at full size.)"""
     import torch
     rng = np.random.default_rng(4242)
-    kind = np.array([PREFILL] * 130 + [DECODE] * 6, np.int32)
-    q_len = np.array([1 + i % 8 for i in range(130)] + [1] * 6, np.int32)
-    ctx_len = np.concatenate([rng.integers(3100, 3500, 130), [700, 33, 1500, 257, 4096, 16]]).astype(np.int32)
-    indptr = np.concatenate([[0], np.cumsum((ctx_len + 15) // 16)]).astype(np.int32)
-    n_pages = 700
-    b = synth.StepBatch(12, 4, 128, n_pages, kind, q_len, ctx_len, indptr, rng.integers(0, n_pages, indptr[-1]).astype(np.int32),
-                        synth.f32_to_bf16_bits(rng.standard_normal((int(q_len.sum()), 12, 128)).astype(np.float32)),
-                        synth.f32_to_bf16_bits(rng.standard_normal((n_pages, 4, 2, 16 * 128)).astype(np.float32)), name="queue-per-die")
+    b = small_pool_batch(rng, 12, 4, 128, [PREFILL] * 130 + [DECODE] * 6, [1 + i % 8 for i in range(130)] + [1] * 6,
+                         [*rng.integers(3100, 3500, 130), 700, 33, 1500, 257, 4096, 16], "queue-per-die")
     step, _ = check_full(hb, oracle, b)
     d = hb.parse_desc(step.host_desc.numpy())
     assert d["header"].queue_classes == 8 and np.all(d["items"]["home"] >= 0)
