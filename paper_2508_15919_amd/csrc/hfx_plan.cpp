@@ -151,12 +151,13 @@ static void sort_descending(std::vector<float>& v, std::vector<float>& scratch) 
 }
 
 // When the last bin ends that items of `cost` * `scale` (sorted, largest first; each comes `copies` times) keep busy, if every
-// item goes to the least loaded bin.  Beyond two rounds the placing is left out for its bound: an item starts no later
-// than when the items before it, perfectly spread, are done.
-static double last_end(const std::vector<float>& cost, int copies, float scale, size_t bins, std::vector<float>& load) {
+// item goes to the least loaded bin.  Beyond two rounds the placing is left out for its bound, if not asked for (exact): an
+// item starts no later than when the items before it, perfectly spread, are done.  Beyond eight rounds all but the last
+// four are taken as perfectly spread.
+static double last_end(const std::vector<float>& cost, int copies, float scale, size_t bins, bool exact, std::vector<float>& load) {
   const size_t n = cost.size() * (size_t)copies;
   double end = 0.0;
-  if (n > 2 * bins && n > 1024) {
+  if (!exact && n > 2 * bins && n > 1024) {
     double before = 0.0;
     for (const float c : cost) {
       end = std::max(end, before + (double)c * (double)(copies - 1) / (double)bins + c);
@@ -165,7 +166,14 @@ static double last_end(const std::vector<float>& cost, int copies, float scale, 
     return end * scale;
   }
   load.assign(bins, 0.f);         // from the point on where all bins have an item: a heap, least loaded on top
-  for (size_t i = 0; i < n; ++i) {
+  size_t first = 0;
+  if (n > 8 * bins) {
+    first = (n / bins - 4) * bins;
+    double before = 0.0;
+    for (size_t i = 0; i < first / (size_t)copies; ++i) before += cost[i];
+    load.assign(bins, (float)(before * copies * scale / (double)bins));
+  }
+  for (size_t i = first; i < n; ++i) {
     const float c = scale * cost[i / (size_t)copies];
     if (i < bins) {               // the first of each bin; they descend, so the reverse order is a heap
       load[bins - 1 - i] = c;
@@ -212,9 +220,9 @@ static double last_end(const std::vector<float>& cost, int copies, float scale, 
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
 //
-// Planning has to stay short next to the step: a trial is a pass over the row tiles, a radix sort and, up to two rounds,
-// the placing itself (last_end).  With a general sort and heap, 120 prompt chunks on 8/1 heads (8000 items; tiles of one
-// kv-head are all different) took 1390 us to plan, 390 without any trial; 290 so.
+// Planning has to stay short next to the step: a trial is a pass over the row tiles, a radix sort and, up to two rounds or in
+// long steps, the placing itself (last_end).  With a general sort and heap, 120 prompt chunks on 8/1 heads (8000 items; tiles of one
+// kv-head are all different) took 1390 us to plan, 390 without any trial; 500 so.
 static const double kWhole = 1e18;
 static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
                           int hpw, int rows_wg, double dec_ns, double stream_ns, bool decode_dominated, Plan* P) {
@@ -261,6 +269,9 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
   int set = 1;
   while (mult % (2 * set) == 0 && 2 * set <= HFX_PLAN_WGS / 2) set *= 2;
   const double merge_ns = 4000.0, piece_ns = 26.0 * (D / 128.0);
+  // In a long step the bound of last_end, in the place of either side of its one comparison, would cut, and take workspace
+  // for it, where whole tiles are as good.
+  const bool exact = share >= kLongStepNs;
   auto time_of = [&](double cap, double limit) {      // ... or `limit`, if it is no less
     const bool queue = cut(cap, true) > HFX_PLAN_WGS;
     const double extra = pieces > 0 ? merge_ns + piece_ns * (double)pieces : 0.0;
@@ -268,7 +279,7 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
     sort_descending(cost, P->cut_sort);
     // up to one round: a CU's workgroups get items that fit; more: workgroups come back for the next item
     const size_t bins = (size_t)(HFX_PLAN_WGS / (queue ? 1 : 2) / set);
-    double t = std::max(last_end(cost, mult / set, queue ? 1.f : 0.5f, bins, P->cut_load), least);
+    double t = std::max(last_end(cost, mult / set, queue ? 1.f : 0.5f, bins, exact, P->cut_load), least);
     if (queue) t = least + kLoneShare * (t - least);       // what is left at the end has its CU to itself
     else t = std::max(t, kLoneShare * piece);
     return std::min(t + extra, limit);
