@@ -455,7 +455,7 @@ def test_planning_time_per_item_does_not_depend_on_the_head_layout(lib):
             best = min(best, time.perf_counter() - t)
         return best / size
 
-    assert seconds_per_byte(8, 1, 1) < 3 * seconds_per_byte(32, 8, 4)
+    assert seconds_per_byte(8, 1, 1) < 3.5 * seconds_per_byte(32, 8, 4)      # 1.6 to 2.3; 4.6 to 5.6 with a general sort and heap
 
 
 def test_dealing_is_straight_where_the_layout_is_by_workgroup(lib):
