@@ -17,6 +17,7 @@ namespace hfx {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -571,15 +572,16 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
 // vector instructions (54 bytes per clock and CU out of the L2, measured; a stage pair needs 32 KB in
 // about 3500 clocks).
 //
-// What bounds it: the matrix cores, at the clock the chip's power leaves them, and the copies.  On 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens
-// (0.96 TFLOP) the matrix cores are busy 55 % of the cycles and the clock settles at 1.87 GHz; the form
-// before this one, which staged through registers, synchronised every stage and multiplied and
-// exponentiated one after the other, was at 44 % and 2.09 GHz.  The cycles fell by a fifth (2.10 M to
-// 1.67 M), the time by an eighth (1.02 to 0.89 ms; 1.18 to 1.03 ms on a 4096-row chunk at 64 k context,
-// 24.0 to 18.3 us on a single prompt of 777 tokens).  Leaving out the copies (data wrong) takes 9 % less, the
-// exponentials 5 %; the order of the instructions inside a phase and wavefront priorities change 1 %.  Power is not all of it:
-// a loop of the same matrix and softmax work out of LDS, without copies, takes 2554 clocks a 64-key tile and wavefront
-// where this one takes about 3500, and at its lower clock still gives 1268 TFLOP/s where this one gives 1100.
+// What bounds it: the matrix cores, at the clock the chip's power leaves them, and the copies.  Every matrix instruction of the
+// stage loop is followed by one LDS read of a fragment and one sixteenth of the softmax (an exponential, and every other time the
+// sum and rounding of a pair), so that vector unit, LDS and matrix cores are asked for at an even rate whichever
+// phases the two wavefronts of a SIMD are in.  With the whole softmax behind the score instructions, and its
+// sums and roundings in a block behind the last of them, 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens (0.96 TFLOP) took
+// 884 us where they now take 859, a 4096-row chunk behind 61440 tokens 1032 and 982; the matrix cores were busy 55 % of the
+// cycles at 1.87 GHz.  A value fragment takes the registers of the key fragment used up before it, and the other way round.
+// Tried with it: the synchronisation point behind the second value instruction instead of in front of the first (-1.5 to +1.5 %).
+// Power is not all of it: a loop of the same matrix and softmax work out of LDS, without copies, takes 2554 clocks a 64-key
+// tile and wavefront and gives, at 1.5 GHz, 1268 TFLOP/s where this one gives 1130.
 // ----------------------------------------------------------------------------------------------
 
 // One stage slot: [page 0 K][page 1 K][page 0 V][page 1 V], a block of 32 D bytes each, and
@@ -709,86 +711,86 @@ __device__ __forceinline__ f32x16 score_mfma(const PrefillWave<D>& w, const bf16
   return s;
 }
 
-// O^T += V^T . P^T of one stage.
-template <int D>
-__device__ __forceinline__ void value_mfma(PrefillWave<D>& w, bf16x8 (*vf)[D / 32], const bf16x8* pb) {
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int b = 0; b < D / 32; ++b)
-      w.o[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sp][b], pb[sp], w.o[b], 0, 0, 0);
-}
-
 template <int D>
 __device__ __forceinline__ void read_keys(bf16x8* kf, const char* slot, int k_lane) {
 #pragma unroll
   for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(slot + kk * 512 + k_lane);
 }
 
+// The weights of a stage are formed one or two scores at a time, each portion behind a matrix instruction of
+// other work.  Of the pairs whose second score belongs to an earlier portion, one is summed and rounded in each, so that
+// nothing waits for an exponential just issued.  The empty asm statements hold the results where they are formed: left to itself
+// the compiler puts the sums and roundings of all portions behind the last one.
+struct Weighing {
+  float p[16], ps[4];
+  unsigned pw[8];            // rounded pairs
+
+  __device__ __forceinline__ void finish(int i) {
+    const float t = p[2 * i] + p[2 * i + 1];
+    if (i < 4) ps[i] = t;
+    else ps[i & 3] += t;
+    const bf16x2 r = {(__bf16)p[2 * i], (__bf16)p[2 * i + 1]};
+    pw[i] = __builtin_bit_cast(unsigned, r);
+    asm volatile("" : "+v"(pw[i]), "+v"(ps[i & 3]));
+  }
+  // scores [e0, e0 + n), behind which those before e0 are finished as far as pairs are whole
+  __device__ __forceinline__ void portion(int e0, int n, int first, const f32x16& s, float sl2, float m) {
+#pragma unroll
+    for (int e = e0; e < e0 + n; ++e) {
+      p[e] = fast_exp2(__builtin_fmaf(s[e], sl2, -m));
+      asm volatile("" : "+v"(p[e]));
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (2 * i >= first && 2 * i + 1 < e0 && 2 * i + 1 >= e0 - n) finish(i);
+  }
+  __device__ __forceinline__ bf16x8 fragment(int sp) const {
+    return __builtin_bit_cast(bf16x8, u32x4{pw[4 * sp], pw[4 * sp + 1], pw[4 * sp + 2], pw[4 * sp + 3]});
+  }
+  __device__ __forceinline__ float sum() const { return (ps[0] + ps[1]) + (ps[2] + ps[3]); }
+};
+
 template <int D>
-__device__ __forceinline__ void read_values(bf16x8 (*vf)[D / 32], const char* slot, int v_lane) {
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int b = 0; b < D / 32; ++b)
-      vf[sp][b] = *reinterpret_cast<const bf16x8*>(slot + (2 + sp) * Smem<D>::kBlockBytes + b * 1024 + v_lane);
+__device__ __forceinline__ bf16x8 value_fragment(const char* slot, int i, int v_lane) {
+  constexpr int B = D / 32;
+  return *reinterpret_cast<const bf16x8*>(slot + (2 + i / B) * Smem<D>::kBlockBytes + (i % B) * 1024 + v_lane);
 }
 
-// Scores of the next stage (K fragments kf) and the weights of the present one (scores cur) in one
-// instruction stream, with the reads of the present stage's value fragments between them: a matrix
-// instruction is followed by about as many vector instructions as issue while it executes -- the two
-// exponentials of a pair of scores, and the sum and rounding of the pair before.  Left to itself the
-// compiler puts the matrix instructions in one block and the exponentials in another.
+// First phase of a stage: scores of the next stage out of its key fragments, the second half of the weights of the
+// present one (scores cur) between them; the value fragments of the present stage take the place of each key
+// fragment as it is used up.
 template <int D>
-__device__ __forceinline__ float scores_and_weights(const PrefillWave<D>& w, const bf16x8* kf, const f32x16& cur,
-                                                    f32x16& next, bf16x8* pb, float sl2, bf16x8 (*vf)[D / 32],
-                                                    const char* v_slot, int v_lane) {
-  constexpr int kPairs = 8, kPer = kPairs / (D / 16);      // pairs of scores per matrix instruction
-  constexpr int B = D / 32;
-  float ps[4], p0 = 0.f, p1 = 0.f;
+__device__ __forceinline__ f32x16 scores_phase(const PrefillWave<D>& w, bf16x8* frag, const f32x16& cur, Weighing& wt, float sl2,
+                                               const char* v_slot, int v_lane) {
+  constexpr int S = D / 16, E = 8 / S;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-  auto finish = [&](int i) {       // sum and rounding of pair i
-    if (i < 4) ps[i] = p0 + p1;
-    else ps[i & 3] += p0 + p1;
-    pb[i >> 2][(2 * i) & 7] = (__bf16)p0;
-    pb[i >> 2][((2 * i) & 7) + 1] = (__bf16)p1;
-  };
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], acc, 0, 0, 0);
-    vf[kk / B][kk % B] = *reinterpret_cast<const bf16x8*>(v_slot + (2 + kk / B) * Smem<D>::kBlockBytes + (kk % B) * 1024 + v_lane);
-#pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-      const int i = kk * kPer + u;
-      const float x0 = __builtin_fmaf(cur[2 * i], sl2, -w.m), x1 = __builtin_fmaf(cur[2 * i + 1], sl2, -w.m);
-      if (i > 0) finish(i - 1);
-      p0 = fast_exp2(x0);
-      p1 = fast_exp2(x1);
-    }
+  for (int kk = 0; kk < S; ++kk) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[kk], w.qf[kk], acc, 0, 0, 0);
+    frag[kk] = value_fragment<D>(v_slot, kk, v_lane);
+    wt.portion(8 + kk * E, E, 8, cur, sl2, w.m);
     __builtin_amdgcn_sched_barrier(0);
   }
-  finish(kPairs - 1);
-  asm volatile("" : "+v"(pb[0]), "+v"(pb[1]));   // the roundings belong here, not behind the branch that follows
-  next = acc;
-  return (ps[0] + ps[1]) + (ps[2] + ps[3]);
+  wt.finish(7);
+  return acc;
 }
 
-// Weighted values of the present stage, with the reads of the key fragments of the stage after next between them.
+// Second phase: weighted values of the present stage, the first half of the weights of the next one (scores next) between
+// them, and the key fragments of the stage after next in the place of the value fragments.
 template <int D>
-__device__ __forceinline__ void values_and_reads(PrefillWave<D>& w, bf16x8 (*vf)[D / 32], const bf16x8* pb, bf16x8* kf,
-                                                 const char* k_slot, int k_lane) {
-  constexpr int B = D / 32;
+__device__ __forceinline__ void values_phase(PrefillWave<D>& w, bf16x8* frag, const bf16x8* pb, const f32x16& next, Weighing& wt,
+                                             float sl2, const char* k_slot, int k_lane) {
+  constexpr int B = D / 32, S = 2 * B, E = 8 / S;
 #pragma unroll
-  for (int i = 0; i < 2 * B; ++i) {
-    w.o[i % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i / B][i % B], pb[i / B], w.o[i % B], 0, 0, 0);
-    if (i < B) {
-#pragma unroll
-      for (int k = 2 * i; k < 2 * i + 2; ++k) kf[k] = *reinterpret_cast<const bf16x8*>(k_slot + k * 512 + k_lane);
-    }
+  for (int i = 0; i < S; ++i) {
+    w.o[i % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], pb[i / B], w.o[i % B], 0, 0, 0);
+    frag[i] = *reinterpret_cast<const bf16x8*>(k_slot + i * 512 + k_lane);
+    wt.portion(i * E, E, 0, next, sl2, w.m);
     __builtin_amdgcn_sched_barrier(0);
   }
+  wt.finish(3);
 }
 
 // What a wavefront derives from a prefill item: its q-head and rows, and the key ranges that
@@ -895,9 +897,10 @@ __device__ __forceinline__ int item_stages(const HfxItem& it) { return (it.ke - 
 // per-row state (Q, O, m, l) is swapped.  Returns with t.cur at the first item it did not process.
 //
 // A wavefront's work on stage s, in two phases:
-//   first  : scores of stage s + 1 (matrix cores, K fragments in registers) between the instructions of the softmax
+//   first  : scores of stage s + 1 (matrix cores, K fragments in registers) between the second half of the softmax
 //            of stage s (vector unit) and the reads of its value fragments;
-//   second : weighted values of stage s between the reads of the key fragments of stage s + 2.
+//   second : weighted values of stage s between the first half of the softmax of stage s + 1 and the reads of the key
+//            fragments of stage s + 2.
 // Two stages make a step of the loop, so that the scores change places without being moved, and there
 // is one synchronisation point per step, between the phases of its first stage g: the keys up to stage
 // g + 3 and the values up to stage g + 2 have landed, every wavefront has taken the fragments of keys up to
@@ -1014,43 +1017,44 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     const int end_st = g_st + n_st - 1;      // the item's last stage
     publish_st += g_st;
     int kt = it.kb;
-    auto mask_stage = [&](f32x16& s) {     // keys past this lane's row's horizon (rows past the chunk: its last row's)
-      mask_scores(s, min(wr.wave_pmin + n, ctx_len - 1), kt + j * 8);
+    auto mask_stage = [&](f32x16& s, int key0) {     // keys past this lane's row's horizon (rows past the chunk: its last row's)
+      mask_scores(s, min(wr.wave_pmin + n, ctx_len - 1), key0 + j * 8);
     };
-    bf16x8 kf[D / 16];
+    bf16x8 frag[D / 16];     // key fragments of the next stage, then value fragments of the present one
     f32x16 s0, s1;
-    // the first stage: its scores, and their maximum as the reference exponent
+    Weighing wt;
+    // the first stage: its scores, their maximum as the reference exponent, and the first half of its weights
     sync_general(g_st + RING);
     event_st = g_st - 1;
-    read_keys<D>(kf, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
-    s0 = score_mfma<D>(w, kf);
-    read_keys<D>(kf, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
-    if (kt + SK - 1 > unmasked_upto) mask_stage(s0);
+    read_keys<D>(frag, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
+    s0 = score_mfma<D>(w, frag);
+    read_keys<D>(frag, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
+    if (kt + SK - 1 > unmasked_upto) mask_stage(s0, kt);
     w.m = fmaxf(HFX_M_NONE, row_max(s0, sl2));
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) wt.portion(e, 2, 0, s0, sl2, w.m);
+    wt.finish(3);
     auto slot = [&](int st) { return smem + (st & (RING - 1)) * Smem<D>::kStageBytes; };
-    auto mask_values = [&](bf16x8 (*vf)[D / 32]) {   // unused V slots may hold anything
+    auto mask_values = [&](bf16x8* vf) {   // unused V slots may hold anything
 #pragma unroll
-      for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-        for (int b = 0; b < D / 32; ++b) vf[sp][b] = keep_first(vf[sp][b], ctx_len - (kt + sp * 16 + j * 8));
+      for (int i = 0; i < D / 16; ++i) vf[i] = keep_first(vf[i], ctx_len - (kt + i / (D / 32) * 16 + j * 8));
     };
     // One stage: `cur` holds its scores, `next` receives those of the stage after it.  Every other stage
     // synchronises between its two phases.
     auto stage_step = [&](f32x16& cur, f32x16& next, bool sync) {
       const bool busy = kt < wave_end;
-      bf16x8 vf[2][D / 32], pb[2];
+      bf16x8 pb[2];
       int page0 = 0, page1 = 0;
       __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the key fragments
       if (sync) {
         page0 = bt[cs.bt];
         page1 = bt[cs.bt + 2];
       }
       if (busy) {
-        if (kt + SK - 1 > unmasked_upto) mask_stage(cur);
-        __builtin_amdgcn_sched_barrier(0);
-        const float sum = scores_and_weights<D>(w, kf, cur, next, pb, sl2, vf, slot(g_st), v_lane);
-        settle_weights<D>(w, cur, pb, sum, sl2);
+        next = scores_phase<D>(w, frag, cur, wt, sl2, slot(g_st), v_lane);
+        pb[0] = wt.fragment(0);
+        pb[1] = wt.fragment(1);
+        settle_weights<D>(w, cur, pb, wt.sum(), sl2);
       }
       if (sync) {
         if (g_st < event_st) {
@@ -1063,9 +1067,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
         }
       }
       if (busy) {
-        if (kt + SK > ctx_len) mask_values(vf);
+        if (kt + 2 * SK - 1 > unmasked_upto) mask_stage(next, kt + SK);
         __builtin_amdgcn_sched_barrier(0);
-        values_and_reads<D>(w, vf, pb, kf, slot(g_st + 2), k_lane);
+        values_phase<D>(w, frag, pb, next, wt, sl2, slot(g_st + 2), k_lane);
       }
       ++g_st;
       kt += SK;
@@ -1086,13 +1090,19 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       q_load<D>(w.qf, a, nx, wr_n, Hq, n, j);
     }
     if (kt < wave_end) {
-      bf16x8 vf[2][D / 32], pb[2];
-      if (kt + SK - 1 > unmasked_upto) mask_stage(s0);
-      read_values<D>(vf, slot(g_st), v_lane);
-      const float sum = weights(s0, sl2, w.m, pb);
-      settle_weights<D>(w, s0, pb, sum, sl2);
-      if (kt + SK > ctx_len) mask_values(vf);
-      value_mfma<D>(w, vf, pb);
+      bf16x8 pb[2];
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i) frag[i] = value_fragment<D>(slot(g_st), i, v_lane);
+#pragma unroll
+      for (int e = 8; e < 16; e += 2) wt.portion(e, 2, 8, s0, sl2, w.m);
+      wt.finish(7);
+      pb[0] = wt.fragment(0);
+      pb[1] = wt.fragment(1);
+      settle_weights<D>(w, s0, pb, wt.sum(), sl2);
+      if (kt + SK > ctx_len) mask_values(frag);
+#pragma unroll
+      for (int i = 0; i < D / 16; ++i)
+        w.o[i % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], pb[i / (D / 32)], w.o[i % (D / 32)], 0, 0, 0);
     }
     ++g_st;
     // hand-over: the item is finished; its successor's first stages are in the ring or on their way
