@@ -281,12 +281,15 @@ __device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, i
     const int base = kDealtTickets * (int)gridDim.x;
     int pos = base + pending * nc + ((int)blockIdx.x & (nc - 1));
     if (nc > 1) {
+      // (formed here and not, for all eight classes, at the start of every workgroup)
+      int behind = n_items - base;
+      asm volatile("" : "+s"(behind));
       for (int attempt = 0; attempt < kStealAttempts && pos >= n_items; ++attempt) {
         int best = 0, best_left = 0;
         for (int k = 0; k < HFX_QUEUE_CLASSES; ++k) {
           const int taken = __hip_atomic_load(ctrl + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           // positions base + r * classes + k below n_items with r >= taken
-          const int left = (n_items - base - k + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - taken;
+          const int left = (behind - k + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - taken;
           if (left > best_left) {
             best_left = left;
             best = k;
@@ -385,10 +388,10 @@ __device__ __forceinline__ int decode_page(const int* __restrict__ bt, const Dec
 
 __device__ __forceinline__ DecodeWave decode_wave(const int* __restrict__ bt, const HfxItem& it, int wave) {
   DecodeWave d;
-  const int HW = it.hn, TW = 4 / HW;
-  d.g = it.h0 + wave % HW;
-  d.step = 2 * TW;
-  d.pp = it.kb + 2 * (wave / HW);
+  const int HW = it.hn, sh = HW >> 1;      // 1, 2 or 4, and its logarithm
+  d.g = it.h0 + (wave & (HW - 1));
+  d.step = 8 >> sh;
+  d.pp = it.kb + 2 * (wave >> sh);
   d.pe = it.ke;
   d.tend = min(it.ke * HFX_PAGE, it.rq.ctx_len);
   d.bt0 = it.rq.bt_start;
@@ -512,7 +515,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     __syncthreads();
 
     // combine the TW token partitions of each head; row = hwi * G + hh
-    const int HW = it.hn, TW = 4 / HW;
+    const int HW = it.hn, TW = 4 >> (HW >> 1);
     const int rows = HW * G;
     float* ws_acc = a.ws;
     float* ws_ml = reinterpret_cast<float*>(reinterpret_cast<char*>(a.ws) + H->ws_off_ml);
@@ -570,18 +573,19 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
 // Keys arrive in stages of 32 (two pages' K and V blocks, 16 KB at D = 128) in a ring of four stage
 // slots, filled by direct-to-LDS loads about four stages ahead of their use: they take no registers and no
 // vector instructions (54 bytes per clock and CU out of the L2, measured; a stage pair needs 32 KB in
-// about 3500 clocks).
+// about 2150 clocks).
 //
-// What bounds it: the matrix cores, at the clock the chip's power leaves them, and the copies.  Every matrix instruction of the
+// What bounds it: the matrix cores, at the clock the chip's power leaves them.  Every matrix instruction of the
 // stage loop is followed by one LDS read of a fragment and one sixteenth of the softmax (an exponential, and every other time the
 // sum and rounding of a pair), so that vector unit, LDS and matrix cores are asked for at an even rate whichever
-// phases the two wavefronts of a SIMD are in.  With the whole softmax behind the score instructions, and its
-// sums and roundings in a block behind the last of them, 4 prompt chunks of 2048 rows behind up to 12288 earlier tokens (0.96 TFLOP) took
-// 884 us where they now take 859, a 4096-row chunk behind 61440 tokens 1032 and 982; the matrix cores were busy 55 % of the
-// cycles at 1.87 GHz.  A value fragment takes the registers of the key fragment used up before it, and the other way round.
-// Tried with it: the synchronisation point behind the second value instruction instead of in front of the first (-1.5 to +1.5 %).
-// Power is not all of it: a loop of the same matrix and softmax work out of LDS, without copies, takes 2554 clocks a 64-key
-// tile and wavefront and gives, at 1.5 GHz, 1268 TFLOP/s where this one gives 1130.
+// phases the two wavefronts of a SIMD are in; and the common stage pairs run in a loop of their own, without conditions,
+// scalar loads or bursts of copies.  A wavefront that has its SIMD to itself takes 1520 clocks a pair of stages (the matrix
+// instructions take 1024), the older of two 1820, the younger 2480: the matrix cores are busy 85 % of that time.  With the whole softmax behind the score instructions and one loop for all stages it was
+// 2350, 2450 and 3050 clocks.  4 prompt chunks of 2048 rows behind up to 12288 earlier tokens (0.96 TFLOP): 909 us then, 867 now on the
+// same card; a 4096-row chunk behind 61440 tokens 1053 and 968; a single prompt of 777 tokens 18.7 and 17.2.
+// A value fragment takes the registers of the key fragment used up before it, and the other way round.
+// Tried with it: the synchronisation point behind the second value instruction instead of in front of the first (-1.5 to +1.5 %); a ring
+// of eight stages where a workgroup has its CU to itself (slower: nobody waits for a copy with four).
 // ----------------------------------------------------------------------------------------------
 
 // One stage slot: [page 0 K][page 1 K][page 0 V][page 1 V], a block of 32 D bytes each, and
@@ -596,7 +600,7 @@ __device__ __forceinline__ unsigned copy_lane_offset(int wave, int lane) {
   return (unsigned)((lane >> 1) * 32 + ((lane & 1) ^ ((lane >> 4) & 1)) * 16);
 }
 
-// Direct-to-LDS copy of one block: base (scalar) + voff (lane) in memory, lds + 16 * lane in LDS.  The
+// Direct-to-LDS copy of one kilobyte, number `piece` of a block: base (scalar) + voff (lane) in memory, lds + 16 * lane in LDS.  The
 // instruction has no destination register; the compiler does not know of the load, so its own
 // vector-memory waits only become stricter by it, and the ring's waits are the explicit ones below.  The LDS
 // address travels in m0: the compiler reserves that register but merges its own settings of it where it sees no
@@ -604,22 +608,22 @@ __device__ __forceinline__ unsigned copy_lane_offset(int wave, int lane) {
 // reserved register is switched off: nothing lives in m0 across a statement.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
-template <int D>
-__device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
-  if (D == 128)
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, %1\n\t"
-                 "global_load_lds_dwordx4 %0, %1 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %0, %1 offset:2048\n\t"
-                 "global_load_lds_dwordx4 %0, %1 offset:3072"
-                 :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, %1\n\t"
-                 "global_load_lds_dwordx4 %0, %1 offset:1024"
-                 :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
+__device__ __forceinline__ void piece_copy(const char* base, unsigned voff, unsigned lds, int piece) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+               :: "v"(voff), "s"(base), "s"(lds), "n"(piece * 1024) : "memory", "m0");
+}
+// The same for 64 page ids, one a lane.
+__device__ __forceinline__ void ids_copy(const char* bt, unsigned voff, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(voff), "s"(bt), "s"(lds) : "memory", "m0");
 }
 #pragma clang diagnostic pop
+
+// A whole block.
+template <int D>
+__device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
+#pragma unroll
+  for (int piece = 0; piece < D / 32; ++piece) piece_copy(base, voff, lds, piece);
+}
 
 // Workgroup barrier of the ring: this wavefront's LDS reads are done.  The compiler may move loads across
 // the barrier builtin, which claims no memory effect, so the empty asm on both sides holds them.
@@ -717,9 +721,23 @@ __device__ __forceinline__ void read_keys(bf16x8* kf, const char* slot, int k_la
   for (int kk = 0; kk < D / 16; ++kk) kf[kk] = *reinterpret_cast<const bf16x8*>(slot + kk * 512 + k_lane);
 }
 
-// The weights of a stage are formed one or two scores at a time, each portion behind a matrix instruction of
-// other work.  Of the pairs whose second score belongs to an earlier portion, one is summed and rounded in each, so that
-// nothing waits for an exponential just issued.  The empty asm statements hold the results where they are formed: left to itself
+// Which scores have their weights formed behind which matrix instruction: number i of the value phase takes scores
+// [values[i], values[i + 1]) of the next stage, number i of the score phase [scores[i], scores[i + 1]) of the present one.
+// The first value instruction takes none, because the scores of the next stage come out of the matrix instruction just before it,
+// and the last score instruction none, so that the sum of the weights is known by the end of its phase.
+template <int D>
+struct Share;
+template <>
+struct Share<128> {
+  static constexpr int values[9] = {0, 0, 1, 2, 3, 5, 6, 7, 8}, scores[9] = {8, 9, 10, 11, 13, 14, 15, 16, 16};
+};
+template <>
+struct Share<64> {
+  static constexpr int values[5] = {0, 2, 4, 6, 8}, scores[5] = {8, 10, 12, 14, 16};
+};
+
+// The weights of a stage on their way.  A pair is summed and rounded one portion after its exponentials, so that nothing
+// waits for an exponential just issued.  The empty asm statements hold the results where they are formed: left to itself
 // the compiler puts the sums and roundings of all portions behind the last one.
 struct Weighing {
   float p[16], ps[4];
@@ -733,16 +751,17 @@ struct Weighing {
     pw[i] = __builtin_bit_cast(unsigned, r);
     asm volatile("" : "+v"(pw[i]), "+v"(ps[i & 3]));
   }
-  // scores [e0, e0 + n), behind which those before e0 are finished as far as pairs are whole
-  __device__ __forceinline__ void portion(int e0, int n, int first, const f32x16& s, float sl2, float m) {
+  // weights of scores [e0, e1), and the pairs that were completed in [before, e0)
+  __device__ __forceinline__ void portion(int before, int e0, int e1, const f32x16& s, float sl2, float m) {
 #pragma unroll
-    for (int e = e0; e < e0 + n; ++e) {
-      p[e] = fast_exp2(__builtin_fmaf(s[e], sl2, -m));
-      asm volatile("" : "+v"(p[e]));
-    }
+    for (int e = 0; e < 16; ++e)
+      if (e >= e0 && e < e1) {
+        p[e] = fast_exp2(__builtin_fmaf(s[e], sl2, -m));
+        asm volatile("" : "+v"(p[e]));
+      }
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (2 * i >= first && 2 * i + 1 < e0 && 2 * i + 1 >= e0 - n) finish(i);
+      if (2 * i + 1 >= before && 2 * i + 1 < e0) finish(i);
   }
   __device__ __forceinline__ bf16x8 fragment(int sp) const {
     return __builtin_bit_cast(bf16x8, u32x4{pw[4 * sp], pw[4 * sp + 1], pw[4 * sp + 2], pw[4 * sp + 3]});
@@ -756,41 +775,46 @@ __device__ __forceinline__ bf16x8 value_fragment(const char* slot, int i, int v_
   return *reinterpret_cast<const bf16x8*>(slot + (2 + i / B) * Smem<D>::kBlockBytes + (i % B) * 1024 + v_lane);
 }
 
+struct NoCopy {
+  __device__ __forceinline__ void operator()(int) const {}
+};
+
 // First phase of a stage: scores of the next stage out of its key fragments, the second half of the weights of the
 // present one (scores cur) between them; the value fragments of the present stage take the place of each key
-// fragment as it is used up.
-template <int D>
+// fragment as it is used up.  copy(i) issues what is to be copied behind instruction i.
+template <int D, class Copy>
 __device__ __forceinline__ f32x16 scores_phase(const PrefillWave<D>& w, bf16x8* frag, const f32x16& cur, Weighing& wt, float sl2,
-                                               const char* v_slot, int v_lane) {
-  constexpr int S = D / 16, E = 8 / S;
+                                               const char* v_slot, int v_lane, Copy copy) {
+  constexpr int S = D / 16;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < S; ++kk) {
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[kk], w.qf[kk], acc, 0, 0, 0);
-    frag[kk] = value_fragment<D>(v_slot, kk, v_lane);
-    wt.portion(8 + kk * E, E, 8, cur, sl2, w.m);
+  for (int i = 0; i < S; ++i) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], w.qf[i], acc, 0, 0, 0);
+    frag[i] = value_fragment<D>(v_slot, i, v_lane);
+    copy(i);
+    wt.portion(i == 0 ? Share<D>::values[S - 1] : Share<D>::scores[i - 1], Share<D>::scores[i], Share<D>::scores[i + 1], cur, sl2, w.m);
     __builtin_amdgcn_sched_barrier(0);
   }
-  wt.finish(7);
+  wt.portion(Share<D>::scores[S - 1], 16, 16, cur, sl2, w.m);
   return acc;
 }
 
 // Second phase: weighted values of the present stage, the first half of the weights of the next one (scores next) between
 // them, and the key fragments of the stage after next in the place of the value fragments.
-template <int D>
+template <int D, class Copy>
 __device__ __forceinline__ void values_phase(PrefillWave<D>& w, bf16x8* frag, const bf16x8* pb, const f32x16& next, Weighing& wt,
-                                             float sl2, const char* k_slot, int k_lane) {
-  constexpr int B = D / 32, S = 2 * B, E = 8 / S;
+                                             float sl2, const char* k_slot, int k_lane, Copy copy) {
+  constexpr int B = D / 32, S = 2 * B;
 #pragma unroll
   for (int i = 0; i < S; ++i) {
     w.o[i % B] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], pb[i / B], w.o[i % B], 0, 0, 0);
     frag[i] = *reinterpret_cast<const bf16x8*>(k_slot + i * 512 + k_lane);
-    wt.portion(i * E, E, 0, next, sl2, w.m);
+    copy(i);
+    wt.portion(i == 0 ? 0 : Share<D>::values[i - 1], Share<D>::values[i], Share<D>::values[i + 1], next, sl2, w.m);
     __builtin_amdgcn_sched_barrier(0);
   }
-  wt.finish(3);
 }
 
 // What a wavefront derives from a prefill item: its q-head and rows, and the key ranges that
@@ -802,8 +826,9 @@ struct WaveRows {
 
 __device__ __forceinline__ WaveRows wave_rows(const HfxItem& it, int wave) {
   WaveRows r;
-  r.head = it.h0 + wave % it.hn;
-  r.row0 = it.row0 + (wave / it.hn) * HFX_WAVE_ROWS;
+  // hn is 1, 2 or 4 (a division would take the vector unit, and with it all that follows from its result)
+  r.head = it.h0 + (wave & (it.hn - 1));
+  r.row0 = it.row0 + (wave >> (it.hn >> 1)) * HFX_WAVE_ROWS;
   const int p = it.rq.ctx_len - it.rq.q_len;
   r.wave_kend = r.row0 < it.rq.q_len ? min(it.ke, p + min(r.row0 + HFX_WAVE_ROWS, it.rq.q_len)) : 0;   // keys >= this: nothing to do
   r.wave_pmin = p + r.row0;                                                            // keys <= this are visible to every row
@@ -885,6 +910,7 @@ struct CopyStream {
   int count;          // stages copied so far, over all items of the run
   int left;           // stages of the item being copied that are still to come
   int bt;             // stored block-table entry of the next stage's page that this wavefront copies
+  int last;           // block-table entry of the request's last page
   int limit;          // stages that may be copied without overwriting one still to be read
   const char* base;   // block of page 0: the item's kv-head, keys or values
   int in_next;        // the item being copied is the next one, not the current one
@@ -908,7 +934,7 @@ __device__ __forceinline__ int item_stages(const HfxItem& it) { return (it.ke - 
 // of 1.67 M.)
 template <int D>
 __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* __restrict__ items, int n_items,
-                            Tickets& t, int* s_tk, int* ctrl, char* smem, char* o_stage) {
+                            Tickets& t, int* s_tk, int* ctrl, char* smem, char* o_stage, int* s_ids) {
   constexpr int SK = HFX_STAGE_KEYS;
   constexpr int RING = Smem<D>::kStages;
   const int tid = threadIdx.x;
@@ -935,10 +961,25 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   HfxItem nx = items[t.nxt < n_items ? t.nxt : t.cur];
   bool next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
   CopyStream cs;
+  // The pages of the stages to be copied next lie in LDS: of 64 stages from block-table entry ids_bt on (ids_ok: of the item being
+  // copied).  A scalar load in the middle of the stage loop makes the next wait for an LDS read wait for it as well.
+  int ids_bt = 0;
+  bool ids_ok = false;
+  int* ids = s_ids + wave * 64;
+  const unsigned lds_ids = (unsigned)(uintptr_t)(__attribute__((address_space(3))) int*)ids;
+  // (the block table by way of the control words: a pointer that an asm statement has seen is no longer read by scalar loads)
+  const char* bt_bytes = reinterpret_cast<const char*>(ctrl) + ((long)H->off_bt - (long)H->off_ctrl);
+  auto load_ids = [&]() {
+    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids);
+    ids_bt = cs.bt;
+    ids_ok = true;
+  };
   auto stream_start = [&](const HfxItem& item) {
     cs.left = item_stages(item);
     cs.base = pool + (long)(item.h0 / G) * (2 * Smem<D>::kBlockBytes);
     cs.bt = item.rq.bt_start + item.kb / HFX_PAGE + (wave & 1);
+    cs.last = item.rq.bt_start + item.rq.n_pages - 1;
+    ids_ok = false;
   };
   auto copy_page = [&](int page) {     // slots are handed out round-robin over the whole run
     block_copy<D>(cs.base + (unsigned long)(unsigned)page * page_bytes, voff,
@@ -951,7 +992,13 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   auto stream_catch_up = [&]() {
 #pragma unroll 1
     while (cs.left > 0 && cs.count < cs.limit) {
-      copy_page(bt[cs.bt]);
+      const int n = min(cs.left, cs.limit - cs.count);
+      int page[4];                 // four at a time, so that their latency is paid once
+#pragma unroll
+      for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < n) copy_page(page[i]);
       if (cs.left == 0 && !cs.in_next && next_ok) {
         cs.in_next = 1;
         stream_start(nx);
@@ -959,9 +1006,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     }
   };
   // Block-table entries are read a little past the last page of a request: the second page of a partly filled last stage
-  // (1 entry), and at every synchronisation point the pages of the stream's next two stages, whether or not they are
-  // copied (up to the fifth entry behind the last page).  Those entries name the last page again.
-  static_assert(HFX_BT_PAD >= 5, "entries behind a request's last page that the copy stream may read");
+  // (1 entry), and the pages of four stages wherever copies are caught up with (up to the seventh entry behind
+  // the last page).  Those entries name the last page again.
+  static_assert(HFX_BT_PAD >= 7, "entries behind a request's last page that the copy stream may read");
   cs.count = 0;
   cs.in_next = 0;
   stream_start(it);
@@ -1002,10 +1049,12 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     ring_barrier();
     cs.limit = limit;
     stream_catch_up();
+    if (cs.left > 2 && (!ids_ok || cs.bt - ids_bt > 64)) load_ids();
     // the short form copies two stages at stage g if count is g + 3 (values) or g + 4 (keys) there, and must
     // leave one for the general form to notice the item's end by
     event_st = cs.count == limit ? g_st + (cs.left > 0 ? (cs.left - 1) / 2 * 2 : 0) + 1 : g_st;
     if (publish_st > g_st) event_st = min(event_st, publish_st - 1);
+    event_st = min(event_st, g_st + ((64 - ((cs.bt - ids_bt) >> 1)) & ~1) + 1);     // ... as far as the ids go
   };
   for (;;) {
     w.l = 0.f;
@@ -1031,9 +1080,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     read_keys<D>(frag, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
     if (kt + SK - 1 > unmasked_upto) mask_stage(s0, kt);
     w.m = fmaxf(HFX_M_NONE, row_max(s0, sl2));
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) wt.portion(e, 2, 0, s0, sl2, w.m);
-    wt.finish(3);
+    wt.portion(0, 0, 4, s0, sl2, w.m);
+    wt.portion(0, 4, 8, s0, sl2, w.m);
+    wt.portion(4, Share<D>::values[D / 16 - 1], Share<D>::values[D / 16 - 1], s0, sl2, w.m);
     auto slot = [&](int st) { return smem + (st & (RING - 1)) * Smem<D>::kStageBytes; };
     auto mask_values = [&](bf16x8* vf) {   // unused V slots may hold anything
 #pragma unroll
@@ -1044,14 +1093,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     auto stage_step = [&](f32x16& cur, f32x16& next, bool sync) {
       const bool busy = kt < wave_end;
       bf16x8 pb[2];
-      int page0 = 0, page1 = 0;
       __builtin_amdgcn_sched_barrier(0);
-      if (sync) {
-        page0 = bt[cs.bt];
-        page1 = bt[cs.bt + 2];
-      }
       if (busy) {
-        next = scores_phase<D>(w, frag, cur, wt, sl2, slot(g_st), v_lane);
+        next = scores_phase<D>(w, frag, cur, wt, sl2, slot(g_st), v_lane, NoCopy());
         pb[0] = wt.fragment(0);
         pb[1] = wt.fragment(1);
         settle_weights<D>(w, cur, pb, wt.sum(), sl2);
@@ -1059,9 +1103,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       if (sync) {
         if (g_st < event_st) {
           HFX_WAIT_VMCNT(0);
+          const int* id = ids + ((cs.bt - ids_bt) >> 1);
+          const int id0 = id[0], id1 = id[1];
           ring_barrier();
-          copy_page(page0);
-          copy_page(page1);
+          copy_page(uniform(id0));
+          copy_page(uniform(id1));
         } else {
           sync_general(g_st + RING + 1 + key_wave);
         }
@@ -1069,12 +1115,48 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       if (busy) {
         if (kt + 2 * SK - 1 > unmasked_upto) mask_stage(next, kt + SK);
         __builtin_amdgcn_sched_barrier(0);
-        values_phase<D>(w, frag, pb, next, wt, sl2, slot(g_st + 2), k_lane);
+        values_phase<D>(w, frag, pb, next, wt, sl2, slot(g_st + 2), k_lane, NoCopy());
       }
       ++g_st;
       kt += SK;
     };
     for (;;) {
+      // Pairs of stages that every row of the wavefront sees whole, with the short form of the synchronisation point: the common
+      // case, without any other condition.  The copies are spread over the 16 matrix instructions behind that point.
+      int pairs = wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto ? (unmasked_upto - kt - 3 * SK + 1) / (2 * SK) + 1 : 0;
+      pairs = uniform(min(pairs, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
+      if (pairs > 0) {
+        HFX_WAIT_VMCNT(0);            // the ids
+        const int* id = ids + ((cs.bt - ids_bt) >> 1);
+        kt += pairs * (2 * SK);
+        cs.left -= 2 * pairs;
+        cs.bt += 4 * pairs;
+#pragma unroll 1
+        do {
+          __builtin_amdgcn_sched_barrier(0);
+          s1 = scores_phase<D>(w, frag, s0, wt, sl2, slot(g_st), v_lane, NoCopy());
+          const int id0 = id[0], id1 = id[1];
+          bf16x8 pb[2] = {wt.fragment(0), wt.fragment(1)};
+          settle_weights<D>(w, s0, pb, wt.sum(), sl2);
+          HFX_WAIT_VMCNT(0);
+          ring_barrier();
+          const char* base0 = cs.base + (unsigned long)(unsigned)uniform(id0) * page_bytes;
+          const char* base1 = cs.base + (unsigned long)(unsigned)uniform(id1) * page_bytes;
+          const unsigned lds0 = lds_ring + (cs.count & (RING - 1)) * Smem<D>::kStageBytes;
+          const unsigned lds1 = lds_ring + ((cs.count + 1) & (RING - 1)) * Smem<D>::kStageBytes;
+          __builtin_amdgcn_sched_barrier(0);
+          values_phase<D>(w, frag, pb, s1, wt, sl2, slot(g_st + 2), k_lane, [&](int i) { if (i & 1) piece_copy(base0, voff, lds0, i >> 1); });
+          s0 = scores_phase<D>(w, frag, s1, wt, sl2, slot(g_st + 1), v_lane, [&](int i) { if (i & 1) piece_copy(base1, voff, lds1, i >> 1); });
+          pb[0] = wt.fragment(0);
+          pb[1] = wt.fragment(1);
+          settle_weights<D>(w, s1, pb, wt.sum(), sl2);
+          __builtin_amdgcn_sched_barrier(0);
+          values_phase<D>(w, frag, pb, s0, wt, sl2, slot(g_st + 3), k_lane, NoCopy());
+          g_st += 2;
+          cs.count += 2;
+          id += 2;
+        } while (--pairs > 0);
+      }
       if (g_st == end_st) break;
       stage_step(s0, s1, true);
       if (g_st == end_st) {
@@ -1093,9 +1175,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       bf16x8 pb[2];
 #pragma unroll
       for (int i = 0; i < D / 16; ++i) frag[i] = value_fragment<D>(slot(g_st), i, v_lane);
-#pragma unroll
-      for (int e = 8; e < 16; e += 2) wt.portion(e, 2, 8, s0, sl2, w.m);
-      wt.finish(7);
+      wt.portion(Share<D>::values[D / 16 - 1], 8, 12, s0, sl2, w.m);
+      wt.portion(8, 12, 16, s0, sl2, w.m);
+      wt.portion(12, 16, 16, s0, sl2, w.m);
       pb[0] = wt.fragment(0);
       pb[1] = wt.fragment(1);
       settle_weights<D>(w, s0, pb, wt.sum(), sl2);
@@ -1154,6 +1236,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   __shared__ int s_tk[2];
   // result rows on their way out (prefill_store)
   __shared__ __attribute__((aligned(128))) char s_ostage[4 * 2048];
+  __shared__ int s_ids[4 * 64];     // page ids of stages to come (prefill_run)
   const HfxHeader* H = &hdr;
   const HfxItem* items = reinterpret_cast<const HfxItem*>(a.desc + H->off_items);
   const int n_items = H->n_items;
@@ -1166,7 +1249,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
     if (items[t.cur].type == HFX_ITEM_DECODE) {
       decode_run<D>(a, H, items, n_items, t, s_tk, &ctrl[0], smem);
     } else {
-      prefill_run<D>(a, H, items, n_items, t, s_tk, &ctrl[0], smem, s_ostage);
+      prefill_run<D>(a, H, items, n_items, t, s_tk, &ctrl[0], smem, s_ostage, s_ids);
     }
   }
   // the ticket fetched last is never used; it must have reached the counter before this

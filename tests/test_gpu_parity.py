@@ -267,6 +267,21 @@ def test_prefill_items_of_one_to_fifteen_stages(hb, oracle, Hq, Hkv, D):
     check_full(hb, oracle, synth.make_batch(Hq, Hkv, D, kinds, ql, cl, 97, name=f"stages-{D}"))
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(4, 1, 128), (2, 1, 64), (1, 1, 128)])
+def test_prefill_items_around_the_refill_of_page_ids(hb, oracle, Hq, Hkv, D):
+    """The prefill loop runs pairs of whole stages by page ids read 64 stages at a time: items of 55 to 75 and of 118 to 138
+    stages, aligned to pages or not, with rows of several horizons where a wavefront has rows of its own."""
+    rng = np.random.default_rng(64)
+    stages = [*range(55, 76), *range(118, 139)] * 13
+    q = [int(rng.integers(1, 33)) if i % 3 else 128 * Hkv // Hq for i in range(len(stages))]
+    c = [max(n, 32 * k - (int(rng.integers(0, 32)) if i % 2 else 0)) for i, (n, k) in enumerate(zip(q, stages))]
+    b = small_pool_batch(rng, Hq, Hkv, D, [PREFILL] * len(q), q, c, f"refill-{Hq}-{D}", n_pages=300)
+    step, _ = check_full(hb, oracle, b)
+    items = hb.parse_desc(step.host_desc.numpy())["items"]
+    seen = set(((items["ke"] - items["kb"] + 31) // 32).tolist())
+    assert set(range(57, 73)) <= seen and set(range(120, 136)) <= seen, sorted(seen)
+
+
 @pytest.mark.parametrize("n_items", [255, 256, 257, 300, 511, 512, 513, 770, 1023, 1024, 1025, 1300])
 def test_every_item_is_dealt_once(hb, oracle, n_items):
     """The first two tickets of a workgroup are a permutation of the queue's first positions that depends on
