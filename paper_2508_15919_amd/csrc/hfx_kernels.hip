@@ -704,14 +704,24 @@ __device__ __forceinline__ void settle_weights(PrefillWave<D>& w, const f32x16& 
   w.l += sum;
 }
 
-// Scores of one stage: S^T = K . Q^T out of K fragments in registers.
+// Scores of an item's first stage: S^T = K . Q^T out of K fragments in registers; the accumulators are cleared between the
+// instructions.
 template <int D>
-__device__ __forceinline__ f32x16 score_mfma(const PrefillWave<D>& w, const bf16x8* kf) {
+__device__ __forceinline__ f32x16 first_scores(PrefillWave<D>& w, const bf16x8* kf) {
   f32x16 s;
 #pragma unroll
   for (int v = 0; v < 16; ++v) s[v] = 0.f;
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], s, 0, 0, 0);
+  for (int kk = 0; kk < D / 16; ++kk) {
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], w.qf[kk], s, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      float zero = 0.f;
+      asm volatile("" : "+v"(zero));
+      w.o[kk / 2][kk % 2 * 8 + v] = zero;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
   return s;
 }
 
@@ -837,9 +847,8 @@ __device__ __forceinline__ WaveRows wave_rows(const HfxItem& it, int wave) {
 
 // Q^T operand fragments of this lane's row (rows past the chunk read the last row and are never stored)
 template <int D>
-__device__ __forceinline__ void q_load(bf16x8* qf, const KArgs& a, const HfxItem& it, const WaveRows& r, int Hq, int n, int j) {
-  const int qc = min(r.row0 + n, it.rq.q_len - 1);
-  const __bf16* qp = a.q + (((long)it.rq.q_start + qc) * Hq + r.head) * D + j * 8;
+__device__ __forceinline__ void q_load(bf16x8* qf, const __bf16* q, int row0, int last, int Hq, int n, int j) {
+  const __bf16* qp = q + (long)min(row0 + n, last) * Hq * D + j * 8;
 #pragma unroll
   for (int kk = 0; kk < D / 16; ++kk) qf[kk] = ld16(qp + kk * 16);
 }
@@ -868,6 +877,9 @@ __device__ __forceinline__ void prefill_store(const KArgs& a, const HfxHeader* H
     __bf16* dst = a.out + (((long)it.rq.q_start + row0 + rr) * Hq + r.head) * D + u * 8;
     char* wr = stage + n * 64 + (j ^ (n >> 4)) * 8;
     const char* rd = stage + rr * 64 + ((u ^ ((rr >> 2) & 3)) * 16);
+    // LDS serves a wavefront's accesses in order, so the next 32 dimensions are written while the lines of these are on
+    // their way back
+    u32x4 line[D / 32][2];
 #pragma unroll
     for (int b = 0; b < D / 32; ++b) {
 #pragma unroll
@@ -878,13 +890,17 @@ __device__ __forceinline__ void prefill_store(const KArgs& a, const HfxHeader* H
         *reinterpret_cast<bf16x4*>(wr + ((q4 ^ ((n >> 2) & 3)) * 16)) = ob;
       }
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        u32x4 line = *reinterpret_cast<const u32x4*>(rd + i * 1024);
-        if (i == 1) line = u32x4{line[2], line[3], line[0], line[1]};
-        if (row0 + rr + 16 * i < it.rq.q_len)
-          *reinterpret_cast<u32x4*>(dst + (long)i * 16 * Hq * D + b * 32) = line;
-      }
+      for (int i = 0; i < 2; ++i) line[b][i] = *reinterpret_cast<const u32x4*>(rd + i * 1024);
     }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      if (row0 + rr + 16 * i < it.rq.q_len) {
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b) {
+          const u32x4 t = line[b][i];
+          *reinterpret_cast<u32x4*>(dst + (long)i * 16 * Hq * D + b * 32) = i == 1 ? u32x4{t[2], t[3], t[0], t[1]} : t;
+        }
+      }
   } else {
     float* ws_acc = a.ws;
     float* ws_ml = reinterpret_cast<float*>(reinterpret_cast<char*>(a.ws) + H->ws_off_ml);
@@ -916,7 +932,17 @@ struct CopyStream {
   int in_next;        // the item being copied is the next one, not the current one
 };
 
-__device__ __forceinline__ int item_stages(const HfxItem& it) { return (it.ke - it.kb + HFX_STAGE_KEYS - 1) / HFX_STAGE_KEYS; }
+__device__ __forceinline__ int item_stages(const HfxItem& it) { return (int)((unsigned)(it.ke - it.kb + HFX_STAGE_KEYS - 1) / HFX_STAGE_KEYS); }
+
+// What the loop over an item's stages needs to know of the item after it: how to copy its stages and where its Q rows are.
+// (Its whole record kept in scalar registers through that loop, and everything that can be derived from it formed
+// ahead of it, cost 67 registers' worth of spills and about 150 instructions an item.)
+struct NextItem {
+  int left, bt, last;         // as in CopyStream
+  const char* base;
+  int q_row0, q_last;         // first chunk row of this wavefront, last of the chunk
+  const __bf16* q;            // row 0 of the chunk, this wavefront's head
+};
 
 // Runs the prefill item t.cur and, for as long as the workgroup's next item is a prefill item as
 // well, carries straight on into it: the stage ring does not drain between items, only the
@@ -958,28 +984,53 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   const int key_wave = 1 - (wave >> 1);   // 1: this wavefront copies keys, which are read a stage before the values
 
   HfxItem it = items[t.cur];
-  HfxItem nx = items[t.nxt < n_items ? t.nxt : t.cur];
-  bool next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
   CopyStream cs;
-  // The pages of the stages to be copied next lie in LDS: of 64 stages from block-table entry ids_bt on (ids_ok: of the item being
-  // copied).  A scalar load in the middle of the stage loop makes the next wait for an LDS read wait for it as well.
-  int ids_bt = 0;
-  bool ids_ok = false;
-  int* ids = s_ids + wave * 64;
+  const unsigned inv_g = 0xffffffffu / (unsigned)G + 1u;      // h / G by a multiplication (0 for G = 1)
+  auto q_rows = [&](const HfxItem& item, const WaveRows& r) { return a.q + ((long)item.rq.q_start * Hq + r.head) * D; };
+  auto next_item = [&](const HfxItem& item) {
+    const WaveRows r = wave_rows(item, wave);
+    const int g = G == 1 ? item.h0 : (int)__umulhi((unsigned)item.h0, inv_g);
+    NextItem x;
+    x.left = item_stages(item);
+    x.bt = item.rq.bt_start + (int)((unsigned)item.kb / HFX_PAGE) + (wave & 1);
+    x.last = item.rq.bt_start + item.rq.n_pages - 1;
+    x.base = pool + (long)g * (2 * Smem<D>::kBlockBytes);
+    x.q_row0 = r.row0;
+    x.q_last = item.rq.q_len - 1;
+    x.q = q_rows(item, r);
+    return x;
+  };
+  const HfxItem item1 = items[t.nxt < n_items ? t.nxt : t.cur];
+  NextItem nx = next_item(item1);
+  bool next_ok = t.nxt < n_items && item1.type == HFX_ITEM_PREFILL;
+  // The pages of the stages to be copied lie in LDS, 64 stages of the item being copied from block-table entry ids_bt on (if
+  // ids_ok), and the first 64 of the item after it (if next_ids) in the other of two arrays.  A scalar load in the middle of the
+  // stage loop makes the next wait for an LDS read wait for it as well, and takes about 800 clocks.
+  int ids_bt = 0, ids_buf = 0;
+  bool ids_ok = false, next_ids = false;
+  int* const ids = s_ids + wave * 128;
   const unsigned lds_ids = (unsigned)(uintptr_t)(__attribute__((address_space(3))) int*)ids;
   // (the block table by way of the control words: a pointer that an asm statement has seen is no longer read by scalar loads)
   const char* bt_bytes = reinterpret_cast<const char*>(ctrl) + ((long)H->off_bt - (long)H->off_ctrl);
   auto load_ids = [&]() {
-    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids);
+    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids + ids_buf * 256);
     ids_bt = cs.bt;
     ids_ok = true;
   };
-  auto stream_start = [&](const HfxItem& item) {
-    cs.left = item_stages(item);
-    cs.base = pool + (long)(item.h0 / G) * (2 * Smem<D>::kBlockBytes);
-    cs.bt = item.rq.bt_start + item.kb / HFX_PAGE + (wave & 1);
-    cs.last = item.rq.bt_start + item.rq.n_pages - 1;
-    ids_ok = false;
+  auto load_next_ids = [&]() {
+    next_ids = next_ok;
+    if (next_ok)
+      ids_copy(bt_bytes, 4u * (unsigned)min(nx.bt + 2 * lane, nx.last), lds_ids + (ids_buf ^ 1) * 256);
+  };
+  auto stream_start = [&](const NextItem& item) {
+    cs.left = item.left;
+    cs.base = item.base;
+    cs.bt = item.bt;
+    cs.last = item.last;
+    ids_ok = next_ids;
+    next_ids = false;
+    ids_bt = cs.bt;
+    ids_buf ^= 1;
   };
   auto copy_page = [&](int page) {     // slots are handed out round-robin over the whole run
     block_copy<D>(cs.base + (unsigned long)(unsigned)page * page_bytes, voff,
@@ -988,14 +1039,23 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     --cs.left;
     cs.bt += 2;
   };
-  // copies what there is room for, as far as the items to come are known
-  auto stream_catch_up = [&]() {
+  // copies what there is room for, as far as the items to come are known; landed: so have the ids asked for so far
+  auto stream_catch_up = [&](bool landed) {
 #pragma unroll 1
     while (cs.left > 0 && cs.count < cs.limit) {
       const int n = min(cs.left, cs.limit - cs.count);
       int page[4];                 // four at a time, so that their latency is paid once
+      const int at = (cs.bt - ids_bt) >> 1;
+      if (landed && ids_ok && at <= 60) {
+        const int* id = ids + ids_buf * 64 + at;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
+        for (int i = 0; i < 4; ++i) page[i] = id[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) page[i] = uniform(page[i]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (i < n) copy_page(page[i]);
@@ -1011,7 +1071,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   static_assert(HFX_BT_PAD >= 7, "entries behind a request's last page that the copy stream may read");
   cs.count = 0;
   cs.in_next = 0;
-  stream_start(it);
+  stream_start(next_item(it));
 
   // The stage in which the next ticket is asked for and published (the workgroup waits for the reply there:
   // a reply in flight through the stage loop would make the compiler wait for it, and with it for every copy
@@ -1028,10 +1088,12 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
 
   PrefillWave<D> w;
   WaveRows wr = wave_rows(it, wave);
-  q_load<D>(w.qf, a, it, wr, Hq, n, j);
+  q_load<D>(w.qf, q_rows(it, wr), wr.row0, it.rq.q_len - 1, Hq, n, j);
   int g_st = 0;      // stages multiplied so far, over all items of the run: the ring position
   cs.limit = RING;
-  stream_catch_up();
+  stream_catch_up(false);
+  if (cs.left > 0 && !cs.in_next) load_ids();
+  if (!cs.in_next) load_next_ids();
   if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
 
   // Synchronisation point of the ring: what has been copied so far has landed, everyone's fragment reads
@@ -1048,7 +1110,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     HFX_WAIT_VMCNT(0);
     ring_barrier();
     cs.limit = limit;
-    stream_catch_up();
+    stream_catch_up(true);
     if (cs.left > 2 && (!ids_ok || cs.bt - ids_bt > 64)) load_ids();
     // the short form copies two stages at stage g if count is g + 3 (values) or g + 4 (keys) there, and must
     // leave one for the general form to notice the item's end by
@@ -1058,10 +1120,6 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   };
   for (;;) {
     w.l = 0.f;
-#pragma unroll
-    for (int b = 0; b < D / 32; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) w.o[b][v] = 0.f;
     const int wave_end = wr.wave_kend, unmasked_upto = wr.wave_pmin, ctx_len = it.rq.ctx_len;
     const int end_st = g_st + n_st - 1;      // the item's last stage
     publish_st += g_st;
@@ -1076,7 +1134,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     sync_general(g_st + RING);
     event_st = g_st - 1;
     read_keys<D>(frag, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
-    s0 = score_mfma<D>(w, frag);
+    s0 = first_scores<D>(w, frag);
     read_keys<D>(frag, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
     if (kt + SK - 1 > unmasked_upto) mask_stage(s0, kt);
     w.m = fmaxf(HFX_M_NONE, row_max(s0, sl2));
@@ -1103,7 +1161,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       if (sync) {
         if (g_st < event_st) {
           HFX_WAIT_VMCNT(0);
-          const int* id = ids + ((cs.bt - ids_bt) >> 1);
+          const int* id = ids + ids_buf * 64 + ((cs.bt - ids_bt) >> 1);
           const int id0 = id[0], id1 = id[1];
           ring_barrier();
           copy_page(uniform(id0));
@@ -1123,11 +1181,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     for (;;) {
       // Pairs of stages that every row of the wavefront sees whole, with the short form of the synchronisation point: the common
       // case, without any other condition.  The copies are spread over the 16 matrix instructions behind that point.
-      int pairs = wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto ? (unmasked_upto - kt - 3 * SK + 1) / (2 * SK) + 1 : 0;
+      int pairs = wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto ? (int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1 : 0;
       pairs = uniform(min(pairs, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
       if (pairs > 0) {
         HFX_WAIT_VMCNT(0);            // the ids
-        const int* id = ids + ((cs.bt - ids_bt) >> 1);
+        const int* id = ids + ids_buf * 64 + ((cs.bt - ids_bt) >> 1);
         kt += pairs * (2 * SK);
         cs.left -= 2 * pairs;
         cs.bt += 4 * pairs;
@@ -1166,11 +1224,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       stage_step(s1, s0, false);
     }
     // the item's last stage: Q is not needed any more, and the next item's is asked for
-    WaveRows wr_n = wr;
-    if (next_ok) {
-      wr_n = wave_rows(nx, wave);
-      q_load<D>(w.qf, a, nx, wr_n, Hq, n, j);
-    }
+    if (next_ok) q_load<D>(w.qf, nx.q, nx.q_row0, nx.q_last, Hq, n, j);
     if (kt < wave_end) {
       bf16x8 pb[2];
 #pragma unroll
@@ -1187,14 +1241,17 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
         w.o[i % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], pb[i / (D / 32)], w.o[i % (D / 32)], 0, 0, 0);
     }
     ++g_st;
-    // hand-over: the item is finished; its successor's first stages are in the ring or on their way
-    prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
+    // hand-over: the item is finished; its successor's first stages are in the ring or on their way.  The records of the
+    // successor and of the item after that are asked for ahead of the store.
     tickets_take(t, s_tk);
+    const HfxItem item_c = items[t.cur < n_items ? t.cur : 0];
+    const HfxItem item_n = items[t.nxt < n_items ? t.nxt : 0];
+    prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
     if (!next_ok) break;
-    it = nx;
-    wr = wr_n;
-    nx = items[t.nxt < n_items ? t.nxt : t.cur];
-    next_ok = t.nxt < n_items && nx.type == HFX_ITEM_PREFILL;
+    it = item_c;
+    wr = wave_rows(it, wave);
+    nx = next_item(item_n);
+    next_ok = t.nxt < n_items && item_n.type == HFX_ITEM_PREFILL;
     set_ticket_points();
     pending = 0;
     if (n_st <= 6) tickets_reserve(pending, ctrl, (int)H->queue_classes);
@@ -1202,8 +1259,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     if (cs.left <= 0 && next_ok) {     // the new current item is wholly copied already
       cs.in_next = 1;
       stream_start(nx);
+    } else {
+      load_next_ids();
     }
-    stream_catch_up();
+    stream_catch_up(false);
     // Q is needed by the next MFMA; waiting for it in so many words also tells the compiler that
     // nothing is in flight when the stage loop is re-entered
     if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
@@ -1236,7 +1295,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   __shared__ int s_tk[2];
   // result rows on their way out (prefill_store)
   __shared__ __attribute__((aligned(128))) char s_ostage[4 * 2048];
-  __shared__ int s_ids[4 * 64];     // page ids of stages to come (prefill_run)
+  __shared__ int s_ids[4 * 128];     // page ids of stages to come (prefill_run)
   const HfxHeader* H = &hdr;
   const HfxItem* items = reinterpret_cast<const HfxItem*>(a.desc + H->off_items);
   const int n_items = H->n_items;
