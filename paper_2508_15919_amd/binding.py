@@ -58,6 +58,7 @@ def load() -> ctypes.CDLL:
                                "(hipcc, gfx950).  There is no fallback path.")
         lib = ctypes.CDLL(LIB_PATH)
         i32p = ctypes.POINTER(ctypes.c_int32)
+        ints = ctypes.c_void_p            # int32 array of a step: takes a pointer, an address or bytes (see _ints)
         szp = ctypes.POINTER(ctypes.c_size_t)
         shp = ctypes.POINTER(hfx_shape)
         vp = ctypes.c_void_p
@@ -65,11 +66,11 @@ def load() -> ctypes.CDLL:
         lib.hfx_status_string.restype = ctypes.c_char_p
         lib.hfx_version.argtypes = [i32p, i32p]
         lib.hfx_version.restype = ctypes.c_int32
-        lib.hfx_batch_desc_sizes.argtypes = [shp, ctypes.c_int32, i32p, i32p, i32p, szp, szp, szp]
+        lib.hfx_batch_desc_sizes.argtypes = [shp, ctypes.c_int32, ints, ints, ints, szp, szp, szp]
         lib.hfx_batch_desc_sizes.restype = ctypes.c_int32
-        lib.hfx_fill_batch_desc.argtypes = [shp, ctypes.c_int32, i32p, i32p, i32p, i32p, i32p, vp, ctypes.c_size_t]
+        lib.hfx_fill_batch_desc.argtypes = [shp, ctypes.c_int32, ints, ints, ints, ints, ints, vp, ctypes.c_size_t]
         lib.hfx_fill_batch_desc.restype = ctypes.c_int32
-        lib.hfx_build_batch_desc.argtypes = [shp, ctypes.c_int32, i32p, i32p, i32p, i32p, i32p, vp,
+        lib.hfx_build_batch_desc.argtypes = [shp, ctypes.c_int32, ints, ints, ints, ints, ints, vp,
                                              ctypes.c_size_t, vp, ctypes.c_size_t, vp]
         lib.hfx_build_batch_desc.restype = ctypes.c_int32
         lib.hfx_mixed_paged_attention.argtypes = [shp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp, vp]
@@ -80,7 +81,7 @@ def load() -> ctypes.CDLL:
         lib.hfx_gather_kv.restype = ctypes.c_int32
         lib.hfx_append_kv.argtypes = [shp, vp, vp, vp, vp, vp, vp]
         lib.hfx_append_kv.restype = ctypes.c_int32
-        lib.hfx_copy_pages.argtypes = [shp, vp, vp, ctypes.c_int32, ctypes.c_int32, i32p, i32p, vp, vp,
+        lib.hfx_copy_pages.argtypes = [shp, vp, vp, ctypes.c_int32, ctypes.c_int32, ints, ints, vp, vp,
                                        ctypes.c_size_t, vp]
         lib.hfx_copy_pages.restype = ctypes.c_int32
         dbl, dblp = ctypes.c_double, ctypes.POINTER(ctypes.c_double)
@@ -106,33 +107,38 @@ def _i32(a):
     return arr, arr.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
 
 
+_COPY_BELOW = 1 << 14      # bytes of an array that take less time to copy than its address takes to be had
+
+
+def _ints(a):
+    """int32 array `a` in a form that is passed as its address, and what keeps that alive: asking a numpy array for its
+    address takes about a microsecond, as long as copying 16 KB into a bytes object (a step has five arrays;
+    marshalling them took 12 of the 15 us that describing a step of four requests took)."""
+    if a is None:
+        return None, None
+    arr = np.ascontiguousarray(a, dtype=np.int32)
+    if arr.nbytes < _COPY_BELOW:
+        return arr, arr.tobytes()
+    return arr, arr.ctypes.data
+
+
 def _ptr(x):
     """Raw address of a torch tensor, numpy array, int, or None."""
-    if x is None:
-        return None
-    if isinstance(x, int):
-        return ctypes.c_void_p(x)
+    if x is None or isinstance(x, int):
+        return x
     if hasattr(x, "data_ptr"):
-        return ctypes.c_void_p(x.data_ptr())
+        return x.data_ptr()
     if isinstance(x, np.ndarray):
-        return ctypes.c_void_p(x.ctypes.data)
+        return x.ctypes.data
     raise TypeError(f"cannot take the address of {type(x)}")
 
 
 def _nbytes(x) -> int:
-    if x is None:
-        return 0
-    if hasattr(x, "element_size"):
-        return x.numel() * x.element_size()
-    return int(x.nbytes)
+    return 0 if x is None else x.nbytes
 
 
 def _stream(stream):
-    if stream is None:
-        return None
-    if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+    return stream if stream is None or isinstance(stream, int) else stream.cuda_stream
 
 
 def make_shape(num_q_heads, num_kv_heads, head_dim, num_pages, softmax_scale=0.0, page_size=16) -> hfx_shape:
@@ -152,9 +158,9 @@ def hfx_version():
 
 def hfx_batch_desc_sizes(shape: hfx_shape, kind, q_len, ctx_len):
     """Returns (host_desc_bytes, device_desc_bytes, device_workspace_bytes)."""
-    k, pk = _i32(kind)
-    q, pq = _i32(q_len)
-    c, pc = _i32(ctx_len)
+    k, pk = _ints(kind)
+    q, pq = _ints(q_len)
+    c, pc = _ints(ctx_len)
     h, d, w = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
     rc = load().hfx_batch_desc_sizes(ctypes.byref(shape), len(k), pk, pq, pc, ctypes.byref(h), ctypes.byref(d),
                                      ctypes.byref(w))
@@ -164,11 +170,11 @@ def hfx_batch_desc_sizes(shape: hfx_shape, kind, q_len, ctx_len):
 
 
 def hfx_fill_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc) -> None:
-    k, pk = _i32(kind)
-    q, pq = _i32(q_len)
-    c, pc = _i32(ctx_len)
-    bi, pbi = _i32(bt_indptr)
-    bp, pbp = _i32(bt_pages)
+    k, pk = _ints(kind)
+    q, pq = _ints(q_len)
+    c, pc = _ints(ctx_len)
+    bi, pbi = _ints(bt_indptr)
+    bp, pbp = _ints(bt_pages)
     rc = load().hfx_fill_batch_desc(ctypes.byref(shape), len(k), pk, pq, pc, pbi, pbp, _ptr(host_desc),
                                     _nbytes(host_desc))
     if rc != HFX_OK:
@@ -177,11 +183,11 @@ def hfx_fill_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pa
 
 def hfx_build_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc,
                          stream=None) -> None:
-    k, pk = _i32(kind)
-    q, pq = _i32(q_len)
-    c, pc = _i32(ctx_len)
-    bi, pbi = _i32(bt_indptr)
-    bp, pbp = _i32(bt_pages)
+    k, pk = _ints(kind)
+    q, pq = _ints(q_len)
+    c, pc = _ints(ctx_len)
+    bi, pbi = _ints(bt_indptr)
+    bp, pbp = _ints(bt_pages)
     rc = load().hfx_build_batch_desc(ctypes.byref(shape), len(k), pk, pq, pc, pbi, pbp, _ptr(host_desc),
                                      _nbytes(host_desc), _ptr(device_desc), _nbytes(device_desc), _stream(stream))
     if rc != HFX_OK:
@@ -221,8 +227,8 @@ def hfx_append_kv(shape: hfx_shape, k_new, v_new, kv_pool, host_desc, device_des
 
 def hfx_copy_pages(shape: hfx_shape, src_pool, dst_pool, dst_num_pages: int, src_ids, dst_ids, host_stage,
                    device_stage, stream=None, stage_bytes=None) -> None:
-    s_arr, ps = _i32(np.asarray(src_ids, dtype=np.int32))
-    d_arr, pd = _i32(np.asarray(dst_ids, dtype=np.int32))
+    s_arr, ps = _ints(src_ids)
+    d_arr, pd = _ints(dst_ids)
     assert len(s_arr) == len(d_arr)
     rc = load().hfx_copy_pages(ctypes.byref(shape), _ptr(src_pool), _ptr(dst_pool), int(dst_num_pages), len(s_arr),
                                ps, pd, _ptr(host_stage), _ptr(device_stage),
