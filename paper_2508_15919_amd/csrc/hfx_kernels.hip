@@ -944,6 +944,11 @@ struct NextItem {
   const __bf16* q;            // row 0 of the chunk, this wavefront's head
 };
 
+// Stages still to be copied from which on their page ids are read into LDS: with fewer the short form of the synchronisation point
+// is not worth the extra load (short prompts of 64-wide heads 133.5 us at 8 or 4, 134.7 always and for the next item too; two prompts
+// of each of six tasks, where a workgroup is alone, 16.4 us at 4, 17.3 at 8).
+constexpr int kIdsFrom = 4;
+
 // Runs the prefill item t.cur and, for as long as the workgroup's next item is a prefill item as
 // well, carries straight on into it: the stage ring does not drain between items, only the
 // per-row state (Q, O, m, l) is swapped.  Returns with t.cur at the first item it did not process.
@@ -1003,34 +1008,26 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   const HfxItem item1 = items[t.nxt < n_items ? t.nxt : t.cur];
   NextItem nx = next_item(item1);
   bool next_ok = t.nxt < n_items && item1.type == HFX_ITEM_PREFILL;
-  // The pages of the stages to be copied lie in LDS, 64 stages of the item being copied from block-table entry ids_bt on (if
-  // ids_ok), and the first 64 of the item after it (if next_ids) in the other of two arrays.  A scalar load in the middle of the
-  // stage loop makes the next wait for an LDS read wait for it as well, and takes about 800 clocks.
-  int ids_bt = 0, ids_buf = 0;
-  bool ids_ok = false, next_ids = false;
-  int* const ids = s_ids + wave * 128;
+  // The pages of the stages to be copied lie in LDS where an item is long enough to run in pairs: of 64 stages from
+  // block-table entry ids_bt on, if ids_ok.  A scalar load in the middle of the stage loop makes the next wait for an LDS read wait
+  // for it as well.
+  int ids_bt = 0;
+  bool ids_ok = false;
+  int* const ids = s_ids + wave * 64;
   const unsigned lds_ids = (unsigned)(uintptr_t)(__attribute__((address_space(3))) int*)ids;
   // (the block table by way of the control words: a pointer that an asm statement has seen is no longer read by scalar loads)
   const char* bt_bytes = reinterpret_cast<const char*>(ctrl) + ((long)H->off_bt - (long)H->off_ctrl);
   auto load_ids = [&]() {
-    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids + ids_buf * 256);
+    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids);
     ids_bt = cs.bt;
     ids_ok = true;
-  };
-  auto load_next_ids = [&]() {
-    next_ids = next_ok;
-    if (next_ok)
-      ids_copy(bt_bytes, 4u * (unsigned)min(nx.bt + 2 * lane, nx.last), lds_ids + (ids_buf ^ 1) * 256);
   };
   auto stream_start = [&](const NextItem& item) {
     cs.left = item.left;
     cs.base = item.base;
     cs.bt = item.bt;
     cs.last = item.last;
-    ids_ok = next_ids;
-    next_ids = false;
-    ids_bt = cs.bt;
-    ids_buf ^= 1;
+    ids_ok = false;
   };
   auto copy_page = [&](int page) {     // slots are handed out round-robin over the whole run
     block_copy<D>(cs.base + (unsigned long)(unsigned)page * page_bytes, voff,
@@ -1039,23 +1036,14 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     --cs.left;
     cs.bt += 2;
   };
-  // copies what there is room for, as far as the items to come are known; landed: so have the ids asked for so far
-  auto stream_catch_up = [&](bool landed) {
+  // copies what there is room for, as far as the items to come are known
+  auto stream_catch_up = [&]() {
 #pragma unroll 1
     while (cs.left > 0 && cs.count < cs.limit) {
       const int n = min(cs.left, cs.limit - cs.count);
       int page[4];                 // four at a time, so that their latency is paid once
-      const int at = (cs.bt - ids_bt) >> 1;
-      if (landed && ids_ok && at <= 60) {
-        const int* id = ids + ids_buf * 64 + at;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) page[i] = id[i];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) page[i] = uniform(page[i]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
-      }
+      for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (i < n) copy_page(page[i]);
@@ -1091,9 +1079,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   q_load<D>(w.qf, q_rows(it, wr), wr.row0, it.rq.q_len - 1, Hq, n, j);
   int g_st = 0;      // stages multiplied so far, over all items of the run: the ring position
   cs.limit = RING;
-  stream_catch_up(false);
-  if (cs.left > 0 && !cs.in_next) load_ids();
-  if (!cs.in_next) load_next_ids();
+  stream_catch_up();
   if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
 
   // Synchronisation point of the ring: what has been copied so far has landed, everyone's fragment reads
@@ -1110,12 +1096,13 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     HFX_WAIT_VMCNT(0);
     ring_barrier();
     cs.limit = limit;
-    stream_catch_up(true);
-    if (cs.left > 2 && (!ids_ok || cs.bt - ids_bt > 64)) load_ids();
+    stream_catch_up();
+    if (cs.left > kIdsFrom && (!ids_ok || cs.bt - ids_bt > 64)) load_ids();
     // the short form copies two stages at stage g if count is g + 3 (values) or g + 4 (keys) there, and must
     // leave one for the general form to notice the item's end by
     event_st = cs.count == limit ? g_st + (cs.left > 0 ? (cs.left - 1) / 2 * 2 : 0) + 1 : g_st;
     if (publish_st > g_st) event_st = min(event_st, publish_st - 1);
+    if (!ids_ok) event_st = g_st;
     event_st = min(event_st, g_st + ((64 - ((cs.bt - ids_bt) >> 1)) & ~1) + 1);     // ... as far as the ids go
   };
   for (;;) {
@@ -1161,7 +1148,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       if (sync) {
         if (g_st < event_st) {
           HFX_WAIT_VMCNT(0);
-          const int* id = ids + ids_buf * 64 + ((cs.bt - ids_bt) >> 1);
+          const int* id = ids + ((cs.bt - ids_bt) >> 1);
           const int id0 = id[0], id1 = id[1];
           ring_barrier();
           copy_page(uniform(id0));
@@ -1185,7 +1172,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       pairs = uniform(min(pairs, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
       if (pairs > 0) {
         HFX_WAIT_VMCNT(0);            // the ids
-        const int* id = ids + ids_buf * 64 + ((cs.bt - ids_bt) >> 1);
+        const int* id = ids + ((cs.bt - ids_bt) >> 1);
         kt += pairs * (2 * SK);
         cs.left -= 2 * pairs;
         cs.bt += 4 * pairs;
@@ -1259,10 +1246,8 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     if (cs.left <= 0 && next_ok) {     // the new current item is wholly copied already
       cs.in_next = 1;
       stream_start(nx);
-    } else {
-      load_next_ids();
     }
-    stream_catch_up(false);
+    stream_catch_up();
     // Q is needed by the next MFMA; waiting for it in so many words also tells the compiler that
     // nothing is in flight when the stage loop is re-entered
     if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
@@ -1295,7 +1280,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   __shared__ int s_tk[2];
   // result rows on their way out (prefill_store)
   __shared__ __attribute__((aligned(128))) char s_ostage[4 * 2048];
-  __shared__ int s_ids[4 * 128];     // page ids of stages to come (prefill_run)
+  __shared__ int s_ids[4 * 64];     // page ids of stages to come (prefill_run)
   const HfxHeader* H = &hdr;
   const HfxItem* items = reinterpret_cast<const HfxItem*>(a.desc + H->off_items);
   const int n_items = H->n_items;
