@@ -146,8 +146,7 @@ hfx_status hfx_build_batch_desc(const hfx_shape* shape, int32_t num_requests, co
   HfxHeader h;
   std::memcpy(&h, host_desc, sizeof h);
   if (device_desc_bytes < h.total_bytes) return HFX_ERR_BUFSIZE;
-  if (hipMemcpyAsync(device_desc, host_desc, (size_t)h.total_bytes, hipMemcpyHostToDevice,
-                     static_cast<hipStream_t>(stream)) != hipSuccess)
+  if (hfx::upload(host_desc, device_desc, (size_t)h.total_bytes, static_cast<hipStream_t>(stream)) != hipSuccess)
     return HFX_ERR_DEVICE;
   return HFX_OK;
 }
@@ -229,7 +228,7 @@ hfx_status hfx_copy_pages(const hfx_shape* shape, const void* src_pool, void* ds
     stage[2 * i + 1] = dst_ids[i];
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hipMemcpyAsync(device_stage, host_stage, 8ull * (size_t)num_pairs, hipMemcpyHostToDevice, s) != hipSuccess)
+  if (hfx::upload(host_stage, device_stage, 8ull * (size_t)num_pairs, s) != hipSuccess)
     return HFX_ERR_DEVICE;
   const int units_per_page = shape->num_kv_heads * 2 * HFX_PAGE * shape->head_dim * 2 / 16;
   if (hfx::launch_copy_pages(device_stage, num_pairs, units_per_page, src_pool, dst_pool, s) != hipSuccess)

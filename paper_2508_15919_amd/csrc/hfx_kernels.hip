@@ -1338,6 +1338,19 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict_
     if (to[j] >= 0) __builtin_nontemporal_store(v[j], dst + to[j]);
 }
 
+// Upload of a staging buffer that the GPU can read (pinned host memory): 8-byte words, four of a thread in flight.  Loads of
+// system scope, so that no cache of the GPU answers with what the buffer held before.  Bound: the host link.
+__global__ __launch_bounds__(256) void upload_kernel(const uint64_t* __restrict__ src, uint64_t* __restrict__ dst, long n) {
+  const long base = (long)blockIdx.x * 1024 + threadIdx.x;
+  uint64_t v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (base + 256 * j < n) v[j] = __hip_atomic_load(src + base + 256 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (base + 256 * j < n) dst[base + 256 * j] = v[j];
+}
+
 // Page gather: a workgroup of 2 D threads takes one (page, kv-head) at a time.  A thread moves one 16-byte
 // piece of keys, taken in the order of the destination rows (a row of D elements leaves whole; four rows are
 // 128 contiguous bytes of the source block), and one of values, which are dimension-major in the
@@ -1516,6 +1529,25 @@ hipError_t launch_mixed_attention(const HfxHeader& h, int grid, void* desc, cons
       hipLaunchKernelGGL(merge_kernel<64>, dim3(n_units), dim3(HFX_WG_THREADS), 0, stream, units, groups, wp, ml, Hq, G, op);
   }
   return hipGetLastError();
+}
+
+// Pinned memory is read by a kernel: the runtime gives a megabyte to a copy engine, and the next kernel started 10 to
+// 20 us after that engine's end (a step of 384 short requests, 0.96 MB of descriptor: 397 us with the runtime's copy, 388 so); a few
+// kilobytes it copies with a kernel too.
+hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stream) {
+  hipPointerAttribute_t at;
+  if (bytes % 8 == 0 && ((reinterpret_cast<uintptr_t>(host) | reinterpret_cast<uintptr_t>(device)) & 7u) == 0) {
+    if (hipPointerGetAttributes(&at, host) != hipSuccess) {
+      (void)hipGetLastError();        // memory that the runtime does not know: not an error of the caller's
+    } else if (at.type == hipMemoryTypeHost && at.devicePointer == host) {
+      const long n = (long)(bytes / 8);
+      if (n == 0) return hipSuccess;
+      hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, static_cast<const uint64_t*>(host),
+                         static_cast<uint64_t*>(device), n);
+      return hipGetLastError();
+    }
+  }
+  return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
 }
 
 hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page, const void* src, void* dst,

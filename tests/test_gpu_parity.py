@@ -454,6 +454,53 @@ def test_copy_pages_is_bit_exact_and_attention_follows_the_pages(hb, oracle, Hq,
 
 
 
+@pytest.mark.parametrize("staging,offset", [("pinned", 0), ("pinned", 8), ("pinned", 4), ("pageable", 0), ("pageable", 4)])
+@pytest.mark.parametrize("requests", [3, 400])
+def test_staging_memory_of_every_kind_is_uploaded(hb, staging, offset, requests):
+    """The descriptor is uploaded by a kernel from pinned memory on 8 bytes and by the runtime from any other; the same buffers
+    again with another step, and page ids likewise."""
+    import torch
+    rng = np.random.default_rng(requests)
+    for again in range(3):
+        ctx = rng.integers(1, 300, requests)
+        b = synth.make_batch(4, 2, 64, [DECODE] * requests, [1] * requests, ctx, 41 + again)
+        shape = hb.make_shape(4, 2, 64, b.num_pages)
+        n = hb.hfx_batch_desc_sizes(shape, b.kind, b.q_len, b.ctx_len)[0]
+        if not again:
+            room = 2 * n
+            whole = torch.zeros(room + 16, dtype=torch.uint8, pin_memory=staging == "pinned")
+            dev = torch.zeros(room, dtype=torch.uint8, device="cuda")
+        host = whole[offset:offset + room]
+        hb.hfx_build_batch_desc(shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, b.bt_pages, host, dev, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(dev[:n].cpu(), host[:n]), again
+
+
+def test_captured_upload_reads_the_staging_buffer_at_each_replay(hb, oracle):
+    """Plan, upload and attention under capture: a replay uploads what the staging buffer holds by then."""
+    import torch
+    b = synth.config(1)
+    step = hb.DeviceStep(b)
+    step.run()
+    want = step.out_bits().copy()
+    s = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=s):
+        step.build(torch.cuda.current_stream())
+        step.run(torch.cuda.current_stream())
+    good = step.host_desc.clone()
+    for replay in range(4):
+        step.host_desc.copy_(good)
+        step.device_desc.zero_()
+        step.out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(step.out_bits(), want), replay
+        assert torch.equal(step.device_desc.cpu()[256:], good[256:])
+
+
 def test_device_side_errors(hb):
     import torch
     b = synth.config(1)
