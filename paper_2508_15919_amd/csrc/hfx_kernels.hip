@@ -228,11 +228,16 @@ __global__ __launch_bounds__(HFX_WG_THREADS) void merge_kernel(const HfxUnit* __
 // time, and in a step with about three items per workgroup that left half the chip idle while
 // the other half worked through its reservations.  The first two tickets of a workgroup are its
 // index plus 0 and 1 grids (the queue is in descending cost, so this deals the largest items
-// out evenly, and a workgroup starts without a round trip to a counter).
+// out evenly, and a workgroup starts without a round trip to a counter).  Where that deals all items, no counter
+// is touched: atomics on one address from all over the chip take about 14 ns each, one after the other, and 256 workgroups that
+// ask for a ticket and report their end spend 7 us on them (4 decodes of 100 to 2000 tokens 13.7 us, 12.7 without; a prompt of 777
+// tokens 17.5 and 16.7; 300 rows behind 3000 on 64-wide heads 25.7 and 23.5; 512 workgroups of one short decode piece each 21.2
+// and 12.2).
 constexpr int kDealtTickets = 2;
 struct Tickets {
   int cur, nxt;
   int parity;
+  bool queue;        // there are items behind the dealt ones
 };
 
 // The dealt tickets of a step whose queue is in descending cost.  Workgroups b and b + 256 share a CU, so
@@ -266,8 +271,8 @@ __device__ __forceinline__ void deal_balanced(Tickets& t, int mode, int n_items)
 // Thread 0 asks its class's counter for one more ticket; the reply, an offset from the dealt
 // tickets, goes to tickets_publish.  The other lanes keep what `pending` held: a select on it would
 // wait for the reply, and with it for everything in flight, wherever the compiler places it.
-__device__ __forceinline__ void tickets_reserve(int& pending, int* ctrl, int nc) {
-  if (threadIdx.x == 0) pending = atomicAdd(ctrl + ((int)blockIdx.x & (nc - 1)), 1);
+__device__ __forceinline__ void tickets_reserve(const Tickets& t, int& pending, int* ctrl, int nc) {
+  if (t.queue && threadIdx.x == 0) pending = atomicAdd(ctrl + ((int)blockIdx.x & (nc - 1)), 1);
 }
 // Thread 0 puts the reserved ticket into LDS (two slots alternate, so one barrier per hand-over is
 // enough).  A reply past the end of the queue means the workgroup's class is empty.  It then reads
@@ -277,7 +282,7 @@ __device__ __forceinline__ void tickets_reserve(int& pending, int* ctrl, int nc)
 // correctness: every class is drained by its own workgroups whether or not others help.
 constexpr int kStealAttempts = 4;
 __device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, int* s_tk, int* ctrl, int n_items, int nc) {
-  if (threadIdx.x == 0) {
+  if (t.queue && threadIdx.x == 0) {
     const int base = kDealtTickets * (int)gridDim.x;
     int pos = base + pending * nc + ((int)blockIdx.x & (nc - 1));
     if (nc > 1) {
@@ -305,7 +310,8 @@ __device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, i
 // ... after a workgroup barrier that follows tickets_publish
 __device__ __forceinline__ void tickets_take(Tickets& t, int* s_tk) {
   t.cur = t.nxt;
-  t.nxt = uniform(s_tk[t.parity]);
+  t.nxt = 0x7fffffff;
+  if (t.queue) t.nxt = uniform(s_tk[t.parity]);
   t.parity ^= 1;
 }
 
@@ -461,7 +467,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     // page ids are fetched one pair ahead of the KV loads that need them
     while (pp < pe) {
       if (!reserved && pp + 4 * step >= pe) {   // a few pairs before the end (thread 0 sits in the first wavefront, which always has pairs)
-        tickets_reserve(pending, ctrl, (int)H->queue_classes);
+        tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
         reserved = true;
       }
       if (pp + step < pe) decode_load<D>(r1, a.pool, b0, b1, Hkv, g, k_sel, k_off, v_sel, v_off);
@@ -1072,7 +1078,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   };
   set_ticket_points();
   int pending = 0;
-  if (n_st <= 6) tickets_reserve(pending, ctrl, (int)H->queue_classes);
+  if (n_st <= 6) tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
 
   PrefillWave<D> w;
   WaveRows wr = wave_rows(it, wave);
@@ -1090,7 +1096,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   auto sync_general = [&](int limit) {
     if (g_st == publish_st || g_st + 1 == publish_st) {
       int reply = 0;
-      tickets_reserve(reply, ctrl, (int)H->queue_classes);
+      tickets_reserve(t, reply, ctrl, (int)H->queue_classes);
       tickets_publish(t, reply, s_tk, ctrl, n_items, (int)H->queue_classes);
     }
     HFX_WAIT_VMCNT(0);
@@ -1241,7 +1247,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     next_ok = t.nxt < n_items && item_n.type == HFX_ITEM_PREFILL;
     set_ticket_points();
     pending = 0;
-    if (n_st <= 6) tickets_reserve(pending, ctrl, (int)H->queue_classes);
+    if (n_st <= 6) tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
     cs.in_next = 0;
     if (cs.left <= 0 && next_ok) {     // the new current item is wholly copied already
       cs.in_next = 1;
@@ -1259,8 +1265,8 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
 // ----------------------------------------------------------------------------------------------
 // The persistent kernel: workgroups pull items in descending modelled cost until the queue is
 // empty.  A workgroup always knows its next item (see Tickets).  The queue counters live in the
-// descriptor; the last workgroup to leave restores them to zero so the descriptor can serve the
-// next launch.
+// descriptor; the last workgroup to leave a launch that uses them restores them to zero so the descriptor can serve the
+// next one.
 // ----------------------------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
@@ -1289,6 +1295,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   t.nxt = (int)(blockIdx.x + gridDim.x);
   if (hdr.deal_balanced) deal_balanced(t, (int)hdr.deal_balanced, n_items);
   t.parity = 0;
+  t.queue = n_items > kDealtTickets * (int)gridDim.x;
   while (t.cur < n_items) {
     if (items[t.cur].type == HFX_ITEM_DECODE) {
       decode_run<D>(a, H, items, n_items, t, s_tk, &ctrl[0], smem);
@@ -1300,7 +1307,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   // workgroup reports itself finished, or it could land after the reset below
   HFX_WAIT_VMCNT(0);
   asm volatile("" ::: "memory");
-  if (threadIdx.x == 0) {
+  if (t.queue && threadIdx.x == 0) {
     const int done = atomicAdd(&ctrl[HFX_QUEUE_CLASSES], 1);
     if (done == (int)gridDim.x - 1) {
       for (int c = 0; c <= HFX_QUEUE_CLASSES; ++c) atomicExch(&ctrl[c], 0);
