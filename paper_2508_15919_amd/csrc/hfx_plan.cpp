@@ -381,13 +381,67 @@ static double cap_within_workspace(const int32_t* kind, const int32_t* q_len, co
   return hi;
 }
 
-// The work items of the step's requests (P.reqs), decode pieces of at most about cap_ns and prefill tiles cut
+// How the contexts of decode requests are cut: kv-heads of an item, and tokens of a piece at most.
+struct DecodeCut {
+  int heads;
+  int64_t tokens;
+};
+
+// By default an item has up to four kv-heads, one for each wavefront, and takes about cap_ns.  Steps whose items all have a place on the
+// chip at once do better with fewer heads an item: its wavefronts then walk a quarter or half of the pages each, so that pieces
+// can be longer and partials fewer, or there is nothing to merge.  `n_pre`: prefill items of the step.
+// Decodes alone take up to two items a CU (all on 32/8 heads of 128 unless named): 4 of 100 to 2000 tokens 12.9 us by default, 10.9 so;
+// 12 of 200 to 400 12.0 and 8.2; 16 of 2000 34.1 and 29.4; 64 of 1000 55.0 and 50.5; 128 of 500 to 2000 133 and 118 (two heads);
+// 100 of 500 to 5000 on 64-wide heads 112 and 107; 8 of 20000 to 60000 on one kv-head 38.0 and 36.2; at worst 64 of 1000 to 4000 there,
+// 20.2 and 20.6.  A context is left whole if that saves the merge launch (3.3 us) for at most 1024 more tokens of one head (4 us): 500 tokens
+// 11.0 us in pieces, 8.4 whole; with 2048 more, the 4 decodes above 14.4.  Pieces have 256 tokens of one head at least (128, 512: the same within
+// 3 % where they differ).
+// Beside prefill items decodes keep to CUs of their own, or the longer piece beside a prefill item ends last, and to pieces no
+// longer than the default: 3 of 200 to 900 beside a prompt of 100 11.5 us and 8.5; where up to 512 items were allowed, 6 of 500 to 5000 beside 777
+// 24.0 and 26.6, and 10 of 200 to 3000 on 8/8 heads beside 192 rows 15.4 and 18.3 (15.0 so).
+static const int64_t kHeadTokensMin = 256;
+static const int64_t kHeadTokensWhole = 1024;
+static const int64_t kHeadTokensBeside = 700;
+static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, int Hkv, int D, double cap_ns, int64_t n_dec, int64_t dec_tokens,
+                            int64_t n_pre) {
+  const int most = kv_heads_per_item(Hkv);
+  const DecodeCut by_time = {most, std::max<int64_t>((int64_t)(cap_ns / ((double)most * D * 4.0 / kDecodeBytesPerNs)), kMinDecodeTokens)};
+  const int64_t room = n_pre == 0 ? HFX_PLAN_WGS : HFX_PLAN_WGS / 2 - n_pre;
+  int h = 1;
+  while (h < most && n_dec * (Hkv / h) > room) h *= 2;
+  if (n_dec == 0 || h > 2 || n_dec * (Hkv / h) > room || (n_pre > 0 && h == most)) return by_time;
+  int32_t longest = 0;
+  for (int r = 0; r < R; ++r)
+    if (kind[r] == HFX_DECODE) longest = std::max(longest, ctx_len[r]);
+  auto items = [&](uint32_t pairs) {          // with pieces of that many page pairs
+    int64_t n = 0;
+    for (int r = 0; r < R; ++r) {
+      if (kind[r] != HFX_DECODE) continue;
+      const uint32_t all = ((uint32_t)ctx_len[r] + 2 * HFX_PAGE - 1) / (2 * HFX_PAGE);
+      const uint32_t piece = std::max(pairs, (all + kMaxSplits - 1) / kMaxSplits);
+      n += (all + piece - 1) / piece;
+    }
+    return n * (Hkv / h);
+  };
+  uint32_t lo = (uint32_t)std::max(kHeadTokensMin / h, dec_tokens * (Hkv / h) / room) / (2 * HFX_PAGE), hi = (uint32_t)longest / (2 * HFX_PAGE) + 1;
+  lo = std::max(lo, 1u);
+  while (lo < hi) {
+    const uint32_t mid = lo + (hi - lo) / 2;
+    if (items(mid) <= room) hi = mid;
+    else lo = mid + 1;
+  }
+  const int64_t tokens = (int64_t)lo * 2 * HFX_PAGE;
+  if (n_pre > 0 && tokens * h > kHeadTokensBeside) return by_time;
+  return {h, longest <= tokens + kHeadTokensWhole / h ? std::max<int64_t>(longest, tokens) : tokens};
+}
+
+// The work items of the step's requests (P.reqs), decode requests cut by dec_cut and prefill tiles
 // by cap_prefill_ns, with their merge groups; *rows: partial rows of all of them, *dec_rows: those of decode items,
 // *pre_ord: prefill requests.
-static hfx_status make_items(const hfx_shape* shape, int32_t R, double cap_ns, double cap_prefill_ns, Plan* out,
+static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut& dec_cut, double cap_prefill_ns, Plan* out,
                              int64_t* rows_out, int64_t* dec_rows_out, int64_t* pre_ord_out) {
   const int Hkv = shape->num_kv_heads, D = shape->head_dim, G = shape->num_q_heads / Hkv;
-  const int ngc = kv_heads_per_item(Hkv);
+  const int ngc = dec_cut.heads;
   const int hpw = q_heads_per_item(G);
   const int rows_wg = HFX_WAVE_ROWS * (4 / hpw);
   Plan& P = *out;
@@ -402,9 +456,7 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, double cap_ns, d
     const HfxReq& q = P.reqs[(size_t)r];
     if (q.kind == HFX_DECODE) {
       const double ns_per_token = (double)ngc * D * 4.0 / kDecodeBytesPerNs;
-      int64_t L = (int64_t)(cap_ns / ns_per_token);
-      L = std::max<int64_t>(L, kMinDecodeTokens);
-      L = std::max<int64_t>(L, ((int64_t)q.ctx_len + kMaxSplits - 1) / kMaxSplits);
+      const int64_t L = std::max<int64_t>(dec_cut.tokens, ((int64_t)q.ctx_len + kMaxSplits - 1) / kMaxSplits);
       int64_t pages_per = (L + HFX_PAGE - 1) / HFX_PAGE;
       pages_per += pages_per & 1;                     // page pairs stay aligned across splits
       int nsplit = (int)((q.n_pages + pages_per - 1) / pages_per);
@@ -515,7 +567,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
 
   Plan& P = *out;
   P.reqs.assign((size_t)R, HfxReq());
-  int64_t T = 0, nbt = 0;
+  int64_t T = 0, nbt = 0, n_dec = 0, dec_tokens = 0;
   double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work, prefill by (row, key) pairs
   double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes ...
   double apart_ns = 0.0;               // ... or by every row tile and head block of a request that has one row tile
@@ -538,6 +590,8 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     nbt += q.bt_len;
     if (kind[r] == HFX_DECODE) {
       dec_ns += (double)ctx_len[r] * Hkv * D * 4.0 / kDecodeBytesPerNs;
+      ++n_dec;
+      dec_tokens += ctx_len[r];
     } else {
       double ql = q_len[r], p = ctx_len[r] - q_len[r];
       pre_ns += 4.0 * D * Hq * (ql * p + ql * (ql + 1) / 2) / kPrefillFlopsPerNs;
@@ -576,13 +630,20 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
   const double cap_prefill_ns =
       pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, stream_ns, decode_dominated, &P) : kMinItemNs;
 
+  int64_t n_pre = 0;                   // prefill items
+  if (pre_ns > 0.0 && n_dec > 0 && n_dec * (Hkv / kv_heads_per_item(Hkv)) < HFX_PLAN_WGS / 2)
+    cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, cap_prefill_ns, [&](int64_t p, int64_t, int64_t r1) { return tile_ns(D, p + r1); }, &n_pre);
+  else if (pre_ns > 0.0)
+    n_pre = HFX_PLAN_WGS;
+  const DecodeCut dec_cut = decode_cut(kind, ctx_len, R, Hkv, D, cap_ns, n_dec, dec_tokens, n_pre);
+
   int64_t rows = 0, dec_rows = 0, pre_ord = 0;
-  st = make_items(shape, R, cap_ns, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
+  st = make_items(shape, R, dec_cut, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
   if (st != HFX_OK) return st;
   if (rows * (4ll * D + 8) + 512 > (int64_t)HFX_STATIC_WS_BYTES && rows > dec_rows) {
     const double c = cap_within_workspace(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, pre_ns, dec_rows, cap_prefill_ns);
     if (c > cap_prefill_ns) {
-      st = make_items(shape, R, cap_ns, c, &P, &rows, &dec_rows, &pre_ord);
+      st = make_items(shape, R, dec_cut, c, &P, &rows, &dec_rows, &pre_ord);
       if (st != HFX_OK) return st;
     }
   }

@@ -328,6 +328,22 @@ def test_merge_of_two_to_sixty_splits(hb, oracle):
     check_full(hb, oracle, b)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,prompt", [
+    (32, 8, 128, 5, 1, 2500, 0), (24, 8, 128, 40, 15, 1300, 0), (16, 16, 128, 30, 1, 1024, 0), (16, 4, 64, 100, 30, 2100, 0), (32, 4, 64, 128, 1, 300, 0),
+    (8, 8, 128, 64, 900, 1100, 0), (8, 2, 64, 129, 500, 1600, 0), (16, 1, 128, 9, 200, 9000, 0), (32, 8, 128, 3, 30, 900, 70), (12, 4, 128, 7, 1, 700, 33)])
+def test_decode_items_of_one_and_two_heads(hb, oracle, Hq, Hkv, D, n, lo, hi, prompt):
+    """Small steps give each decode item one or two kv-heads, so that two or four wavefronts share a head's pages: contexts of less
+    than a page pair per wavefront, whole ones and pieces, alone and beside a prompt."""
+    rng = np.random.default_rng(1000 * n + hi)
+    c = rng.integers(lo, hi + 1, n).tolist()
+    k = bool(prompt)
+    b = small_pool_batch(rng, Hq, Hkv, D, [DECODE] * n + [PREFILL] * k, [1] * n + [prompt] * k, c + [prompt] * k, f"dec-heads-{Hq}-{Hkv}-{D}-{n}",
+                         n_pages=400)
+    step, _ = check_full(hb, oracle, b)
+    items = hb.parse_desc(step.host_desc.numpy())["items"]
+    assert set(items["hn"][items["type"] == 0].tolist()) <= {1, 2}
+
+
 def test_shared_prefix_pages(hb, oracle):
     b = synth.make_batch(32, 8, 128, [DECODE, DECODE, PREFILL], [1, 1, 40], [300, 300, 296], 13)
     n = 16
