@@ -1235,12 +1235,15 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     }
     ++g_st;
     // hand-over: the item is finished; its successor's first stages are in the ring or on their way.  The records of the
-    // successor and of the item after that are asked for ahead of the store.
+    // successor and of the item after that are asked for ahead of the store; a workgroup's last item waits for none.
     tickets_take(t, s_tk);
-    const HfxItem item_c = items[t.cur < n_items ? t.cur : 0];
-    const HfxItem item_n = items[t.nxt < n_items ? t.nxt : 0];
+    if (!next_ok) {
+      prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
+      break;
+    }
+    const HfxItem item_c = items[t.cur];
+    const HfxItem item_n = items[t.nxt < n_items ? t.nxt : t.cur];
     prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
-    if (!next_ok) break;
     it = item_c;
     wr = wave_rows(it, wave);
     nx = next_item(item_n);
