@@ -1322,29 +1322,36 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
 // Page copy: pool pages named by (src, dst) id pairs move between two pools of the same
 // geometry (or inside one).  The device half of handing a request's KV blocks from the
 // instance that prefilled it to the instance that decodes it (HFX Section 3.3.1,
-// disaggregated mode; Section 3.4).  16-byte units; a workgroup moves 16 KB with all of its
-// loads in flight before the first store.
+// disaggregated mode; Section 3.4).  16-byte units, of which a page has a multiple of 256; a workgroup moves 16 KB with all of its
+// loads in flight before the first store.  The page of a 4 KB piece is the same for the whole workgroup, so that its id
+// is one scalar load and nothing is divided per thread.
+// Stream: the pages are not read again, nor do they find a place in the last-level cache.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict__ pairs, long n_units,
-                                                         int units_per_page, const u32x4* __restrict__ src,
-                                                         u32x4* __restrict__ dst) {
-  const long base = (long)blockIdx.x * 1024 + threadIdx.x;
-  u32x4 v[4];
-  long to[4];
+template <bool Stream>
+__global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict__ pairs, long n_pairs, unsigned units_per_page,
+                                                         const u32x4* __restrict__ src, u32x4* __restrict__ dst) {
+  constexpr unsigned kPiece = 256, kPieces = 4;
+  const bool whole = units_per_page >= kPieces * kPiece;        // the workgroup stays inside a page
+  const unsigned per_page = whole ? units_per_page / (kPieces * kPiece) : 1;
+  const unsigned page = blockIdx.x / per_page, part = blockIdx.x - page * per_page;
+  u32x4 v[kPieces];
+  long to[kPieces];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const long u = base + 256 * j;
+  for (unsigned j = 0; j < kPieces; ++j) {
+    const unsigned unit = part * (kPieces * kPiece) + j * kPiece;
+    const unsigned skip = whole ? 0 : unit / units_per_page;     // small pages: this piece's, from the workgroup's first
+    const long pr = whole ? (long)page : (long)page * (kPieces * kPiece / units_per_page) + skip;
     to[j] = -1;
-    if (u < n_units) {
-      const long pr = u / units_per_page;
-      const int off = (int)(u - pr * units_per_page);
+    if (pr < n_pairs) {
       const int2 id = pairs[pr];
-      v[j] = __builtin_nontemporal_load(src + (long)id.x * units_per_page + off);
+      const unsigned off = unit - skip * units_per_page + threadIdx.x;
+      const u32x4* from = src + (long)id.x * units_per_page + off;
+      v[j] = Stream ? __builtin_nontemporal_load(from) : *from;
       to[j] = (long)id.y * units_per_page + off;
     }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (unsigned j = 0; j < kPieces; ++j)
     if (to[j] >= 0) __builtin_nontemporal_store(v[j], dst + to[j]);
 }
 
@@ -1560,15 +1567,23 @@ hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stre
   return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
 }
 
+// Copies of at most a quarter of the last-level cache leave their source in it, where it may still be from the writing of those pages (41 MB
+// each way, three sets of buffers in turn: 21.1 us, 25.1 streaming; 268 MB 61.2 and 60.2).  With a division by the page size for each
+// 16 bytes the kernel took 26.8 and 61.2.
+constexpr long kCopyStreamBytes = 64l << 20;
 hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page, const void* src, void* dst,
                              hipStream_t stream) {
   const long n_units = n_pairs * units_per_page;
   if (n_units == 0) return hipSuccess;
   const long blocks = (n_units + 1023) / 1024;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(copy_pages_kernel, dim3((unsigned)blocks), dim3(256), 0, stream,
-                     static_cast<const int2*>(pairs), n_units, units_per_page, static_cast<const u32x4*>(src),
-                     static_cast<u32x4*>(dst));
+  const int2* p = static_cast<const int2*>(pairs);
+  const u32x4* from = static_cast<const u32x4*>(src);
+  u32x4* to = static_cast<u32x4*>(dst);
+  if (n_units * 16 > kCopyStreamBytes)
+    hipLaunchKernelGGL(copy_pages_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, p, n_pairs, (unsigned)units_per_page, from, to);
+  else
+    hipLaunchKernelGGL(copy_pages_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, p, n_pairs, (unsigned)units_per_page, from, to);
   return hipGetLastError();
 }
 

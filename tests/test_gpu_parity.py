@@ -470,6 +470,24 @@ def test_copy_pages_is_bit_exact_and_attention_follows_the_pages(hb, oracle, Hq,
 
 
 
+@pytest.mark.parametrize("Hkv,D,pairs", [(1, 64, 1), (1, 64, 3), (1, 64, 9), (1, 128, 1), (2, 64, 5), (4, 64, 7), (12, 64, 3), (12, 128, 2), (8, 128, 1100)])
+def test_copy_pages_of_every_page_size(hb, Hkv, D, pairs):
+    """Pages of 4 KB to 96 KB: several pages to a workgroup, several workgroups to a page, part of a workgroup past the last pair, and
+    a copy large enough to go past the caches; pages that are not named stay as they were."""
+    import torch
+    rng = np.random.default_rng(pairs + Hkv)
+    n = pairs + 5
+    src = torch.from_numpy(rng.integers(-2**15, 2**15, (n, Hkv, 2, 16 * D), dtype=np.int16)).cuda()
+    dst = torch.from_numpy(rng.integers(-2**15, 2**15, (n + 3, Hkv, 2, 16 * D), dtype=np.int16)).cuda()
+    s_ids, d_ids = rng.permutation(n)[:pairs], rng.permutation(n + 3)[:pairs]
+    want = dst.clone()
+    want[torch.from_numpy(d_ids).cuda()] = src[torch.from_numpy(s_ids).cuda()]
+    host, dev = torch.empty(8 * pairs, dtype=torch.uint8, pin_memory=True), torch.empty(8 * pairs, dtype=torch.uint8, device="cuda")
+    hb.hfx_copy_pages(hb.make_shape(Hkv, Hkv, D, n), src, dst, n + 3, s_ids, d_ids, host, dev, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert torch.equal(dst, want)
+
+
 @pytest.mark.parametrize("staging,offset", [("pinned", 0), ("pinned", 8), ("pinned", 4), ("pageable", 0), ("pageable", 4)])
 @pytest.mark.parametrize("requests", [3, 400])
 def test_staging_memory_of_every_kind_is_uploaded(hb, staging, offset, requests):
