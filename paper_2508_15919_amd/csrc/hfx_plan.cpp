@@ -399,39 +399,58 @@ struct DecodeCut {
 // Beside prefill items decodes keep to CUs of their own, or the longer piece beside a prefill item ends last, and to pieces no
 // longer than the default: 3 of 200 to 900 beside a prompt of 100 11.5 us and 8.5; where up to 512 items were allowed, 6 of 500 to 5000 beside 777
 // 24.0 and 26.6, and 10 of 200 to 3000 on 8/8 heads beside 192 rows 15.4 and 18.3 (15.0 so).
+//
+// Beside prefill items that a decode stream outweighs, a step that takes a few more than the 1024 items of two rounds (up to
+// kRoundsOver of them) has its pieces lengthened to that: all items are then dealt, and no round has a few items in it (64 of 100 to 8192
+// beside chunks of 512 and 512 behind 1536, 1304 items: 103.4 us, 98.6 so; 50 of 1500 to 4000 beside 400 115.2 and 113.8).  70 decodes alone, 1.5 times
+// 1024 items: 117.5 and 125.9, hence neither more nor without prefill items.
+static const double kRoundsOver = 1.3;
 static const int64_t kHeadTokensMin = 256;
 static const int64_t kHeadTokensWhole = 1024;
 static const int64_t kHeadTokensBeside = 700;
 static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, int Hkv, int D, double cap_ns, int64_t n_dec, int64_t dec_tokens,
-                            int64_t n_pre) {
+                            int64_t n_pre, bool decode_dominated) {
   const int most = kv_heads_per_item(Hkv);
   const DecodeCut by_time = {most, std::max<int64_t>((int64_t)(cap_ns / ((double)most * D * 4.0 / kDecodeBytesPerNs)), kMinDecodeTokens)};
-  const int64_t room = n_pre == 0 ? HFX_PLAN_WGS : HFX_PLAN_WGS / 2 - n_pre;
-  int h = 1;
-  while (h < most && n_dec * (Hkv / h) > room) h *= 2;
-  if (n_dec == 0 || h > 2 || n_dec * (Hkv / h) > room || (n_pre > 0 && h == most)) return by_time;
-  int32_t longest = 0;
-  for (int r = 0; r < R; ++r)
-    if (kind[r] == HFX_DECODE) longest = std::max(longest, ctx_len[r]);
-  auto items = [&](uint32_t pairs) {          // with pieces of that many page pairs
+  constexpr uint32_t kPair = 2 * HFX_PAGE;    // tokens of a page pair
+  auto items = [&](uint32_t pairs, int heads) {          // with pieces of that many page pairs
     int64_t n = 0;
     for (int r = 0; r < R; ++r) {
       if (kind[r] != HFX_DECODE) continue;
-      const uint32_t all = ((uint32_t)ctx_len[r] + 2 * HFX_PAGE - 1) / (2 * HFX_PAGE);
+      const uint32_t all = ((uint32_t)ctx_len[r] + kPair - 1) / kPair;
       const uint32_t piece = std::max(pairs, (all + kMaxSplits - 1) / kMaxSplits);
       n += (all + piece - 1) / piece;
     }
-    return n * (Hkv / h);
+    return n * (Hkv / heads);
   };
-  uint32_t lo = (uint32_t)std::max(kHeadTokensMin / h, dec_tokens * (Hkv / h) / room) / (2 * HFX_PAGE), hi = (uint32_t)longest / (2 * HFX_PAGE) + 1;
-  lo = std::max(lo, 1u);
-  while (lo < hi) {
-    const uint32_t mid = lo + (hi - lo) / 2;
-    if (items(mid) <= room) hi = mid;
-    else lo = mid + 1;
-  }
-  const int64_t tokens = (int64_t)lo * 2 * HFX_PAGE;
-  if (n_pre > 0 && tokens * h > kHeadTokensBeside) return by_time;
+  auto shortest = [&](uint32_t lo, uint32_t hi, int heads, int64_t most_items) {    // pieces in [lo, hi] that make no more items
+    while (lo < hi) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      if (items(mid, heads) <= most_items) hi = mid;
+      else lo = mid + 1;
+    }
+    return lo;
+  };
+  auto by_rounds = [&]() -> DecodeCut {      // by time, but lengthened to two rounds if that is close
+    const int64_t two_rounds = 2 * HFX_PLAN_WGS - n_pre;
+    if (!decode_dominated || n_pre == 0 || n_pre >= HFX_PLAN_WGS || n_dec * (Hkv / most) > HFX_PLAN_WGS) return by_time;
+    const uint32_t piece = (uint32_t)(by_time.tokens + kPair - 1) / kPair;
+    const int64_t now = items(piece, most);
+    if (now <= two_rounds || (double)(now + n_pre) > kRoundsOver * (double)(2 * HFX_PLAN_WGS)) return by_time;
+    return {most, (int64_t)shortest(piece, 4 * piece, most, two_rounds) * kPair};
+  };
+  const int64_t room = n_pre == 0 ? HFX_PLAN_WGS : HFX_PLAN_WGS / 2 - n_pre;
+  int h = 1;
+  while (h < most && n_dec * (Hkv / h) > room) h *= 2;
+  if (n_dec == 0) return by_time;
+  if (h > 2 || n_dec * (Hkv / h) > room || (n_pre > 0 && h == most)) return by_rounds();
+  int32_t longest = 0;
+  for (int r = 0; r < R; ++r)
+    if (kind[r] == HFX_DECODE) longest = std::max(longest, ctx_len[r]);
+  const uint32_t least = (uint32_t)std::max(kHeadTokensMin / h, dec_tokens * (Hkv / h) / room) / kPair;
+  const uint32_t lo = shortest(std::max(least, 1u), (uint32_t)longest / kPair + 1, h, room);
+  const int64_t tokens = (int64_t)lo * kPair;
+  if (n_pre > 0 && tokens * h > kHeadTokensBeside) return by_rounds();
   return {h, longest <= tokens + kHeadTokensWhole / h ? std::max<int64_t>(longest, tokens) : tokens};
 }
 
@@ -631,11 +650,11 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       pre_ns > 0.0 ? prefill_cap(kind, q_len, ctx_len, R, mult, D, hpw, rows_wg, dec_ns, stream_ns, decode_dominated, &P) : kMinItemNs;
 
   int64_t n_pre = 0;                   // prefill items
-  if (pre_ns > 0.0 && n_dec > 0 && n_dec * (Hkv / kv_heads_per_item(Hkv)) < HFX_PLAN_WGS / 2)
+  if (pre_ns > 0.0 && n_dec > 0 && (decode_dominated || n_dec * (Hkv / kv_heads_per_item(Hkv)) < HFX_PLAN_WGS / 2))
     cut_rows(kind, q_len, ctx_len, R, mult, rows_wg, cap_prefill_ns, [&](int64_t p, int64_t, int64_t r1) { return tile_ns(D, p + r1); }, &n_pre);
   else if (pre_ns > 0.0)
     n_pre = HFX_PLAN_WGS;
-  const DecodeCut dec_cut = decode_cut(kind, ctx_len, R, Hkv, D, cap_ns, n_dec, dec_tokens, n_pre);
+  const DecodeCut dec_cut = decode_cut(kind, ctx_len, R, Hkv, D, cap_ns, n_dec, dec_tokens, n_pre, decode_dominated);
 
   int64_t rows = 0, dec_rows = 0, pre_ord = 0;
   st = make_items(shape, R, dec_cut, cap_prefill_ns, &P, &rows, &dec_rows, &pre_ord);
