@@ -408,6 +408,12 @@ static const double kRoundsOver = 1.3;
 static const int64_t kHeadTokensMin = 256;
 static const int64_t kHeadTokensWhole = 1024;
 static const int64_t kHeadTokensBeside = 700;
+// One round has to come out even: no piece may be longer than kLongestPiece times an even share, or what is left of a long context when
+// there is room for one piece of each ends last (64 contexts spread evenly over the logarithm from 16 to 8192: 60.4 us by default, 84.1 in
+// one round of one-head items, 59.8 of two-head items; 20 such families 1.05 on average, none slower; at 2 times 1.045, at 1.5 1.037).  Only in
+// steps of at most kHeadShareWhole tokens of a head for each item is the longer piece bound by latency and not by the stream.
+static const double kLongestPiece = 3.0;
+static const int64_t kHeadShareWhole = 512;
 static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, int Hkv, int D, double cap_ns, int64_t n_dec, int64_t dec_tokens,
                             int64_t n_pre, bool decode_dominated) {
   const int most = kv_heads_per_item(Hkv);
@@ -447,11 +453,17 @@ static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, 
   int32_t longest = 0;
   for (int r = 0; r < R; ++r)
     if (kind[r] == HFX_DECODE) longest = std::max(longest, ctx_len[r]);
-  const uint32_t least = (uint32_t)std::max(kHeadTokensMin / h, dec_tokens * (Hkv / h) / room) / kPair;
-  const uint32_t lo = shortest(std::max(least, 1u), (uint32_t)longest / kPair + 1, h, room);
-  const int64_t tokens = (int64_t)lo * kPair;
-  if (n_pre > 0 && tokens * h > kHeadTokensBeside) return by_rounds();
-  return {h, longest <= tokens + kHeadTokensWhole / h ? std::max<int64_t>(longest, tokens) : tokens};
+  for (; h <= std::min(2, most); h *= 2) {
+    const int64_t share = dec_tokens * (Hkv / h) / room;
+    const uint32_t least = (uint32_t)std::max<int64_t>(std::max(kHeadTokensMin / h, share) / kPair, 1);
+    const uint32_t lo = shortest(least, (uint32_t)longest / kPair + 1, h, room);
+    const int64_t tokens = (int64_t)lo * kPair;
+    if (tokens > kLongestPiece * (double)(least * kPair)) continue;
+    if (n_pre > 0 && (tokens * h > kHeadTokensBeside || h == most)) break;
+    const bool whole = longest <= tokens + kHeadTokensWhole / h && share * h <= kHeadShareWhole;
+    return {h, whole ? std::max<int64_t>(longest, tokens) : tokens};
+  }
+  return by_rounds();
 }
 
 // The work items of the step's requests (P.reqs), decode requests cut by dec_cut and prefill tiles
