@@ -1548,23 +1548,45 @@ hipError_t launch_mixed_attention(const HfxHeader& h, int grid, void* desc, cons
   return hipGetLastError();
 }
 
+// Whether a kernel on `stream` may copy `bytes` from host to device by itself: from pinned memory that the GPU sees under the same
+// address to memory of the stream's own GPU, which is the current one, both whole inside one allocation.  (A query of
+// any other address succeeds and tells of no memory; it leaves no error behind.)
+static bool kernel_may_upload(const void* host, const void* device, size_t bytes, hipStream_t stream) {
+  if ((reinterpret_cast<uintptr_t>(host) | reinterpret_cast<uintptr_t>(device) | bytes) & 7u) return false;
+  struct Memory {
+    unsigned type = hipMemoryTypeUnregistered;
+    int gpu = -1;
+    void* on_gpu = nullptr;
+    char* start = nullptr;
+    size_t size = 0;
+  } from, to;
+  auto query = [](const void* p, Memory* m) {
+    hipPointer_attribute which[] = {HIP_POINTER_ATTRIBUTE_MEMORY_TYPE, HIP_POINTER_ATTRIBUTE_DEVICE_ORDINAL, HIP_POINTER_ATTRIBUTE_DEVICE_POINTER,
+                                    HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, HIP_POINTER_ATTRIBUTE_RANGE_SIZE};
+    void* answer[] = {&m->type, &m->gpu, &m->on_gpu, &m->start, &m->size};
+    return hipDrvPointerGetAttributes(5, which, answer, const_cast<void*>(p)) == hipSuccess;
+  };
+  auto whole = [&](const void* p, const Memory& m) {
+    const char* at = static_cast<const char*>(p);
+    return at >= m.start && (size_t)(at - m.start) <= m.size && m.size - (size_t)(at - m.start) >= bytes;
+  };
+  if (!query(host, &from) || from.type != hipMemoryTypeHost || from.on_gpu != host || !whole(host, from)) return false;
+  if (!query(device, &to) || to.type != hipMemoryTypeDevice || !whole(device, to)) return false;
+  int current = -1;
+  hipDevice_t streams = -1;
+  return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(stream, &streams) == hipSuccess && current == to.gpu && streams == to.gpu;
+}
+
 // Pinned memory is read by a kernel: the runtime gives a megabyte to a copy engine, and the next kernel started 10 to
 // 20 us after that engine's end (a step of 384 short requests, 0.96 MB of descriptor: 397 us with the runtime's copy, 388 so); a few
 // kilobytes it copies with a kernel too.
 hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stream) {
-  hipPointerAttribute_t at;
-  if (bytes % 8 == 0 && ((reinterpret_cast<uintptr_t>(host) | reinterpret_cast<uintptr_t>(device)) & 7u) == 0) {
-    if (hipPointerGetAttributes(&at, host) != hipSuccess) {
-      (void)hipGetLastError();        // memory that the runtime does not know: not an error of the caller's
-    } else if (at.type == hipMemoryTypeHost && at.devicePointer == host) {
-      const long n = (long)(bytes / 8);
-      if (n == 0) return hipSuccess;
-      hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, static_cast<const uint64_t*>(host),
-                         static_cast<uint64_t*>(device), n);
-      return hipGetLastError();
-    }
-  }
-  return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
+  if (bytes == 0) return hipSuccess;
+  if (!kernel_may_upload(host, device, bytes, stream)) return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
+  const long n = (long)(bytes / 8);
+  hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, static_cast<const uint64_t*>(host),
+                     static_cast<uint64_t*>(device), n);
+  return hipGetLastError();
 }
 
 // Copies of at most a quarter of the last-level cache leave their source in it, where it may still be from the writing of those pages (41 MB

@@ -18,8 +18,8 @@ hipError_t launch_gather_kv(const HfxHeader& h, int n_tokens, const void* desc, 
 hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_new, const void* v_new, void* pool,
                             hipStream_t stream);
 
-// Copies a host staging buffer to the device on `stream`: by a kernel where the GPU can read the buffer (pinned memory),
-// by the runtime otherwise.  Either way the buffer is read when the stream gets there.
+// Copies a host staging buffer to the device on `stream`: by a kernel from pinned memory to memory of the
+// stream's GPU, by the runtime otherwise.  Either way the buffer is read when the stream gets there.
 hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stream);
 
 hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page, const void* src, void* dst,

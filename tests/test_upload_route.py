@@ -1,0 +1,121 @@
+"""Which way a staging buffer is uploaded (by a kernel or by the runtime's copy) and what the caller is told.  The library runs in a
+small program that answers the HIP calls in the runtime's place: no GPU is needed, and memory that no kernel may touch can be named."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2508_15919_amd import binding as hb
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <hip/hip_runtime_api.h>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include "hfxattn.h"
+
+struct Memory { char* at; size_t size; int type, device; char* on_gpu; };
+static Memory memory[2];                      // the staging buffer and the descriptor
+static int current, stream_device, launches, copies, pending, fail_launch;
+
+static const Memory* find(const void* p) {
+  for (const Memory& m : memory)
+    if (m.type != hipMemoryTypeUnregistered && (char*)p >= m.at && (char*)p < m.at + m.size) return &m;
+  return nullptr;
+}
+
+extern "C" {
+hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = s ? stream_device : current; return hipSuccess; }
+hipError_t hipPeekAtLastError(void) { return (hipError_t)pending; }
+hipError_t hipGetLastError(void) { int e = pending; pending = 0; return (hipError_t)e; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
+  std::memset(a, 0, sizeof *a);
+  if (const Memory* m = find(p)) {
+    a->type = (hipMemoryType)m->type;
+    a->device = m->device;
+    a->devicePointer = m->on_gpu + ((char*)p - m->at);
+  }
+  return hipSuccess;
+}
+hipError_t hipDrvPointerGetAttributes(unsigned n, hipPointer_attribute* which, void** data, hipDeviceptr_t p) {
+  const Memory* m = find(p);
+  for (unsigned i = 0; i < n; ++i) switch (which[i]) {
+    case HIP_POINTER_ATTRIBUTE_MEMORY_TYPE: *(unsigned*)data[i] = m ? m->type : 0; break;
+    case HIP_POINTER_ATTRIBUTE_DEVICE_POINTER: *(void**)data[i] = m ? m->on_gpu + ((char*)p - m->at) : nullptr; break;
+    case HIP_POINTER_ATTRIBUTE_DEVICE_ORDINAL: *(int*)data[i] = m ? m->device : -2; break;
+    case HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR: *(void**)data[i] = m ? m->at : nullptr; break;
+    case HIP_POINTER_ATTRIBUTE_RANGE_SIZE: *(size_t*)data[i] = m ? m->size : 0; break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q) { *g = *b = dim3(1); *s = 0; *q = nullptr; return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  if (fail_launch) return (hipError_t)(pending = hipErrorInvalidConfiguration);
+  ++launches;
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { ++copies; return hipSuccess; }
+}
+
+// staging: type, bytes of it that are known; descriptor: type, device, bytes; current device, the stream's device; pending error; a launch fails
+int main(int, char** v) {
+  static const int32_t kind[3] = {0, 0, 1}, q_len[3] = {1, 1, 20}, ctx[3] = {40, 33, 20}, indptr[4] = {0, 3, 6, 8}, pages[8] = {0, 1, 2, 3, 4, 5, 6, 7};
+  const hfx_shape shape = {4, 2, 64, 16, 8, 0.f};
+  size_t host_bytes, device_bytes, ws;
+  if (hfx_batch_desc_sizes(&shape, 3, kind, q_len, ctx, &host_bytes, &device_bytes, &ws)) return 1;
+  char* host = (char*)aligned_alloc(4096, 1 << 20);
+  char* dev = (char*)aligned_alloc(4096, 1 << 20);
+  auto bytes = [&](const char* s) { return std::strcmp(s, "all") ? (size_t)std::atoi(s) : device_bytes; };
+  const bool elsewhere = std::atoi(v[1]) == 9;          // pinned, but at another address on the GPU
+  memory[0] = Memory{host, bytes(v[2]), elsewhere ? (int)hipMemoryTypeHost : std::atoi(v[1]), 0, elsewhere ? host + 4096 : host};
+  memory[1] = Memory{dev, bytes(v[5]), std::atoi(v[3]), std::atoi(v[4]), dev};
+  current = std::atoi(v[6]);
+  stream_device = std::atoi(v[7]);
+  pending = std::atoi(v[8]);
+  fail_launch = std::atoi(v[9]);
+  const hfx_status st = hfx_build_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes, dev, device_bytes, (void*)0x1000);
+  std::printf("%d %s pending %d\n", st, launches + copies != 1 ? launches + copies ? "both" : "none" : launches ? "kernel" : "copy", pending);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    if not os.path.exists(hb.LIB_PATH):
+        from paper_2508_15919_amd import build
+        build.build()
+    d = tmp_path_factory.mktemp("upload")
+    src, exe = d / "upload.cpp", d / "upload"
+    src.write_text(PROGRAM)
+    lib = os.path.dirname(hb.LIB_PATH)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I", os.path.join(ROOT, "include"),
+                    str(src), "-o", str(exe), "-L", lib, f"-l:{os.path.basename(hb.LIB_PATH)}", f"-Wl,-rpath,{lib}:/opt/rocm/lib",
+                    "-Wl,--allow-shlib-undefined"], check=True)
+
+    def call(host=1, host_bytes="all", dev=2, device=0, dev_bytes="all", current=0, stream=0, pending=0, fail=0):
+        args = [host, host_bytes, dev, device, dev_bytes, current, stream, pending, fail]
+        return subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.strip()
+    return call
+
+
+UNKNOWN, PINNED, DEVICE, MANAGED, PINNED_ELSEWHERE = 0, 1, 2, 3, 9
+
+
+@pytest.mark.parametrize("what,route", [
+    ({}, "kernel"), ({"device": 1, "current": 1, "stream": 1}, "kernel"),
+    # staging memory that the GPU does not see, or not under this address, or not all of it
+    ({"host": UNKNOWN}, "copy"), ({"host": MANAGED}, "copy"), ({"host": PINNED_ELSEWHERE}, "copy"), ({"host_bytes": 256}, "copy"),
+    # a destination that is no device memory, too small a piece of it, or another GPU's than the stream's
+    ({"dev": UNKNOWN}, "copy"), ({"dev": PINNED}, "copy"), ({"dev": MANAGED}, "copy"), ({"dev_bytes": 256}, "copy"),
+    ({"device": 1}, "copy"), ({"stream": 1}, "copy"), ({"stream": 1, "device": 1}, "copy"), ({"current": 1}, "copy")])
+def test_a_kernel_uploads_only_between_memory_it_may_touch(program, what, route):
+    """Everything else is left to the runtime's copy, which takes it or refuses it: a kernel that is handed a wrong address faults the GPU."""
+    assert program(**what) == f"0 {route} pending 0"
