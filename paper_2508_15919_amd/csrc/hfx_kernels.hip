@@ -1513,6 +1513,21 @@ hipError_t static_workspace(void** ptr) {
 }
 
 // ------------------------------------------------------------------ host-side launch helpers
+// Launches a kernel without dynamic LDS and answers for this launch alone.  (hipGetLastError() names the last error of any
+// earlier call of the thread: with one that the caller had not read yet, work was enqueued and HFX_ERR_DEVICE returned.)  The error
+// of a launch that fails is read here, because the caller learns of it; an older one stays the caller's to read.
+template <typename... P, typename... A>
+static hipError_t launch(void (*kernel)(P...), dim3 grid, unsigned threads, hipStream_t stream, const A&... args) {
+  static_assert(sizeof...(P) == sizeof...(A), "one value for each parameter");
+  auto call = [&](P... values) {
+    void* address[] = {(void*)&values...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(threads), address, 0, stream);
+  };
+  const hipError_t e = call(args...);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e;
+}
+
 hipError_t max_resident_workgroups(int head_dim, int* per_cu) {
   if (head_dim == 128)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, mixed_attention_kernel<128>, HFX_WG_THREADS, 0);
@@ -1531,21 +1546,16 @@ hipError_t launch_mixed_attention(const HfxHeader& h, int grid, void* desc, cons
   const __bf16* pp = static_cast<const __bf16*>(pool);
   float* wp = static_cast<float*>(ws);
   __bf16* op = static_cast<__bf16*>(out);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(mixed_attention_kernel<128>, dim3(grid), dim3(HFX_WG_THREADS), 0, stream, hk, d, ctrl, qp, pp, wp, op);
-  else
-    hipLaunchKernelGGL(mixed_attention_kernel<64>, dim3(grid), dim3(HFX_WG_THREADS), 0, stream, hk, d, ctrl, qp, pp, wp, op);
-  if (n_units > 0) {
+  hipError_t e = launch(head_dim == 128 ? mixed_attention_kernel<128> : mixed_attention_kernel<64>, dim3(grid), HFX_WG_THREADS, stream, hk, d, ctrl, qp,
+                        pp, wp, op);
+  if (e == hipSuccess && n_units > 0) {
     const HfxUnit* units = reinterpret_cast<const HfxUnit*>(d + h.off_units);
     const HfxGroup* groups = reinterpret_cast<const HfxGroup*>(d + h.off_groups);
     const float* ml = reinterpret_cast<const float*>(static_cast<const char*>(ws) + h.ws_off_ml);
     const int Hq = h.num_q_heads, G = h.num_q_heads / h.num_kv_heads;
-    if (head_dim == 128)
-      hipLaunchKernelGGL(merge_kernel<128>, dim3(n_units), dim3(HFX_WG_THREADS), 0, stream, units, groups, wp, ml, Hq, G, op);
-    else
-      hipLaunchKernelGGL(merge_kernel<64>, dim3(n_units), dim3(HFX_WG_THREADS), 0, stream, units, groups, wp, ml, Hq, G, op);
+    e = launch(head_dim == 128 ? merge_kernel<128> : merge_kernel<64>, dim3(n_units), HFX_WG_THREADS, stream, units, groups, wp, ml, Hq, G, op);
   }
-  return hipGetLastError();
+  return e;
 }
 
 // Whether a kernel on `stream` may copy `bytes` from host to device by itself: from pinned memory that the GPU sees under the same
@@ -1584,9 +1594,7 @@ hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stre
   if (bytes == 0) return hipSuccess;
   if (!kernel_may_upload(host, device, bytes, stream)) return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
   const long n = (long)(bytes / 8);
-  hipLaunchKernelGGL(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, static_cast<const uint64_t*>(host),
-                     static_cast<uint64_t*>(device), n);
-  return hipGetLastError();
+  return launch(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), 256, stream, static_cast<const uint64_t*>(host), static_cast<uint64_t*>(device), n);
 }
 
 // Copies of at most a quarter of the last-level cache leave their source in it, where it may still be from the writing of those pages (41 MB
@@ -1602,11 +1610,8 @@ hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page
   const int2* p = static_cast<const int2*>(pairs);
   const u32x4* from = static_cast<const u32x4*>(src);
   u32x4* to = static_cast<u32x4*>(dst);
-  if (n_units * 16 > kCopyStreamBytes)
-    hipLaunchKernelGGL(copy_pages_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, stream, p, n_pairs, (unsigned)units_per_page, from, to);
-  else
-    hipLaunchKernelGGL(copy_pages_kernel<false>, dim3((unsigned)blocks), dim3(256), 0, stream, p, n_pairs, (unsigned)units_per_page, from, to);
-  return hipGetLastError();
+  return launch(n_units * 16 > kCopyStreamBytes ? copy_pages_kernel<true> : copy_pages_kernel<false>, dim3((unsigned)blocks), 256, stream, p, n_pairs,
+                (unsigned)units_per_page, from, to);
 }
 
 // Far more than are resident (8 to a CU), so that only very long requests go round the loop.
@@ -1622,16 +1627,10 @@ hipError_t launch_gather_kv(const HfxHeader& h, int n_tokens, const void* desc, 
   if (((reinterpret_cast<uintptr_t>(pool) | reinterpret_cast<uintptr_t>(k_out) | reinterpret_cast<uintptr_t>(v_out)) & 15u) == 0) {
     const long units = (long)((n_tokens + HFX_PAGE - 1) / HFX_PAGE) * h.num_kv_heads;      // (page, kv-head) pairs
     const unsigned grid = (unsigned)std::min<long>(std::max<long>(units, 1), kGatherMaxWgs);
-    if (h.head_dim == 128)
-      hipLaunchKernelGGL(gather_kv_kernel<128>, dim3(grid), dim3(256), 0, stream, ds, src, request, ko, vo);
-    else
-      hipLaunchKernelGGL(gather_kv_kernel<64>, dim3(grid), dim3(128), 0, stream, ds, src, request, ko, vo);
-  } else {
-    const long blocks = ((long)n_tokens * h.num_kv_heads * h.head_dim + 255) / 256;
-    hipLaunchKernelGGL(gather_kv_unaligned_kernel, dim3((unsigned)std::min<long>(std::max<long>(blocks, 1), 4096)), dim3(256), 0,
-                       stream, ds, src, request, ko, vo);
+    return launch(h.head_dim == 128 ? gather_kv_kernel<128> : gather_kv_kernel<64>, dim3(grid), 2u * (unsigned)h.head_dim, stream, ds, src, request, ko, vo);
   }
-  return hipGetLastError();
+  const long blocks = ((long)n_tokens * h.num_kv_heads * h.head_dim + 255) / 256;
+  return launch(gather_kv_unaligned_kernel, dim3((unsigned)std::min<long>(std::max<long>(blocks, 1), 4096)), 256, stream, ds, src, request, ko, vo);
 }
 
 hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_new, const void* v_new, void* pool,
@@ -1643,15 +1642,8 @@ hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_
   // which holds at most 65535
   const unsigned per_z = (unsigned)std::min(h.n_runs, 32768);
   const dim3 grid((unsigned)h.num_kv_heads, per_z, ((unsigned)h.n_runs + per_z - 1) / per_z);
-  if (h.head_dim == 128)
-    hipLaunchKernelGGL(append_kv_kernel<128>, grid, dim3(256), 0, stream, runs, h.n_runs,
-                       static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
-                       static_cast<uint16_t*>(pool));
-  else
-    hipLaunchKernelGGL(append_kv_kernel<64>, grid, dim3(128), 0, stream, runs, h.n_runs,
-                       static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new),
-                       static_cast<uint16_t*>(pool));
-  return hipGetLastError();
+  return launch(h.head_dim == 128 ? append_kv_kernel<128> : append_kv_kernel<64>, grid, 2u * (unsigned)h.head_dim, stream, runs, h.n_runs,
+                static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), static_cast<uint16_t*>(pool));
 }
 
 }  // namespace hfx

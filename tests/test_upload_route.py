@@ -1,4 +1,4 @@
-"""Which way a staging buffer is uploaded (by a kernel or by the runtime's copy) and what the caller is told.  The library runs in a
+"""Which way a staging buffer is uploaded (by a kernel or by the runtime's copy), and what callers are told of launches.  The library runs in a
 small program that answers the HIP calls in the runtime's place: no GPU is needed, and memory that no kernel may touch can be named."""
 import os
 import shutil
@@ -15,6 +15,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 #include "hfxattn.h"
 
 struct Memory { char* at; size_t size; int type, device; char* on_gpu; };
@@ -55,6 +56,9 @@ hipError_t hipDrvPointerGetAttributes(unsigned n, hipPointer_attribute* which, v
 }
 hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q) { *g = *b = dim3(1); *s = 0; *q = nullptr; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 2; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { static char scratch[256]; *p = scratch; return hipSuccess; }
 hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
   if (fail_launch) return (hipError_t)(pending = hipErrorInvalidConfiguration);
   ++launches;
@@ -63,7 +67,8 @@ hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t)
 hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t) { ++copies; return hipSuccess; }
 }
 
-// staging: type, bytes of it that are known; descriptor: type, device, bytes; current device, the stream's device; pending error; a launch fails
+// staging: type, bytes of it that are known; descriptor: type, device, bytes; current device, the stream's device; pending error; a
+// launch fails; the call after building
 int main(int, char** v) {
   static const int32_t kind[3] = {0, 0, 1}, q_len[3] = {1, 1, 20}, ctx[3] = {40, 33, 20}, indptr[4] = {0, 3, 6, 8}, pages[8] = {0, 1, 2, 3, 4, 5, 6, 7};
   const hfx_shape shape = {4, 2, 64, 16, 8, 0.f};
@@ -79,8 +84,19 @@ int main(int, char** v) {
   stream_device = std::atoi(v[7]);
   pending = std::atoi(v[8]);
   fail_launch = std::atoi(v[9]);
-  const hfx_status st = hfx_build_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes, dev, device_bytes, (void*)0x1000);
-  std::printf("%d %s pending %d\n", st, launches + copies != 1 ? launches + copies ? "both" : "none" : launches ? "kernel" : "copy", pending);
+  char* any = dev + (1 << 19);
+  int32_t ids[2] = {2, 3};
+  const std::string what = v[10];
+  hfx_status st = 0;
+  if (what == "build") st = hfx_build_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes, dev, device_bytes, (void*)0x1000);
+  else hfx_fill_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes);
+  if (what == "attention") st = hfx_mixed_paged_attention(&shape, any, any, host, dev, any, 1 << 18, any, nullptr);
+  if (what == "static") st = hfx_mixed_paged_attention_static(&shape, any, any, host, dev, any, nullptr);
+  if (what == "gather") st = hfx_gather_kv(&shape, any, host, dev, 0, any, any, nullptr);
+  if (what == "gather unaligned") st = hfx_gather_kv(&shape, any, host, dev, 0, any + 2, any, nullptr);
+  if (what == "append") st = hfx_append_kv(&shape, any, any, any, host, dev, nullptr);
+  if (what == "pages") st = hfx_copy_pages(&shape, any, any + 4096, 8, 2, ids, ids, host, dev, 4096, nullptr);
+  std::printf("%d %s pending %d\n", st, launches && copies ? "copy and kernel" : launches ? "kernel" : copies ? "copy" : "nothing", pending);
 }
 """
 
@@ -100,8 +116,8 @@ def program(tmp_path_factory):
                     str(src), "-o", str(exe), "-L", lib, f"-l:{os.path.basename(hb.LIB_PATH)}", f"-Wl,-rpath,{lib}:/opt/rocm/lib",
                     "-Wl,--allow-shlib-undefined"], check=True)
 
-    def call(host=1, host_bytes="all", dev=2, device=0, dev_bytes="all", current=0, stream=0, pending=0, fail=0):
-        args = [host, host_bytes, dev, device, dev_bytes, current, stream, pending, fail]
+    def call(host=1, host_bytes="all", dev=2, device=0, dev_bytes="all", current=0, stream=0, pending=0, fail=0, entry="build"):
+        args = [host, host_bytes, dev, device, dev_bytes, current, stream, pending, fail, entry]
         return subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.strip()
     return call
 
@@ -119,3 +135,23 @@ UNKNOWN, PINNED, DEVICE, MANAGED, PINNED_ELSEWHERE = 0, 1, 2, 3, 9
 def test_a_kernel_uploads_only_between_memory_it_may_touch(program, what, route):
     """Everything else is left to the runtime's copy, which takes it or refuses it: a kernel that is handed a wrong address faults the GPU."""
     assert program(**what) == f"0 {route} pending 0"
+
+
+ENTRIES = ["build", "attention", "static", "gather", "gather unaligned", "append", "pages"]
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_an_unread_error_of_an_earlier_call_is_left_alone(program, entry):
+    """The thread's last error may be of any call before and unread (hipErrorInvalidDevice here): a call of the library that enqueues its work
+    says so, and the error is there for whoever looks for it."""
+    assert program(pending=101, entry=entry) == "0 kernel pending 101"
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_a_failed_launch_is_reported(program, entry):
+    assert program(fail=1, entry=entry) == f"{hb.HFX_ERR_DEVICE} nothing pending 0"
+
+
+def test_an_unread_error_does_not_disturb_the_runtimes_copy(program):
+    assert program(host=UNKNOWN, pending=101) == "0 copy pending 101"
+    assert program(host=UNKNOWN, pending=101, entry="pages") == "0 copy and kernel pending 101"
