@@ -1357,15 +1357,29 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict_
 
 // Upload of a staging buffer that the GPU can read (pinned host memory): 8-byte words, four of a thread in flight.  Loads of
 // system scope, so that no cache of the GPU answers with what the buffer held before.  Bound: the host link.
-__global__ __launch_bounds__(256) void upload_kernel(const uint64_t* __restrict__ src, uint64_t* __restrict__ dst, long n) {
-  const long base = (long)blockIdx.x * 1024 + threadIdx.x;
-  uint64_t v[4];
+// An engine uploads the next step's descriptor while the present step's attention runs.  Two workgroups of that kernel with 128-wide heads take
+// 2 * 248 of a SIMD's 512 registers (247 a lane, handed out eight at a time), so this one takes no more than 16: with 18 it
+// found no place until the first workgroups of the launch ended.  And a CU answers its loads in order, so that one which
+// hosts a workgroup of this kernel waits for the host link with all it has: few of them, going round a loop, 2 KB a wavefront.
+// Steps of 384 and 1152 short requests (0.94 and 2.96 MB), us a step, uploaded beside the launch before and, second, ahead of the launch
+// on the same stream: by a copy engine 315.3 and 339.4, 1063 and 1116; one workgroup for each 8 KB with 18 registers 324.0 and 329.8,
+// 1105 and 1110, with 16 registers 320.2 and 328.5, 1091 and 1108; 128 workgroups 320.5 and 328.6, 1080 and 1107; 32 315.3 and 328.3,
+// 1063 and 1107; 12 315.8 and 329.8, 1064 and 1110.
+constexpr unsigned kUploadWgs = 32;
+__global__ __launch_bounds__(256) void upload_kernel(const char* __restrict__ src, char* __restrict__ dst, unsigned words) {
+  const int word = (threadIdx.x >> 6) * 256 + (threadIdx.x & 63);       // and 64, 128, 192 further on: one address for all four
+  for (unsigned first = blockIdx.x * 1024; first < words; first += gridDim.x * 1024) {
+    const int left = (int)min(words - first, 1024u) - word;
+    const uint64_t* from = reinterpret_cast<const uint64_t*>(src) + first + word;
+    uint64_t* to = reinterpret_cast<uint64_t*>(dst) + first + word;
+    uint64_t v[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (base + 256 * j < n) v[j] = __hip_atomic_load(src + base + 256 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int j = 0; j < 4; ++j)
+      if (64 * j < left) v[j] = __hip_atomic_load(from + 64 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-    if (base + 256 * j < n) dst[base + 256 * j] = v[j];
+    for (int j = 0; j < 4; ++j)
+      if (64 * j < left) to[64 * j] = v[j];
+  }
 }
 
 // Page gather: a workgroup of 2 D threads takes one (page, kv-head) at a time.  A thread moves one 16-byte
@@ -1562,7 +1576,7 @@ hipError_t launch_mixed_attention(const HfxHeader& h, int grid, void* desc, cons
 // address to memory of the stream's own GPU, which is the current one, both whole inside one allocation.  (A query of
 // any other address succeeds and tells of no memory; it leaves no error behind.)
 static bool kernel_may_upload(const void* host, const void* device, size_t bytes, hipStream_t stream) {
-  if ((reinterpret_cast<uintptr_t>(host) | reinterpret_cast<uintptr_t>(device) | bytes) & 7u) return false;
+  if (((reinterpret_cast<uintptr_t>(host) | reinterpret_cast<uintptr_t>(device) | bytes) & 7u) != 0 || bytes >> 34 != 0) return false;    // 2^31 words
   struct Memory {
     unsigned type = hipMemoryTypeUnregistered;
     int gpu = -1;
@@ -1587,14 +1601,13 @@ static bool kernel_may_upload(const void* host, const void* device, size_t bytes
   return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(stream, &streams) == hipSuccess && current == to.gpu && streams == to.gpu;
 }
 
-// Pinned memory is read by a kernel: the runtime gives a megabyte to a copy engine, and the next kernel started 10 to
-// 20 us after that engine's end (a step of 384 short requests, 0.96 MB of descriptor: 397 us with the runtime's copy, 388 so); a few
-// kilobytes it copies with a kernel too.
+// Pinned memory is read by a kernel: the runtime gives a megabyte to a copy engine, and the next kernel on the same stream started 10 to
+// 20 us after that engine's end; a few kilobytes it copies with a kernel too.  What that gives and costs is said at upload_kernel.
 hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stream) {
   if (bytes == 0) return hipSuccess;
   if (!kernel_may_upload(host, device, bytes, stream)) return hipMemcpyAsync(device, host, bytes, hipMemcpyHostToDevice, stream);
-  const long n = (long)(bytes / 8);
-  return launch(upload_kernel, dim3((unsigned)((n + 1023) / 1024)), 256, stream, static_cast<const uint64_t*>(host), static_cast<uint64_t*>(device), n);
+  const unsigned n = (unsigned)(bytes / 8);
+  return launch(upload_kernel, dim3(std::min((n + 1023u) / 1024u, kUploadWgs)), 256, stream, static_cast<const char*>(host), static_cast<char*>(device), n);
 }
 
 // Copies of at most a quarter of the last-level cache leave their source in it, where it may still be from the writing of those pages (41 MB

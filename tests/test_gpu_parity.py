@@ -510,6 +510,38 @@ def test_staging_memory_of_every_kind_is_uploaded(hb, staging, offset, requests)
         assert torch.equal(dev[:n].cpu(), host[:n]), again
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (32, 8, 64)])
+def test_a_descriptor_is_uploaded_beside_a_launch_that_fills_the_chip(hb, Hq, Hkv, D):
+    """What an engine does: the next step is planned and uploaded on a second stream while the present step's attention, whose workgroups stay to
+    its end, runs on the first.  The upload ends well before the launch does."""
+    import torch
+    rng = np.random.default_rng(D)
+    b = small_pool_batch(rng, Hq, Hkv, D, [DECODE] * 64, [1] * 64, [60000] * 64, f"long-{D}")
+    step = hb.DeviceStep(b)
+    n = 1200
+    nxt = synth.make_batch(Hq, Hkv, D, [DECODE] * n, [1] * n, rng.integers(1, 30, n), 3)
+    shape = hb.make_shape(Hq, Hkv, D, nxt.num_pages)
+    size = hb.hfx_batch_desc_sizes(shape, nxt.kind, nxt.q_len, nxt.ctx_len)[0]
+    assert size > 1 << 18
+    host, dev = torch.empty(size, dtype=torch.uint8, pin_memory=True), torch.empty(size, dtype=torch.uint8, device="cuda")
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    share = []
+    for again in range(4):
+        dev.zero_()
+        torch.cuda.synchronize()
+        start, end, uploaded = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+        start.record(main)
+        step.run(main)
+        end.record(main)
+        hb.hfx_build_batch_desc(shape, nxt.kind, nxt.q_len, nxt.ctx_len, nxt.bt_indptr, nxt.bt_pages, host, dev, side)
+        uploaded.record(side)
+        torch.cuda.synchronize()
+        assert torch.equal(dev.cpu(), host)
+        share.append(start.elapsed_time(uploaded) / start.elapsed_time(end))
+    print("upload done after", share, "of", start.elapsed_time(end), "ms")
+    assert min(share[1:]) < 0.7, share          # (its planning takes a few hundred microseconds of that)
+
+
 def test_captured_upload_reads_the_staging_buffer_at_each_replay(hb, oracle):
     """Plan, upload and attention under capture: a replay uploads what the staging buffer holds by then."""
     import torch
