@@ -400,11 +400,12 @@ struct DecodeCut {
 // longer than the default: 3 of 200 to 900 beside a prompt of 100 11.5 us and 8.5; where up to 512 items were allowed, 6 of 500 to 5000 beside 777
 // 24.0 and 26.6, and 10 of 200 to 3000 on 8/8 heads beside 192 rows 15.4 and 18.3 (15.0 so).
 //
-// Beside prefill items that a decode stream outweighs, a step that takes a few more than the 1024 items of two rounds (up to
-// kRoundsOver of them) has its pieces lengthened to that: all items are then dealt, and no round has a few items in it (64 of 100 to 8192
-// beside chunks of 512 and 512 behind 1536, 1304 items: 103.4 us, 98.6 so; 50 of 1500 to 4000 beside 400 115.2 and 113.8).  70 decodes alone, 1.5 times
-// 1024 items: 117.5 and 125.9, hence neither more nor without prefill items.
-static const double kRoundsOver = 1.3;
+// Beside prefill items that a decode stream outweighs, a step of up to kRoundsOver times the 1024 items of two rounds has its pieces
+// lengthened to that, if pieces four times as long are enough: all items are then dealt, and no round has a few items in it.  150 steps of 1.0 to
+// 2.0 times 1024 items on seven head layouts: 1.007 to 1.044 times as fast on average in each tenth, the slowest 0.965, the fastest 1.112; six
+// steps of 2.0 to 2.4 times 1.020, six of 2.4 to 2.6 times 0.991.  70 decodes alone, 1.5 times 1024 items: 117.5 and 125.9 us,
+// hence not without prefill items.
+static const double kRoundsOver = 2.0;
 static const int64_t kHeadTokensMin = 256;
 static const int64_t kHeadTokensWhole = 1024;
 static const int64_t kHeadTokensBeside = 700;
@@ -443,7 +444,9 @@ static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, 
     const uint32_t piece = (uint32_t)(by_time.tokens + kPair - 1) / kPair;
     const int64_t now = items(piece, most);
     if (now <= two_rounds || (double)(now + n_pre) > kRoundsOver * (double)(2 * HFX_PLAN_WGS)) return by_time;
-    return {most, (int64_t)shortest(piece, 4 * piece, most, two_rounds) * kPair};
+    const uint32_t longer = shortest(piece, 4 * piece, most, two_rounds);
+    if (items(longer, most) > two_rounds) return by_time;
+    return {most, (int64_t)longer * kPair};
   };
   const int64_t room = n_pre == 0 ? HFX_PLAN_WGS : HFX_PLAN_WGS / 2 - n_pre;
   int h = 1;

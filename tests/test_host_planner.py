@@ -388,25 +388,69 @@ def test_decodes_of_steps_that_fit_the_chip_at_once(lib, Hq, Hkv, D, n, lo, hi, 
             assert d["header"].n_groups == 0 and d["header"].workspace_bytes == 0
 
 
+def decode_items_by_time(b):
+    """Decode items where pieces go by time alone: four kv-heads an item, whole rounds of 512 pieces of at least 32 us at 12 bytes a ns."""
+    heads = 4 if b.num_kv_heads % 4 == 0 else 2 if b.num_kv_heads % 2 == 0 else 1
+    ctx = b.ctx_len[b.kind == DECODE].astype(np.int64)
+    ns = float(ctx.sum()) * b.num_kv_heads * b.head_dim * 4 / 12
+    rounds = min(max(ns // (512 * 32000), 1), 4)
+    tokens = max(int(max(ns / (512 * rounds), 32000) / (heads * b.head_dim * 4 / 12)), 128)
+    pairs, piece = (ctx + 31) // 32, (tokens + 31) // 32
+    piece = np.maximum(piece, (pairs + 63) // 64)
+    return int(((pairs + piece - 1) // piece).sum()) * (b.num_kv_heads // heads)
+
+
+def mixed_step_is_dealt_whole(b):
+    """Whether the decode pieces of a step that decodes outweigh were lengthened until two rounds of 512 hold all items: where
+    pieces by time would make one to two times as many, and only there."""
+    d = fill(b)
+    h = d["header"]
+    check_coverage(b, d)
+    assert h.deal_balanced == 0 and h.n_prefill_items < 512
+    by_time = decode_items_by_time(b) + h.n_prefill_items
+    lengthened = 1024 < by_time <= 2048
+    assert h.n_items <= 1024 if lengthened else h.n_items == by_time, (h.n_items, by_time)
+    return lengthened
+
+
 @pytest.mark.parametrize("seed", range(6))
 def test_mixed_steps_of_a_little_more_than_two_rounds_are_dealt_whole(lib, seed):
-    """Decodes that outweigh the prefills beside them: no step ends up with between 1024 and 1.3 times 1024 items while its decodes could
-    be cut into fewer, and everything is covered once."""
+    """Decodes that outweigh the prefills beside them: a step of up to twice the 1024 items of two rounds has longer decode pieces, one of more
+    has not, and everything is covered once."""
     rng = np.random.default_rng(seed)
     dealt = 0
     for _ in range(8):
         n = int(rng.integers(30, 60))
         c = rng.integers(100, 5000, n).tolist()
-        q = [int(x) for x in rng.integers(30, 600, rng.integers(1, 4))]
-        p = [int(x) for x in rng.integers(0, 1500, len(q))]
+        q = [int(x) for x in rng.integers(30, 400, rng.integers(1, 4))]
+        p = [int(x) for x in rng.integers(0, 1000, len(q))]
         b = lengths_only(32, 8, 128, [DECODE] * n + [PREFILL] * len(q), [1] * n + q, c + [x + y for x, y in zip(q, p)])
-        d = fill(b)
-        h = d["header"]
-        check_coverage(b, d)
-        if h.deal_balanced == 0 and h.n_prefill_items < 512:
-            assert not 1024 < h.n_items <= 1331, h.n_items
-            dealt += h.n_items <= 1024
-    assert dealt or seed, "some of the steps fit"
+        dealt += mixed_step_is_dealt_whole(b)
+    assert dealt > 0
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,chunks,dealt", [
+    (32, 8, 128, 64, 100, 8192, [(512, 0), (512, 1536)], True),                     # 1.1 to 1.9 times 1024 items by time
+    (8, 8, 128, 96, 500, 10000, [(20, 80), (150, 117)], True), (32, 8, 64, 118, 2500, 3900, [(566, 0), (96, 0), (266, 628)], True),
+    (16, 4, 128, 83, 800, 21000, [(76, 35), (187, 0), (30, 0)], True), (16, 16, 128, 13, 7300, 10200, [(185, 0), (103, 587)], True),
+    (32, 8, 128, 200, 1000, 12000, [(134, 46), (668, 661)], False)])                # 2.4
+def test_mixed_steps_dealt_whole_on_other_layouts(lib, Hq, Hkv, D, n, lo, hi, chunks, dealt):
+    c = np.rint(np.exp(np.random.default_rng(n).uniform(np.log(lo), np.log(hi), n))).astype(int).tolist()
+    b = lengths_only(Hq, Hkv, D, [DECODE] * n + [PREFILL] * len(chunks), [1] * n + [q for q, _ in chunks], c + [q + p for q, p in chunks])
+    assert mixed_step_is_dealt_whole(b) == dealt
+
+
+def test_decode_pieces_are_not_lengthened_where_two_rounds_are_out_of_reach(lib):
+    """480 prefill items leave 544 of two rounds' places to decodes that have 494 items when uncut and two contexts of many
+    pieces: pieces four times as long would not be enough, and pieces stay as they are by time."""
+    c = [150] * 245 + [20000] * 2
+    q = [32] * 60
+    b = lengths_only(32, 8, 128, [DECODE] * len(c) + [PREFILL] * len(q), [1] * len(c) + q, c + q)
+    d = fill(b)
+    h = d["header"]
+    check_coverage(b, d)
+    assert h.deal_balanced == 0 and h.n_prefill_items == 480
+    assert 1024 < h.n_items == decode_items_by_time(b) + 480 < 1331
 
 
 def check_coverage_of_groups(d):
