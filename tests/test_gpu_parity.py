@@ -328,11 +328,18 @@ def test_merge_of_two_to_sixty_splits(hb, oracle):
     check_full(hb, oracle, b)
 
 
-@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,prompt", [
-    (32, 8, 128, 5, 1, 2500, 0), (24, 8, 128, 40, 15, 1300, 0), (16, 16, 128, 30, 1, 1024, 0), (16, 4, 64, 100, 30, 2100, 0), (32, 4, 64, 128, 1, 300, 0),
-    (8, 8, 128, 64, 900, 1100, 0), (8, 2, 64, 129, 500, 1600, 0), (16, 1, 128, 9, 200, 9000, 0), (32, 8, 128, 3, 30, 900, 70), (12, 4, 128, 7, 1, 700, 33)])
-def test_decode_items_of_one_and_two_heads(hb, oracle, Hq, Hkv, D, n, lo, hi, prompt):
-    """Small steps give each decode item one or two kv-heads, so that two or four wavefronts share a head's pages: contexts of less
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,prompt,heads", [
+    (32, 8, 128, 5, 1, 2500, 0, 1), (24, 8, 128, 40, 15, 1300, 0, 1), (16, 16, 128, 30, 1, 1024, 0, 1), (16, 4, 64, 100, 30, 2100, 0, 1),
+    (32, 4, 64, 128, 1, 300, 0, 1), (8, 8, 128, 64, 900, 1100, 0, 1), (8, 2, 64, 129, 500, 1600, 0, 1), (16, 1, 128, 9, 200, 9000, 0, 1),
+    (32, 8, 128, 3, 30, 900, 70, 1), (12, 4, 128, 7, 1, 700, 33, 1),
+    # two heads: whole contexts from less than a page pair a wavefront on, then pieces, then beside a prompt
+    (32, 8, 128, 65, 1, 60, 0, 2), (32, 8, 128, 128, 1, 900, 0, 2), (8, 8, 128, 70, 1, 512, 0, 2), (8, 8, 64, 90, 1, 40, 0, 2),
+    (16, 4, 64, 129, 1, 70, 0, 2), (12, 4, 128, 256, 20, 500, 0, 2), (8, 2, 64, 512, 1, 33, 0, 2), (2, 2, 128, 257, 1, 300, 0, 2),
+    (6, 2, 64, 300, 100, 700, 0, 2), (24, 8, 128, 100, 15, 1300, 0, 2), (32, 8, 64, 120, 500, 2600, 0, 2), (24, 8, 64, 66, 100, 1500, 0, 2),
+    (4, 4, 64, 135, 200, 2500, 0, 2), (16, 4, 128, 180, 900, 2600, 0, 2), (8, 2, 128, 400, 1000, 1100, 0, 2), (6, 2, 128, 257, 600, 1800, 0, 2),
+    (24, 8, 128, 33, 10, 250, 20, 2), (32, 8, 64, 40, 20, 300, 40, 2), (16, 4, 64, 70, 1, 280, 64, 2)])
+def test_decode_items_of_one_and_two_heads(hb, oracle, Hq, Hkv, D, n, lo, hi, prompt, heads):
+    """Small steps give each decode item one or two kv-heads, so that four or two wavefronts share a head's pages: contexts of less
     than a page pair per wavefront, whole ones and pieces, alone and beside a prompt."""
     rng = np.random.default_rng(1000 * n + hi)
     c = rng.integers(lo, hi + 1, n).tolist()
@@ -341,7 +348,7 @@ def test_decode_items_of_one_and_two_heads(hb, oracle, Hq, Hkv, D, n, lo, hi, pr
                          n_pages=400)
     step, _ = check_full(hb, oracle, b)
     items = hb.parse_desc(step.host_desc.numpy())["items"]
-    assert set(items["hn"][items["type"] == 0].tolist()) <= {1, 2}
+    assert set(items["hn"][items["type"] == 0].tolist()) == {heads}
 
 
 def test_shared_prefix_pages(hb, oracle):
