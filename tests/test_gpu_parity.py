@@ -550,28 +550,69 @@ def test_a_descriptor_is_uploaded_beside_a_launch_that_fills_the_chip(hb, Hq, Hk
 
 
 def test_captured_upload_reads_the_staging_buffer_at_each_replay(hb, oracle):
-    """Plan, upload and attention under capture: a replay uploads what the staging buffer holds by then."""
+    """Plan, upload and attention under capture: a replay uploads what the staging buffer holds by then, here in turn the captured step's
+    descriptor and those of two steps of the same lengths whose requests lie in other pages."""
     import torch
-    b = synth.config(1)
+    rng = np.random.default_rng(31)
+    b = small_pool_batch(rng, 8, 2, 128, [DECODE] * 3 + [PREFILL], [1] * 3 + [40], [37, 64, 129, 45], "captured", n_pages=60)
     step = hb.DeviceStep(b)
-    step.run()
-    want = step.out_bits().copy()
     s = torch.cuda.Stream()
     graph = torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=s):
         step.build(torch.cuda.current_stream())
         step.run(torch.cuda.current_stream())
-    good = step.host_desc.clone()
-    for replay in range(4):
+    steps = []
+    for ids in (b.bt_pages, *rng.integers(0, 60, (2, len(b.bt_pages))).astype(np.int32)):
+        other = np.zeros(step.host_desc.numel(), np.uint8)
+        hb.hfx_fill_batch_desc(step.shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, ids, other)
+        hb.hfx_build_batch_desc(step.shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, ids, step.host_desc, step.device_desc)
+        step.run()
+        torch.cuda.synchronize()
+        steps.append((torch.from_numpy(other), step.out_bits().copy()))
+    assert not np.array_equal(steps[0][1], steps[1][1]) and not np.array_equal(steps[1][1], steps[2][1])
+    for replay, which in enumerate((1, 0, 2, 1, 2, 0)):
+        good, want = steps[which]
         step.host_desc.copy_(good)
         step.device_desc.zero_()
         step.out.zero_()
         torch.cuda.synchronize()
         graph.replay()
         torch.cuda.synchronize()
-        assert np.array_equal(step.out_bits(), want), replay
+        assert np.array_equal(step.out_bits(), want), (replay, which)
         assert torch.equal(step.device_desc.cpu()[256:], good[256:])
+
+
+@pytest.mark.parametrize("offset,kind", [(0, "kernel"), (8, "kernel"), (4, "copy")])
+def test_which_node_a_captured_upload_becomes(hb, offset, kind):
+    """The way of an upload, read from the graph that captured it: pinned staging memory on 8 bytes is read by a kernel, other goes by the
+    runtime's copy."""
+    import ctypes
+    import torch
+    b = synth.config(1)
+    shape = hb.make_shape(b.num_q_heads, b.num_kv_heads, b.head_dim, b.num_pages)
+    n = hb.hfx_batch_desc_sizes(shape, b.kind, b.q_len, b.ctx_len)[0]
+    host = torch.zeros(n + 16, dtype=torch.uint8, pin_memory=True)[offset:offset + n]
+    dev = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        hb.hfx_build_batch_desc(shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, b.bt_pages, host, dev, torch.cuda.current_stream())
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    raw, count, what = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), ctypes.c_int(-1)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0 and count.value == 1
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    assert hip.hipGraphNodeGetType(ctypes.c_void_p(nodes[0]), ctypes.byref(what)) == 0
+    assert {0: "kernel", 1: "copy"}.get(what.value) == kind
+    graph.instantiate()
+    for _ in range(3):
+        dev.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dev.cpu(), host)
 
 
 def test_device_side_errors(hb):
