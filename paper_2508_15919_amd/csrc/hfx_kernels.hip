@@ -791,16 +791,12 @@ __device__ __forceinline__ bf16x8 value_fragment(const char* slot, int i, int v_
   return *reinterpret_cast<const bf16x8*>(slot + (2 + i / B) * Smem<D>::kBlockBytes + (i % B) * 1024 + v_lane);
 }
 
-struct NoCopy {
-  __device__ __forceinline__ void operator()(int) const {}
-};
-
 // First phase of a stage: scores of the next stage out of its key fragments, the second half of the weights of the
 // present one (scores cur) between them; the value fragments of the present stage take the place of each key
-// fragment as it is used up.  copy(i) issues what is to be copied behind instruction i.
-template <int D, class Copy>
+// fragment as it is used up.
+template <int D>
 __device__ __forceinline__ f32x16 scores_phase(const PrefillWave<D>& w, bf16x8* frag, const f32x16& cur, Weighing& wt, float sl2,
-                                               const char* v_slot, int v_lane, Copy copy) {
+                                               const char* v_slot, int v_lane) {
   constexpr int S = D / 16;
   f32x16 acc;
 #pragma unroll
@@ -809,7 +805,6 @@ __device__ __forceinline__ f32x16 scores_phase(const PrefillWave<D>& w, bf16x8* 
   for (int i = 0; i < S; ++i) {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[i], w.qf[i], acc, 0, 0, 0);
     frag[i] = value_fragment<D>(v_slot, i, v_lane);
-    copy(i);
     wt.portion(i == 0 ? Share<D>::values[S - 1] : Share<D>::scores[i - 1], Share<D>::scores[i], Share<D>::scores[i + 1], cur, sl2, w.m);
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -817,8 +812,13 @@ __device__ __forceinline__ f32x16 scores_phase(const PrefillWave<D>& w, bf16x8* 
   return acc;
 }
 
+struct NoCopy {
+  __device__ __forceinline__ void operator()(int) const {}
+};
+
 // Second phase: weighted values of the present stage, the first half of the weights of the next one (scores next) between
-// them, and the key fragments of the stage after next in the place of the value fragments.
+// them, and the key fragments of the stage after next in the place of the value fragments.  copy(i) issues what is to be
+// copied behind instruction i.
 template <int D, class Copy>
 __device__ __forceinline__ void values_phase(PrefillWave<D>& w, bf16x8* frag, const bf16x8* pb, const f32x16& next, Weighing& wt,
                                              float sl2, const char* k_slot, int k_lane, Copy copy) {
@@ -1146,7 +1146,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       bf16x8 pb[2];
       __builtin_amdgcn_sched_barrier(0);
       if (busy) {
-        next = scores_phase<D>(w, frag, cur, wt, sl2, slot(g_st), v_lane, NoCopy());
+        next = scores_phase<D>(w, frag, cur, wt, sl2, slot(g_st), v_lane);
         pb[0] = wt.fragment(0);
         pb[1] = wt.fragment(1);
         settle_weights<D>(w, cur, pb, wt.sum(), sl2);
@@ -1173,7 +1173,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     };
     for (;;) {
       // Pairs of stages that every row of the wavefront sees whole, with the short form of the synchronisation point: the common
-      // case, without any other condition.  The copies are spread over the 16 matrix instructions behind that point.
+      // case, without any other condition.  The copies are issued one behind each of the matrix instructions that follow that point: in a
+      // burst in front of them they hold up the wavefront (a 4096-row chunk behind 61440 tokens 970 us, 950 so), and spread over
+      // twice as many they land later, which chunks of few rows wait for (42 of 4 rows behind 5321 on 8/8 heads of 64 97.5 and 92.6,
+      // 97 of one row behind 12208 on 24/8 heads 1294 and 1251; 90.7 and 1182 with one burst and the loop before).
       int pairs = wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto ? (int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1 : 0;
       pairs = uniform(min(pairs, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
       if (pairs > 0) {
@@ -1185,7 +1188,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
 #pragma unroll 1
         do {
           __builtin_amdgcn_sched_barrier(0);
-          s1 = scores_phase<D>(w, frag, s0, wt, sl2, slot(g_st), v_lane, NoCopy());
+          s1 = scores_phase<D>(w, frag, s0, wt, sl2, slot(g_st), v_lane);
           const int id0 = id[0], id1 = id[1];
           bf16x8 pb[2] = {wt.fragment(0), wt.fragment(1)};
           settle_weights<D>(w, s0, pb, wt.sum(), sl2);
@@ -1196,8 +1199,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
           const unsigned lds0 = lds_ring + (cs.count & (RING - 1)) * Smem<D>::kStageBytes;
           const unsigned lds1 = lds_ring + ((cs.count + 1) & (RING - 1)) * Smem<D>::kStageBytes;
           __builtin_amdgcn_sched_barrier(0);
-          values_phase<D>(w, frag, pb, s1, wt, sl2, slot(g_st + 2), k_lane, [&](int i) { if (i & 1) piece_copy(base0, voff, lds0, i >> 1); });
-          s0 = scores_phase<D>(w, frag, s1, wt, sl2, slot(g_st + 1), v_lane, [&](int i) { if (i & 1) piece_copy(base1, voff, lds1, i >> 1); });
+          values_phase<D>(w, frag, pb, s1, wt, sl2, slot(g_st + 2), k_lane, [&](int i) {
+            if (i < D / 32) piece_copy(base0, voff, lds0, i);
+            else piece_copy(base1, voff, lds1, i - D / 32);
+          });
+          s0 = scores_phase<D>(w, frag, s1, wt, sl2, slot(g_st + 1), v_lane);
           pb[0] = wt.fragment(0);
           pb[1] = wt.fragment(1);
           settle_weights<D>(w, s1, pb, wt.sum(), sl2);
