@@ -954,6 +954,11 @@ struct NextItem {
 // is not worth the extra load (short prompts of 64-wide heads 133.5 us at 8 or 4, 134.7 always and for the next item too; two prompts
 // of each of six tasks, where a workgroup is alone, 16.4 us at 4, 17.3 at 8).
 constexpr int kIdsFrom = 4;
+// Stages that an item must have left for whole pairs to be looked for: with fewer, which is all that short prompts have, the look costs
+// more than the pairs give.  Against no such limit: 96 steps of short prompts of six tasks 1.004 times as fast, 96 of one to six prompts 1.007,
+// 96 of few-row chunks 1.005, one prompt of 777 tokens 15.9 us and 15.6; at 2 and 4 1.002 to 1.006 on the first half of these, at 10
+// 1.001 to 1.004.
+constexpr int kPairsFrom = 6;
 
 // Runs the prefill item t.cur and, for as long as the workgroup's next item is a prefill item as
 // well, carries straight on into it: the stage ring does not drain between items, only the
@@ -1177,8 +1182,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       // burst in front of them they hold up the wavefront (a 4096-row chunk behind 61440 tokens 970 us, 950 so), and spread over
       // twice as many they land later, which chunks of few rows wait for (42 of 4 rows behind 5321 on 8/8 heads of 64 97.5 and 92.6,
       // 97 of one row behind 12208 on 24/8 heads 1294 and 1251; 90.7 and 1182 with one burst and the loop before).
-      int pairs = wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto ? (int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1 : 0;
-      pairs = uniform(min(pairs, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
+      int pairs = 0;
+      if (end_st - g_st >= kPairsFrom && wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto)
+        pairs = uniform(min((int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
       if (pairs > 0) {
         HFX_WAIT_VMCNT(0);            // the ids
         const int* id = ids + ((cs.bt - ids_bt) >> 1);
