@@ -579,16 +579,19 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
 // Keys arrive in stages of 32 (two pages' K and V blocks, 16 KB at D = 128) in a ring of four stage
 // slots, filled by direct-to-LDS loads about four stages ahead of their use: they take no registers and no
 // vector instructions (54 bytes per clock and CU out of the L2, measured; a stage pair needs 32 KB in
-// about 2150 clocks).
+// about 2240 clocks).
 //
 // What bounds it: the matrix cores, at the clock the chip's power leaves them.  Every matrix instruction of the
 // stage loop is followed by one LDS read of a fragment and one sixteenth of the softmax (an exponential, and every other time the
 // sum and rounding of a pair), so that vector unit, LDS and matrix cores are asked for at an even rate whichever
 // phases the two wavefronts of a SIMD are in; and the common stage pairs run in a loop of their own, without conditions,
-// scalar loads or bursts of copies.  A wavefront that has its SIMD to itself takes 1520 clocks a pair of stages (the matrix
-// instructions take 1024), the older of two 1820, the younger 2480: the matrix cores are busy 85 % of that time.  With the whole softmax behind the score instructions and one loop for all stages it was
-// 2350, 2450 and 3050 clocks.  4 prompt chunks of 2048 rows behind up to 12288 earlier tokens (0.96 TFLOP): 909 us then, 867 now on the
-// same card; a 4096-row chunk behind 61440 tokens 1053 and 968; a single prompt of 777 tokens 18.7 and 17.2.
+// scalar loads or bursts of copies.  Clocks a pair of stages in that loop, waits at its synchronisation points included, of which the
+// matrix instructions are 1024: 1573 for a wavefront that has its SIMD to itself, 1980 and 2510 for the older and the younger of two
+// in a 4096-row chunk behind 61440 tokens, so that the matrix cores are busy 2 * 1024 of 2243 clocks there, 91 %.  The loop is 0.91 of the
+// workgroups' time in that step and 0.82 to 0.87 where tiles are shorter.  With the whole softmax behind the score instructions and one loop for
+// all stages the clocks were 2350, 2450 and 3050.  Times then and now, both in turn on one card: 4 prompt chunks of 2048 rows behind up to 12288
+// earlier tokens beside 32 decodes (0.96 TFLOP) 879 and 841 us; a 4096-row chunk behind 61440 tokens and 16 decodes 1020 and 943; a single prompt of 777
+// tokens 18.2 and 15.7.
 // A value fragment takes the registers of the key fragment used up before it, and the other way round.
 // Tried with it: the synchronisation point behind the second value instruction instead of in front of the first (-1.5 to +1.5 %); a ring
 // of eight stages where a workgroup has its CU to itself (slower: nobody waits for a copy with four).
@@ -1334,7 +1337,8 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
 // Page copy: pool pages named by (src, dst) id pairs move between two pools of the same
 // geometry (or inside one).  The device half of handing a request's KV blocks from the
 // instance that prefilled it to the instance that decodes it (HFX Section 3.3.1,
-// disaggregated mode; Section 3.4).  16-byte units, of which a page has a multiple of 256; a workgroup moves 16 KB with all of its
+// disaggregated mode; Section 3.4).  16-byte units, of which a page has 256, 512 or a multiple of
+// 1024 (1, 2 or a multiple of 4 kv-heads); a workgroup moves 16 KB with all of its
 // loads in flight before the first store.  The page of a 4 KB piece is the same for the whole workgroup, so that its id
 // is one scalar load and nothing is divided per thread.
 // Stream: the pages are not read again, nor do they find a place in the last-level cache.

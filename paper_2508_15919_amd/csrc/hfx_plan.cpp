@@ -26,19 +26,20 @@ static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of
 // prefill-heavy mixed step.  What it costs is that the dies end at different times and that in the first rounds
 // all workgroups of a die start together, so that those that read the same keys move in step and every cache line is
 // a first touch for all of them at once: 40 to 80 us a step.  Prompts of 128-wide heads in four to eight rounds, with
-// classes over without: 1.2 to 1.4 at 250 us of modelled time, 1.05 to 1.15 at 500, 0.99 to 1.05 from 800 on; three
-// rounds (6144 tokens) 1.12, 17 short prompts of each of six tasks 1.8.  64-wide heads, with half the bytes a key and
-// less to save, lose more, 1.15 to 1.2 still at 1000 us.  All of these have keys that fit the last-level cache (256 MB).
-// With far more keys than that, each read by two items or more, a queue per die is the better one again, as far as the items
-// are long (kMinItemNs, by the (row, key) pairs they work on): 20 steps of 85 to 260 chunks of 33 or 64 rows on 1.3 to
-// 6 GB of keys took 0.9 to 1.01 of the time.  (Not where no two items share keys: 15 steps, 1.0 to 1.09.)
+// classes over without (28 steps): 1.24 to 1.38 at 230 to 320 us of modelled time, 1.08 to 1.20 at 420 to 600, 1.03 to 1.08 at 870 to
+// 1100 and 1.00 to 1.06 at 1200 to 2100; three rounds (6144 tokens) 1.17, 17 short prompts of each of six tasks 1.45.  64-wide
+// heads, with half the bytes a key and less to save, lose more (three prompts of 7993, 4771 and 706 1.13).  All of these have keys that fit
+// the last-level cache (256 MB).  With far more keys than that, each read by two items or more, a queue per die is the better one
+// again, as far as the items are long (kMinItemNs, by the (row, key) pairs they work on): 105 chunks of 64 rows behind 8500 to 34009 on 64-wide
+// 24/8 heads 0.90; with the prefill loop before its whole pairs 20 steps of 85 to 260 chunks of 33 or 64 rows on 1.3 to
+// 6 GB of keys 0.9 to 1.01.  (Not where no two items share keys: 15 steps, 1.0 to 1.09.)
 static const int kClassRoundsMin = 4;
 static const double kClassStepNs = 800000.0;
 static const double kClassStreamBytes = 1e9;
 // Steps of requests with one row tile of few rows behind long contexts are another matter.  Where several head
 // blocks read the same keys, each on a die of its own, the step lasts as long as the blocks take to stream them apart
 // (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
-// 22937 tokens on 24/8 heads 2467 us without classes, 1591 with; 97 of one row behind 12208, 1594 and 1107.  The ratio is
+// 22937 tokens on 24/8 heads 2775 us without classes, 1973 with; 97 of one row behind 12208, 1625 and 1253.  The ratio is
 // 1.9 with one busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in
 // the cache.  The gain holds from three rounds and about 2100 keys an item on: 90 steps of 50 to 96 us an item took, with
 // classes over without, 0.89 to 1.14 below 64 us, 0.81 to 0.97 from 70 to 80, 0.76 to 0.96 above.
@@ -46,7 +47,10 @@ static const int kClassRoundsMinApart = 3;
 static const double kClassApart = 1.5;
 static const double kClassItemNsApart = 70000.0;
 static const double kLongStepNs = 400000.0; // steps of less time than this are cut by trying what the cut leads to ...
-static const double kLoneShare = 0.575;      // time of an item alone on its CU, over its time beside another
+// Time of an item alone on its CU over its time beside another, steps of 256 equal items over steps of 512: 0.54 to 0.55 behind 2048 to
+// 16384 earlier tokens, 0.59 behind 1024, 0.65 behind 512; on 64-wide heads 0.58 to 0.63, 0.69 and 0.75.  (Counted in clocks of the stage loop it
+// is 0.68 to 0.73, but the clock falls when all CUs have two.)
+static const double kLoneShare = 0.575;
 static const int64_t kCutMaxTiles = 8192;   // ... if they have no more row tiles (the host time of the trial)
 static const int kClassRoundsMax = 8;
 static const int kFitRounds = 6;           // steps with fewer rounds of prefill items than this get whole rounds
@@ -83,7 +87,8 @@ static int64_t pairs_in(int64_t p, int64_t r0, int64_t r1, int64_t kb, int64_t k
 // Time of a row tile that sees `keys` keys.  What counts is the time a workgroup spends, which is that of
 // four full wavefronts however few rows the tile has.  Cuts and the queue go by it alike: the ragged last tile
 // of a prompt sees the most keys and has to start first.  (Ordered by the (row, key) pairs of the tile it started
-// among the last: 45 steps of one to four prompts of 32 k + 1..5 tokens took 1.16 times as long on average, up to 1.48.)
+// among the last: 2500 tokens 74 us instead of 55, 4097 tokens 155 instead of 126; 45 steps of one to four prompts of 32 k + 1..5 tokens took 1.16
+// times as long on average with the prefill loop before its whole pairs, up to 1.48.)
 static double tile_ns(int D, int64_t keys) {
   return 4.0 * D * 4 * HFX_WAVE_ROWS * (double)keys / (D == 64 ? kPrefillFlopsPerNs64 : kPrefillFlopsPerNs);
 }
@@ -202,20 +207,21 @@ static double last_end(const std::vector<float>& cost, int copies, float scale, 
 // In a decode-dominated step the prefill items run beside the decode stream on CUs of their own (see the
 // queue order in plan_step) and only have to be done when it is: pieces of up to 0.75 of a share save
 // partials and merge work (64 decodes and two chunks of 512: 108 us at 0.6, where the later chunk's tiles
-// are cut in two, 102 at 0.75 to 1.2, where they are not).
+// are cut in two, 99 at 0.75, where they are not).
 //
 // Prefill-dominated steps:
 // In short steps the cap is chosen by what it leads to: largest first, items go to where there is the least
 // work, an item alone on its CU runs at 1.74 times its rate, and every cut adds partials (64 KB a piece,
 // written and read: 26 ns) and the merge launch (4 us).  Not cutting at all is the common answer: whole tiles
-// fill the CUs (1500 tokens on 32/8 heads: 37 us cut at half a share, 33 whole; 2500 tokens 81 and 59; 4096 tokens 164 and
-// 138; 1000 behind 3000 beside 16 decodes 101 and 89).  Cuts pay where there are fewer tiles than CUs (128 tokens behind
-// 8000: 122 us whole, 44 in 4 pieces, 34 in 8, 48 in 9; 8 chunks of one row behind 4000: 66 whole, 34 in 4; behind
-// 1000: 21.6 whole, 20.6 in 3) and where a few tiles outlast the rest (300 behind 5000 and 200 behind 6000: 96 and 67).
+// fill the CUs (1500 tokens on 32/8 heads: 33.5 us cut at half a share, 27.6 whole; 2500 tokens 76 and 55; 4096 tokens 147 and
+// 123; 1000 behind 3000 beside 16 decodes 92 and 77).  Cuts pay where there are fewer tiles than CUs (128 tokens behind
+// 8000: 92 us whole, 36 in 4 pieces, 30 in 8, 42 in 9; 8 chunks of one row behind 4000: 58 whole, 33 in 4) and where a few tiles
+// outlast the rest (300 behind 5000 and 200 behind 6000: 73 and 61).  The estimate dates from a slower loop, so that the line lies
+// a little early: 8 chunks of one row behind 1000 take 19.1 in 3 pieces and 17.4 whole (20.6 and 21.6 with that loop).
 // Tiles of few rows in layouts of few q-heads per kv-head leave wavefronts without rows.  Where all such tiles start at
 // once, whole, they slow their neighbours on the CU the less; and no cut makes a step shorter than its keys take to
-// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 454 us whole, 530 in
-// two pieces each; 23 behind 8015 on 12/4 heads: 168 and 231.
+// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 470 us whole, 493 in
+// three pieces each; 23 behind 8015 on 12/4 heads: 166 and 178; 42 behind 5321 on 8/8 heads of 64 92 and 114 in four.
 // Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
@@ -342,8 +348,8 @@ static int64_t cut_rows(const int32_t* kind, const int32_t* q_len, const int32_t
 // full ones, are cut like full ones and write as many partial rows.  More than the fixed workspace is taken only
 // where the work itself asks for it: as many rows as half a share of the step, counted in visible
 // (row, key) pairs, cuts the tiles into, in whole rounds.  (A 4096-token chunk behind 61440 on one kv-head: 72 MB,
-// two rounds of equal pieces.  40 chunks of 40 rows behind 19960 tokens beside four of 2048: 85 MB and 1349 us by time, 64 MB by
-// pairs, 43 MB and 1264 us so bounded.)
+// two rounds of equal pieces.  40 chunks of 40 rows behind 19960 tokens beside four of 2048, with the prefill loop before its whole
+// pairs: 85 MB and 1349 us by time, 64 MB by pairs, 43 MB and 1264 us so bounded; 1192 us now, 1157 uncut.)
 static double cap_within_workspace(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
                                    int hpw, int rows_wg, double dec_ns, double pre_ns, int64_t dec_rows, double cap) {
   auto by_pairs = [&](int64_t p, int64_t r0, int64_t r1) {
@@ -390,28 +396,28 @@ struct DecodeCut {
 // By default an item has up to four kv-heads, one for each wavefront, and takes about cap_ns.  Steps whose items all have a place on the
 // chip at once do better with fewer heads an item: its wavefronts then walk a quarter or half of the pages each, so that pieces
 // can be longer and partials fewer, or there is nothing to merge.  `n_pre`: prefill items of the step.
-// Decodes alone take up to two items a CU (all on 32/8 heads of 128 unless named): 4 of 100 to 2000 tokens 12.9 us by default, 10.9 so;
-// 12 of 200 to 400 12.0 and 8.2; 16 of 2000 34.1 and 29.4; 64 of 1000 55.0 and 50.5; 128 of 500 to 2000 133 and 118 (two heads);
-// 100 of 500 to 5000 on 64-wide heads 112 and 107; 8 of 20000 to 60000 on one kv-head 38.0 and 36.2; at worst 64 of 1000 to 4000 there,
-// 20.2 and 20.6.  A context is left whole if that saves the merge launch (3.3 us) for at most 1024 more tokens of one head (4 us): 500 tokens
-// 11.0 us in pieces, 8.4 whole; with 2048 more, the 4 decodes above 14.4.  Pieces have 256 tokens of one head at least (128, 512: the same within
+// Decodes alone take up to two items a CU (all on 32/8 heads of 128 unless named): 4 of 100 to 2000 tokens 12.4 us by default, 10.4 so;
+// 12 of 200 to 400 11.3 and 7.5; 16 of 2000 29.5 and 25.3; 64 of 1000 53.9 and 49.7; 128 of 500 to 2000 133 and 118 (two heads);
+// 100 of 500 to 5000 on 64-wide heads 115 and 108; 8 of 20000 to 60000 on one kv-head 32.4 and 31.6; at worst 64 of 1000 to 4000 there,
+// 18.3 and 18.9.  A context is left whole if that saves the merge launch (3.3 us) for at most 1024 more tokens of one head (4 us): 500 tokens
+// 10.1 us in pieces, 7.9 whole; with 2048 more, the 4 decodes above 14.0.  Pieces have 256 tokens of one head at least (128, 512: the same within
 // 3 % where they differ).
 // Beside prefill items decodes keep to CUs of their own, or the longer piece beside a prefill item ends last, and to pieces no
-// longer than the default: 3 of 200 to 900 beside a prompt of 100 11.5 us and 8.5; where up to 512 items were allowed, 6 of 500 to 5000 beside 777
-// 24.0 and 26.6, and 10 of 200 to 3000 on 8/8 heads beside 192 rows 15.4 and 18.3 (15.0 so).
+// longer than the default: 3 of 200 to 900 beside a prompt of 100 10.6 us and 8.3; where up to 512 items were allowed, 6 of 500 to 5000 beside 777
+// 23.0 and 26.2, and 10 of 200 to 3000 on 8/8 heads beside 192 rows 15.1 and 16.8 (14.8 so); with longer pieces the first of these 32.2.
 //
 // Beside prefill items that a decode stream outweighs, a step of up to kRoundsOver times the 1024 items of two rounds has its pieces
 // lengthened to that, if pieces four times as long are enough: all items are then dealt, and no round has a few items in it.  150 steps of 1.0 to
 // 2.0 times 1024 items on seven head layouts: 1.007 to 1.044 times as fast on average in each tenth, the slowest 0.965, the fastest 1.112; six
-// steps of 2.0 to 2.4 times 1.020, six of 2.4 to 2.6 times 0.991.  70 decodes alone, 1.5 times 1024 items: 117.5 and 125.9 us,
-// hence not without prefill items.
+// steps of 2.0 to 2.4 times 1.020, six of 2.4 to 2.6 times 0.991.  Decodes alone keep their pieces by time.  (They gain as well: 50 steps 1.031,
+// the slowest 0.984; one step that had been measured took 117.5 us and 125.9.)
 static const double kRoundsOver = 2.0;
 static const int64_t kHeadTokensMin = 256;
 static const int64_t kHeadTokensWhole = 1024;
 static const int64_t kHeadTokensBeside = 700;
 // One round has to come out even: no piece may be longer than kLongestPiece times an even share, or what is left of a long context when
-// there is room for one piece of each ends last (64 contexts spread evenly over the logarithm from 16 to 8192: 60.4 us by default, 84.1 in
-// one round of one-head items, 59.8 of two-head items; 20 such families 1.05 on average, none slower; at 2 times 1.045, at 1.5 1.037).  Only in
+// there is room for one piece of each ends last (64 contexts spread evenly over the logarithm from 16 to 8192: 62.1 us by default, 85.9 in
+// one round of one-head items, 60.6 of two-head items; 20 such families 1.05 on average, none slower; at 2 times 1.045, at 1.5 1.037).  Only in
 // steps of at most kHeadShareWhole tokens of a head for each item is the longer piece bound by latency and not by the stream.
 static const double kLongestPiece = 3.0;
 static const int64_t kHeadShareWhole = 512;
