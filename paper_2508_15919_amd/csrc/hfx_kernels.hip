@@ -1613,8 +1613,11 @@ static bool kernel_may_upload(const void* host, const void* device, size_t bytes
   if (!query(host, &from) || from.type != hipMemoryTypeHost || from.on_gpu != host || !whole(host, from)) return false;
   if (!query(device, &to) || to.type != hipMemoryTypeDevice || !whole(device, to)) return false;
   int current = -1;
+  if (hipGetDevice(&current) != hipSuccess || current != to.gpu) return false;
+  // the handles that name a stream of the current GPU without being one: asked for the GPU of these, the runtime follows them
+  if (stream == nullptr || stream == hipStreamLegacy || stream == hipStreamPerThread) return true;
   hipDevice_t streams = -1;
-  return hipGetDevice(&current) == hipSuccess && hipStreamGetDevice(stream, &streams) == hipSuccess && current == to.gpu && streams == to.gpu;
+  return hipStreamGetDevice(stream, &streams) == hipSuccess && streams == to.gpu;
 }
 
 // Pinned memory is read by a kernel: the runtime gives a megabyte to a copy engine, and the next kernel on the same stream started 10 to

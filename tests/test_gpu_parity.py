@@ -615,6 +615,22 @@ def test_which_node_a_captured_upload_becomes(hb, offset, kind):
         assert torch.equal(dev.cpu(), host)
 
 
+@pytest.mark.parametrize("stream", [None, 2])       # the default stream, and the one of each thread (hipStreamPerThread)
+def test_a_step_on_a_stream_that_is_named_and_not_made(hb, stream):
+    import torch
+    b = synth.config(1)
+    step = hb.DeviceStep(b)
+    step.run()
+    want = step.out_bits().copy()
+    step.out.zero_()
+    step.device_desc.zero_()
+    torch.cuda.synchronize()
+    hb.hfx_build_batch_desc(step.shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, b.bt_pages, step.host_desc, step.device_desc, stream)
+    hb.hfx_mixed_paged_attention(step.shape, step.q, step.pool, step.host_desc, step.device_desc, step.workspace, step.out, stream)
+    torch.cuda.synchronize()
+    assert np.array_equal(step.out_bits(), want)
+
+
 def test_device_side_errors(hb):
     import torch
     b = synth.config(1)

@@ -30,7 +30,11 @@ static const Memory* find(const void* p) {
 
 extern "C" {
 hipError_t hipGetDevice(int* d) { *d = current; return hipSuccess; }
-hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) { *d = s ? stream_device : current; return hipSuccess; }
+hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) {      // the runtime's reads through the handle
+  if ((uintptr_t)s < 4096) std::abort();
+  *d = stream_device;
+  return hipSuccess;
+}
 hipError_t hipPeekAtLastError(void) { return (hipError_t)pending; }
 hipError_t hipGetLastError(void) { int e = pending; pending = 0; return (hipError_t)e; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t* a, const void* p) {
@@ -68,7 +72,7 @@ hipError_t hipMemcpyAsync(void*, const void*, size_t, hipMemcpyKind, hipStream_t
 }
 
 // staging: type, bytes of it that are known; descriptor: type, device, bytes; current device, the stream's device; pending error; a
-// launch fails; the call after building
+// launch fails; the call after building; the stream's handle
 int main(int, char** v) {
   static const int32_t kind[3] = {0, 0, 1}, q_len[3] = {1, 1, 20}, ctx[3] = {40, 33, 20}, indptr[4] = {0, 3, 6, 8}, pages[8] = {0, 1, 2, 3, 4, 5, 6, 7};
   const hfx_shape shape = {4, 2, 64, 16, 8, 0.f};
@@ -87,15 +91,16 @@ int main(int, char** v) {
   char* any = dev + (1 << 19);
   int32_t ids[2] = {2, 3};
   const std::string what = v[10];
+  void* stream = (void*)(uintptr_t)std::atoi(v[11]);
   hfx_status st = 0;
-  if (what == "build") st = hfx_build_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes, dev, device_bytes, (void*)0x1000);
+  if (what == "build") st = hfx_build_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes, dev, device_bytes, stream);
   else hfx_fill_batch_desc(&shape, 3, kind, q_len, ctx, indptr, pages, host, host_bytes);
-  if (what == "attention") st = hfx_mixed_paged_attention(&shape, any, any, host, dev, any, 1 << 18, any, nullptr);
-  if (what == "static") st = hfx_mixed_paged_attention_static(&shape, any, any, host, dev, any, nullptr);
-  if (what == "gather") st = hfx_gather_kv(&shape, any, host, dev, 0, any, any, nullptr);
-  if (what == "gather unaligned") st = hfx_gather_kv(&shape, any, host, dev, 0, any + 2, any, nullptr);
-  if (what == "append") st = hfx_append_kv(&shape, any, any, any, host, dev, nullptr);
-  if (what == "pages") st = hfx_copy_pages(&shape, any, any + 4096, 8, 2, ids, ids, host, dev, 4096, nullptr);
+  if (what == "attention") st = hfx_mixed_paged_attention(&shape, any, any, host, dev, any, 1 << 18, any, stream);
+  if (what == "static") st = hfx_mixed_paged_attention_static(&shape, any, any, host, dev, any, stream);
+  if (what == "gather") st = hfx_gather_kv(&shape, any, host, dev, 0, any, any, stream);
+  if (what == "gather unaligned") st = hfx_gather_kv(&shape, any, host, dev, 0, any + 2, any, stream);
+  if (what == "append") st = hfx_append_kv(&shape, any, any, any, host, dev, stream);
+  if (what == "pages") st = hfx_copy_pages(&shape, any, any + 4096, 8, 2, ids, ids, host, dev, 4096, stream);
   std::printf("%d %s pending %d\n", st, launches && copies ? "copy and kernel" : launches ? "kernel" : copies ? "copy" : "nothing", pending);
 }
 """
@@ -116,8 +121,8 @@ def program(tmp_path_factory):
                     str(src), "-o", str(exe), "-L", lib, f"-l:{os.path.basename(hb.LIB_PATH)}", f"-Wl,-rpath,{lib}:/opt/rocm/lib",
                     "-Wl,--allow-shlib-undefined"], check=True)
 
-    def call(host=1, host_bytes="all", dev=2, device=0, dev_bytes="all", current=0, stream=0, pending=0, fail=0, entry="build"):
-        args = [host, host_bytes, dev, device, dev_bytes, current, stream, pending, fail, entry]
+    def call(host=1, host_bytes="all", dev=2, device=0, dev_bytes="all", current=0, stream=0, pending=0, fail=0, entry="build", handle=4096):
+        args = [host, host_bytes, dev, device, dev_bytes, current, stream, pending, fail, entry, handle]
         return subprocess.run([str(exe), *map(str, args)], check=True, capture_output=True, text=True, timeout=60).stdout.strip()
     return call
 
@@ -155,3 +160,9 @@ def test_a_failed_launch_is_reported(program, entry):
 def test_an_unread_error_does_not_disturb_the_runtimes_copy(program):
     assert program(host=UNKNOWN, pending=101) == "0 copy pending 101"
     assert program(host=UNKNOWN, pending=101, entry="pages") == "0 copy and kernel pending 101"
+
+
+@pytest.mark.parametrize("handle", [0, 1, 2])       # the default stream, hipStreamLegacy, hipStreamPerThread
+@pytest.mark.parametrize("entry", ENTRIES)
+def test_streams_that_are_named_and_not_made(program, handle, entry):
+    assert program(handle=handle, entry=entry) == "0 kernel pending 0"
