@@ -523,7 +523,7 @@ def test_a_descriptor_is_uploaded_beside_a_launch_that_fills_the_chip(hb, Hq, Hk
     its end, runs on the first.  The upload ends well before the launch does."""
     import torch
     rng = np.random.default_rng(D)
-    b = small_pool_batch(rng, Hq, Hkv, D, [DECODE] * 64, [1] * 64, [60000] * 64, f"long-{D}")
+    b = small_pool_batch(rng, Hq, Hkv, D, [DECODE] * 256, [1] * 256, [60000] * 256, f"long-{D}")
     step = hb.DeviceStep(b)
     n = 1200
     nxt = synth.make_batch(Hq, Hkv, D, [DECODE] * n, [1] * n, rng.integers(1, 30, n), 3)
@@ -546,7 +546,7 @@ def test_a_descriptor_is_uploaded_beside_a_launch_that_fills_the_chip(hb, Hq, Hk
         assert torch.equal(dev.cpu(), host)
         share.append(start.elapsed_time(uploaded) / start.elapsed_time(end))
     print("upload done after", share, "of", start.elapsed_time(end), "ms")
-    assert min(share[1:]) < 0.7, share          # (its planning takes a few hundred microseconds of that)
+    assert min(share[1:]) < 0.6, share          # (its planning takes a tenth of that; without a place on the chip it ends after 0.8 and more)
 
 
 def test_captured_upload_reads_the_staging_buffer_at_each_replay(hb, oracle):
