@@ -4,7 +4,7 @@
 #include <stdint.h>
 
 #define HFX_DESC_MAGIC 0x31584648u /* "HFX1" */
-#define HFX_DESC_VERSION 16u
+#define HFX_DESC_VERSION 17u
 #define HFX_PAGE 16
 #define HFX_WG_THREADS 256
 #define HFX_PLAN_WGS 512         /* planning width: 256 compute units x 2 resident workgroups */
@@ -13,6 +13,11 @@
 #define HFX_BT_PAD 16            /* stored block-table entries after a request's last page, all naming that page */
 #define HFX_WAVE_ROWS 32         /* query rows one wavefront owns in a prefill item (one MFMA row block) */
 #define HFX_QUEUE_CLASSES 8      /* queue positions p with equal p % 8 form a class: one per accelerator die (XCD), each with an L2 of its own */
+
+// Control words, each on a line of its own: atomics on one line from all over the chip are served one after the other.
+#define HFX_CTRL_TICKETS(c) ((c) * 32)                          /* tickets of class c handed out past the two dealt to each workgroup by index */
+#define HFX_CTRL_DONE(c) ((HFX_QUEUE_CLASSES + (c)) * 32)       /* finished workgroups of class c; c == HFX_QUEUE_CLASSES: finished classes */
+#define HFX_CTRL_WORDS ((2 * HFX_QUEUE_CLASSES + 1) * 32)
 
 #define HFX_STATIC_WS_BYTES (64u << 20) /* fixed workspace of the entry point that allocates nothing */
 #define HFX_MAX_DEVICES 64
@@ -28,8 +33,7 @@ struct HfxHeader {
   int32_t n_partial_rows;       /* workspace rows: one (query row, q-head) partial each */
   int32_t n_bt;                 /* page ids stored */
   uint32_t off_ctrl, off_req, off_bt, off_items, off_groups;
-  uint32_t n_ctrl;              /* control words: [c], c < queue_classes: tickets of class c handed out past the two dealt
-                                   to each workgroup by index; [HFX_QUEUE_CLASSES]: finished workgroups */
+  uint32_t n_ctrl;              /* control words, HFX_CTRL_WORDS */
   uint64_t total_bytes;
   uint64_t workspace_bytes;
   uint64_t ws_off_ml;           /* byte offset of the (m, l) pairs inside the workspace; acc rows start at 0 */

@@ -237,7 +237,7 @@ constexpr int kDealtTickets = 2;
 struct Tickets {
   int cur, nxt;
   int parity;
-  bool queue;        // there are items behind the dealt ones
+  bool queue;        // there may be items behind the next one
 };
 
 // The dealt tickets of a step whose queue is in descending cost.  Workgroups b and b + 256 share a CU, so
@@ -268,50 +268,61 @@ __device__ __forceinline__ void deal_balanced(Tickets& t, int mode, int n_items)
 // one die, and the planner puts items that read the same keys into one class: they then share
 // that die's L2.
 //
+// What bounds the counters: atomics and atomic loads on one line from all over the chip are served one after the other, 14 ns
+// each.  With all of them on one line, and every workgroup reading the eight of them one by one whenever its class was empty, the end
+// of a step with classes took 40 to 90 us, whatever the step: 17 short prompts of each of six tasks 87 us from one queue and 185 with classes.
+// Now each has a line of its own, a look at all eight is one load, a workgroup that knows the queue to be empty asks no more, and workgroups report
+// their end by class: 83 and 86 us; the prefill-heavy mixed step, which has classes, 858 -> 818; 58 short prompts of each of six
+// tasks on 64-wide heads, one queue, 190 -> 186.
+//
 // Thread 0 asks its class's counter for one more ticket; the reply, an offset from the dealt
 // tickets, goes to tickets_publish.  The other lanes keep what `pending` held: a select on it would
 // wait for the reply, and with it for everything in flight, wherever the compiler places it.
 __device__ __forceinline__ void tickets_reserve(const Tickets& t, int& pending, int* ctrl, int nc) {
-  if (t.queue && threadIdx.x == 0) pending = atomicAdd(ctrl + ((int)blockIdx.x & (nc - 1)), 1);
+  if (t.queue && threadIdx.x == 0) pending = atomicAdd(ctrl + HFX_CTRL_TICKETS((int)blockIdx.x & (nc - 1)), 1);
 }
 // Thread 0 puts the reserved ticket into LDS (two slots alternate, so one barrier per hand-over is
-// enough).  A reply past the end of the queue means the workgroup's class is empty.  It then reads
-// all counters (one round trip) and asks the class that has most positions left for one, so
+// enough).  A reply past the end of the queue means the workgroup's class is empty.  Its first wavefront then reads
+// all counters (one load, a lane each) and asks the class that has most positions left for one, so
 // that a die that finishes early helps the others; when other workgroups got there first (the
 // reply is past the end again) it looks again, a few times.  Giving up early costs balance, not
 // correctness: every class is drained by its own workgroups whether or not others help.
 constexpr int kStealAttempts = 4;
 __device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, int* s_tk, int* ctrl, int n_items, int nc) {
-  if (t.queue && threadIdx.x == 0) {
-    const int base = kDealtTickets * (int)gridDim.x;
-    int pos = base + pending * nc + ((int)blockIdx.x & (nc - 1));
-    if (nc > 1) {
-      // (formed here and not, for all eight classes, at the start of every workgroup)
-      int behind = n_items - base;
-      asm volatile("" : "+s"(behind));
-      for (int attempt = 0; attempt < kStealAttempts && pos >= n_items; ++attempt) {
-        int best = 0, best_left = 0;
-        for (int k = 0; k < HFX_QUEUE_CLASSES; ++k) {
-          const int taken = __hip_atomic_load(ctrl + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          // positions base + r * classes + k below n_items with r >= taken
-          const int left = (behind - k + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - taken;
-          if (left > best_left) {
-            best_left = left;
-            best = k;
-          }
+  if (!t.queue || threadIdx.x >= 64) return;
+  const int base = kDealtTickets * (int)gridDim.x;
+  int pos = base + uniform(pending) * nc + ((int)blockIdx.x & (nc - 1));
+  if (nc > 1 && pos >= n_items) {
+    // (formed here and not at the start of every workgroup)
+    int k = (int)threadIdx.x & (HFX_QUEUE_CLASSES - 1), behind = n_items - base;
+    asm volatile("" : "+v"(k), "+s"(behind));
+    for (int attempt = 0; attempt < kStealAttempts && pos >= n_items; ++attempt) {
+      const int taken = __hip_atomic_load(ctrl + HFX_CTRL_TICKETS(k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // positions base + r * classes + k below n_items with r >= taken
+      const int left = (behind - k + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - taken;
+      int best = 0, best_left = 0;
+#pragma unroll
+      for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) {
+        const int l = __builtin_amdgcn_readlane(left, c);
+        if (l > best_left) {
+          best_left = l;
+          best = c;
         }
-        if (best_left <= 0) break;
-        pos = base + atomicAdd(ctrl + best, 1) * HFX_QUEUE_CLASSES + best;
       }
+      if (best_left <= 0) break;
+      int reply = 0;
+      if (threadIdx.x == 0) reply = atomicAdd(ctrl + HFX_CTRL_TICKETS(best), 1);
+      pos = base + uniform(reply) * HFX_QUEUE_CLASSES + best;
     }
-    s_tk[t.parity] = pos;
   }
+  if (threadIdx.x == 0) s_tk[t.parity] = pos;
 }
-// ... after a workgroup barrier that follows tickets_publish
-__device__ __forceinline__ void tickets_take(Tickets& t, int* s_tk) {
+// ... after a workgroup barrier that follows tickets_publish.  Counters only grow: once a ticket is past the end, so are all later ones.
+__device__ __forceinline__ void tickets_take(Tickets& t, int* s_tk, int n_items) {
   t.cur = t.nxt;
   t.nxt = 0x7fffffff;
   if (t.queue) t.nxt = uniform(s_tk[t.parity]);
+  t.queue = t.nxt < n_items;
   t.parity ^= 1;
 }
 
@@ -555,7 +566,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
       }
     }
     __syncthreads();                  // frees the LDS partials; the ticket was published before the one above
-    tickets_take(t, s_tk);
+    tickets_take(t, s_tk, n_items);
     if (!carry_on) break;
     it = nx;
     d = dn;
@@ -1251,7 +1262,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     ++g_st;
     // hand-over: the item is finished; its successor's first stages are in the ring or on their way.  The records of the
     // successor and of the item after that are asked for ahead of the store; a workgroup's last item waits for none.
-    tickets_take(t, s_tk);
+    tickets_take(t, s_tk, n_items);
     if (!next_ok) {
       prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
       break;
@@ -1325,10 +1336,16 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   // workgroup reports itself finished, or it could land after the reset below
   HFX_WAIT_VMCNT(0);
   asm volatile("" ::: "memory");
-  if (t.queue && threadIdx.x == 0) {
-    const int done = atomicAdd(&ctrl[HFX_QUEUE_CLASSES], 1);
-    if (done == (int)gridDim.x - 1) {
-      for (int c = 0; c <= HFX_QUEUE_CLASSES; ++c) atomicExch(&ctrl[c], 0);
+  if (n_items > kDealtTickets * (int)gridDim.x && threadIdx.x == 0) {
+    // the workgroups of a class count themselves, and its last one the classes
+    const int cls = (int)blockIdx.x & (HFX_QUEUE_CLASSES - 1);
+    if (atomicAdd(ctrl + HFX_CTRL_DONE(cls), 1) == ((int)gridDim.x - cls + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - 1 &&
+        atomicAdd(ctrl + HFX_CTRL_DONE(HFX_QUEUE_CLASSES), 1) == min((int)gridDim.x, HFX_QUEUE_CLASSES) - 1) {
+      for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) {
+        atomicExch(ctrl + HFX_CTRL_TICKETS(c), 0);
+        atomicExch(ctrl + HFX_CTRL_DONE(c), 0);
+      }
+      atomicExch(ctrl + HFX_CTRL_DONE(HFX_QUEUE_CLASSES), 0);
     }
   }
 }

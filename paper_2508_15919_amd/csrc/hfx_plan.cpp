@@ -898,7 +898,7 @@ void layout_blob(const hfx_shape* shape, const Plan& P, HfxHeader* h) {
   h->n_groups = (int32_t)P.groups.size();
   h->n_partial_rows = P.n_partial_rows;
   h->n_bt = P.n_bt;
-  h->n_ctrl = 16;
+  h->n_ctrl = HFX_CTRL_WORDS;
   h->queue_classes = (uint32_t)P.queue_classes;
   h->deal_balanced = (uint32_t)P.deal_balanced;
   h->max_group_rows = 0;

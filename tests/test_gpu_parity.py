@@ -160,6 +160,22 @@ def small_pool_batch(rng, Hq, Hkv, D, kind, q_len, ctx_len, name, n_pages=700):
                            synth.f32_to_bf16_bits(rng.standard_normal((n_pages, Hkv, 2, 16 * D)).astype(np.float32)), name=name)
 
 
+@pytest.mark.parametrize("n", [1024, 1025, 1031, 1600])
+def test_queue_counters_of_short_queues(hb, oracle, n):
+    """One item a prompt: exactly the two dealt rounds, one item more, one for some of the dies, and more than one for each workgroup.
+    Every launch finds the counters as the first one did."""
+    rng = np.random.default_rng(n)
+    q = rng.integers(1, 33, n)
+    b = small_pool_batch(rng, 4, 1, 64, [PREFILL] * n, q, q + rng.integers(0, 40, n), f"queue-{n}")
+    step, bits = check_full(hb, oracle, b)
+    assert hb.parse_desc(step.host_desc.numpy())["header"].n_items == n
+    for _ in range(2):
+        step.out.zero_()
+        step.run()
+        assert np.array_equal(step.out_bits(), bits)
+    assert np.all(hb.parse_desc(step.device_desc.cpu().numpy())["ctrl"] == 0), "control words must be restored to zero"
+
+
 @pytest.mark.parametrize("decodes", [0, 3])
 @pytest.mark.parametrize("Hq,Hkv,D", [(24, 8, 128), (32, 4, 64), (8, 8, 128), (16, 1, 128)])
 def test_chunks_of_a_few_rows_in_pieces(hb, oracle, Hq, Hkv, D, decodes):
