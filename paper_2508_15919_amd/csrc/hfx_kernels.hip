@@ -632,10 +632,6 @@ __device__ __forceinline__ void piece_copy(const char* base, unsigned voff, unsi
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
                :: "v"(voff), "s"(base), "s"(lds), "n"(piece * 1024) : "memory", "m0");
 }
-// The same for 64 page ids, one a lane.
-__device__ __forceinline__ void ids_copy(const char* bt, unsigned voff, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(voff), "s"(bt), "s"(lds) : "memory", "m0");
-}
 #pragma clang diagnostic pop
 
 // A whole block.
@@ -941,16 +937,24 @@ __device__ __forceinline__ void prefill_store(const KArgs& a, const HfxHeader* H
 }
 
 // The workgroup's stream of stage copies: the stages of the current item and then those of the next
-// item, if that is a prefill item too (the item after next has no ticket yet).  Wave-uniform.
+// item, if that is a prefill item too (the item after next has no ticket yet).  Which block a copy takes is read from a list in LDS,
+// one a wavefront, whose entries run on from item to item, so that a copy is the same few instructions wherever it is issued: no scalar loads of page
+// ids (which the next wait for an LDS read would wait for as well), and whole pairs run up to the end of an item.  With page ids of the
+// present item alone in LDS, and only of long ones, a prompt of 777 tokens took 15.9 us instead of 15.1, 14 steps of one to five prompts 1.017
+// times as long on average, 21 of short prompts 1.016 times.  Wave-uniform.
 struct CopyStream {
   int count;          // stages copied so far, over all items of the run
-  int left;           // stages of the item being copied that are still to come
-  int bt;             // stored block-table entry of the next stage's page that this wavefront copies
+  int listed;         // stages whose blocks are in the list, likewise
+  int left;           // stages of the item being listed that are still to be asked for
+  int bt;             // stored block-table entry of the next of them: the page that this wavefront copies
   int last;           // block-table entry of the request's last page
-  int limit;          // stages that may be copied without overwriting one still to be read
-  const char* base;   // block of page 0: the item's kv-head, keys or values
-  int in_next;        // the item being copied is the next one, not the current one
+  int head;           // kv-head of the item being listed
+  int asked;          // stages whose page ids are on their way, to be listed next ...
+  int asked_head;     // ... and their kv-head
+  int in_next;        // the item being listed is the next one, not the current one
+  int limit;          // stages that could be copied at the last synchronisation point without overwriting one still to be read
 };
+constexpr int kListed = 128;      // entries of a wavefront's list; up to 64 are asked for when that many are free
 
 __device__ __forceinline__ int item_stages(const HfxItem& it) { return (int)((unsigned)(it.ke - it.kb + HFX_STAGE_KEYS - 1) / HFX_STAGE_KEYS); }
 
@@ -958,20 +962,13 @@ __device__ __forceinline__ int item_stages(const HfxItem& it) { return (int)((un
 // (Its whole record kept in scalar registers through that loop, and everything that can be derived from it formed
 // ahead of it, cost 67 registers' worth of spills and about 150 instructions an item.)
 struct NextItem {
-  int left, bt, last;         // as in CopyStream
-  const char* base;
+  int left, bt, last, head;   // as in CopyStream
   int q_row0, q_last;         // first chunk row of this wavefront, last of the chunk
   const __bf16* q;            // row 0 of the chunk, this wavefront's head
 };
 
-// Stages still to be copied from which on their page ids are read into LDS: with fewer the short form of the synchronisation point
-// is not worth the extra load (short prompts of 64-wide heads 133.5 us at 8 or 4, 134.7 always and for the next item too; two prompts
-// of each of six tasks, where a workgroup is alone, 16.4 us at 4, 17.3 at 8).
-constexpr int kIdsFrom = 4;
-// Stages that an item must have left for whole pairs to be looked for: with fewer, which is all that short prompts have, the look costs
-// more than the pairs give.  Against no such limit: 96 steps of short prompts of six tasks 1.004 times as fast, 96 of one to six prompts 1.007,
-// 96 of few-row chunks 1.005, one prompt of 777 tokens 15.9 us and 15.6; at 2 and 4 1.002 to 1.006 on the first half of these, at 10
-// 1.001 to 1.004.
+// Stages that an item must have left for whole pairs to be looked for.  (2, 3 or 4 instead: 22 steps of short prompts 0.996 to 0.997 times as fast,
+// 38 others the same within 0.1 %.)
 constexpr int kPairsFrom = 6;
 
 // Runs the prefill item t.cur and, for as long as the workgroup's next item is a prefill item as
@@ -1010,7 +1007,6 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   const unsigned voff = copy_lane_offset(wave, lane);
   const unsigned lds_ring = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)smem + wave * Smem<D>::kBlockBytes;
   const char* pool = reinterpret_cast<const char*>(a.pool) + (wave >> 1) * Smem<D>::kBlockBytes;
-  const unsigned long page_bytes = (unsigned long)(unsigned)Hkv * (2 * Smem<D>::kBlockBytes);
   const int key_wave = 1 - (wave >> 1);   // 1: this wavefront copies keys, which are read a stage before the values
 
   HfxItem it = items[t.cur];
@@ -1024,7 +1020,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     x.left = item_stages(item);
     x.bt = item.rq.bt_start + (int)((unsigned)item.kb / HFX_PAGE) + (wave & 1);
     x.last = item.rq.bt_start + item.rq.n_pages - 1;
-    x.base = pool + (long)g * (2 * Smem<D>::kBlockBytes);
+    x.head = g;
     x.q_row0 = r.row0;
     x.q_last = item.rq.q_len - 1;
     x.q = q_rows(item, r);
@@ -1033,58 +1029,59 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   const HfxItem item1 = items[t.nxt < n_items ? t.nxt : t.cur];
   NextItem nx = next_item(item1);
   bool next_ok = t.nxt < n_items && item1.type == HFX_ITEM_PREFILL;
-  // The pages of the stages to be copied lie in LDS where an item is long enough to run in pairs: of 64 stages from
-  // block-table entry ids_bt on, if ids_ok.  A scalar load in the middle of the stage loop makes the next wait for an LDS read wait
-  // for it as well.
-  int ids_bt = 0;
-  bool ids_ok = false;
-  int* const ids = s_ids + wave * 64;
-  const unsigned lds_ids = (unsigned)(uintptr_t)(__attribute__((address_space(3))) int*)ids;
-  // (the block table by way of the control words: a pointer that an asm statement has seen is no longer read by scalar loads)
-  const char* bt_bytes = reinterpret_cast<const char*>(ctrl) + ((long)H->off_bt - (long)H->off_ctrl);
-  auto load_ids = [&]() {
-    ids_copy(bt_bytes, 4u * (unsigned)min(cs.bt + 2 * lane, cs.last), lds_ids);
-    ids_bt = cs.bt;
-    ids_ok = true;
-  };
-  auto stream_start = [&](const NextItem& item) {
+  int* const list = s_ids + wave * kListed;
+  int page_ids = 0;                    // of the stages asked for, one a lane
+  auto list_start = [&](const NextItem& item) {
     cs.left = item.left;
-    cs.base = item.base;
     cs.bt = item.bt;
     cs.last = item.last;
-    ids_ok = false;
+    cs.head = item.head;
   };
-  auto copy_page = [&](int page) {     // slots are handed out round-robin over the whole run
-    block_copy<D>(cs.base + (unsigned long)(unsigned)page * page_bytes, voff,
-                  lds_ring + (cs.count & (RING - 1)) * Smem<D>::kStageBytes);
-    ++cs.count;
-    --cs.left;
-    cs.bt += 2;
-  };
-  // copies what there is room for, as far as the items to come are known
-  auto stream_catch_up = [&]() {
-#pragma unroll 1
-    while (cs.left > 0 && cs.count < cs.limit) {
-      const int n = min(cs.left, cs.limit - cs.count);
-      int page[4];                 // four at a time, so that their latency is paid once
-#pragma unroll
-      for (int i = 0; i < 4; ++i) page[i] = bt[cs.bt + 2 * i];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (i < n) copy_page(page[i]);
-      if (cs.left == 0 && !cs.in_next && next_ok) {
-        cs.in_next = 1;
-        stream_start(nx);
-      }
+  // asks for page ids if there is room for them; the item after the current one follows it as soon as it is known
+  auto list_ask = [&]() {
+    if (cs.left <= 0 && !cs.in_next && next_ok) {
+      cs.in_next = 1;
+      list_start(nx);
+    }
+    if (cs.left > 0 && cs.asked == 0 && cs.listed - cs.count <= kListed - 64) {
+      page_ids = bt[min(cs.bt + 2 * lane, cs.last)];
+      cs.asked = min(cs.left, 64);
+      cs.asked_head = cs.head;
+      cs.left -= cs.asked;
+      cs.bt += 2 * 64;
     }
   };
-  // Block-table entries are read a little past the last page of a request: the second page of a partly filled last stage
-  // (1 entry), and the pages of four stages wherever copies are caught up with (up to the seventh entry behind
-  // the last page).  Those entries name the last page again.
-  static_assert(HFX_BT_PAD >= 7, "entries behind a request's last page that the copy stream may read");
+  // ... and lists them, behind a wait for all loads.  (Entries past the item's last stage are overwritten by the next item's.)
+  auto list_write = [&]() {
+    if (cs.asked > 0) {
+      list[(cs.listed + lane) & (kListed - 1)] = page_ids * Hkv + cs.asked_head;
+      cs.listed += cs.asked;
+      cs.asked = 0;
+    }
+  };
+  // waits until the list reaches `limit`, as far as the items to come are known
+  auto list_until = [&](int limit) {
+    while (cs.listed < limit) {
+      list_ask();
+      if (cs.asked == 0) break;
+      HFX_WAIT_VMCNT(0);
+      list_write();
+    }
+  };
+  auto block_base = [&](int entry) { return pool + (unsigned long)(unsigned)entry * (2 * Smem<D>::kBlockBytes); };
+  auto slot_lds = [&](int stage_no) { return lds_ring + (stage_no & (RING - 1)) * Smem<D>::kStageBytes; };   // slots are handed out round-robin over the whole run
+  // copies the next n stages, all in a row
+  auto copy_stages = [&](int n) {
+#pragma unroll 1
+    for (; n > 0; --n) {
+      block_copy<D>(block_base(uniform(list[cs.count & (kListed - 1)])), voff, slot_lds(cs.count));
+      ++cs.count;
+    }
+  };
   cs.count = 0;
+  cs.listed = 0;
+  cs.asked = 0;
   cs.in_next = 0;
-  stream_start(next_item(it));
 
   // The stage in which the next ticket is asked for and published (the workgroup waits for the reply there:
   // a reply in flight through the stage loop would make the compiler wait for it, and with it for every copy
@@ -1103,16 +1100,31 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   WaveRows wr = wave_rows(it, wave);
   q_load<D>(w.qf, q_rows(it, wr), wr.row0, it.rq.q_len - 1, Hq, n, j);
   int g_st = 0;      // stages multiplied so far, over all items of the run: the ring position
-  cs.limit = RING;
-  stream_catch_up();
+  // The first copies of the run do not wait for a list: their page ids are scalar loads.  Block-table entries are read a little past the last page of a
+  // request, up to the seventh entry behind it; those entries name the last page again.
+  static_assert(HFX_BT_PAD >= 7, "entries behind a request's last page that the copy stream may read");
+  {
+    const NextItem first = next_item(it);
+    list_start(first);
+    cs.limit = RING - 1 + key_wave;
+    const int n0 = min(n_st, cs.limit);
+    int page[RING];
+#pragma unroll
+    for (int i = 0; i < RING; ++i) page[i] = bt[cs.bt + 2 * i];
+#pragma unroll
+    for (int i = 0; i < RING; ++i)
+      if (i < n0) block_copy<D>(block_base(page[i] * Hkv + cs.head), voff, slot_lds(i));
+    cs.count = cs.listed = n0;
+    cs.left -= n0;
+    cs.bt += 2 * n0;
+    list_ask();
+  }
   if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
 
-  // Synchronisation point of the ring: what has been copied so far has landed, everyone's fragment reads
-  // so far are done, and copies may go on up to `limit`.  In the general form the next ticket is asked
-  // for and published and the copy stream catches up or changes items; it also says up to which stage
-  // (event_st) nothing of that kind will happen, so that the short form, two copies, does.
-  int event_st = 0;
-  auto sync_general = [&](int limit) {
+  // Synchronisation point of the ring: what has been copied so far has landed and everyone's fragment reads
+  // so far are done, so that copies may go on up to `limit`; returns how many that are.  The next ticket is asked
+  // for and published here, and the list goes on.
+  auto sync_point = [&](int limit) {
     if (g_st == publish_st || g_st + 1 == publish_st) {
       int reply = 0;
       tickets_reserve(t, reply, ctrl, (int)H->queue_classes);
@@ -1120,15 +1132,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     }
     HFX_WAIT_VMCNT(0);
     ring_barrier();
+    list_write();
+    list_until(limit);
+    list_ask();
     cs.limit = limit;
-    stream_catch_up();
-    if (cs.left > kIdsFrom && (!ids_ok || cs.bt - ids_bt > 64)) load_ids();
-    // the short form copies two stages at stage g if count is g + 3 (values) or g + 4 (keys) there, and must
-    // leave one for the general form to notice the item's end by
-    event_st = cs.count == limit ? g_st + (cs.left > 0 ? (cs.left - 1) / 2 * 2 : 0) + 1 : g_st;
-    if (publish_st > g_st) event_st = min(event_st, publish_st - 1);
-    if (!ids_ok) event_st = g_st;
-    event_st = min(event_st, g_st + ((64 - ((cs.bt - ids_bt) >> 1)) & ~1) + 1);     // ... as far as the ids go
+    return min(limit, cs.listed) - cs.count;
   };
   for (;;) {
     w.l = 0.f;
@@ -1143,9 +1151,9 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     f32x16 s0, s1;
     Weighing wt;
     // the first stage: its scores, their maximum as the reference exponent, and the first half of its weights
-    sync_general(g_st + RING);
-    event_st = g_st - 1;
+    const int due = sync_point(g_st + RING - 1 + key_wave);
     read_keys<D>(frag, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
+    copy_stages(due);
     s0 = first_scores<D>(w, frag);
     read_keys<D>(frag, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
     if (kt + SK - 1 > unmasked_upto) mask_stage(s0, kt);
@@ -1170,18 +1178,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
         pb[1] = wt.fragment(1);
         settle_weights<D>(w, cur, pb, wt.sum(), sl2);
       }
-      if (sync) {
-        if (g_st < event_st) {
-          HFX_WAIT_VMCNT(0);
-          const int* id = ids + ((cs.bt - ids_bt) >> 1);
-          const int id0 = id[0], id1 = id[1];
-          ring_barrier();
-          copy_page(uniform(id0));
-          copy_page(uniform(id1));
-        } else {
-          sync_general(g_st + RING + 1 + key_wave);
-        }
-      }
+      if (sync) copy_stages(sync_point(g_st + RING + 1 + key_wave));
       if (busy) {
         if (kt + 2 * SK - 1 > unmasked_upto) mask_stage(next, kt + SK);
         __builtin_amdgcn_sched_barrier(0);
@@ -1197,27 +1194,23 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       // twice as many they land later, which chunks of few rows wait for (42 of 4 rows behind 5321 on 8/8 heads of 64 97.5 and 92.6,
       // 97 of one row behind 12208 on 24/8 heads 1294 and 1251; 90.7 and 1182 with one burst and the loop before).
       int pairs = 0;
-      if (end_st - g_st >= kPairsFrom && wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto)
-        pairs = uniform(min((int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1, min((event_st - g_st + 1) >> 1, (end_st - g_st) >> 1)));
+      if (end_st - g_st >= kPairsFrom && wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto && cs.asked == 0 && cs.count == g_st + RING - 1 + key_wave)
+        pairs = uniform(min(min((int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1, (cs.listed - cs.count - (cs.left > 0 ? 2 : 0)) >> 1),
+                            ((publish_st > g_st ? min(publish_st - 1, end_st - 1) : end_st - 1) - g_st + 1) >> 1));
       if (pairs > 0) {
-        HFX_WAIT_VMCNT(0);            // the ids
-        const int* id = ids + ((cs.bt - ids_bt) >> 1);
         kt += pairs * (2 * SK);
-        cs.left -= 2 * pairs;
-        cs.bt += 4 * pairs;
 #pragma unroll 1
         do {
           __builtin_amdgcn_sched_barrier(0);
           s1 = scores_phase<D>(w, frag, s0, wt, sl2, slot(g_st), v_lane);
-          const int id0 = id[0], id1 = id[1];
+          const int id0 = list[cs.count & (kListed - 1)], id1 = list[(cs.count + 1) & (kListed - 1)];
           bf16x8 pb[2] = {wt.fragment(0), wt.fragment(1)};
           settle_weights<D>(w, s0, pb, wt.sum(), sl2);
           HFX_WAIT_VMCNT(0);
           ring_barrier();
-          const char* base0 = cs.base + (unsigned long)(unsigned)uniform(id0) * page_bytes;
-          const char* base1 = cs.base + (unsigned long)(unsigned)uniform(id1) * page_bytes;
-          const unsigned lds0 = lds_ring + (cs.count & (RING - 1)) * Smem<D>::kStageBytes;
-          const unsigned lds1 = lds_ring + ((cs.count + 1) & (RING - 1)) * Smem<D>::kStageBytes;
+          const char* base0 = block_base(uniform(id0));
+          const char* base1 = block_base(uniform(id1));
+          const unsigned lds0 = slot_lds(cs.count), lds1 = slot_lds(cs.count + 1);
           __builtin_amdgcn_sched_barrier(0);
           values_phase<D>(w, frag, pb, s1, wt, sl2, slot(g_st + 2), k_lane, [&](int i) {
             if (i < D / 32) piece_copy(base0, voff, lds0, i);
@@ -1231,7 +1224,6 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
           values_phase<D>(w, frag, pb, s0, wt, sl2, slot(g_st + 3), k_lane, NoCopy());
           g_st += 2;
           cs.count += 2;
-          id += 2;
         } while (--pairs > 0);
       }
       if (g_st == end_st) break;
@@ -1269,24 +1261,28 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     }
     const HfxItem item_c = items[t.cur];
     const HfxItem item_n = items[t.nxt < n_items ? t.nxt : t.cur];
+    if (!cs.in_next) list_start(nx);
+    cs.in_next = 0;
+    nx = next_item(item_n);
+    next_ok = t.nxt < n_items && item_n.type == HFX_ITEM_PREFILL;
+    list_ask();
     prefill_store<D>(a, H, it, wr, w, Hq, wave, lane, stage);
     it = item_c;
     wr = wave_rows(it, wave);
-    nx = next_item(item_n);
-    next_ok = t.nxt < n_items && item_n.type == HFX_ITEM_PREFILL;
     set_ticket_points();
     pending = 0;
     if (n_st <= 6) tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
-    cs.in_next = 0;
-    if (cs.left <= 0 && next_ok) {     // the new current item is wholly copied already
-      cs.in_next = 1;
-      stream_start(nx);
-    }
-    stream_catch_up();
     // Q is needed by the next MFMA; waiting for it in so many words also tells the compiler that
     // nothing is in flight when the stage loop is re-entered
     if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
     HFX_WAIT_VMCNT(0);
+    list_write();
+    // the list went no further than the last item, or less far than its first stages: these are waited for
+    if (cs.count < g_st + min(n_st, 2)) {
+      list_until(cs.limit);
+      copy_stages(min(cs.limit, cs.listed) - cs.count);
+      HFX_WAIT_VMCNT(0);
+    }
   }
   __syncthreads();     // every wavefront is done with the ring before the LDS is used for anything else
 }
@@ -1315,7 +1311,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   __shared__ int s_tk[2];
   // result rows on their way out (prefill_store)
   __shared__ __attribute__((aligned(128))) char s_ostage[4 * 2048];
-  __shared__ int s_ids[4 * 64];     // page ids of stages to come (prefill_run)
+  __shared__ int s_ids[4 * kListed];     // blocks of stages to come (prefill_run)
   const HfxHeader* H = &hdr;
   const HfxItem* items = reinterpret_cast<const HfxItem*>(a.desc + H->off_items);
   const int n_items = H->n_items;

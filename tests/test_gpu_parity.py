@@ -176,6 +176,23 @@ def test_queue_counters_of_short_queues(hb, oracle, n):
     assert np.all(hb.parse_desc(step.device_desc.cpu().numpy())["ctrl"] == 0), "control words must be restored to zero"
 
 
+@pytest.mark.parametrize("Hkv,D", [(1, 64), (2, 128)])
+def test_copy_stream_over_items_of_all_lengths(hb, oracle, Hkv, D):
+    """Items of 1 to 130 stages of 32 keys behind each other in every workgroup, in an order in which long ones follow short ones: around the 64 page ids
+    that are asked for at once and the 128 that are kept, and the four stages of the ring."""
+    rng = np.random.default_rng(7 * D + Hkv)
+    stages = np.array([1, 1, 1, 2, 3, 4, 5, 6, 7, 8, 9, 31, 62, 63, 64, 65, 66, 67, 68, 69, 70, 127, 128, 129, 130])
+    n = 1300 // Hkv
+    q = rng.integers(1, 6, n)
+    c = rng.permutation(np.resize(stages, n)) * 32 - rng.integers(0, 28, n)
+    b = small_pool_batch(rng, 4 * Hkv, Hkv, D, [PREFILL] * n, q, np.maximum(c, q), f"copy-stream-{Hkv}-{D}")
+    step, bits = check_full(hb, oracle, b)
+    assert hb.parse_desc(step.host_desc.numpy())["header"].n_items > 1024
+    step.out.zero_()
+    step.run()
+    assert np.array_equal(step.out_bits(), bits)
+
+
 @pytest.mark.parametrize("decodes", [0, 3])
 @pytest.mark.parametrize("Hq,Hkv,D", [(24, 8, 128), (32, 4, 64), (8, 8, 128), (16, 1, 128)])
 def test_chunks_of_a_few_rows_in_pieces(hb, oracle, Hq, Hkv, D, decodes):
