@@ -632,13 +632,18 @@ __device__ __forceinline__ void piece_copy(const char* base, unsigned voff, unsi
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
                :: "v"(voff), "s"(base), "s"(lds), "n"(piece * 1024) : "memory", "m0");
 }
+// Numbers `piece` and piece + 1.
+__device__ __forceinline__ void two_pieces_copy(const char* base, unsigned voff, unsigned lds, int piece) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4"
+               :: "v"(voff), "s"(base), "s"(lds), "n"(piece * 1024), "n"(piece * 1024 + 1024) : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // A whole block.
 template <int D>
 __device__ __forceinline__ void block_copy(const char* base, unsigned voff, unsigned lds) {
 #pragma unroll
-  for (int piece = 0; piece < D / 32; ++piece) piece_copy(base, voff, lds, piece);
+  for (int piece = 0; piece < D / 32; piece += 2) two_pieces_copy(base, voff, lds, piece);
 }
 
 // Workgroup barrier of the ring: this wavefront's LDS reads are done.  The compiler may move loads across
