@@ -310,7 +310,8 @@ class DescHeader(ctypes.Structure):
                 ("ws_off_ml", ctypes.c_uint64), ("max_group_rows", ctypes.c_int32),
                 ("n_units", ctypes.c_int32), ("off_units", ctypes.c_uint32), ("n_runs", ctypes.c_int32),
                 ("off_runs", ctypes.c_uint32), ("queue_classes", ctypes.c_uint32),
-                ("deal_balanced", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
+                ("deal_balanced", ctypes.c_uint32), ("off_queue", ctypes.c_uint32),
+                ("die_items", ctypes.c_uint32), ("reserved", ctypes.c_uint32)]
 
 
 ITEM_DTYPE = np.dtype([(n, np.int32) for n in ("type", "req", "group", "slot_row", "h0", "hn", "row0", "nrows",
@@ -332,6 +333,8 @@ def parse_desc(host_desc: np.ndarray) -> dict:
         "reqs": buf[h.off_req:h.off_req + REQ_DTYPE.itemsize * h.num_requests].view(REQ_DTYPE),
         "bt": buf[h.off_bt:h.off_bt + 4 * h.n_bt].view(np.int32),
         "items": buf[h.off_items:h.off_items + ITEM_DTYPE.itemsize * h.n_items].view(ITEM_DTYPE),
+        # the items in the order in which they are taken, where that is not their own
+        "queue": buf[h.off_queue:h.off_queue + 4 * h.n_items].view(np.int32) if h.off_queue else None,
         "groups": buf[h.off_groups:h.off_groups + GROUP_DTYPE.itemsize * h.n_groups].view(GROUP_DTYPE),
         "units": buf[h.off_units:h.off_units + 8 * h.n_units].view(np.int32).reshape(-1, 2),
         # append runs: (first packed row, tokens, physical page, first slot)

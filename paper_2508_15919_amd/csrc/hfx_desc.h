@@ -16,8 +16,9 @@
 
 // Control words, each on a line of its own: atomics on one line from all over the chip are served one after the other.
 #define HFX_CTRL_TICKETS(c) ((c) * 32)                          /* tickets of class c handed out past the two dealt to each workgroup by index */
+#define HFX_CTRL_SHARED ((2 * HFX_QUEUE_CLASSES + 1) * 32)      /* tickets for the positions that belong to no class */
 #define HFX_CTRL_DONE(c) ((HFX_QUEUE_CLASSES + (c)) * 32)       /* finished workgroups of class c; c == HFX_QUEUE_CLASSES: finished classes */
-#define HFX_CTRL_WORDS ((2 * HFX_QUEUE_CLASSES + 1) * 32)
+#define HFX_CTRL_WORDS ((2 * HFX_QUEUE_CLASSES + 2) * 32)
 
 #define HFX_STATIC_WS_BYTES (64u << 20) /* fixed workspace of the entry point that allocates nothing */
 #define HFX_MAX_DEVICES 64
@@ -42,8 +43,10 @@ struct HfxHeader {
   uint32_t off_units;
   int32_t n_runs;               /* append runs: the new tokens of the step, cut at page boundaries */
   uint32_t off_runs;
-  uint32_t queue_classes;       /* 1 or HFX_QUEUE_CLASSES: how many classes the queue positions past the dealt ones fall into */
+  uint32_t queue_classes;       /* HFX_QUEUE_CLASSES where the items themselves lie die by die (see `home`), else 1 */
   uint32_t deal_balanced;       /* the two dealt rounds pair large items with small ones (see the kernel) instead of running straight */
+  uint32_t off_queue;           /* 0: queue position p is item p; else n_items item indices, by position */
+  uint32_t die_items;           /* of the queue positions, the first die_items belong to dies, p to die p % HFX_QUEUE_CLASSES, and those behind to all */
   uint32_t reserved;
 };
 

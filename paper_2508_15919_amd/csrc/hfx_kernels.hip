@@ -238,6 +238,8 @@ struct Tickets {
   int cur, nxt;
   int parity;
   bool queue;        // there may be items behind the next one
+  bool own;          // ... and among them some for this die (first wavefront)
+  const int* order;  // queue position -> item, if the queue does not hold the items in their order
 };
 
 // The dealt tickets of a step whose queue is in descending cost.  Workgroups b and b + 256 share a CU, so
@@ -261,60 +263,47 @@ __device__ __forceinline__ void deal_balanced(Tickets& t, int mode, int n_items)
   }
 }
 
-// Queue positions past the dealt ones fall into `nc` classes (1 or HFX_QUEUE_CLASSES, the
-// planner's choice per step), position p into class p % nc, each with a counter of its own, and a
-// workgroup asks the counter of the class of its index.  Workgroups are placed on the chip's dies
-// round-robin by index, so with HFX_QUEUE_CLASSES classes a class is served by the workgroups of
+// Queue positions past the dealt ones, up to die_items, fall into HFX_QUEUE_CLASSES classes, position p into class
+// p % HFX_QUEUE_CLASSES, each with a counter of its own; those behind are shared.  A workgroup asks the counter of the class of its index and, once that class
+// is empty, the shared one.  Workgroups are placed on the chip's dies round-robin by index, so a class is served by the workgroups of
 // one die, and the planner puts items that read the same keys into one class: they then share
-// that die's L2.
+// that die's L2.  The shared end of the queue, the smallest items, is what lets the dies end together.  Without die_items all positions are shared.
 //
 // What bounds the counters: atomics and atomic loads on one line from all over the chip are served one after the other, 14 ns
-// each.  With all of them on one line, and every workgroup reading the eight of them one by one whenever its class was empty, the end
-// of a step with classes took 40 to 90 us, whatever the step: 17 short prompts of each of six tasks 87 us from one queue and 185 with classes.
-// Now each has a line of its own, a look at all eight is one load, a workgroup that knows the queue to be empty asks no more, and workgroups report
-// their end by class: 83 and 86 us; the prefill-heavy mixed step, which has classes, 858 -> 818; 58 short prompts of each of six
-// tasks on 64-wide heads, one queue, 190 -> 186.
+// each.  With all counters on one line, and every workgroup whose class was empty reading the eight of them one by one to find work elsewhere, the end
+// of a step with classes took 40 to 90 us, whatever the step (17 short prompts of each of six tasks 87 us from one queue and 185 with classes);
+// with a line each, and one load for all eight, still 4 to 6 us, which the shared end does not cost (31 short prompts on 8/1 heads 46 us and 40).
+// A workgroup that knows the queue to be empty asks no more, and workgroups report their end by class.  The prefill-heavy mixed step, which has classes,
+// took 858 us before and 818 after.
 //
-// Thread 0 asks its class's counter for one more ticket; the reply, an offset from the dealt
-// tickets, goes to tickets_publish.  The other lanes keep what `pending` held: a select on it would
+// Thread 0 asks for one more ticket; the reply, an offset from the dealt tickets or from the shared positions, goes to
+// tickets_publish.  The other lanes keep what `pending` held: a select on it would
 // wait for the reply, and with it for everything in flight, wherever the compiler places it.
-__device__ __forceinline__ void tickets_reserve(const Tickets& t, int& pending, int* ctrl, int nc) {
-  if (t.queue && threadIdx.x == 0) pending = atomicAdd(ctrl + HFX_CTRL_TICKETS((int)blockIdx.x & (nc - 1)), 1);
+__device__ __forceinline__ void tickets_reserve(const Tickets& t, int& pending, int* ctrl) {
+  if (!t.queue) return;
+  int word = t.own ? HFX_CTRL_TICKETS((int)blockIdx.x & (HFX_QUEUE_CLASSES - 1)) : HFX_CTRL_SHARED;
+  asm volatile("" : "+s"(word));      // (the address is formed here and not kept in vector registers)
+  if (threadIdx.x == 0) pending = atomicAdd(ctrl + word, 1);
 }
-// Thread 0 puts the reserved ticket into LDS (two slots alternate, so one barrier per hand-over is
-// enough).  A reply past the end of the queue means the workgroup's class is empty.  Its first wavefront then reads
-// all counters (one load, a lane each) and asks the class that has most positions left for one, so
-// that a die that finishes early helps the others; when other workgroups got there first (the
-// reply is past the end again) it looks again, a few times.  Giving up early costs balance, not
-// correctness: every class is drained by its own workgroups whether or not others help.
-constexpr int kStealAttempts = 4;
-__device__ __forceinline__ void tickets_publish(const Tickets& t, int pending, int* s_tk, int* ctrl, int n_items, int nc) {
-  if (!t.queue || threadIdx.x >= 64) return;
-  const int base = kDealtTickets * (int)gridDim.x;
-  int pos = base + uniform(pending) * nc + ((int)blockIdx.x & (nc - 1));
-  if (nc > 1 && pos >= n_items) {
-    // (formed here and not at the start of every workgroup)
-    int k = (int)threadIdx.x & (HFX_QUEUE_CLASSES - 1), behind = n_items - base;
-    asm volatile("" : "+v"(k), "+s"(behind));
-    for (int attempt = 0; attempt < kStealAttempts && pos >= n_items; ++attempt) {
-      const int taken = __hip_atomic_load(ctrl + HFX_CTRL_TICKETS(k), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // positions base + r * classes + k below n_items with r >= taken
-      const int left = (behind - k + HFX_QUEUE_CLASSES - 1) / HFX_QUEUE_CLASSES - taken;
-      int best = 0, best_left = 0;
-#pragma unroll
-      for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) {
-        const int l = __builtin_amdgcn_readlane(left, c);
-        if (l > best_left) {
-          best_left = l;
-          best = c;
-        }
-      }
-      if (best_left <= 0) break;
-      int reply = 0;
-      if (threadIdx.x == 0) reply = atomicAdd(ctrl + HFX_CTRL_TICKETS(best), 1);
-      pos = base + uniform(reply) * HFX_QUEUE_CLASSES + best;
+// The first wavefront turns the reply into an item and thread 0 puts it into LDS (two slots alternate, so one barrier per hand-over is
+// enough).
+__device__ __forceinline__ void tickets_publish(Tickets& t, int pending, int* s_tk, int* ctrl, const HfxHeader* H) {
+  if (!t.queue || uniform((int)threadIdx.x >> 6) != 0) return;
+  const int dealt = kDealtTickets * (int)gridDim.x, die_items = (int)H->die_items, shared = max(dealt, die_items);
+  int pos = uniform(pending);
+  if (t.own) {
+    pos = dealt + pos * HFX_QUEUE_CLASSES + ((int)blockIdx.x & (HFX_QUEUE_CLASSES - 1));
+    if (pos >= die_items) {
+      t.own = false;
+      int word = HFX_CTRL_SHARED, reply = 0;
+      asm volatile("" : "+s"(word));
+      if (threadIdx.x == 0) reply = atomicAdd(ctrl + word, 1);
+      pos = shared + uniform(reply);
     }
+  } else {
+    pos += shared;
   }
+  if (t.order && pos < H->n_items) pos = t.order[pos];
   if (threadIdx.x == 0) s_tk[t.parity] = pos;
 }
 // ... after a workgroup barrier that follows tickets_publish.  Counters only grow: once a ticket is past the end, so are all later ones.
@@ -478,7 +467,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     // page ids are fetched one pair ahead of the KV loads that need them
     while (pp < pe) {
       if (!reserved && pp + 4 * step >= pe) {   // a few pairs before the end (thread 0 sits in the first wavefront, which always has pairs)
-        tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
+        tickets_reserve(t, pending, ctrl);
         reserved = true;
       }
       if (pp + step < pe) decode_load<D>(r1, a.pool, b0, b1, Hkv, g, k_sel, k_off, v_sel, v_off);
@@ -508,7 +497,7 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
     // The reply to the ticket request has come back in front of the last pairs' loads (returns
     // are in order), so publishing it here waits for nothing; after the requests below it would
     // wait for them.  The barriers of the epilogue stand between this write and its readers.
-    tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
+    tickets_publish(t, pending, s_tk, ctrl, H);
     // both register sets and the Q operand are free now: start on the next item
     if (carry_on) {
       if (dn.pp < dn.pe) decode_load<D>(r0, a.pool, dn.a0, dn.a1, Hkv, dn.g, k_sel, k_off, v_sel, v_off);
@@ -1099,7 +1088,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   };
   set_ticket_points();
   int pending = 0;
-  if (n_st <= 6) tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
+  if (n_st <= 6) tickets_reserve(t, pending, ctrl);
 
   PrefillWave<D> w;
   WaveRows wr = wave_rows(it, wave);
@@ -1124,7 +1113,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     cs.bt += 2 * n0;
     list_ask();
   }
-  if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
+  if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, H);
 
   // Synchronisation point of the ring: what has been copied so far has landed and everyone's fragment reads
   // so far are done, so that copies may go on up to `limit`; returns how many that are.  The next ticket is asked
@@ -1132,8 +1121,8 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   auto sync_point = [&](int limit) {
     if (g_st == publish_st || g_st + 1 == publish_st) {
       int reply = 0;
-      tickets_reserve(t, reply, ctrl, (int)H->queue_classes);
-      tickets_publish(t, reply, s_tk, ctrl, n_items, (int)H->queue_classes);
+      tickets_reserve(t, reply, ctrl);
+      tickets_publish(t, reply, s_tk, ctrl, H);
     }
     HFX_WAIT_VMCNT(0);
     ring_barrier();
@@ -1276,10 +1265,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     wr = wave_rows(it, wave);
     set_ticket_points();
     pending = 0;
-    if (n_st <= 6) tickets_reserve(t, pending, ctrl, (int)H->queue_classes);
+    if (n_st <= 6) tickets_reserve(t, pending, ctrl);
     // Q is needed by the next MFMA; waiting for it in so many words also tells the compiler that
     // nothing is in flight when the stage loop is re-entered
-    if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, n_items, (int)H->queue_classes);
+    if (n_st <= 6) tickets_publish(t, pending, s_tk, ctrl, H);
     HFX_WAIT_VMCNT(0);
     list_write();
     // the list went no further than the last item, or less far than its first stages: these are waited for
@@ -1324,6 +1313,13 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   t.cur = (int)blockIdx.x;
   t.nxt = (int)(blockIdx.x + gridDim.x);
   if (hdr.deal_balanced) deal_balanced(t, (int)hdr.deal_balanced, n_items);
+  t.order = nullptr;
+  if (H->off_queue) {
+    t.order = reinterpret_cast<const int*>(a.desc + H->off_queue);
+    if (t.cur < n_items) t.cur = t.order[t.cur];
+    if (t.nxt < n_items) t.nxt = t.order[t.nxt];
+  }
+  t.own = (int)H->die_items > kDealtTickets * (int)gridDim.x;
   t.parity = 0;
   t.queue = n_items > kDealtTickets * (int)gridDim.x;
   while (t.cur < n_items) {
@@ -1346,6 +1342,7 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
         atomicExch(ctrl + HFX_CTRL_TICKETS(c), 0);
         atomicExch(ctrl + HFX_CTRL_DONE(c), 0);
       }
+      atomicExch(ctrl + HFX_CTRL_SHARED, 0);
       atomicExch(ctrl + HFX_CTRL_DONE(HFX_QUEUE_CLASSES), 0);
     }
   }
@@ -1586,6 +1583,7 @@ hipError_t launch_mixed_attention(const HfxHeader& h, int grid, void* desc, cons
                                   void* out, hipStream_t stream) {
   const int head_dim = h.head_dim, n_units = h.n_units;
   HfxHeader hk = h;          // as the kernel gets it: how the first tickets are dealt also depends on the grid
+  if (grid != HFX_PLAN_WGS) hk.die_items = 0;      // every class needs its workgroups
   if (h.deal_balanced)
     hk.deal_balanced = grid == HFX_PLAN_WGS ? 1u : grid > HFX_PLAN_WGS / 2 && grid == h.n_items ? 2u : 0u;
   const char* d = static_cast<const char*>(desc);

@@ -17,22 +17,19 @@ static const double kDecodeBytesPerNs = 12.0;
 static const double kPrefillFlopsPerNs = 2000.0;
 static const double kPrefillFlopsPerNs64 = 1400.0;   // 64-wide heads: twice the exponentials per MFMA
 static const double kMinItemNs = 32000.0;
+static const double kItemNs = 3000.0;      // of a prefill item, besides its keys
 static const int kMinDecodeTokens = 128;
 static const int kMinPrefillKeys = 256;
 static const int kMaxSplits = 64;
 static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of D + 2 floats per q-head)
-// Which prefill-dominated steps get a queue per die (see the queue order in plan_step), by items per
+// Which prefill-dominated steps have their items laid out die by die (see the queue order in plan_step), by items per
 // workgroup of the planning width and by the time of the step.  What it buys is HBM traffic: 0.6 instead of 1.06 GB on the
-// prefill-heavy mixed step.  What it costs is that the dies end at different times and that in the first rounds
-// all workgroups of a die start together, so that those that read the same keys move in step and every cache line is
-// a first touch for all of them at once: 40 to 80 us a step.  Prompts of 128-wide heads in four to eight rounds, with
-// classes over without (28 steps): 1.24 to 1.38 at 230 to 320 us of modelled time, 1.08 to 1.20 at 420 to 600, 1.03 to 1.08 at 870 to
-// 1100 and 1.00 to 1.06 at 1200 to 2100; three rounds (6144 tokens) 1.17, 17 short prompts of each of six tasks 1.45.  64-wide
-// heads, with half the bytes a key and less to save, lose more (three prompts of 7993, 4771 and 706 1.13).  All of these have keys that fit
-// the last-level cache (256 MB).  With far more keys than that, each read by two items or more, a queue per die is the better one
-// again, as far as the items are long (kMinItemNs, by the (row, key) pairs they work on): 105 chunks of 64 rows behind 8500 to 34009 on 64-wide
-// 24/8 heads 0.90; with the prefill loop before its whole pairs 20 steps of 85 to 260 chunks of 33 or 64 rows on 1.3 to
-// 6 GB of keys 0.9 to 1.01.  (Not where no two items share keys: 15 steps, 1.0 to 1.09.)
+// prefill-heavy mixed step.  It costs no time any more: 17 steps of one to four prompts in two to six rounds, classes over one queue
+// 0.97 to 1.02, the prefill-heavy step 813 and 815 us.  (While the counters were on one line it cost 40 to 80 us a step, 1.03 to 1.45 times, and the lines
+// were drawn by that; nothing is gained by moving them.  Steps of many prompts are under queue_per_die.)  With far more keys than the
+// last-level cache (256 MB) holds, each read by two items or more, a queue per die was the better one even then,
+// as far as the items are long (kMinItemNs, by the (row, key) pairs they work on): 105 chunks of 64 rows behind 8500 to 34009 on 64-wide
+// 24/8 heads 0.90.
 static const int kClassRoundsMin = 4;
 static const double kClassStepNs = 800000.0;
 static const double kClassStreamBytes = 1e9;
@@ -41,8 +38,8 @@ static const double kClassStreamBytes = 1e9;
 // (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
 // 22937 tokens on 24/8 heads 2775 us without classes, 1973 with; 97 of one row behind 12208, 1625 and 1253.  The ratio is
 // 1.9 with one busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in
-// the cache.  The gain holds from three rounds and about 2100 keys an item on: 90 steps of 50 to 96 us an item took, with
-// classes over without, 0.89 to 1.14 below 64 us, 0.81 to 0.97 from 70 to 80, 0.76 to 0.96 above.
+// the cache.  The gain held from three rounds and about 2100 keys an item on (90 steps, with the counters on one line); below that, queue_per_die
+// takes over.
 static const int kClassRoundsMinApart = 3;
 static const double kClassApart = 1.5;
 static const double kClassItemNsApart = 70000.0;
@@ -255,7 +252,7 @@ static double prefill_cap(const int32_t* kind, const int32_t* q_len, const int32
         count += nsplit * mult;
         if (nsplit > 1) pieces += nsplit * mult;
         if (list) {
-          const double one = ns / (double)nsplit + 3000.0;
+          const double one = ns / (double)nsplit + kItemNs;
           const double busy = idle_waves ? tile_busy(hpw, r1 - (int64_t)rt * rows_wg) : 1.0;
           piece = std::max(piece, one);
           cost.insert(cost.end(), (size_t)nsplit, (float)(one * (kLoneShare + (1.0 - kLoneShare) * busy)));
@@ -487,8 +484,8 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
   Plan& P = *out;
   P.items.clear();
   P.groups.clear();
-  P.item_unit.clear();
-  P.item_frac.clear();
+  P.notes.clear();
+  P.n_decode_items = 0;
   int64_t rows = 0, dec_rows = 0;
   std::vector<int32_t>& split_cost = P.split_cost;
   int64_t pre_ord = 0;              // prefill requests seen so far
@@ -517,6 +514,7 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
           HfxGroup gr = {nsplit, (int32_t)rows, ngc * G, HFX_ITEM_DECODE, r, g0, ngc, 0, q.q_start, q.q_len};
           P.groups.push_back(gr);
         }
+        P.n_decode_items += nsplit;
         for (int s = 0; s < nsplit; ++s) {
           HfxItem it = proto;
           it.group = group;
@@ -528,8 +526,7 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
           it.cost = clamp_cost((double)toks * ns_per_token + 2000.0);
           it.home = -1;
           P.items.push_back(it);
-          P.item_unit.push_back(kNoUnit);
-          P.item_frac.push_back(0.f);
+          P.notes.push_back(ItemNote{(uint32_t)it.cost, kNoUnit, 0.f});
         }
         if (nsplit > 1) {
           rows += (int64_t)nsplit * ngc * G;
@@ -547,8 +544,9 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
         split_cost.resize((size_t)nsplit);
         for (int64_t s = 0; s < nsplit; ++s) {
           const int64_t kb = s * tiles_per * HFX_KEY_TILE, ke = std::min<int64_t>(kmax, (s + 1) * tiles_per * HFX_KEY_TILE);
-          split_cost[(size_t)s] = clamp_cost(tile_ns(D, ke - kb) + 3000.0);
+          split_cost[(size_t)s] = clamp_cost(tile_ns(D, ke - kb) + kItemNs);
         }
+        const float frac = (float)rt / (float)n_rt;
         HfxItem proto;                // what all items of the row tile share
         std::memset(&proto, 0, sizeof proto);
         proto.type = HFX_ITEM_PREFILL;
@@ -577,8 +575,7 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
               P.items.push_back(it);
               // the row tiles and head blocks that read the s-th piece of the keys of (request, kv-head)
               const int64_t unit = (pre_ord * Hkv + g) * kMaxSplits + s;
-              P.item_unit.push_back(unit < (int64_t)kNoUnit ? (uint32_t)unit : kNoUnit);
-              P.item_frac.push_back((float)rt / (float)n_rt);
+              P.notes.push_back(ItemNote{(uint32_t)it.cost, unit < (int64_t)kNoUnit ? (uint32_t)unit : kNoUnit, frac});
             }
             if (nsplit > 1) rows += nsplit * 4 * HFX_WAVE_ROWS;
           }
@@ -587,10 +584,122 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
     }
     if (rows > 0x7fffffff / 2 || P.items.size() > 0x3fffffffu) return HFX_ERR_LEN;
   }
+  P.n_prefill_items = (int32_t)P.items.size() - P.n_decode_items;
   *rows_out = rows;
   *dec_rows_out = dec_rows;
   *pre_ord_out = pre_ord;
   return HFX_OK;
+}
+
+// The order in which the items of a step of many prompts are taken, where that is not their own (descending cost).
+//
+// Row tiles and head blocks of one (request, kv-head) read the same keys.  In a step of many prompts the 64 workgroups of a die work on as many different ones
+// at a time, the tiles of one meet on a die by chance only, and every tile fetches its keys again: 1.79 GB fetched for 0.65 GB of keys, Q and
+// decodes in a step of 384 short requests, 6.9 TB/s with the results, at a matrix rate of a third and at any core clock the same time.
+// So the items of a unit go to one die, one behind the other, units in the order of their largest item: 0.73 GB, 304 -> 272 us.  The
+// last prompts of the queue are the shortest ones, so that the dies end close to each other, and what is left is for all (kSharedTail).
+//
+// Measured on random steps, over one queue for all.  A workgroup's share at least 1.5 times the longest item: 50 steps of 80 streams
+// ((request, kv-head) pairs) or more 1.06 times as fast on average, the slowest 1.00; 14 of 40 to 79 streams 1.03 (0.99 to 1.07); 12 of fewer streams 1.00 (0.985
+// to 1.03: one prompt's tiles on all dies share their keys as it is).  A share of 0.75 to 1.5 of the longest item and at least 160 streams 1.02 (0.97 to
+// 1.07; 0.94 to 1.0 where decodes are more than a fifth of the step).  Chunks of a few rows whose head blocks share keys gain
+// most: 59 of 1 to 2 rows behind 2600 to 7700 on 24/8 heads 451 us and 285.
+static const int64_t kDieStreams = 32, kDieStreamsShort = 160;
+static const double kDieShare = 1.5, kDieShareShort = 0.75, kDieDecodes = 0.2;
+// A unit is at most this part of a die's share of the step: a longer one is cut into consecutive row tiles.  (2: 1.026 over the steps that 16 to 128 take 1.039 to
+// 1.044 over.)
+static const int kDieUnits = 32;
+// The share of a step's cost at the end of the queue that is handed out to all dies.  (3, 6, 12 and 25 %: 1.024, 1.023, 1.015 and 1.018 over 21 steps of
+// short prompts; the prefill-heavy mixed step the same within 1 %.)
+static const double kSharedTail = 0.06;
+
+// `sorted`: the n items in descending cost, as keys of plan_step's sort (max_cost minus cost, index); P.stream_ns: time of the items of each stream
+// of each request with a prompt; all: that of all items.
+static void queue_per_die(const uint64_t* sorted, size_t n, int Hkv, double all, Plan* out) {
+  Plan& P = *out;
+  struct Stream {
+    uint32_t first, pieces;      // its pieces
+    double work;                 // of one of them
+  };
+  static_assert(sizeof(Stream) == 2 * sizeof(uint64_t), "kept in unit_keys");
+  const double most = all / (kDieUnits * HFX_QUEUE_CLASSES);
+  std::vector<uint64_t>& store = P.unit_keys;
+  store.resize(2 * P.stream_ns.size() * (size_t)Hkv);
+  Stream* const streams = reinterpret_cast<Stream*>(store.data());
+  uint32_t n_pieces = 0;
+  for (size_t r = 0, st = 0; r < P.stream_ns.size(); ++r) {
+    const double pieces = std::min(std::max(std::ceil(P.stream_ns[r] / most), 1.0), 1024.0);
+    for (int g = 0; g < Hkv; ++g, ++st, n_pieces += (uint32_t)pieces) streams[st] = Stream{n_pieces, (uint32_t)pieces, P.stream_ns[r] / pieces};
+  }
+  // In the order of the items: a piece that is met for the first time goes to the die with the least work so far, behind that die's
+  // other pieces.  A decode item is a piece of its own.
+  std::vector<uint32_t>& count = P.unit_fill;            // items of a piece
+  std::vector<uint32_t>& place = P.unit_start;           // die of a piece; then the position of its next item
+  std::vector<uint32_t>& piece_of = P.order_pre;         // of the i-th item
+  count.assign(n_pieces + n, 0);
+  place.resize(n_pieces + n);
+  piece_of.resize(n);
+  static_assert(HFX_QUEUE_CLASSES == 8, "loads compared below");
+  double load[HFX_QUEUE_CLASSES] = {0.0};
+  std::vector<uint32_t>* lists = P.die_lists;            // pieces of each die
+  for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) lists[c].clear();
+  for (size_t i = 0; i < n; ++i) {
+    const ItemNote& note = P.notes[(uint32_t)sorted[i]];
+    uint32_t piece;
+    double work;
+    if (note.unit != kNoUnit) {
+      const Stream& st = streams[note.unit / kMaxSplits];
+      piece = st.first;
+      if (st.pieces > 1) piece += std::min(st.pieces - 1, (uint32_t)(note.frac * (float)st.pieces));
+      work = st.work;
+    } else {
+      piece = n_pieces++;
+      work = note.cost;
+    }
+    piece_of[i] = piece;
+    if (count[piece]++) continue;
+    // (a chain of eight comparisons, each waiting for the one before, was two thirds of this function's time)
+    const double least = std::min(std::min(std::min(load[0], load[1]), std::min(load[2], load[3])),
+                                  std::min(std::min(load[4], load[5]), std::min(load[6], load[7])));
+    unsigned mask = 0;
+    for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) mask |= (unsigned)(load[c] == least) << c;
+    const int home = __builtin_ctz(mask);
+    load[home] += work;
+    lists[home].push_back(piece);
+  }
+  size_t end[HFX_QUEUE_CLASSES];
+  for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) {
+    size_t at = (size_t)c;
+    for (const uint32_t piece : lists[c]) {
+      place[piece] = (uint32_t)at;
+      at += (size_t)HFX_QUEUE_CLASSES * count[piece];
+    }
+    end[c] = at;
+  }
+  // position p is for die p % HFX_QUEUE_CLASSES; when a die's list ends, its positions take what is left of the longer ones
+  std::vector<uint32_t>& left = P.order_dec;
+  left.clear();
+  P.queue.resize(n);
+  for (size_t i = 0; i < n; ++i) {
+    const uint32_t at = place[piece_of[i]];
+    place[piece_of[i]] = at + HFX_QUEUE_CLASSES;
+    if (at < n) P.queue[at] = (int32_t)i;
+    else left.push_back((uint32_t)i);
+  }
+  for (int c = 0; c < HFX_QUEUE_CLASSES; ++c)
+    for (size_t at = end[c]; at < n; at += HFX_QUEUE_CLASSES) {
+      P.queue[at] = (int32_t)left.back();
+      left.pop_back();
+    }
+}
+
+// How many of the positions of a queue per die are handed out by die; cost(p) is that of position p, all that of all n.
+template <typename F>
+static int32_t positions_by_die(size_t n, double all, F cost) {
+  double behind = 0.0;
+  size_t at = n;
+  while (at > 0 && behind + cost(at - 1) <= kSharedTail * all) behind += cost(--at);
+  return (int32_t)(at / HFX_QUEUE_CLASSES * HFX_QUEUE_CLASSES);
 }
 
 hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
@@ -607,6 +716,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
 
   Plan& P = *out;
   P.reqs.assign((size_t)R, HfxReq());
+  P.stream_ns.clear();
   int64_t T = 0, nbt = 0, n_dec = 0, dec_tokens = 0;
   double dec_ns = 0.0, pre_ns = 0.0;   // modelled time of each kind of work, prefill by (row, key) pairs
   double stream_ns = 0.0;              // the prefills' keys streamed once, at the rate of decodes ...
@@ -645,6 +755,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       streams += Hkv;
       readers += (full + (rest ? 1 : 0)) * mult;
       tiles_ns += full_ns + rest_ns;
+      P.stream_ns.push_back((full_ns + rest_ns + kItemNs * (double)((full + (rest ? 1 : 0)) * mult)) / Hkv);
       beside_ns += full_ns + rest_ns * (kLoneShare + (1.0 - kLoneShare) * tile_busy(hpw, rest));
     }
   }
@@ -699,10 +810,10 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     // keys count down from the largest cost, so that the number of digit passes follows the range
     // of costs in the step and not the width of the field
     uint32_t max_cost = 0;
-    for (size_t i = 0; i < n; ++i) max_cost = std::max(max_cost, (uint32_t)P.items[i].cost);
+    for (size_t i = 0; i < n; ++i) max_cost = std::max(max_cost, P.notes[i].cost);
     uint32_t top = 0;
     for (size_t i = 0; i < n; ++i) {
-      const uint32_t inv = max_cost - (uint32_t)P.items[i].cost;
+      const uint32_t inv = max_cost - P.notes[i].cost;
       a[i] = ((uint64_t)inv << 32) | (uint64_t)i;
       top |= inv;
     }
@@ -722,6 +833,9 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     std::vector<uint32_t>& order = P.order;
     order.resize(n);
     P.queue_classes = 1;
+    P.queue.clear();
+    P.die_items = 0;
+    auto cost_of = [&](size_t i) { return (double)(max_cost - (uint32_t)(a[i] >> 32)); };     // of the i-th in descending cost
     P.deal_balanced = !(decode_dominated && pre_ns > 0.0);   // the layout below is by workgroup
     if (decode_dominated && pre_ns > 0.0) {
       // A step whose decode work outweighs its prefill work.  The first two items of workgroup b
@@ -788,8 +902,8 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       ucost.assign(n_slots, 0);
       int64_t all_cost = 0;
       for (size_t i = 0; i < n; ++i) {
-        all_cost += P.items[i].cost;
-        if (P.item_unit[i] != kNoUnit) ucost[P.item_unit[i]] += P.items[i].cost;
+        all_cost += P.notes[i].cost;
+        if (P.notes[i].unit != kNoUnit) ucost[P.notes[i].unit] += P.notes[i].cost;
       }
       const int64_t sub_cost = std::max<int64_t>(1, all_cost / (2 * HFX_QUEUE_CLASSES));
       ufill.assign(n_slots, 0);     // sub-units of the slot
@@ -803,15 +917,15 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         }
       // decode items (and anything else without a unit) get singleton units behind those
       for (size_t i = 0; i < n; ++i) {
-        const uint32_t u = P.item_unit[i];
-        if (u == kNoUnit) P.item_unit[i] = (uint32_t)n_units++;
-        else P.item_unit[i] = ustart[u] + std::min<uint32_t>(ufill[u] - 1, (uint32_t)(P.item_frac[i] * (float)ufill[u]));
+        const uint32_t u = P.notes[i].unit;
+        if (u == kNoUnit) P.notes[i].unit = (uint32_t)n_units++;
+        else P.notes[i].unit = ustart[u] + std::min<uint32_t>(ufill[u] - 1, (uint32_t)(P.notes[i].frac * (float)ufill[u]));
       }
       ucost.assign(n_units, 0);     // total cost of the unit; once it has a home, the home
       ustart.assign(n_units, 0);    // items in the unit
       for (size_t i = 0; i < n; ++i) {
-        const uint32_t u = P.item_unit[i];
-        ucost[u] += P.items[i].cost;
+        const uint32_t u = P.notes[i].unit;
+        ucost[u] += P.notes[i].cost;
         ustart[u]++;
       }
       // home classes: units by descending total cost (36 bits of it, saturating; the low 28 bits
@@ -836,7 +950,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       for (int c = 0; c < HFX_QUEUE_CLASSES; ++c) tail[c] = 0;
       for (size_t i = 0; i < n; ++i) {
         const uint32_t idx = (uint32_t)(a[i] & 0xffffffffu);
-        const int home = (int)ucost[P.item_unit[idx]];
+        const int home = (int)ucost[P.notes[idx].unit];
         P.items[idx].home = home;
         tail[home]++;
       }
@@ -859,8 +973,16 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
           order[o] = (uint32_t)(a[--tail[from]] & 0xffffffffu);
         }
       }
+      P.die_items = positions_by_die(n, (double)all_cost, [&](size_t p) { return (double)P.items[order[p]].cost; });
     } else {
       for (size_t i = 0; i < n; ++i) order[i] = (uint32_t)(a[i] & 0xffffffffu);
+      if (pre_ns > 0.0 && n > 2 * (size_t)HFX_PLAN_WGS && streams >= kDieStreams && readers >= 2 * streams && pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {
+        const double all = dec_ns + tiles_ns + kItemNs * (double)n, even = (double)HFX_PLAN_WGS * max_cost;
+        if (all >= kDieShare * even || (all >= kDieShareShort * even && dec_ns <= kDieDecodes * all && streams >= kDieStreamsShort)) {
+          queue_per_die(a, n, Hkv, all, &P);
+          P.die_items = positions_by_die(n, all, [&](size_t p) { return cost_of((size_t)P.queue[p]); });
+        }
+      }
     }
   }
   // merge work units: groups with many splits get 8 threads per (row, column) and one row per
@@ -873,8 +995,6 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       P.units.push_back(u);
     }
   }
-  P.n_decode_items = P.n_prefill_items = 0;
-  for (const HfxItem& it : P.items) (it.type == HFX_ITEM_DECODE ? P.n_decode_items : P.n_prefill_items)++;
   return HFX_OK;
 }
 
@@ -901,6 +1021,7 @@ void layout_blob(const hfx_shape* shape, const Plan& P, HfxHeader* h) {
   h->n_ctrl = HFX_CTRL_WORDS;
   h->queue_classes = (uint32_t)P.queue_classes;
   h->deal_balanced = (uint32_t)P.deal_balanced;
+  h->die_items = (uint32_t)P.die_items;
   h->max_group_rows = 0;
   for (const HfxGroup& g : P.groups) h->max_group_rows = std::max(h->max_group_rows, g.rows_per_split);
   uint64_t off = align_up(sizeof(HfxHeader), 256);
@@ -912,6 +1033,8 @@ void layout_blob(const hfx_shape* shape, const Plan& P, HfxHeader* h) {
   off = align_up(off + 4ull * (uint64_t)P.n_bt, 64);
   h->off_items = (uint32_t)off;
   off = align_up(off + sizeof(HfxItem) * P.items.size(), 64);
+  h->off_queue = P.queue.empty() ? 0u : (uint32_t)off;
+  off = align_up(off + 4ull * P.queue.size(), 64);
   h->off_groups = (uint32_t)off;
   off = align_up(off + sizeof(HfxGroup) * P.groups.size(), 64);
   h->off_units = (uint32_t)off;
@@ -963,7 +1086,13 @@ hfx_status fill_blob(const hfx_shape* shape, Plan& P, const int32_t* bt_indptr, 
   put(h.off_bt + 4ull * (uint64_t)P.n_bt, nullptr, 0, h.off_items);
   HfxItem* queue = (HfxItem*)(base + h.off_items);
   for (size_t i = 0; i < P.items.size(); ++i) queue[i] = P.items[P.order[i]];
-  put(h.off_items + sizeof(HfxItem) * P.items.size(), nullptr, 0, h.off_groups);
+  const uint64_t items_end = h.off_items + sizeof(HfxItem) * P.items.size();
+  if (h.off_queue) {
+    put(items_end, nullptr, 0, h.off_queue);
+    put(h.off_queue, P.queue.data(), 4ull * P.queue.size(), h.off_groups);
+  } else {
+    put(items_end, nullptr, 0, h.off_groups);
+  }
   put(h.off_groups, P.groups.data(), sizeof(HfxGroup) * P.groups.size(), h.off_units);
   put(h.off_units, P.units.data(), sizeof(HfxUnit) * P.units.size(), h.off_runs);
   // append runs: each request's new tokens, cut at page boundaries

@@ -9,6 +9,13 @@
 
 namespace hfx {
 
+// What the queue order needs of an item, side by side (the records themselves are 80 bytes apart).
+struct ItemNote {
+  uint32_t cost;
+  uint32_t unit;     // of items that read the same keys (see the queue order in plan_step)
+  float frac;        // of a prefill item: its row tile's place in the chunk, in [0, 1)
+};
+
 struct Plan {
   std::vector<HfxReq> reqs;
   std::vector<HfxItem> items;
@@ -16,17 +23,20 @@ struct Plan {
   std::vector<HfxUnit> units;
   int32_t total_q = 0, n_bt = 0, n_partial_rows = 0, n_decode_items = 0, n_prefill_items = 0, n_runs = 0;
   int32_t queue_classes = 1;            // 1: plain queue; HFX_QUEUE_CLASSES: one list per die, interleaved by position
+  int32_t die_items = 0;                // see HfxHeader
   int32_t deal_balanced = 0;            // see HfxHeader
   // scratch of plan_step, kept so that a reused Plan allocates nothing once it has grown
   std::vector<uint64_t> sort_keys;
   std::vector<uint32_t> order;          // queue position -> index into items
   std::vector<int32_t> split_cost;
   std::vector<uint32_t> order_dec, order_pre;
-  std::vector<uint32_t> item_unit;      // item -> sharing unit (see the queue order in plan_step)
-  std::vector<float> item_frac;         // prefill item -> its row tile's place in the chunk, in [0, 1)
+  std::vector<ItemNote> notes;          // of each item
   std::vector<int64_t> unit_cost;
   std::vector<uint32_t> unit_fill, unit_start;
   std::vector<uint64_t> unit_keys;
+  std::vector<double> stream_ns;        // of each request with a prompt: time of the items that read the keys of one of its kv-heads
+  std::vector<uint32_t> die_lists[HFX_QUEUE_CLASSES];
+  std::vector<int32_t> queue;           // order in which items are taken, if it is not theirs; n_items or none
   std::vector<float> cut_cost, cut_sort, cut_load;   // trial of a cut: item times, sort scratch, CU loads
 };
 

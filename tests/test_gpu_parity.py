@@ -176,6 +176,22 @@ def test_queue_counters_of_short_queues(hb, oracle, n):
     assert np.all(hb.parse_desc(step.device_desc.cpu().numpy())["ctrl"] == 0), "control words must be restored to zero"
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,longest,decodes", [(8, 2, 128, 200, 300, 7), (24, 8, 64, 40, 500, 0), (4, 4, 128, 300, 400, 0), (16, 2, 64, 300, 120, 200)])
+def test_queue_per_die_of_many_prompts(hb, oracle, Hq, Hkv, D, n, longest, decodes):
+    """Items taken by a list: per die, then by all; against the oracle, again on the same descriptor, and with decodes among them."""
+    rng = np.random.default_rng(Hq + n)
+    q = rng.integers(5, longest, n)
+    b = small_pool_batch(rng, Hq, Hkv, D, [PREFILL] * n + [DECODE] * decodes, [*q, *[1] * decodes], [*q, *rng.integers(1, 300, decodes)], f"per-die-{Hq}-{Hkv}-{D}")
+    step, bits = check_full(hb, oracle, b)
+    d = hb.parse_desc(step.host_desc.numpy())
+    assert d["queue"] is not None and 1024 < d["header"].die_items < d["header"].n_items
+    for _ in range(3):
+        step.out.zero_()
+        step.run()
+        assert np.array_equal(step.out_bits(), bits)
+    assert np.all(hb.parse_desc(step.device_desc.cpu().numpy())["ctrl"] == 0), "control words must be restored to zero"
+
+
 @pytest.mark.parametrize("Hkv,D", [(1, 64), (2, 128)])
 def test_copy_stream_over_items_of_all_lengths(hb, oracle, Hkv, D):
     """Items of 1 to 130 stages of 32 keys behind each other in every workgroup, in an order in which long ones follow short ones: around the 64 page ids

@@ -281,6 +281,44 @@ def test_queue_per_die_where_few_row_tiles_read_the_same_keys(lib, Hq, Hkv, D, n
         check_class_order(b, d["items"])
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,decodes,per_die", [
+    (32, 8, 128, 64, 20, 700, 0, True), (32, 4, 64, 60, 100, 900, 20, True), (24, 8, 128, 20, 500, 3000, 0, True), (8, 8, 128, 120, 50, 600, 5, True),
+    (8, 1, 128, 170, 20, 500, 0, True), (32, 8, 128, 4, 1500, 2500, 0, True), (32, 8, 128, 3, 2500, 2500, 0, False), (8, 1, 128, 25, 1000, 2000, 0, False),
+    (32, 8, 128, 100, 1, 32, 0, False), (32, 8, 128, 24, 30, 1200, 0, True), (8, 8, 128, 130, 50, 600, 400, False)])
+def test_order_of_a_queue_per_die(lib, Hq, Hkv, D, n, lo, hi, decodes, per_die):
+    """Steps of many prompts list the order in which their items are taken: every item once, position p for die p % 8 up to a
+    multiple of 8 behind which little is left for all; the tiles of a (request, kv-head) on as few dies as its share of the step allows, one behind the
+    other, and the dies about equally loaded.  Not where few prompts share the chip, items are few, no two items share keys or decodes weigh much."""
+    g = np.random.default_rng(n)
+    q = g.integers(lo, hi + 1, n).tolist()
+    b = lengths_only(Hq, Hkv, D, [PREFILL] * n + [DECODE] * decodes, q + [1] * decodes, q + g.integers(100, 2000, decodes).tolist())
+    d = fill(b)
+    h, items, queue = d["header"], d["items"], d["queue"]
+    assert (queue is not None) == per_die and (h.die_items > 0) == per_die
+    assert h.queue_classes == 1 and np.all(items["home"] == -1)
+    check_coverage(b, d)
+    if not per_die:
+        return
+    assert np.array_equal(np.sort(queue), np.arange(h.n_items))
+    cost = items["cost"].astype(np.float64)[queue]
+    assert h.die_items % 8 == 0 and h.die_items <= h.n_items
+    assert cost[h.die_items:].sum() <= 0.07 * cost.sum() + 8 * cost.max()
+    die = np.arange(h.n_items) % 8
+    load = np.array([cost[die == c].sum() for c in range(8)])
+    G = Hq // Hkv
+    unit = np.where(items["type"] == 1, items["req"] * Hkv + items["h0"] // G, -1 - np.arange(h.n_items))[queue]
+    share = cost.sum() / 256                    # of a die's 32nd part
+    largest = max(cost[unit == u].sum() for u in np.unique(unit))
+    assert load.max() - load.min() <= min(largest, share) + 2 * cost.max()
+    front = 8 * min(int((die[:h.die_items] == c).sum()) for c in range(8))
+    for u in np.unique(unit[unit >= 0])[:40]:
+        at = np.flatnonzero(unit[:front] == u)
+        pieces = int(np.ceil(1.1 * cost[unit == u].sum() / share))
+        runs = sum(int(np.count_nonzero(np.diff(at[at % 8 == c]) != 8) + 1) for c in np.unique(at % 8)) if len(at) else 0
+        # (where a die's list ends early, items from the end of a longer one stand in for it)
+        assert runs <= pieces + 8, (u, runs, pieces)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 1, 128), (24, 8, 128), (32, 4, 64), (16, 16, 128)])
 @pytest.mark.parametrize("q,prior", [(5, 20000), (100, 8000), (777, 0), (500, 3000), (1500, 0), (992, 2000), (4096, 0)])
 def test_cut_of_a_single_prompt(lib, Hq, Hkv, D, q, prior):
