@@ -555,8 +555,12 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
         proto.row0 = (int32_t)r0;
         proto.nrows = rows_wg;
         proto.rq = q;
-        for (int g = 0; g < Hkv; ++g)
-          for (int hb = 0; hb < G / hpw; ++hb) {
+        // All items of a row tile cost the same and stay in this order, in which dealt positions go round the dies: with the kv-heads innermost, the head blocks
+        // that read one kv-head's keys come 8 positions apart, on one die, where there are 8 kv-heads.  (24/8 heads: 36 chunks of 7 rows behind 550 to
+        // 760 tokens 47.5 us with the head blocks innermost, 28.3 so; 39 of 2 rows behind 5000 to 9000 310 and 207; 20 steps of a few rows on 24/8, 32/4 and 8/1 heads
+        // 1.09 times as fast on average, 40 of prompts 1.01, none slower than the runs of one side differ.)
+        for (int hb = 0; hb < G / hpw; ++hb)
+          for (int g = 0; g < Hkv; ++g) {
             int group = -1;
             if (nsplit > 1) {
               group = (int)P.groups.size();
