@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libhfxattn's C ABI (include/hfxattn.h).
+"""Thin binding of libhfxattn's C ABI (include/hfxattn.h): ctypes, and for the calls that a serving loop makes per layer and per
+step an extension that marshals their arguments in C.
 
 Argument marshalling only: every step of the path runs inside the library's HIP kernels.
 PyTorch appears here solely as the owner of device memory and streams.  There is no CPU
@@ -96,6 +97,21 @@ def load() -> ctypes.CDLL:
                                          ctypes.c_int32, i32p, i32p, i32p, i32p, i32p,
                                          ctypes.POINTER(hfx_decision)]
         lib.hfx_compose_step.restype = ctypes.c_int32
+        # The calls a serving loop makes: their arguments are marshalled in C (csrc/hfx_call.c, which says what the letters mean).
+        try:
+            from . import _hfxcall
+        except ImportError as e:
+            raise RuntimeError("the call extension is missing or was built for another Python: run "
+                               "`python -m paper_2508_15919_amd.build`") from e
+
+        def caller(function, kinds):
+            return _hfxcall.Caller(ctypes.cast(function, vp).value, kinds, hfx_shape, _ptr, _as_int32)
+        lib.call_build = caller(lib.hfx_build_batch_desc, "SKAAAABBs")
+        lib.call_attention = caller(lib.hfx_mixed_paged_attention, "SPPPPBPs")
+        lib.call_attention_static = caller(lib.hfx_mixed_paged_attention_static, "SPPPPPs")
+        lib.call_gather = caller(lib.hfx_gather_kv, "SPPPiPPs")
+        lib.call_append = caller(lib.hfx_append_kv, "SPPPPPs")
+        lib.call_copy_pages = caller(lib.hfx_copy_pages, "SPPiKAPPzs")
         _lib = lib
     return _lib
 
@@ -107,13 +123,16 @@ def _i32(a):
     return arr, arr.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
 
 
+def _as_int32(a):
+    return None if a is None else np.ascontiguousarray(a, dtype=np.int32)
+
+
 _COPY_BELOW = 1 << 14      # bytes of an array that take less time to copy than its address takes to be had
 
 
 def _ints(a):
     """int32 array `a` in a form that is passed as its address, and what keeps that alive: asking a numpy array for its
-    address takes about a microsecond, as long as copying 16 KB into a bytes object (a step has five arrays;
-    marshalling them took 12 of the 15 us that describing a step of four requests took)."""
+    address takes about a microsecond, as long as copying 16 KB into a bytes object."""
     if a is None:
         return None, None
     arr = np.ascontiguousarray(a, dtype=np.int32)
@@ -135,10 +154,6 @@ def _ptr(x):
 
 def _nbytes(x) -> int:
     return 0 if x is None else x.nbytes
-
-
-def _stream(stream):
-    return stream if stream is None or isinstance(stream, int) else stream.cuda_stream
 
 
 def make_shape(num_q_heads, num_kv_heads, head_dim, num_pages, softmax_scale=0.0, page_size=16) -> hfx_shape:
@@ -183,57 +198,44 @@ def hfx_fill_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pa
 
 def hfx_build_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc,
                          stream=None) -> None:
-    k, pk = _ints(kind)
-    q, pq = _ints(q_len)
-    c, pc = _ints(ctx_len)
-    bi, pbi = _ints(bt_indptr)
-    bp, pbp = _ints(bt_pages)
-    rc = load().hfx_build_batch_desc(ctypes.byref(shape), len(k), pk, pq, pc, pbi, pbp, _ptr(host_desc),
-                                     _nbytes(host_desc), _ptr(device_desc), _nbytes(device_desc), _stream(stream))
+    rc = (_lib or load()).call_build(shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_build_batch_desc")
 
 
 def hfx_mixed_paged_attention(shape: hfx_shape, q, kv_pool, host_desc, device_desc, workspace, out,
                               stream=None) -> None:
-    rc = load().hfx_mixed_paged_attention(ctypes.byref(shape), _ptr(q), _ptr(kv_pool), _ptr(host_desc),
-                                          _ptr(device_desc), _ptr(workspace), _nbytes(workspace), _ptr(out),
-                                          _stream(stream))
+    rc = (_lib or load()).call_attention(shape, q, kv_pool, host_desc, device_desc, workspace, out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_mixed_paged_attention")
 
 
 def hfx_mixed_paged_attention_static(shape: hfx_shape, q, kv_pool, host_desc, device_desc, out, stream=None) -> None:
-    rc = load().hfx_mixed_paged_attention_static(ctypes.byref(shape), _ptr(q), _ptr(kv_pool), _ptr(host_desc),
-                                                 _ptr(device_desc), _ptr(out), _stream(stream))
+    rc = (_lib or load()).call_attention_static(shape, q, kv_pool, host_desc, device_desc, out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_mixed_paged_attention_static")
 
 
 def hfx_gather_kv(shape: hfx_shape, kv_pool, host_desc, device_desc, request: int, k_out, v_out,
                   stream=None) -> None:
-    rc = load().hfx_gather_kv(ctypes.byref(shape), _ptr(kv_pool), _ptr(host_desc), _ptr(device_desc),
-                              int(request), _ptr(k_out), _ptr(v_out), _stream(stream))
+    rc = (_lib or load()).call_gather(shape, kv_pool, host_desc, device_desc, request, k_out, v_out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_gather_kv")
 
 
 def hfx_append_kv(shape: hfx_shape, k_new, v_new, kv_pool, host_desc, device_desc, stream=None) -> None:
-    rc = load().hfx_append_kv(ctypes.byref(shape), _ptr(k_new), _ptr(v_new), _ptr(kv_pool), _ptr(host_desc),
-                              _ptr(device_desc), _stream(stream))
+    rc = (_lib or load()).call_append(shape, k_new, v_new, kv_pool, host_desc, device_desc, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_append_kv")
 
 
 def hfx_copy_pages(shape: hfx_shape, src_pool, dst_pool, dst_num_pages: int, src_ids, dst_ids, host_stage,
                    device_stage, stream=None, stage_bytes=None) -> None:
-    s_arr, ps = _ints(src_ids)
-    d_arr, pd = _ints(dst_ids)
-    assert len(s_arr) == len(d_arr)
-    rc = load().hfx_copy_pages(ctypes.byref(shape), _ptr(src_pool), _ptr(dst_pool), int(dst_num_pages), len(s_arr),
-                               ps, pd, _ptr(host_stage), _ptr(device_stage),
-                               min(_nbytes(host_stage), _nbytes(device_stage)) if stage_bytes is None
-                               else int(stage_bytes), _stream(stream))
+    assert len(src_ids) == len(dst_ids)
+    if stage_bytes is None:
+        stage_bytes = min(_nbytes(host_stage), _nbytes(device_stage))
+    rc = (_lib or load()).call_copy_pages(shape, src_pool, dst_pool, dst_num_pages, src_ids, dst_ids, host_stage, device_stage, stage_bytes,
+                                          stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_copy_pages")
 

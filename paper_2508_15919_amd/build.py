@@ -4,10 +4,12 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhfxattn.so")
+CALL_LIB = os.path.join(HERE, "_hfxcall.so")
 SOURCES = ["hfx_kernels.hip", "hfx_api.cpp", "hfx_plan.cpp", "hfx_sched.cpp"]
 # -fno-honor-nans: no floating-point operation in the kernels is ever fed a NaN (possibly-NaN scores
 # are masked through integer selects first), and without it every max carries a canonicalising twin.
@@ -34,7 +36,20 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         raise RuntimeError("hipcc failed:\n" + err)
     if verbose and err.strip():
         print(err, file=sys.stderr)
+    build_call(verbose)
     return LIB
+
+
+def build_call(verbose: bool = False) -> str:
+    """The extension that marshals the arguments of the calls a serving loop makes (csrc/hfx_call.c)."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-o", CALL_LIB,
+           os.path.join(CSRC, "hfx_call.c")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the call extension did not build:\n" + res.stderr)
+    return CALL_LIB
 
 
 if __name__ == "__main__":
