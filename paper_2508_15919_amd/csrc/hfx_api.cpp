@@ -115,7 +115,7 @@ hfx_status hfx_batch_desc_sizes(const hfx_shape* shape, int32_t num_requests, co
                                 size_t* device_desc_bytes, size_t* device_workspace_bytes) {
   if (!host_desc_bytes || !device_desc_bytes || !device_workspace_bytes) return HFX_ERR_NULL;
   hfx::Plan& plan = tls_plan();
-  hfx_status st = hfx::plan_step(shape, num_requests, kind, q_len, ctx_len, &plan);
+  hfx_status st = hfx::plan_step(shape, num_requests, kind, q_len, ctx_len, &plan, true);
   if (st != HFX_OK) return st;
   HfxHeader h;
   hfx::layout_blob(shape, plan, &h);

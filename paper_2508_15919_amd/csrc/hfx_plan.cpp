@@ -683,7 +683,6 @@ static void queue_per_die(const uint64_t* sorted, size_t n, int Hkv, double all,
   // position p is for die p % HFX_QUEUE_CLASSES; when a die's list ends, its positions take what is left of the longer ones
   std::vector<uint32_t>& left = P.order_dec;
   left.clear();
-  P.queue.resize(n);
   for (size_t i = 0; i < n; ++i) {
     const uint32_t at = place[piece_of[i]];
     place[piece_of[i]] = at + HFX_QUEUE_CLASSES;
@@ -707,7 +706,7 @@ static int32_t positions_by_die(size_t n, double all, F cost) {
 }
 
 hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, const int32_t* q_len,
-                     const int32_t* ctx_len, Plan* out) {
+                     const int32_t* ctx_len, Plan* out, bool sizes_only) {
   hfx_status st = check_shape(shape);
   if (st != HFX_OK) return st;
   if (!kind || !q_len || !ctx_len || !out) return HFX_ERR_NULL;
@@ -803,18 +802,32 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     }
   }
   P.n_partial_rows = (int32_t)rows;
+  const size_t n = P.items.size();
+  uint32_t max_cost = 0;
+  for (size_t i = 0; i < n; ++i) max_cost = std::max(max_cost, P.notes[i].cost);
+  // Which of the queue orders below the step gets.
+  const bool beside = decode_dominated && pre_ns > 0.0;
+  const bool units_fit = pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit;
+  const bool classes = !beside && pre_ns > 0.0 && units_fit && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
+                       ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS &&
+                         ((D == 128 && total_ns >= kClassStepNs * HFX_PLAN_WGS) ||
+                          (stream_ns >= kClassStreamBytes / kDecodeBytesPerNs && readers >= 2 * streams && total_ns >= kMinItemNs * (double)n))) ||
+                        (n >= (size_t)kClassRoundsMinApart * HFX_PLAN_WGS && dec_ns + tiles_ns >= kClassItemNsApart * (double)n &&
+                         mult > Hkv && apart_ns >= kClassApart * beside_ns));
+  const double all_ns = dec_ns + tiles_ns + kItemNs * (double)n, even_ns = (double)HFX_PLAN_WGS * max_cost;
+  const bool per_die = !beside && !classes && pre_ns > 0.0 && units_fit && n > 2 * (size_t)HFX_PLAN_WGS && streams >= kDieStreams && readers >= 2 * streams &&
+                       (all_ns >= kDieShare * even_ns ||
+                        (all_ns >= kDieShareShort * even_ns && dec_ns <= kDieDecodes * all_ns && streams >= kDieStreamsShort));
+  P.queue.resize(per_die ? n : 0);
   // queue order: descending cost, ties in creation order: a stable radix sort (11-bit digits) of
   // (inverted cost, index) keys, then one permutation of the item records.
-  {
-    const size_t n = P.items.size();
+  if (!sizes_only) {
     std::vector<uint64_t>& key = P.sort_keys;
     key.resize(2 * n);
     uint64_t* a = key.data();
     uint64_t* b = a + n;
     // keys count down from the largest cost, so that the number of digit passes follows the range
     // of costs in the step and not the width of the field
-    uint32_t max_cost = 0;
-    for (size_t i = 0; i < n; ++i) max_cost = std::max(max_cost, P.notes[i].cost);
     uint32_t top = 0;
     for (size_t i = 0; i < n; ++i) {
       const uint32_t inv = max_cost - P.notes[i].cost;
@@ -837,11 +850,9 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
     std::vector<uint32_t>& order = P.order;
     order.resize(n);
     P.queue_classes = 1;
-    P.queue.clear();
     P.die_items = 0;
-    auto cost_of = [&](size_t i) { return (double)(max_cost - (uint32_t)(a[i] >> 32)); };     // of the i-th in descending cost
-    P.deal_balanced = !(decode_dominated && pre_ns > 0.0);   // the layout below is by workgroup
-    if (decode_dominated && pre_ns > 0.0) {
+    P.deal_balanced = !beside;   // the layout below is by workgroup
+    if (beside) {
       // A step whose decode work outweighs its prefill work.  The first two items of workgroup b
       // are queue positions b and b + HFX_PLAN_WGS, and workgroups b and b + HFX_PLAN_WGS/2 share a
       // CU.  Over those two rounds the prefill items (largest first) go to the workgroups of the
@@ -875,13 +886,7 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
         for (size_t k = 0; k < kBlockItems && di < dec.size(); ++k) order[o++] = dec[di++];
         for (size_t k = 0; k < kBlockItems && pi < pre.size(); ++k) order[o++] = pre[pi++];
       }
-    } else if (pre_ns > 0.0 && n <= (size_t)kClassRoundsMax * HFX_PLAN_WGS &&
-               ((n >= (size_t)kClassRoundsMin * HFX_PLAN_WGS &&
-                 ((D == 128 && total_ns >= kClassStepNs * HFX_PLAN_WGS) ||
-                  (stream_ns >= kClassStreamBytes / kDecodeBytesPerNs && readers >= 2 * streams && total_ns >= kMinItemNs * (double)n))) ||
-                (n >= (size_t)kClassRoundsMinApart * HFX_PLAN_WGS && dec_ns + tiles_ns >= kClassItemNsApart * (double)n &&
-                 mult > Hkv && apart_ns >= kClassApart * beside_ns)) &&
-               pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {
+    } else if (classes) {
       // A step whose prefill work outweighs its decode work.  Many prefill items read the same
       // keys: all row tiles (and q-head blocks) of one request and kv-head that hold the same
       // piece of the key range.  Call that set a unit.  The chip has HFX_QUEUE_CLASSES dies, each
@@ -980,12 +985,9 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
       P.die_items = positions_by_die(n, (double)all_cost, [&](size_t p) { return (double)P.items[order[p]].cost; });
     } else {
       for (size_t i = 0; i < n; ++i) order[i] = (uint32_t)(a[i] & 0xffffffffu);
-      if (pre_ns > 0.0 && n > 2 * (size_t)HFX_PLAN_WGS && streams >= kDieStreams && readers >= 2 * streams && pre_ord * Hkv * kMaxSplits < (int64_t)kNoUnit) {
-        const double all = dec_ns + tiles_ns + kItemNs * (double)n, even = (double)HFX_PLAN_WGS * max_cost;
-        if (all >= kDieShare * even || (all >= kDieShareShort * even && dec_ns <= kDieDecodes * all && streams >= kDieStreamsShort)) {
-          queue_per_die(a, n, Hkv, all, &P);
-          P.die_items = positions_by_die(n, all, [&](size_t p) { return cost_of((size_t)P.queue[p]); });
-        }
+      if (per_die) {
+        queue_per_die(a, n, Hkv, all_ns, &P);
+        P.die_items = positions_by_die(n, all_ns, [&](size_t p) { return (double)(max_cost - (uint32_t)(a[P.queue[p]] >> 32)); });
       }
     }
   }

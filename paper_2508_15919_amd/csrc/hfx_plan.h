@@ -36,13 +36,14 @@ struct Plan {
   std::vector<uint64_t> unit_keys;
   std::vector<double> stream_ns;        // of each request with a prompt: time of the items that read the keys of one of its kv-heads
   std::vector<uint32_t> die_lists[HFX_QUEUE_CLASSES];
-  std::vector<int32_t> queue;           // order in which items are taken, if it is not theirs; n_items or none
+  std::vector<int32_t> queue;           // order in which items are taken, if it is not theirs; as many as items, or none
   std::vector<float> cut_cost, cut_sort, cut_load;   // trial of a cut: item times, sort scratch, CU loads
 };
 
 hfx_status check_shape(const hfx_shape* shape);
+// sizes_only: the plan is good for layout_blob alone, its items are not put in order.
 hfx_status plan_step(const hfx_shape* shape, int32_t num_requests, const int32_t* kind, const int32_t* q_len,
-                     const int32_t* ctx_len, Plan* out);
+                     const int32_t* ctx_len, Plan* out, bool sizes_only = false);
 void layout_blob(const hfx_shape* shape, const Plan& plan, HfxHeader* header);
 hfx_status fill_blob(const hfx_shape* shape, Plan& plan, const int32_t* bt_indptr, const int32_t* bt_pages,
                      void* host_desc, size_t host_desc_bytes);
