@@ -272,7 +272,8 @@ hfx_status hfx_append_kv(const hfx_shape* shape, const void* k_new, const void* 
  *   host_stage     [host]   >= 8*num_pairs bytes, written here and read by the upload: leave
  *                  it alone until the stream has passed this call (pinned memory keeps the
  *                  call asynchronous)
- *   device_stage   [device] >= 8*num_pairs bytes, 16-byte aligned
+ *   device_stage   [device] >= 8*num_pairs bytes, 16-byte aligned; left as it is where the ids
+ *                  of a short list go with the launch
  *   stage_bytes    size of each staging buffer
  *
  * Asynchronous on `stream`; allocates no device memory.  num_pairs == 0 is a no-op.

@@ -227,11 +227,8 @@ hfx_status hfx_copy_pages(const hfx_shape* shape, const void* src_pool, void* ds
     stage[2 * i] = src_ids[i];
     stage[2 * i + 1] = dst_ids[i];
   }
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hfx::upload(host_stage, device_stage, 8ull * (size_t)num_pairs, s) != hipSuccess)
-    return HFX_ERR_DEVICE;
-  const int units_per_page = shape->num_kv_heads * 2 * HFX_PAGE * shape->head_dim * 2 / 16;
-  if (hfx::launch_copy_pages(device_stage, num_pairs, units_per_page, src_pool, dst_pool, s) != hipSuccess)
+  const unsigned units_per_page = (unsigned)(shape->num_kv_heads * 2 * HFX_PAGE * shape->head_dim * 2 / 16);
+  if (hfx::copy_pages(host_stage, device_stage, num_pairs, units_per_page, src_pool, dst_pool, static_cast<hipStream_t>(stream)) != hipSuccess)
     return HFX_ERR_DEVICE;
   return HFX_OK;
 }

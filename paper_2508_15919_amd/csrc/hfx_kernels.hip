@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cstring>
 #include <mutex>
 
 #include "hfx_desc.h"
@@ -1357,9 +1358,19 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
 // loads in flight before the first store.  The page of a 4 KB piece is the same for the whole workgroup, so that its id
 // is one scalar load and nothing is divided per thread.
 // Stream: the pages are not read again, nor do they find a place in the last-level cache.
+// N: pairs that come with the arguments; 0: they are in device memory.  An upload kernel ahead of this one costs 5 us of a short copy, for a
+// list that fits the arguments of a launch.
 // ---------------------------------------------------------------------------------------
-template <bool Stream>
-__global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict__ pairs, long n_pairs, unsigned units_per_page,
+template <int N>
+struct PagePairs {
+  int2 id[N];
+};
+template <>
+struct PagePairs<0> {
+  const int2* id;
+};
+template <bool Stream, int N>
+__global__ __launch_bounds__(256) void copy_pages_kernel(const PagePairs<N> pairs, long n_pairs, unsigned units_per_page,
                                                          const u32x4* __restrict__ src, u32x4* __restrict__ dst) {
   constexpr unsigned kPiece = 256, kPieces = 4;
   const bool whole = units_per_page >= kPieces * kPiece;        // the workgroup stays inside a page
@@ -1374,7 +1385,7 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const int2* __restrict_
     const long pr = whole ? (long)page : (long)page * (kPieces * kPiece / units_per_page) + skip;
     to[j] = -1;
     if (pr < n_pairs) {
-      const int2 id = pairs[pr];
+      const int2 id = pairs.id[pr];
       const unsigned off = unit - skip * units_per_page + threadIdx.x;
       const u32x4* from = src + (long)id.x * units_per_page + off;
       v[j] = Stream ? __builtin_nontemporal_load(from) : *from;
@@ -1649,17 +1660,38 @@ hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stre
 // each way, three sets of buffers in turn: 21.1 us, 25.1 streaming; 268 MB 61.2 and 60.2).  With a division by the page size for each
 // 16 bytes the kernel took 26.8 and 61.2.
 constexpr long kCopyStreamBytes = 64l << 20;
-hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page, const void* src, void* dst,
-                             hipStream_t stream) {
-  const long n_units = n_pairs * units_per_page;
-  if (n_units == 0) return hipSuccess;
-  const long blocks = (n_units + 1023) / 1024;
+template <int N>
+static hipError_t launch_copy_pages(const PagePairs<N>& pairs, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
+  const long n_units = n_pairs * units_per_page, blocks = (n_units + 1023) / 1024;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  const int2* p = static_cast<const int2*>(pairs);
-  const u32x4* from = static_cast<const u32x4*>(src);
-  u32x4* to = static_cast<u32x4*>(dst);
-  return launch(n_units * 16 > kCopyStreamBytes ? copy_pages_kernel<true> : copy_pages_kernel<false>, dim3((unsigned)blocks), 256, stream, p, n_pairs,
-                (unsigned)units_per_page, from, to);
+  return launch(n_units * 16 > kCopyStreamBytes ? copy_pages_kernel<true, N> : copy_pages_kernel<false, N>, dim3((unsigned)blocks), 256, stream, pairs,
+                n_pairs, units_per_page, static_cast<const u32x4*>(src), static_cast<u32x4*>(dst));
+}
+template <int N>
+static hipError_t copy_named_pages(const void* host, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
+  PagePairs<N> pairs;
+  std::memcpy(pairs.id, host, sizeof(int2) * (size_t)n_pairs);
+  return launch_copy_pages(pairs, n_pairs, units_per_page, src, dst, stream);
+}
+
+// Whether launches on `stream` are being recorded.  The stream of the null handle cannot be.
+static bool may_be_captured(hipStream_t stream) {
+  if (stream == nullptr || stream == hipStreamLegacy) return false;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
+// The list goes with the launch where an upload kernel would carry it and it fits 4 KB of arguments; the host hands over all of these, so there are
+// two sizes.  A recorded launch reads the staging buffer when it is replayed, and goes on doing so.  Copies of one layer's pages, 8 kv-heads of 128,
+// called in a row: 2 to 50 pages 13.1 us uploaded, 11.1 with 60 in the arguments, 11.8 with 496; 188 pages 13.7 and 12.1; 494 pages 17.5 and 14.8.
+constexpr int kFewPairs = 60, kMostPairs = 496;
+hipError_t copy_pages(const void* host, void* device, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
+  const size_t bytes = sizeof(int2) * (size_t)n_pairs;
+  if (n_pairs <= kMostPairs && kernel_may_upload(host, device, bytes, stream) && !may_be_captured(stream))
+    return n_pairs <= kFewPairs ? copy_named_pages<kFewPairs>(host, n_pairs, units_per_page, src, dst, stream)
+                                : copy_named_pages<kMostPairs>(host, n_pairs, units_per_page, src, dst, stream);
+  const hipError_t e = upload(host, device, bytes, stream);
+  return e != hipSuccess ? e : launch_copy_pages(PagePairs<0>{static_cast<const int2*>(device)}, n_pairs, units_per_page, src, dst, stream);
 }
 
 // Far more than are resident (8 to a CU), so that only very long requests go round the loop.

@@ -22,7 +22,7 @@ hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_
 // stream's GPU, by the runtime otherwise.  Either way the buffer is read when the stream gets there.
 hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stream);
 
-hipError_t launch_copy_pages(const void* pairs, long n_pairs, int units_per_page, const void* src, void* dst,
-                             hipStream_t stream);
+// Copies pages by (source, destination) id pairs: `n_pairs` of them in `host`, with room for as many in `device`.
+hipError_t copy_pages(const void* host, void* device, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream);
 
 }  // namespace hfx

@@ -544,6 +544,40 @@ def test_copy_pages_of_every_page_size(hb, Hkv, D, pairs):
     assert torch.equal(dst, want)
 
 
+@pytest.mark.parametrize("pairs", [59, 60, 61, 495, 496, 497])
+def test_copied_page_ids_go_with_the_launch_or_through_the_staging_buffer(hb, pairs):
+    """Short lists travel as arguments, of two sizes.  The staging buffer is free as soon as such a call returns; a recorded call reads it when
+    it is replayed."""
+    import torch
+    rng = np.random.default_rng(pairs)
+    Hkv, D, n = 2, 64, 512
+    src = torch.from_numpy(rng.integers(-2**15, 2**15, (n, Hkv, 2, 16 * D), dtype=np.int16)).cuda()
+    shape = hb.make_shape(Hkv, Hkv, D, n)
+    lists = [(rng.permutation(n)[:pairs].astype(np.int32), rng.permutation(n)[:pairs].astype(np.int32)) for _ in range(3)]
+    host, dev = torch.empty(8 * pairs, dtype=torch.uint8, pin_memory=True), torch.empty(8 * pairs, dtype=torch.uint8, device="cuda")
+
+    def copied(s_ids, d_ids):
+        want = torch.zeros_like(src)
+        want[torch.from_numpy(d_ids.astype(np.int64)).cuda()] = src[torch.from_numpy(s_ids.astype(np.int64)).cuda()]
+        return want
+
+    dst = torch.zeros_like(src)
+    for s_ids, d_ids in lists:
+        dst.zero_()
+        hb.hfx_copy_pages(shape, src, dst, n, s_ids, d_ids, host, dev, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        assert torch.equal(dst, copied(s_ids, d_ids))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        hb.hfx_copy_pages(shape, src, dst, n, *lists[0], host, dev, torch.cuda.current_stream())
+    for s_ids, d_ids in lists + lists[:1]:
+        host.copy_(torch.from_numpy(np.stack([s_ids, d_ids], 1).copy().view(np.uint8).reshape(-1)))
+        dst.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(dst, copied(s_ids, d_ids))
+
+
 @pytest.mark.parametrize("staging,offset", [("pinned", 0), ("pinned", 8), ("pinned", 4), ("pageable", 0), ("pageable", 4)])
 @pytest.mark.parametrize("requests", [3, 400])
 def test_staging_memory_of_every_kind_is_uploaded(hb, staging, offset, requests):
