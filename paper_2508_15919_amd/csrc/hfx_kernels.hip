@@ -1349,6 +1349,36 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
   }
 }
 
+// Upload of a staging buffer that the GPU can read (pinned host memory): 8-byte words, four of a thread in flight.  Loads of
+// system scope, so that no cache of the GPU answers with what the buffer held before.  Bound: the host link.
+// An engine uploads the next step's descriptor while the present step's attention runs.  Two workgroups of that kernel with 128-wide heads take
+// 2 * 248 of a SIMD's 512 registers (247 a lane, handed out eight at a time), so this one takes no more than 16: with 18 it
+// found no place until the first workgroups of the launch ended.  And a CU answers its loads in order, so that one which
+// hosts a workgroup of this kernel waits for the host link with all it has: few of them, going round a loop, 2 KB a wavefront.
+// Steps of 384 and 1152 short requests (0.94 and 2.96 MB), us a step, uploaded beside the launch before and, second, ahead of the launch
+// on the same stream: by a copy engine 315.3 and 339.4, 1063 and 1116; one workgroup for each 8 KB with 18 registers 324.0 and 329.8,
+// 1105 and 1110, with 16 registers 320.2 and 328.5, 1091 and 1108; 128 workgroups 320.5 and 328.6, 1080 and 1107; 32 315.3 and 328.3,
+// 1063 and 1107; 12 315.8 and 329.8, 1064 and 1110.
+constexpr unsigned kUploadWgs = 32;
+__device__ __forceinline__ void upload_words(const char* __restrict__ src, char* __restrict__ dst, unsigned words, unsigned workgroup, unsigned workgroups) {
+  const int word = (threadIdx.x >> 6) * 256 + (threadIdx.x & 63);       // and 64, 128, 192 further on: one address for all four
+  for (unsigned first = workgroup * 1024; first < words; first += workgroups * 1024) {
+    const int left = (int)min(words - first, 1024u) - word;
+    const uint64_t* from = reinterpret_cast<const uint64_t*>(src) + first + word;
+    uint64_t* to = reinterpret_cast<uint64_t*>(dst) + first + word;
+    uint64_t v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (64 * j < left) v[j] = __hip_atomic_load(from + 64 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (64 * j < left) to[64 * j] = v[j];
+  }
+}
+__global__ __launch_bounds__(256) void upload_kernel(const char* __restrict__ src, char* __restrict__ dst, unsigned words) {
+  upload_words(src, dst, words, blockIdx.x, gridDim.x);
+}
+
 // ---------------------------------------------------------------------------------------
 // Page copy: pool pages named by (src, dst) id pairs move between two pools of the same
 // geometry (or inside one).  The device half of handing a request's KV blocks from the
@@ -1361,12 +1391,25 @@ __global__ __launch_bounds__(HFX_WG_THREADS, 2) void mixed_attention_kernel(
 // Bound: memory.  In pieces of 64 KB a die, copies past the caches are 2 to 3 % faster than in pieces of 16 KB: 134 MB each way 58.2 us a call and
 // 59.6, 268 MB 109.3 and 113.3; runs of 8 to 32 workgroups are like 4, smaller copies the same either way.
 // N: pairs that come with the arguments; 0: they are in device memory.  An upload kernel ahead of this one costs 5 us of a short copy, for a
-// list that fits the arguments of a launch.
+// list that fits the arguments of a launch.  Of a longer list the arguments hold the first N, and workgroups ahead of those that copy upload the rest
+// for a second launch meanwhile.
 // ---------------------------------------------------------------------------------------
+constexpr int kFewPairs = 60, kMostPairs = 496;      // the latter fill the 4 KB that the arguments of a launch may take
+struct ListRest {
+  const char* from;
+  char* to;
+  unsigned words, workgroups;     // the first `workgroups` of the launch upload: a multiple of 8
+};
 template <int N>
 struct PagePairs {
   int2 id[N];
 };
+template <>
+struct PagePairs<kMostPairs> {
+  int2 id[kMostPairs];
+  ListRest rest;
+};
+static_assert(sizeof(PagePairs<kMostPairs>) + 32 <= 4096, "with the kernel's other arguments");
 template <>
 struct PagePairs<0> {
   const int2* id;
@@ -1379,8 +1422,16 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const PagePairs<N> pair
   const unsigned per_page = whole ? units_per_page / (kPieces * kPiece) : 1;
   // Workgroups go to the dies by their index modulo 8: of 32 in a row a die takes four that follow each other, 64 KB.
   constexpr unsigned kDies = HFX_QUEUE_CLASSES, kRun = 4;
-  unsigned index = blockIdx.x;
-  if (index < gridDim.x / (kDies * kRun) * (kDies * kRun))
+  unsigned index = blockIdx.x, count = gridDim.x;
+  if constexpr (N == kMostPairs) {
+    if (index < pairs.rest.workgroups) {
+      upload_words(pairs.rest.from, pairs.rest.to, pairs.rest.words, index, pairs.rest.workgroups);
+      return;
+    }
+    index -= pairs.rest.workgroups;
+    count -= pairs.rest.workgroups;
+  }
+  if (index < count / (kDies * kRun) * (kDies * kRun))
     index = index / (kDies * kRun) * (kDies * kRun) + index % kDies * kRun + index / kDies % kRun;
   const unsigned page = index / per_page, part = index - page * per_page;
   u32x4 v[kPieces];
@@ -1402,33 +1453,6 @@ __global__ __launch_bounds__(256) void copy_pages_kernel(const PagePairs<N> pair
 #pragma unroll
   for (unsigned j = 0; j < kPieces; ++j)
     if (to[j] >= 0) __builtin_nontemporal_store(v[j], dst + to[j]);
-}
-
-// Upload of a staging buffer that the GPU can read (pinned host memory): 8-byte words, four of a thread in flight.  Loads of
-// system scope, so that no cache of the GPU answers with what the buffer held before.  Bound: the host link.
-// An engine uploads the next step's descriptor while the present step's attention runs.  Two workgroups of that kernel with 128-wide heads take
-// 2 * 248 of a SIMD's 512 registers (247 a lane, handed out eight at a time), so this one takes no more than 16: with 18 it
-// found no place until the first workgroups of the launch ended.  And a CU answers its loads in order, so that one which
-// hosts a workgroup of this kernel waits for the host link with all it has: few of them, going round a loop, 2 KB a wavefront.
-// Steps of 384 and 1152 short requests (0.94 and 2.96 MB), us a step, uploaded beside the launch before and, second, ahead of the launch
-// on the same stream: by a copy engine 315.3 and 339.4, 1063 and 1116; one workgroup for each 8 KB with 18 registers 324.0 and 329.8,
-// 1105 and 1110, with 16 registers 320.2 and 328.5, 1091 and 1108; 128 workgroups 320.5 and 328.6, 1080 and 1107; 32 315.3 and 328.3,
-// 1063 and 1107; 12 315.8 and 329.8, 1064 and 1110.
-constexpr unsigned kUploadWgs = 32;
-__global__ __launch_bounds__(256) void upload_kernel(const char* __restrict__ src, char* __restrict__ dst, unsigned words) {
-  const int word = (threadIdx.x >> 6) * 256 + (threadIdx.x & 63);       // and 64, 128, 192 further on: one address for all four
-  for (unsigned first = blockIdx.x * 1024; first < words; first += gridDim.x * 1024) {
-    const int left = (int)min(words - first, 1024u) - word;
-    const uint64_t* from = reinterpret_cast<const uint64_t*>(src) + first + word;
-    uint64_t* to = reinterpret_cast<uint64_t*>(dst) + first + word;
-    uint64_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (64 * j < left) v[j] = __hip_atomic_load(from + 64 * j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (64 * j < left) to[64 * j] = v[j];
-  }
 }
 
 // Page gather: a workgroup of 2 D threads takes one (page, kv-head) at a time.  A thread moves one 16-byte
@@ -1668,17 +1692,12 @@ hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stre
 // 16 bytes the kernel took 26.8 and 61.2.
 constexpr long kCopyStreamBytes = 64l << 20;
 template <int N>
-static hipError_t launch_copy_pages(const PagePairs<N>& pairs, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
-  const long n_units = n_pairs * units_per_page, blocks = (n_units + 1023) / 1024;
+static hipError_t launch_copy_pages(const PagePairs<N>& pairs, long n_pairs, unsigned units_per_page, bool past_cache, unsigned others, const void* src,
+                                    void* dst, hipStream_t stream) {
+  const long blocks = (n_pairs * units_per_page + 1023) / 1024 + others;
   if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-  return launch(n_units * 16 > kCopyStreamBytes ? copy_pages_kernel<true, N> : copy_pages_kernel<false, N>, dim3((unsigned)blocks), 256, stream, pairs,
+  return launch(past_cache ? copy_pages_kernel<true, N> : copy_pages_kernel<false, N>, dim3((unsigned)blocks), 256, stream, pairs,
                 n_pairs, units_per_page, static_cast<const u32x4*>(src), static_cast<u32x4*>(dst));
-}
-template <int N>
-static hipError_t copy_named_pages(const void* host, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
-  PagePairs<N> pairs;
-  std::memcpy(pairs.id, host, sizeof(int2) * (size_t)n_pairs);
-  return launch_copy_pages(pairs, n_pairs, units_per_page, src, dst, stream);
 }
 
 // Whether launches on `stream` are being recorded.  The stream of the null handle cannot be.
@@ -1688,17 +1707,31 @@ static bool may_be_captured(hipStream_t stream) {
   return hipStreamIsCapturing(stream, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
 }
 
-// The list goes with the launch where an upload kernel would carry it and it fits 4 KB of arguments; the host hands over all of these, so there are
-// two sizes.  A recorded launch reads the staging buffer when it is replayed, and goes on doing so.  Copies of one layer's pages, 8 kv-heads of 128,
-// called in a row: 2 to 50 pages 13.1 us uploaded, 11.1 with 60 in the arguments, 11.8 with 496; 188 pages 13.7 and 12.1; 494 pages 17.5 and 14.8.
-constexpr int kFewPairs = 60, kMostPairs = 496;
+// The list goes with the launch where an upload kernel would carry it; the host hands over all of the argument block, so there are
+// two sizes.  A recorded launch reads the staging buffer when it is replayed, and goes on doing so.  Copies of pages of 8 kv-heads of 128,
+// called in a row: 2 to 50 pages 13.1 us uploaded, 11.1 with 60 in the arguments, 11.8 with 496; 188 pages 13.7 and 12.1; 494 pages 17.5 and 14.5.
+// Longer lists, uploaded ahead of the copy and, second, beside the first 496 pages: 563 pages 18.8 and 17.9, 688 21.0 and 19.6, 1250 39.1 and 37.9,
+// 4096 109.0 and 108.0; 4063 of 32 KB 27.9 and 26.2.
 hipError_t copy_pages(const void* host, void* device, long n_pairs, unsigned units_per_page, const void* src, void* dst, hipStream_t stream) {
   const size_t bytes = sizeof(int2) * (size_t)n_pairs;
-  if (n_pairs <= kMostPairs && kernel_may_upload(host, device, bytes, stream) && !may_be_captured(stream))
-    return n_pairs <= kFewPairs ? copy_named_pages<kFewPairs>(host, n_pairs, units_per_page, src, dst, stream)
-                                : copy_named_pages<kMostPairs>(host, n_pairs, units_per_page, src, dst, stream);
-  const hipError_t e = upload(host, device, bytes, stream);
-  return e != hipSuccess ? e : launch_copy_pages(PagePairs<0>{static_cast<const int2*>(device)}, n_pairs, units_per_page, src, dst, stream);
+  const bool past_cache = n_pairs * units_per_page * 16 > kCopyStreamBytes;
+  const PagePairs<0> all = {static_cast<const int2*>(device)};
+  if (!kernel_may_upload(host, device, bytes, stream) || may_be_captured(stream)) {
+    const hipError_t e = upload(host, device, bytes, stream);
+    return e != hipSuccess ? e : launch_copy_pages(all, n_pairs, units_per_page, past_cache, 0, src, dst, stream);
+  }
+  if (n_pairs <= kFewPairs) {
+    PagePairs<kFewPairs> few;
+    std::memcpy(few.id, host, bytes);
+    return launch_copy_pages(few, n_pairs, units_per_page, past_cache, 0, src, dst, stream);
+  }
+  const long n = std::min<long>(n_pairs, kMostPairs), left = n_pairs - n;
+  PagePairs<kMostPairs> most;
+  std::memcpy(most.id, host, sizeof(int2) * (size_t)n);
+  const unsigned words = (unsigned)left, workgroups = std::min((words + 8191u) / 8192u * 8u, kUploadWgs);
+  most.rest = {static_cast<const char*>(host) + 8 * n, static_cast<char*>(device) + 8 * n, words, workgroups};
+  const hipError_t e = launch_copy_pages(most, n, units_per_page, past_cache, workgroups, src, dst, stream);
+  return e != hipSuccess || left == 0 ? e : launch_copy_pages(PagePairs<0>{all.id + n}, left, units_per_page, past_cache, 0, src, dst, stream);
 }
 
 // Far more than are resident (8 to a CU), so that only very long requests go round the loop.

@@ -544,14 +544,14 @@ def test_copy_pages_of_every_page_size(hb, Hkv, D, pairs):
     assert torch.equal(dst, want)
 
 
-@pytest.mark.parametrize("pairs", [59, 60, 61, 495, 496, 497])
+@pytest.mark.parametrize("pairs", [59, 60, 61, 495, 496, 497, 9000, 34000])
 def test_copied_page_ids_go_with_the_launch_or_through_the_staging_buffer(hb, pairs):
-    """Short lists travel as arguments, of two sizes.  The staging buffer is free as soon as such a call returns; a recorded call reads it when
-    it is replayed."""
+    """Short lists travel as arguments, of two sizes, and longer ones in part, the rest uploaded by workgroups of the first launch: 8 of them, 16, and
+    32 with a second round.  A recorded call reads the staging buffer when it is replayed."""
     import torch
     rng = np.random.default_rng(pairs)
-    Hkv, D, n = 2, 64, 512
-    src = torch.from_numpy(rng.integers(-2**15, 2**15, (n, Hkv, 2, 16 * D), dtype=np.int16)).cuda()
+    Hkv, D, n = 1, 64, max(pairs, 512)
+    src = torch.randint(-2**15, 2**15, (n, Hkv, 2, 16 * D), dtype=torch.int16, device="cuda")
     shape = hb.make_shape(Hkv, Hkv, D, n)
     lists = [(rng.permutation(n)[:pairs].astype(np.int32), rng.permutation(n)[:pairs].astype(np.int32)) for _ in range(3)]
     host, dev = torch.empty(8 * pairs, dtype=torch.uint8, pin_memory=True), torch.empty(8 * pairs, dtype=torch.uint8, device="cuda")
