@@ -406,9 +406,16 @@ struct DecodeCut {
 // Beside prefill items that a decode stream outweighs, a step of up to kRoundsOver times the 1024 items of two rounds has its pieces
 // lengthened to that, if pieces four times as long are enough: all items are then dealt, and no round has a few items in it.  150 steps of 1.0 to
 // 2.0 times 1024 items on seven head layouts: 1.007 to 1.044 times as fast on average in each tenth, the slowest 0.965, the fastest 1.112; six
-// steps of 2.0 to 2.4 times 1.020, six of 2.4 to 2.6 times 0.991.  Decodes alone keep their pieces by time.  (They gain as well: 50 steps 1.031,
-// the slowest 0.984; one step that had been measured took 117.5 us and 125.9.)
+// steps of 2.0 to 2.4 times 1.020, six of 2.4 to 2.6 times 0.991.
+// Decodes alone gain as well, up to four rounds of pieces by time: a piece that is dealt asks for no ticket, and there are fewer partials.  165 random steps
+// of up to 600 us on eight head layouts with such plans 1.03 times as fast on average (0.998 to 1.10; 249 decodes on 64-wide 32/4 heads 189 us and 175, 143
+// on 32/8 heads 261 and 252).  Beyond kRoundsAloneNs a workgroup the pieces get so long that the dies' different rates show: 17 steps of
+// 700 to 1270 us 1.004, 0.97 to 1.04.  Where the two rounds would not be two thirds full, few long contexts are left whole (288 on 64-wide 32/8 heads
+// in 602 pieces 133 us and 143).
 static const double kRoundsOver = 2.0;
+static const double kRoundsOverAlone = 4.0;
+static const double kRoundsAloneNs = 600000.0;
+static const double kRoundsFilled = 2.0 / 3;
 static const int64_t kHeadTokensMin = 256;
 static const int64_t kHeadTokensWhole = 1024;
 static const int64_t kHeadTokensBeside = 700;
@@ -442,13 +449,16 @@ static DecodeCut decode_cut(const int32_t* kind, const int32_t* ctx_len, int R, 
     return lo;
   };
   auto by_rounds = [&]() -> DecodeCut {      // by time, but lengthened to two rounds if that is close
+    const bool alone = n_pre == 0;
     const int64_t two_rounds = 2 * HFX_PLAN_WGS - n_pre;
-    if (!decode_dominated || n_pre == 0 || n_pre >= HFX_PLAN_WGS || n_dec * (Hkv / most) > HFX_PLAN_WGS) return by_time;
+    if (alone && (double)dec_tokens * Hkv * D * 4.0 > kRoundsAloneNs * HFX_PLAN_WGS * kDecodeBytesPerNs) return by_time;
+    if (!alone && (!decode_dominated || n_pre >= HFX_PLAN_WGS || n_dec * (Hkv / most) > HFX_PLAN_WGS)) return by_time;
     const uint32_t piece = (uint32_t)(by_time.tokens + kPair - 1) / kPair;
     const int64_t now = items(piece, most);
-    if (now <= two_rounds || (double)(now + n_pre) > kRoundsOver * (double)(2 * HFX_PLAN_WGS)) return by_time;
+    if (now <= two_rounds || (double)(now + n_pre) > (alone ? kRoundsOverAlone : kRoundsOver) * (double)(2 * HFX_PLAN_WGS)) return by_time;
     const uint32_t longer = shortest(piece, 4 * piece, most, two_rounds);
-    if (items(longer, most) > two_rounds) return by_time;
+    const int64_t then = items(longer, most);
+    if (then > two_rounds || (alone && (double)then < kRoundsFilled * (double)two_rounds)) return by_time;
     return {most, (int64_t)longer * kPair};
   };
   const int64_t room = n_pre == 0 ? HFX_PLAN_WGS : HFX_PLAN_WGS / 2 - n_pre;

@@ -214,6 +214,21 @@ def test_planner_covers_scaled_configs(lib, idx, scale):
     check_coverage(b, fill(b))
 
 
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,dealt", [
+    (32, 8, 128, 165, 300, 6000, True), (32, 4, 64, 288, 300, 9000, True), (8, 8, 128, 400, 200, 4000, True),
+    (32, 8, 128, 288, 300, 9000, False),       # a workgroup would stream for more than 600 us
+    (32, 8, 64, 288, 4000, 4011, False),       # equal contexts: whole, or in more pieces than are dealt
+    (32, 8, 128, 600, 2000, 2001, False)])     # more contexts than are dealt
+def test_decodes_alone_are_dealt_whole_rounds(lib, Hq, Hkv, D, n, lo, hi, dealt):
+    """Decode pieces of a step without prefills are lengthened until the two dealt rounds hold them all, where these are then filled."""
+    c = np.random.default_rng(5).integers(lo, hi, n)
+    b = lengths_only(Hq, Hkv, D, [DECODE] * n, [1] * n, c)
+    d = fill(b)
+    check_coverage(b, d)
+    items = d["header"].n_items
+    assert 2 * 1024 // 3 <= items <= 1024 if dealt else items > 1024
+
+
 def test_planner_covers_full_size_lengths(lib):
     # full-size length mixes without materialising pools
     g = np.random.default_rng(0)
