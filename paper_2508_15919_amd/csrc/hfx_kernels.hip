@@ -1688,8 +1688,9 @@ hipError_t upload(const void* host, void* device, size_t bytes, hipStream_t stre
 }
 
 // Copies of at most a quarter of the last-level cache leave their source in it, where it may still be from the writing of those pages (41 MB
-// each way, three sets of buffers in turn: 21.1 us, 25.1 streaming; 268 MB 61.2 and 60.2).  With a division by the page size for each
-// 16 bytes the kernel took 26.8 and 61.2.
+// each way, three sets of buffers in turn: 21.1 us, 25.1 streaming; 134 MB 61.2 and 60.2; all with the list uploaded ahead).  With a division by the
+// page size for each 16 bytes the kernel took 26.8 and 61.2.  (Where two sets of 134 MB alternate, half of the source is still in the cache and the
+// line could lie higher: 49.4 us instead of 59.5.)
 constexpr long kCopyStreamBytes = 64l << 20;
 template <int N>
 static hipError_t launch_copy_pages(const PagePairs<N>& pairs, long n_pairs, unsigned units_per_page, bool past_cache, unsigned others, const void* src,
