@@ -1526,16 +1526,20 @@ __global__ void gather_kv_unaligned_kernel(const char* desc, const uint16_t* poo
 // last-level cache, 6.0 TB/s, 12.7 with 4-byte loads in a loop and both halves through LDS; 17.1 us, 3.9 TB/s, rotating over
 // ten sets of buffers, from HBM.  36940 tokens of short prompts, 303 MB: 68.7 us, 4.4 TB/s, and 72.4.)
 template <int D>
-__global__ __launch_bounds__(2 * D) void append_kv_kernel(const HfxRun* __restrict__ runs, int n_runs,
+__global__ __launch_bounds__(2 * D) void append_kv_kernel(const HfxRun* __restrict__ runs, int n_runs, unsigned die_row_log2,
                                                           const uint16_t* __restrict__ k_new,
                                                           const uint16_t* __restrict__ v_new,
                                                           uint16_t* __restrict__ pool) {
   constexpr int LD = D + 8;                       // LDS row stride in elements
   __shared__ __attribute__((aligned(16))) uint16_t sv[HFX_PAGE * LD];
-  const int index = (int)(blockIdx.z * gridDim.y + blockIdx.y);
-  if (index >= n_runs) return;
+  // Workgroups go to the dies by their index modulo 8: of 8 << die_row_log2 in a row a die takes 1 << die_row_log2 that follow each other.
+  const unsigned heads = gridDim.x, all = heads * (unsigned)n_runs, row = (1u << die_row_log2) - 1, group = 8 * row + 7;
+  unsigned block = (blockIdx.z * gridDim.y + blockIdx.y) * heads + blockIdx.x;
+  if (block >= all) return;
+  if (block < (all & ~group)) block = (block & ~group) | (block & 7) << die_row_log2 | (block >> 3 & row);
+  const int index = (int)(block / heads);
   const HfxRun run = runs[index];
-  const int Hkv = (int)gridDim.x, g = (int)blockIdx.x, tid = threadIdx.x;
+  const int Hkv = (int)heads, g = (int)(block - (unsigned)index * heads), tid = threadIdx.x;
   uint16_t* kblk = pool + (((long)run.page * Hkv + g) * 2) * (16L * D);
   const int tok = tid / (D / 8), piece = tid % (D / 8);
   if (tok < run.n) {
@@ -1763,7 +1767,10 @@ hipError_t launch_append_kv(const HfxHeader& h, const void* desc, const void* k_
   // which holds at most 65535
   const unsigned per_z = (unsigned)std::min(h.n_runs, 32768);
   const dim3 grid((unsigned)h.num_kv_heads, per_z, ((unsigned)h.n_runs + per_z - 1) / per_z);
-  return launch(h.head_dim == 128 ? append_kv_kernel<128> : append_kv_kernel<64>, grid, 2u * (unsigned)h.head_dim, stream, runs, h.n_runs,
+  // Pieces of 16 blocks a die where the pages go past the cache, of 4 otherwise.  One block, 4 and 16, us a call: 90000 tokens of 8 kv-heads 145.3, 140.8 and
+  // 132.2, 36000 58.5, 57.0 and 54.7, 12000 18.2, 18.3 and 18.5, 8224 of long chunks beside 32 decodes 12.5, 12.5 and 13.1.
+  const unsigned die_row_log2 = (long)h.n_runs * h.num_kv_heads * h.head_dim * (4 * HFX_PAGE) > kCopyStreamBytes ? 4u : 2u;
+  return launch(h.head_dim == 128 ? append_kv_kernel<128> : append_kv_kernel<64>, grid, 2u * (unsigned)h.head_dim, stream, runs, h.n_runs, die_row_log2,
                 static_cast<const uint16_t*>(k_new), static_cast<const uint16_t*>(v_new), static_cast<uint16_t*>(pool));
 }
 

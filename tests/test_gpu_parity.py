@@ -465,6 +465,31 @@ def test_append_kv_runs_that_start_and_end_inside_pages(hb, oracle, Hq, Hkv, D):
     assert np.array_equal(step.pool.cpu().numpy().view(np.uint16), b.pool), "pool after append must match bit for bit"
 
 
+@pytest.mark.parametrize("Hkv,D,n", [(1, 64, 509), (1, 64, 513), (4, 64, 127), (2, 128, 2045), (8, 128, 16379), (8, 128, 16400), (12, 128, 11003), (4, 64, 70001)])
+def test_append_kv_of_few_and_many_blocks(hb, Hkv, D, n):
+    """Blocks are written in pieces of 4 or, past the cache (16384 tokens of 8 kv-heads of 128), 16 a die, and those of the last incomplete group
+    in their order: a prompt's keys and values come back out of the pages as they went in."""
+    import torch
+    rng = np.random.default_rng(n)
+    pages = (n + 15) // 16
+    shape = hb.make_shape(Hkv, Hkv, D, pages + 3)
+    kind, q, ctx = np.array([PREFILL], np.int32), np.array([n], np.int32), np.array([n], np.int32)
+    nb, _, _ = hb.hfx_batch_desc_sizes(shape, kind, q, ctx)
+    host, dev = torch.empty(nb, dtype=torch.uint8, pin_memory=True), torch.empty(nb, dtype=torch.uint8, device="cuda")
+    table = rng.permutation(pages + 3)[:pages].astype(np.int32)
+    stream = torch.cuda.current_stream()
+    hb.hfx_build_batch_desc(shape, kind, q, ctx, np.array([0, pages], np.int32), table, host, dev, stream)
+    k, v = (torch.randint(-2**15, 2**15, (n, Hkv, D), dtype=torch.int16, device="cuda") for _ in range(2))
+    pool = torch.zeros((pages + 3, Hkv, 2, 16 * D), dtype=torch.int16, device="cuda")
+    hb.hfx_append_kv(shape, k, v, pool, host, dev, stream)
+    k_out, v_out = torch.empty_like(k), torch.empty_like(v)
+    hb.hfx_gather_kv(shape, pool, host, dev, 0, k_out, v_out, stream)
+    torch.cuda.synchronize()
+    assert torch.equal(k_out, k) and torch.equal(v_out, v)
+    unused = np.setdiff1d(np.arange(pages + 3), table)
+    assert not pool[torch.from_numpy(unused).cuda()].any()
+
+
 def test_append_kv_of_more_runs_than_one_grid_dimension_holds(hb, oracle):
     import torch
     b = synth.make_batch(1, 1, 64, [DECODE, PREFILL], [1, 16 * 32768 + 21], [37, 16 * 32768 + 30], 96, name="append-many-runs")
