@@ -231,6 +231,7 @@ def hfx_append_kv(shape: hfx_shape, k_new, v_new, kv_pool, host_desc, device_des
 
 def hfx_copy_pages(shape: hfx_shape, src_pool, dst_pool, dst_num_pages: int, src_ids, dst_ids, host_stage,
                    device_stage, stream=None, stage_bytes=None) -> None:
+    src_ids, dst_ids = _as_int32(src_ids), _as_int32(dst_ids)       # (a single number is an array of one)
     assert len(src_ids) == len(dst_ids)
     if stage_bytes is None:
         stage_bytes = min(_nbytes(host_stage), _nbytes(device_stage))

@@ -103,6 +103,18 @@ def test_validation_of_the_public_calls():
         hb.hfx_append_kv(shape, 16, 16, 16, ref, 16, stream="none")
 
 
+@pytest.mark.parametrize("one", [lambda i: i, np.int64, np.int32, lambda i: np.array(i, np.int32), lambda i: torch.tensor(i)])
+def test_a_single_page_is_a_list_of_one(one):
+    """hfx_copy_pages with a number in the place of a list: 40 is outside the pool, 3 is inside, and the call gets as far as the staging buffers' size."""
+    shape = hb.make_shape(8, 2, 64, 32)
+    for i, code in ((40, hb.HFX_ERR_PAGE_ID), (3, hb.HFX_ERR_BUFSIZE)):
+        with pytest.raises(hb.HfxError) as e:
+            hb.hfx_copy_pages(shape, 16, 16, 32, one(i), one(5), np.zeros(16, np.uint8), 16, stage_bytes=8 if i == 40 else 7)
+        assert e.value.code == code
+    with pytest.raises(AssertionError):
+        hb.hfx_copy_pages(shape, 16, 16, 32, one(1), [2, 3], np.zeros(16, np.uint8), 16, stage_bytes=16)
+
+
 def test_several_threads(fill):
     shape, ref = reference()
     wrong = []
