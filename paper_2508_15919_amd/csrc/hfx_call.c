@@ -33,12 +33,19 @@ static PyObject *s_data_ptr, *s_nbytes, *s_cuda_stream;
 // What a call holds on to until it is done.
 typedef struct {
   Py_buffer views[MAX_HELD];
-  int n;
+  void* copies[MAX_HELD];
+  int n, n_copies;
 } Held;
 
 static void release(Held* held) {
   while (held->n > 0) PyBuffer_Release(&held->views[--held->n]);
+  while (held->n_copies > 0) PyMem_Free(held->copies[--held->n_copies]);
 }
+
+// Arrays of fewer bytes are copied while the interpreter lock is held: the library checks them and reads them again, and another thread
+// may write to the caller's in between.  Larger ones are the caller's to leave alone during the call.  (The copies of the five arrays of a step of four
+// requests take 0.03 us of 0.71, those of 40 with 3500 pages, 15 KB, 0.17 of 0.85.)
+enum { COPY_BELOW = 1 << 14 };
 
 static int integer(PyObject* o, uint64_t* out) {
   if (PyLong_Check(o)) {
@@ -93,7 +100,7 @@ static int plain_int32(PyObject* o, Py_buffer* view) {
 }
 
 static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* address, uint64_t* length, int want_length) {
-  if (held->n == MAX_HELD) {
+  if (held->n + held->n_copies == MAX_HELD) {
     PyErr_SetString(PyExc_SystemError, "too many arrays");
     return -1;
   }
@@ -116,6 +123,18 @@ static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* ad
     if (bad) return -1;
     *length = (uint64_t)n;
   }
+  if (view->len < COPY_BELOW) {
+    void* copy = PyMem_Malloc((size_t)view->len);
+    if (copy && view->len > 0) memcpy(copy, view->buf, (size_t)view->len);
+    PyBuffer_Release(view);
+    if (!copy) {
+      PyErr_NoMemory();
+      return -1;
+    }
+    held->copies[held->n_copies++] = copy;
+    *address = (uint64_t)(uintptr_t)copy;
+    return 0;
+  }
   *address = (uint64_t)(uintptr_t)view->buf;
   held->n++;
   return 0;
@@ -133,7 +152,7 @@ static PyObject* call(PyObject* callable, PyObject* const* args, size_t nargsf, 
   uint64_t a[MAX_ARGS + 2] = {0};
   int n = 0, bad = 0;
   Held held;
-  held.n = 0;
+  held.n = held.n_copies = 0;
   for (int i = 0; i < self->n_kinds && !bad; ++i) {
     PyObject* o = args[i];
     switch (self->kinds[i]) {

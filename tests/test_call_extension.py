@@ -115,6 +115,32 @@ def test_a_single_page_is_a_list_of_one(one):
         hb.hfx_copy_pages(shape, 16, 16, 32, one(1), [2, 3], np.zeros(16, np.uint8), 16, stage_bytes=16)
 
 
+@pytest.mark.parametrize("form", ["int32", "list", "tensor", "strided"])
+@pytest.mark.parametrize("n", [0, 1, 300, 4095])
+def test_small_arrays_are_read_before_the_lock_is_released(n, form):
+    """What a call checks is what it uses: arrays of less than 16 KB that change after it has begun are seen as they were.  (The function called here
+    changes the caller's array and then looks at its arguments.)"""
+    from paper_2508_15919_amd import _hfxcall
+    base = np.arange(1, n + 1, dtype=np.int32)
+    given = FORMS[form](base)
+    if form == "tensor":
+        given = torch.from_numpy(base)
+    seen = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p)
+    def look(length, first, second):
+        if form in ("int32", "strided"):
+            given[:] = -1
+        base[:] = -1
+        seen.append([length] + [np.ctypeslib.as_array(ctypes.cast(p, ctypes.POINTER(ctypes.c_int32)), (n,)).tolist() if n else p != 0 for p in (first, second)])
+        return 7
+
+    call = _hfxcall.Caller(ctypes.cast(look, ctypes.c_void_p).value, "KA", hb.hfx_shape, hb._ptr, hb._as_int32)
+    assert call(given, given) == 7
+    was = list(range(1, n + 1)) if n else True
+    assert seen == [[n, was, was]]
+
+
 def test_several_threads(fill):
     shape, ref = reference()
     wrong = []
