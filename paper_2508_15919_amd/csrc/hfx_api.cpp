@@ -210,23 +210,26 @@ hfx_status hfx_copy_pages(const hfx_shape* shape, const void* src_pool, void* ds
   if (!src_pool || !dst_pool || !src_ids || !dst_ids || !host_stage || !device_stage) return HFX_ERR_NULL;
   if (stage_bytes < 8ull * (size_t)num_pairs) return HFX_ERR_BUFSIZE;
   if (!aligned16(src_pool) || !aligned16(dst_pool) || !aligned16(device_stage)) return HFX_ERR_ALIGN;
-  // a destination page is written once; inside one pool it is not read either
+  // Each id is read once: what has been checked is what is copied, whatever happens to the caller's lists meanwhile.
+  // A destination page is written once; inside one pool it is not read either.
   static thread_local std::vector<uint8_t> mark;
+  static thread_local std::vector<int32_t> ids;
   mark.assign((size_t)dst_num_pages, 0);
+  ids.resize(2 * (size_t)num_pairs);
   for (int i = 0; i < num_pairs; ++i) {
-    if (src_ids[i] < 0 || src_ids[i] >= shape->num_pages || dst_ids[i] < 0 || dst_ids[i] >= dst_num_pages)
-      return HFX_ERR_PAGE_ID;
-    if (mark[(size_t)dst_ids[i]]) return HFX_ERR_PAGES;
-    mark[(size_t)dst_ids[i]] = 1;
+    const int32_t from = src_ids[i], to = dst_ids[i];
+    if (from < 0 || from >= shape->num_pages || to < 0 || to >= dst_num_pages) return HFX_ERR_PAGE_ID;
+    if (mark[(size_t)to]) return HFX_ERR_PAGES;
+    mark[(size_t)to] = 1;
+    ids[2 * (size_t)i] = from;
+    ids[2 * (size_t)i + 1] = to;
   }
   if (src_pool == dst_pool)
-    for (int i = 0; i < num_pairs; ++i)
-      if (src_ids[i] < dst_num_pages && mark[(size_t)src_ids[i]]) return HFX_ERR_PAGES;
-  int32_t* stage = static_cast<int32_t*>(host_stage);
-  for (int i = 0; i < num_pairs; ++i) {
-    stage[2 * i] = src_ids[i];
-    stage[2 * i + 1] = dst_ids[i];
-  }
+    for (int i = 0; i < num_pairs; ++i) {
+      const int32_t from = ids[2 * (size_t)i];
+      if (from < dst_num_pages && mark[(size_t)from]) return HFX_ERR_PAGES;
+    }
+  std::memcpy(host_stage, ids.data(), 8 * (size_t)num_pairs);
   const unsigned units_per_page = (unsigned)(shape->num_kv_heads * 2 * HFX_PAGE * shape->head_dim * 2 / 16);
   if (hfx::copy_pages(host_stage, device_stage, num_pairs, units_per_page, src_pool, dst_pool, static_cast<hipStream_t>(stream)) != hipSuccess)
     return HFX_ERR_DEVICE;

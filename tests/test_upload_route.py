@@ -63,7 +63,11 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* s, hipStream_t* q
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 2; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void** p, const void*) { static char scratch[256]; *p = scratch; return hipSuccess; }
-hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+static bool page_list;
+static int32_t launched[6];                   // what a launch of the page copy carries
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void** args, size_t, hipStream_t) {
+  if (page_list) std::memcpy(launched, args[0], sizeof launched);
   if (fail_launch) return (hipError_t)(pending = hipErrorInvalidConfiguration);
   ++launches;
   return hipSuccess;
@@ -101,6 +105,14 @@ int main(int, char** v) {
   if (what == "gather unaligned") st = hfx_gather_kv(&shape, any, host, dev, 0, any + 2, any, stream);
   if (what == "append") st = hfx_append_kv(&shape, any, any, any, host, dev, stream);
   if (what == "pages") st = hfx_copy_pages(&shape, any, any + 4096, 8, 2, ids, ids, host, dev, 4096, stream);
+  if (what == "shared pages") {                 // the list of source pages lies in the staging buffer, between what is written there
+    int32_t* stage = (int32_t*)host;
+    const int32_t to[3] = {50, 60, 70};
+    for (int i = 0; i < 3; ++i) stage[1 + i] = 1 + i;
+    page_list = true;
+    st = hfx_copy_pages(&shape, any, any + 4096, 100, 3, stage + 1, to, host, dev, 4096, stream);
+    for (int i = 0; i < 6; ++i) std::printf("%d/%d ", stage[i], launched[i]);
+  }
   std::printf("%d %s pending %d\n", st, launches && copies ? "copy and kernel" : launches ? "kernel" : copies ? "copy" : "nothing", pending);
 }
 """
@@ -166,3 +178,8 @@ def test_an_unread_error_does_not_disturb_the_runtimes_copy(program):
 @pytest.mark.parametrize("entry", ENTRIES)
 def test_streams_that_are_named_and_not_made(program, handle, entry):
     assert program(handle=handle, entry=entry) == "0 kernel pending 0"
+
+
+def test_page_ids_are_read_once(program):
+    """Ids that change while they are put down (here by that itself) do not get past the check: 60 and 70 are pages of the destination alone."""
+    assert program(entry="shared pages") == "1/1 50/50 2/2 60/60 3/3 70/70 0 kernel pending 0"
