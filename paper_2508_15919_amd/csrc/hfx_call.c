@@ -30,7 +30,7 @@ typedef struct {
 
 static PyObject *s_data_ptr, *s_nbytes, *s_cuda_stream;
 
-// What a call holds on to until it is done.
+// What a call holds on to until it is done: of each argument of kind S, K or A one thing, and caller_init sees to it that there are no more than MAX_HELD.
 typedef struct {
   Py_buffer views[MAX_HELD];
   void* copies[MAX_HELD];
@@ -100,10 +100,6 @@ static int plain_int32(PyObject* o, Py_buffer* view) {
 }
 
 static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* address, uint64_t* length, int want_length) {
-  if (held->n + held->n_copies == MAX_HELD) {
-    PyErr_SetString(PyExc_SystemError, "too many arrays");
-    return -1;
-  }
   Py_buffer* view = &held->views[held->n];
   if (plain_int32(o, view)) {
     *length = (uint64_t)view->shape[0];
@@ -215,14 +211,15 @@ static int caller_init(PyObject* o, PyObject* args, PyObject* kwargs) {
     return -1;
   }
   if (!PyArg_ParseTuple(args, "KsO!OO", &address, &kinds, &PyType_Type, &structure, &address_of, &as_int32)) return -1;
-  int n = 0, words = 0;
+  int n = 0, words = 0, held = 0;
   for (; kinds[n]; ++n) {
     if (n == MAX_ARGS || !strchr("SPBKAizs", kinds[n])) break;
     words += kinds[n] == 'B' || kinds[n] == 'K' ? 2 : 1;
+    held += strchr("SKA", kinds[n]) != NULL;
     self->kinds[n] = kinds[n];
   }
-  if (kinds[n] || words > 12 || address == 0) {
-    PyErr_SetString(PyExc_ValueError, "kinds of at most 12 arguments out of SPBKAizs, and an address");
+  if (kinds[n] || words > 12 || held > MAX_HELD || address == 0) {
+    PyErr_SetString(PyExc_ValueError, "kinds of at most 12 arguments out of SPBKAizs, at most 8 of them SKA, and an address");
     return -1;
   }
   self->n_kinds = n;

@@ -72,7 +72,7 @@ def test_number_of_arguments(fill):
     with pytest.raises(TypeError):
         fill(shape, KIND, Q, CTX, INDPTR, PAGES, blob=ref)
     from paper_2508_15919_amd import _hfxcall
-    for kinds, address in (("SX", 1), ("S", 0), ("B" * 7, 1), ("P" * 17, 1)):
+    for kinds, address in (("SX", 1), ("S", 0), ("B" * 7, 1), ("P" * 17, 1), ("S" * 9, 1), ("SSSKKKAAA", 1), ("A" * 12, 1)):
         with pytest.raises(ValueError):
             _hfxcall.Caller(address, kinds, hb.hfx_shape, hb._ptr, hb._as_int32)
     with pytest.raises(TypeError):
