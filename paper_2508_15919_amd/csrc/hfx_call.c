@@ -4,6 +4,9 @@
 //
 // Through ctypes a call of the attention took 2.3 us of marshalling (the launch itself takes 2.5), the description of a step of four
 // requests 3.8; here they take 0.7 and 1.0.  Objects that are not met in such loops go to the Python functions that took all before.
+#if !defined(__x86_64__) || defined(__ILP32__) || defined(_WIN32)
+#error "arguments are passed as 64-bit integers, by the System V convention of x86-64"
+#endif
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <stddef.h>

@@ -1,6 +1,9 @@
 """The extension that marshals arguments (csrc/hfx_call.c): every form of an argument that the ctypes calls took is taken, and what they refused is
 refused.  On functions of the library that run on the host."""
 import ctypes
+import os
+import shutil
+import subprocess
 import threading
 
 import numpy as np
@@ -139,6 +142,15 @@ def test_small_arrays_are_read_before_the_lock_is_released(n, form):
     assert call(given, given) == 7
     was = list(range(1, n + 1)) if n else True
     assert seen == [[n, was, was]]
+
+
+@pytest.mark.parametrize("target", [["-U__x86_64__"], ["-D__ILP32__"], ["-D_WIN32"]])
+def test_other_calling_conventions_are_refused(target):
+    if shutil.which("gcc") is None:
+        pytest.skip("gcc not available")
+    source = os.path.join(os.path.dirname(hb.LIB_PATH), "csrc", "hfx_call.c")
+    res = subprocess.run(["gcc", "-E", "-o", os.devnull, *target, source], capture_output=True, text=True)
+    assert res.returncode != 0 and "System V convention" in res.stderr
 
 
 def test_several_threads(fill):
