@@ -9,7 +9,8 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhfxattn.so")
-CALL_LIB = os.path.join(HERE, "_hfxcall.so")
+# The name says for which Python it was built, so that another one does not load it.
+CALL_LIB = os.path.join(HERE, "_hfxcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["hfx_kernels.hip", "hfx_api.cpp", "hfx_plan.cpp", "hfx_sched.cpp"]
 # -fno-honor-nans: no floating-point operation in the kernels is ever fed a NaN (possibly-NaN scores
 # are masked through integer selects first), and without it every max carries a canonicalising twin.
@@ -47,6 +48,9 @@ def build_call(verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
+    untagged = os.path.join(HERE, "_hfxcall.so")      # of an earlier build, which any Python would load
+    if os.path.exists(untagged):
+        os.remove(untagged)
     if res.returncode != 0:
         raise RuntimeError("the call extension did not build:\n" + res.stderr)
     return CALL_LIB

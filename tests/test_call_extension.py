@@ -4,6 +4,7 @@ import ctypes
 import os
 import shutil
 import subprocess
+import sysconfig
 import threading
 
 import numpy as np
@@ -142,6 +143,14 @@ def test_small_arrays_are_read_before_the_lock_is_released(n, form):
     assert call(given, given) == 7
     was = list(range(1, n + 1)) if n else True
     assert seen == [[n, was, was]]
+
+
+def test_the_extension_is_of_this_python(fill):
+    """Another interpreter, whose type records may be laid out otherwise, does not find it."""
+    from paper_2508_15919_amd import _hfxcall
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert suffix != ".so" and os.path.basename(_hfxcall.__file__) == "_hfxcall" + suffix
+    assert not os.path.exists(os.path.join(os.path.dirname(_hfxcall.__file__), "_hfxcall.so"))
 
 
 @pytest.mark.parametrize("target", [["-U__x86_64__"], ["-D__ILP32__"], ["-D_WIN32"]])
