@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import types
 
 import numpy as np
 
@@ -97,7 +98,18 @@ def load() -> ctypes.CDLL:
                                          ctypes.c_int32, i32p, i32p, i32p, i32p, i32p,
                                          ctypes.POINTER(hfx_decision)]
         lib.hfx_compose_step.restype = ctypes.c_int32
-        # The calls a serving loop makes: their arguments are marshalled in C (csrc/hfx_call.c, which says what the letters mean).
+        _lib = lib
+    return _lib
+
+
+_calls = None
+
+
+def _serving() -> types.SimpleNamespace:
+    """The calls a serving loop makes: their arguments are marshalled in C (csrc/hfx_call.c, which says what the letters mean)."""
+    global _calls
+    if _calls is None:
+        lib = load()
         try:
             from . import _hfxcall
         except ImportError as e:
@@ -105,15 +117,12 @@ def load() -> ctypes.CDLL:
                                "`python -m paper_2508_15919_amd.build`") from e
 
         def caller(function, kinds):
-            return _hfxcall.Caller(ctypes.cast(function, vp).value, kinds, hfx_shape, _ptr, _as_int32)
-        lib.call_build = caller(lib.hfx_build_batch_desc, "SKAAAABBs")
-        lib.call_attention = caller(lib.hfx_mixed_paged_attention, "SPPPPBPs")
-        lib.call_attention_static = caller(lib.hfx_mixed_paged_attention_static, "SPPPPPs")
-        lib.call_gather = caller(lib.hfx_gather_kv, "SPPPiPPs")
-        lib.call_append = caller(lib.hfx_append_kv, "SPPPPPs")
-        lib.call_copy_pages = caller(lib.hfx_copy_pages, "SPPiKAPPzs")
-        _lib = lib
-    return _lib
+            return _hfxcall.Caller(ctypes.cast(function, ctypes.c_void_p).value, kinds, hfx_shape, _ptr, _as_int32)
+        _calls = types.SimpleNamespace(
+            build=caller(lib.hfx_build_batch_desc, "SKAAAABBs"), attention=caller(lib.hfx_mixed_paged_attention, "SPPPPBPs"),
+            attention_static=caller(lib.hfx_mixed_paged_attention_static, "SPPPPPs"), gather=caller(lib.hfx_gather_kv, "SPPPiPPs"),
+            append=caller(lib.hfx_append_kv, "SPPPPPs"), copy_pages=caller(lib.hfx_copy_pages, "SPPiKAPPzs"))
+    return _calls
 
 
 def _i32(a):
@@ -198,33 +207,33 @@ def hfx_fill_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pa
 
 def hfx_build_batch_desc(shape: hfx_shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc,
                          stream=None) -> None:
-    rc = (_lib or load()).call_build(shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc, stream)
+    rc = (_calls or _serving()).build(shape, kind, q_len, ctx_len, bt_indptr, bt_pages, host_desc, device_desc, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_build_batch_desc")
 
 
 def hfx_mixed_paged_attention(shape: hfx_shape, q, kv_pool, host_desc, device_desc, workspace, out,
                               stream=None) -> None:
-    rc = (_lib or load()).call_attention(shape, q, kv_pool, host_desc, device_desc, workspace, out, stream)
+    rc = (_calls or _serving()).attention(shape, q, kv_pool, host_desc, device_desc, workspace, out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_mixed_paged_attention")
 
 
 def hfx_mixed_paged_attention_static(shape: hfx_shape, q, kv_pool, host_desc, device_desc, out, stream=None) -> None:
-    rc = (_lib or load()).call_attention_static(shape, q, kv_pool, host_desc, device_desc, out, stream)
+    rc = (_calls or _serving()).attention_static(shape, q, kv_pool, host_desc, device_desc, out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_mixed_paged_attention_static")
 
 
 def hfx_gather_kv(shape: hfx_shape, kv_pool, host_desc, device_desc, request: int, k_out, v_out,
                   stream=None) -> None:
-    rc = (_lib or load()).call_gather(shape, kv_pool, host_desc, device_desc, request, k_out, v_out, stream)
+    rc = (_calls or _serving()).gather(shape, kv_pool, host_desc, device_desc, request, k_out, v_out, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_gather_kv")
 
 
 def hfx_append_kv(shape: hfx_shape, k_new, v_new, kv_pool, host_desc, device_desc, stream=None) -> None:
-    rc = (_lib or load()).call_append(shape, k_new, v_new, kv_pool, host_desc, device_desc, stream)
+    rc = (_calls or _serving()).append(shape, k_new, v_new, kv_pool, host_desc, device_desc, stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_append_kv")
 
@@ -235,7 +244,7 @@ def hfx_copy_pages(shape: hfx_shape, src_pool, dst_pool, dst_num_pages: int, src
     assert len(src_ids) == len(dst_ids)
     if stage_bytes is None:
         stage_bytes = min(_nbytes(host_stage), _nbytes(device_stage))
-    rc = (_lib or load()).call_copy_pages(shape, src_pool, dst_pool, dst_num_pages, src_ids, dst_ids, host_stage, device_stage, stage_bytes,
+    rc = (_calls or _serving()).copy_pages(shape, src_pool, dst_pool, dst_num_pages, src_ids, dst_ids, host_stage, device_stage, stage_bytes,
                                           stream)
     if rc != HFX_OK:
         raise HfxError(rc, "hfx_copy_pages")

@@ -4,6 +4,7 @@ import ctypes
 import os
 import shutil
 import subprocess
+import sys
 import sysconfig
 import threading
 
@@ -151,6 +152,29 @@ def test_the_extension_is_of_this_python(fill):
     suffix = sysconfig.get_config_var("EXT_SUFFIX")
     assert suffix != ".so" and os.path.basename(_hfxcall.__file__) == "_hfxcall" + suffix
     assert not os.path.exists(os.path.join(os.path.dirname(_hfxcall.__file__), "_hfxcall.so"))
+
+
+WITHOUT = """
+import sys
+sys.modules["paper_2508_15919_amd._hfxcall"] = None          # importing it fails
+import numpy as np
+from paper_2508_15919_amd import binding as hb
+shape = hb.make_shape(8, 2, 64, 32)
+size = hb.hfx_batch_desc_sizes(shape, [0], [1], [37])[0]
+hb.hfx_fill_batch_desc(shape, [0], [1], [37], [0, 3], [0, 1, 2], np.zeros(size, np.uint8))
+assert hb.hfx_token_budget(1.0, 0.5, hb.hfx_latency_model(0.01, 0.001, 0.1)) > 0
+assert len(hb.hfx_compose_step(1.0, 0.5, hb.hfx_latency_model(0.01, 0.001, 0.1), [5], [10])) == 5
+try:
+    hb.hfx_append_kv(shape, 16, 16, 16, np.zeros(size, np.uint8), 16)
+except RuntimeError as e:
+    print(e)
+"""
+
+
+def test_calls_that_do_not_use_the_extension_do_not_need_it():
+    root = os.path.dirname(os.path.dirname(hb.LIB_PATH))
+    res = subprocess.run([sys.executable, "-c", WITHOUT], cwd=root, capture_output=True, text=True, timeout=120)
+    assert res.returncode == 0 and "the call extension is missing" in res.stdout, res.stderr
 
 
 @pytest.mark.parametrize("target", [["-U__x86_64__"], ["-D__ILP32__"], ["-D_WIN32"]])
