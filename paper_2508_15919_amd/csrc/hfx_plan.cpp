@@ -631,15 +631,9 @@ static const double kSharedTail = 0.06;
 // of each request with a prompt; all: that of all items.
 static void queue_per_die(const uint64_t* sorted, size_t n, int Hkv, double all, Plan* out) {
   Plan& P = *out;
-  struct Stream {
-    uint32_t first, pieces;      // its pieces
-    double work;                 // of one of them
-  };
-  static_assert(sizeof(Stream) == 2 * sizeof(uint64_t), "kept in unit_keys");
   const double most = all / (kDieUnits * HFX_QUEUE_CLASSES);
-  std::vector<uint64_t>& store = P.unit_keys;
-  store.resize(2 * P.stream_ns.size() * (size_t)Hkv);
-  Stream* const streams = reinterpret_cast<Stream*>(store.data());
+  std::vector<Stream>& streams = P.streams;
+  streams.resize(P.stream_ns.size() * (size_t)Hkv);
   uint32_t n_pieces = 0;
   for (size_t r = 0, st = 0; r < P.stream_ns.size(); ++r) {
     const double pieces = std::min(std::max(std::ceil(P.stream_ns[r] / most), 1.0), 1024.0);

@@ -16,6 +16,12 @@ struct ItemNote {
   float frac;        // of a prefill item: its row tile's place in the chunk, in [0, 1)
 };
 
+// The (request, kv-head) pairs of the prompts, as the queue per die cuts them.
+struct Stream {
+  uint32_t first, pieces;      // its pieces
+  double work;                 // of one of them
+};
+
 struct Plan {
   std::vector<HfxReq> reqs;
   std::vector<HfxItem> items;
@@ -35,6 +41,7 @@ struct Plan {
   std::vector<uint32_t> unit_fill, unit_start;
   std::vector<uint64_t> unit_keys;
   std::vector<double> stream_ns;        // of each request with a prompt: time of the items that read the keys of one of its kv-heads
+  std::vector<Stream> streams;          // of those, each kv-head
   std::vector<uint32_t> die_lists[HFX_QUEUE_CLASSES];
   std::vector<int32_t> queue;           // order in which items are taken, if it is not theirs; as many as items, or none
   std::vector<float> cut_cost, cut_sort, cut_load;   // trial of a cut: item times, sort scratch, CU loads
