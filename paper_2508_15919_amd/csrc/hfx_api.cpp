@@ -65,6 +65,8 @@ hfx_status run_attention(const HfxHeader& h, const void* q, const void* kv_pool,
     return HFX_ERR_ALIGN;
   if (h.n_items < 1) return HFX_ERR_DESC;
   if ((h.queue_classes != 1 && h.queue_classes != HFX_QUEUE_CLASSES) || h.n_ctrl != HFX_CTRL_WORDS) return HFX_ERR_DESC;
+  // positions that belong to dies: the kernel hands them out without looking at the end of the queue
+  if (h.die_items > (uint32_t)h.n_items || h.die_items % HFX_QUEUE_CLASSES != 0) return HFX_ERR_DESC;
   int grid = 0;
   st = persistent_grid(h.head_dim, &grid);
   if (st != HFX_OK) return st;

@@ -693,6 +693,22 @@ def test_validation_errors(lib):
     assert lib.hfx_mixed_paged_attention(sh, 16, 16, bent.ctypes.data, 16, ws, 1 << 40, 16, None) == hb.HFX_ERR_DESC
 
 
+def test_a_header_with_impossible_die_positions_is_refused(lib):
+    """die_items says which queue positions are handed out by die: a multiple of 8, and none past the end of the queue."""
+    b = lengths_only(8, 1, 128, [PREFILL] * 170, [300] * 170, [300] * 170)
+    shape = hb.make_shape(8, 1, 128, b.num_pages)
+    size, _, ws = hb.hfx_batch_desc_sizes(shape, b.kind, b.q_len, b.ctx_len)
+    host = np.zeros(size, np.uint8)
+    hb.hfx_fill_batch_desc(shape, b.kind, b.q_len, b.ctx_len, b.bt_indptr, b.bt_pages, host)
+    h = hb.parse_desc(host)["header"]
+    assert 0 < h.die_items < h.n_items
+    off = hb.DescHeader.die_items.offset
+    for wrong in (h.die_items + 1, (h.n_items + 8) // 8 * 8, 0xfffffff8):
+        bent = host.copy()
+        bent[off:off + 4] = np.frombuffer(np.uint32(wrong).tobytes(), np.uint8)
+        assert lib.hfx_mixed_paged_attention(ctypes.byref(shape), 16, 16, bent.ctypes.data, 16, 16, ws, 16, None) == hb.HFX_ERR_DESC, wrong
+
+
 def test_extra_reserved_pages_are_ignored(lib):
     b = synth.make_batch(4, 2, 64, [DECODE, PREFILL], [1, 20], [37, 50], 3, extra_pages_per_request=3)
     d = fill(b)
