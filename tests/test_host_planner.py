@@ -296,6 +296,20 @@ def test_queue_per_die_where_few_row_tiles_read_the_same_keys(lib, Hq, Hkv, D, n
         check_class_order(b, d["items"])
 
 
+@pytest.mark.parametrize("Hq,Hkv,n,longer,items,per_die", [
+    (32, 8, 87, 0, 1392, False), (32, 8, 88, 0, 1408, True), (8, 8, 44, 0, 1056, False), (16, 16, 87, 0, 4176, True), (32, 8, 80, 400, 1384, False), (32, 8, 89, 400, 1528, False),
+    (32, 8, 90, 400, 1544, True), (16, 4, 160, 0, 1280, True), (16, 4, 129, 0, 1032, True), (8, 2, 260, 0, 1040, True)])
+def test_queue_per_die_starts_where_there_is_something_behind_the_dealt_items(lib, Hq, Hkv, n, longer, items, per_die):
+    """Prompts of two row tiles or more, alone (a share of more than 1.5 of the longest item) or beside a longer one (less): with a multiple of 8 kv-heads from 2.75 and 3
+    rounds on, because dealt items of a stream meet on a die as they are; with fewer kv-heads whenever items are left for the counters."""
+    q = [64 if Hq > Hkv else 257 if Hq == 8 else 300] * n + ([longer] if longer else [])
+    b = lengths_only(Hq, Hkv, 128, [PREFILL] * len(q), q, q)
+    d = fill(b)
+    assert d["header"].n_items == items
+    assert (d["queue"] is not None) == per_die
+    check_coverage(b, d)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,decodes,per_die", [
     (32, 8, 128, 64, 20, 700, 0, True), (32, 4, 64, 60, 100, 900, 20, True), (24, 8, 128, 20, 500, 3000, 0, True), (8, 8, 128, 120, 50, 600, 5, True),
     (8, 1, 128, 170, 20, 500, 0, True), (32, 8, 128, 4, 1500, 2500, 0, True), (32, 8, 128, 3, 2500, 2500, 0, False), (8, 1, 128, 25, 1000, 2000, 0, False),
