@@ -162,13 +162,14 @@ def small_pool_batch(rng, Hq, Hkv, D, kind, q_len, ctx_len, name, n_pages=700):
 
 @pytest.mark.parametrize("n", [1024, 1025, 1031, 1600])
 def test_queue_counters_of_short_queues(hb, oracle, n):
-    """One item a prompt: exactly the two dealt rounds, one item more, one for some of the dies, and more than one for each workgroup.
-    Every launch finds the counters as the first one did."""
+    """One item a prompt, no two of which share keys, so that all behind the dealt ones come from the shared counter: exactly the two dealt rounds, one item more,
+    a few more, and more than one for each workgroup.  Every launch finds the counters as the first one did."""
     rng = np.random.default_rng(n)
     q = rng.integers(1, 33, n)
     b = small_pool_batch(rng, 4, 1, 64, [PREFILL] * n, q, q + rng.integers(0, 40, n), f"queue-{n}")
     step, bits = check_full(hb, oracle, b)
-    assert hb.parse_desc(step.host_desc.numpy())["header"].n_items == n
+    h = hb.parse_desc(step.host_desc.numpy())["header"]
+    assert h.n_items == n and h.die_items == 0
     for _ in range(2):
         step.out.zero_()
         step.run()
@@ -185,6 +186,25 @@ def test_queue_per_die_of_many_prompts(hb, oracle, Hq, Hkv, D, n, longest, decod
     step, bits = check_full(hb, oracle, b)
     d = hb.parse_desc(step.host_desc.numpy())
     assert d["queue"] is not None and 1024 < d["header"].die_items < d["header"].n_items
+    for _ in range(3):
+        step.out.zero_()
+        step.run()
+        assert np.array_equal(step.out_bits(), bits)
+    assert np.all(hb.parse_desc(step.device_desc.cpu().numpy())["ctrl"] == 0), "control words must be restored to zero"
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,die_items", [
+    (4, 4, 128, 121, 129, 300, 1000), (8, 2, 128, 213, 33, 100, 1016), (8, 2, 128, 209, 33, 100, 1024), (16, 4, 64, 105, 33, 100, 1024), (8, 2, 128, 216, 33, 100, 1032),
+    (8, 1, 64, 208, 33, 100, 1040)])
+def test_queue_per_die_that_ends_about_the_dealt_positions(hb, oracle, Hq, Hkv, D, n, lo, hi, die_items):
+    """The positions that belong to dies end before the 1024 dealt ones, with them, and one or two positions a die behind them: then the shared counter alone,
+    from the dealt positions or from die_items on, or a ticket of a die's own first."""
+    rng = np.random.default_rng(n)
+    q = rng.integers(lo, hi, n)
+    b = small_pool_batch(rng, Hq, Hkv, D, [PREFILL] * n, q, q, f"die-end-{die_items}")
+    step, bits = check_full(hb, oracle, b)
+    d = hb.parse_desc(step.host_desc.numpy())
+    assert d["queue"] is not None and d["header"].die_items == die_items and d["header"].n_items > 1032
     for _ in range(3):
         step.out.zero_()
         step.run()
