@@ -272,8 +272,10 @@ hfx_status hfx_append_kv(const hfx_shape* shape, const void* k_new, const void* 
  *   host_stage     [host]   >= 8*num_pairs bytes, written here and read by the upload: leave
  *                  it alone until the stream has passed this call (pinned memory keeps the
  *                  call asynchronous)
- *   device_stage   [device] >= 8*num_pairs bytes, 16-byte aligned; left as it is where the ids
- *                  of a short list go with the launch
+ *   device_stage   [device] >= 8*num_pairs bytes, 16-byte aligned; scratch of this call: the
+ *                  ids may go with the launch in its place (up to 496 of them do, where the
+ *                  staging buffer is pinned and the stream is not being captured), so what
+ *                  it holds afterwards is not defined
  *   stage_bytes    size of each staging buffer
  *
  * Asynchronous on `stream`; allocates no device memory.  num_pairs == 0 is a no-op.
