@@ -1065,11 +1065,13 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
   };
   auto block_base = [&](int entry) { return pool + (unsigned long)(unsigned)entry * (2 * Smem<D>::kBlockBytes); };
   auto slot_lds = [&](int stage_no) { return lds_ring + (stage_no & (RING - 1)) * Smem<D>::kStageBytes; };   // slots are handed out round-robin over the whole run
-  // copies the next n stages, all in a row
-  auto copy_stages = [&](int n) {
+  // the list from the next stage to be copied on, an entry a lane
+  auto list_read = [&]() { return list[(cs.count + lane) & (kListed - 1)]; };
+  // copies the next n stages, all in a row, by what list_read gave
+  auto copy_stages = [&](int n, int entries) {
 #pragma unroll 1
-    for (; n > 0; --n) {
-      block_copy<D>(block_base(uniform(list[cs.count & (kListed - 1)])), voff, slot_lds(cs.count));
+    for (int i = 0; i < n; ++i) {
+      block_copy<D>(block_base(__builtin_amdgcn_readlane(entries, i)), voff, slot_lds(cs.count));
       ++cs.count;
     }
   };
@@ -1118,8 +1120,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
 
   // Synchronisation point of the ring: what has been copied so far has landed and everyone's fragment reads
   // so far are done, so that copies may go on up to `limit`; returns how many that are.  The next ticket is asked
-  // for and published here, and the list goes on.
-  auto sync_point = [&](int limit) {
+  // for and published here, and the list goes on.  The entries are read ahead of the waits (one prompt of 777 tokens 15.1 us, read one by one behind them 15.2;
+  // 42 chunks of 4 rows behind 5321 on 64-wide 8/8 heads 87.0 and 88.9).
+  auto sync_point = [&](int limit, int& entries) {
+    entries = list_read();
     if (g_st == publish_st || g_st + 1 == publish_st) {
       int reply = 0;
       tickets_reserve(t, reply, ctrl);
@@ -1127,8 +1131,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     }
     HFX_WAIT_VMCNT(0);
     ring_barrier();
-    list_write();
-    list_until(limit);
+    if (cs.asked > 0 || cs.listed < limit) {
+      list_write();
+      list_until(limit);
+      entries = list_read();
+    }
     list_ask();
     cs.limit = limit;
     return min(limit, cs.listed) - cs.count;
@@ -1146,9 +1153,10 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     f32x16 s0, s1;
     Weighing wt;
     // the first stage: its scores, their maximum as the reference exponent, and the first half of its weights
-    const int due = sync_point(g_st + RING - 1 + key_wave);
+    int entries;
+    const int due = sync_point(g_st + RING - 1 + key_wave, entries);
     read_keys<D>(frag, smem + (g_st & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
-    copy_stages(due);
+    copy_stages(due, entries);
     s0 = first_scores<D>(w, frag);
     read_keys<D>(frag, smem + ((g_st + 1) & (RING - 1)) * Smem<D>::kStageBytes, k_lane);
     if (kt + SK - 1 > unmasked_upto) mask_stage(s0, kt);
@@ -1173,7 +1181,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
         pb[1] = wt.fragment(1);
         settle_weights<D>(w, cur, pb, wt.sum(), sl2);
       }
-      if (sync) copy_stages(sync_point(g_st + RING + 1 + key_wave));
+      if (sync) {
+        int ahead;
+        const int n_due = sync_point(g_st + RING + 1 + key_wave, ahead);
+        copy_stages(n_due, ahead);
+      }
       if (busy) {
         if (kt + 2 * SK - 1 > unmasked_upto) mask_stage(next, kt + SK);
         __builtin_amdgcn_sched_barrier(0);
@@ -1188,6 +1200,21 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       // burst in front of them they hold up the wavefront (a 4096-row chunk behind 61440 tokens 970 us, 950 so), and spread over
       // twice as many they land later, which chunks of few rows wait for (42 of 4 rows behind 5321 on 8/8 heads of 64 97.5 and 92.6,
       // 97 of one row behind 12208 on 24/8 heads 1294 and 1251; 90.7 and 1182 with one burst and the loop before).
+      // A wavefront without rows copies, in a loop of its own.  In chunks of few rows, where one wavefront of an item has all of them, the others' copies
+      // are what the item waits for: by way of the general form 30 chunks of 2 rows behind 2100 to 4100 on 64-wide 8/8 heads take 49.4 us and 48.0 so, 46 behind
+      // 1100 to 2200 36.8 and 35.1, 42 of 4 behind 5321 87.0 and 85.4; 16 of 2 behind 700 to 1250 on 8/8 heads of 128 19.5 and 20.0.
+      if (wave_end == 0 && end_st - g_st >= kPairsFrom && cs.asked == 0 && cs.count == g_st + RING - 1 + key_wave) {
+        int stages = min(cs.listed - cs.count - (cs.left > 0 ? 2 : 0), (publish_st > g_st ? min(publish_st - 1, end_st - 1) : end_st - 1) - g_st + 1) & ~1;
+        kt += max(stages, 0) * SK;
+#pragma unroll 1
+        for (; stages > 0; stages -= 2) {
+          const int entries = list_read();
+          HFX_WAIT_VMCNT(0);
+          ring_barrier();
+          copy_stages(2, entries);
+          g_st += 2;
+        }
+      }
       int pairs = 0;
       if (end_st - g_st >= kPairsFrom && wave_end > 0 && kt + 3 * SK - 1 <= unmasked_upto && cs.asked == 0 && cs.count == g_st + RING - 1 + key_wave)
         pairs = uniform(min(min((int)((unsigned)(unmasked_upto - kt - 3 * SK + 1) / (2 * SK)) + 1, (cs.listed - cs.count - (cs.left > 0 ? 2 : 0)) >> 1),
@@ -1275,7 +1302,7 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
     // the list went no further than the last item, or less far than its first stages: these are waited for
     if (cs.count < g_st + min(n_st, 2)) {
       list_until(cs.limit);
-      copy_stages(min(cs.limit, cs.listed) - cs.count);
+      copy_stages(min(cs.limit, cs.listed) - cs.count, list_read());
       HFX_WAIT_VMCNT(0);
     }
   }

@@ -229,6 +229,25 @@ def test_copy_stream_over_items_of_all_lengths(hb, oracle, Hkv, D):
     assert np.array_equal(step.out_bits(), bits)
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(1, 1, 64), (3, 1, 128), (2, 1, 64)])
+def test_wavefronts_without_rows_keep_up_the_copies(hb, oracle, Hq, Hkv, D):
+    """Chunks that leave one, two or three wavefronts of an item without rows, which then only copy: items of 1 to 130 stages behind each other, around the
+    six stages from which they run in a loop, the three before an item's end where tickets are asked for, and the 64 and 128 listed blocks; and items with rows for
+    all in between."""
+    rng = np.random.default_rng(31 * Hq + D)
+    stages = np.array([1, 2, 5, 6, 7, 8, 9, 10, 11, 12, 31, 62, 63, 64, 65, 66, 67, 68, 69, 70, 71, 126, 127, 128, 129, 130])
+    n = 1400 // (Hq if Hq == 3 else 1)
+    q = rng.choice([1, 3, 32, 33, 60, 65, 97, 128 // (2 if Hq == 2 else 1)], n)
+    c = rng.permutation(np.resize(stages, n)) * 32 - rng.integers(0, 28, n)
+    b = small_pool_batch(rng, Hq, Hkv, D, [PREFILL] * n, q, np.maximum(c, q), f"idle-{Hq}-{D}")
+    step, bits = check_full(hb, oracle, b)
+    items = hb.parse_desc(step.host_desc.numpy())["items"]
+    assert len(items) > 1024 and len(set(((items["ke"] - items["kb"] + 31) // 32).tolist()) & set(stages.tolist())) > 20
+    step.out.zero_()
+    step.run()
+    assert np.array_equal(step.out_bits(), bits)
+
+
 @pytest.mark.parametrize("decodes", [0, 3])
 @pytest.mark.parametrize("Hq,Hkv,D", [(24, 8, 128), (32, 4, 64), (8, 8, 128), (16, 1, 128)])
 def test_chunks_of_a_few_rows_in_pieces(hb, oracle, Hq, Hkv, D, decodes):
