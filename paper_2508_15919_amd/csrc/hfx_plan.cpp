@@ -614,16 +614,17 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
 // last prompts of the queue are the shortest ones, so that the dies end close to each other, and what is left is for all (kSharedTail).
 //
 // Measured on random steps, over one queue for all.  A workgroup's share at least 1.5 times the longest item: 50 steps of 80 streams
-// ((request, kv-head) pairs) or more 1.06 times as fast on average, the slowest 1.00; 14 of 40 to 79 streams 1.03 (0.99 to 1.07); 12 of fewer streams 1.00 (0.985
-// to 1.03: one prompt's tiles on all dies share their keys as it is).  A share of 0.75 to 1.5 of the longest item and at least 160 streams 1.02 (0.97 to
-// 1.07; 0.94 to 1.0 where decodes are more than a fifth of the step).  Chunks of a few rows whose head blocks share keys gain
-// most: 59 of 1 to 2 rows behind 2600 to 7700 on 24/8 heads 451 us and 285 (with the head blocks innermost; see make_items).
+// ((request, kv-head) pairs) or more 1.06 times as fast on average, the slowest 1.00; of 128-wide heads with 32 to 79 streams 1.018 (41 steps, 0.98 to 1.06); 12 of
+// fewer streams 1.00 (0.985 to 1.03: one prompt's tiles on all dies share their keys as it is).  64-wide heads have half the bytes a key and less to save:
+// 0.990 with 32 to 79 streams (26 steps, 0.96 to 1.02), 1.007 with 104 to 176 (5, 0.99 to 1.03), 1.017 with 200 to 400 (9, 1.00 to 1.04).
+// A share of 0.75 to 1.5 of the longest item and at least 160 streams 1.02 (0.97 to 1.07; 0.94 to 1.0 where decodes are more than a fifth of the
+// step).  Chunks of a few rows whose head blocks share keys gain most: 14 of them behind 1800 to 30000 on 24/8 and 12/4 heads 1.24 (1.08 to 1.32).
 //
 // Where the kv-heads are a multiple of 8, the dealt positions keep a stream on one die as it is, and the order has something to give only behind them.  167 such
 // steps, by items: a share of 1.5 and more from 1025 items on 0.996 times as fast (17 steps, 0.98 to 1.02), from 1408 on 1.024 (11, 0.99 to 1.06), 1536 1.02, 1664
 // 1.03; a smaller share from 1025 on 0.99, 1152 1.00, 1280 0.99, 1408 1.00 (60 in all, 0.93 to 1.05), from 1536 on 1.006 (15), 1664 1.013, 1792 and more 1.02
 // (40, 0.99 to 1.065).  With 1, 2 or 4 kv-heads all sizes gain: 1.03, 1.02, 1.00 and 1.03 from 1025, 1152, 1280 and 1408 items on (24 steps, 0.985 to 1.076).
-static const int64_t kDieStreams = 32, kDieStreamsShort = 160;
+static const int64_t kDieStreams = 32, kDieStreams64 = 80, kDieStreamsShort = 160;
 static const double kDieShare = 1.5, kDieShareShort = 0.75, kDieDecodes = 0.2;
 static const size_t kDieItems = HFX_PLAN_WGS * 11 / 4, kDieItemsShort = HFX_PLAN_WGS * 3;
 // A unit is at most this part of a die's share of the step: a longer one is cut into consecutive row tiles.  (2: 1.026 over the steps that 16 to 128 take 1.039 to
@@ -826,8 +827,8 @@ hfx_status plan_step(const hfx_shape* shape, int32_t R, const int32_t* kind, con
                          mult > Hkv && apart_ns >= kClassApart * beside_ns));
   const double all_ns = dec_ns + tiles_ns + kItemNs * (double)n, even_ns = (double)HFX_PLAN_WGS * max_cost;
   const size_t from = Hkv % HFX_QUEUE_CLASSES == 0 ? kDieItems : 0, from_short = Hkv % HFX_QUEUE_CLASSES == 0 ? kDieItemsShort : 0;
-  const bool per_die = !beside && !classes && pre_ns > 0.0 && units_fit && n > 2 * (size_t)HFX_PLAN_WGS && streams >= kDieStreams && readers >= 2 * streams &&
-                       ((all_ns >= kDieShare * even_ns && n >= from) ||
+  const bool per_die = !beside && !classes && pre_ns > 0.0 && units_fit && n > 2 * (size_t)HFX_PLAN_WGS && readers >= 2 * streams &&
+                       ((all_ns >= kDieShare * even_ns && n >= from && streams >= (D == 64 ? kDieStreams64 : kDieStreams)) ||
                         (all_ns >= kDieShareShort * even_ns && n >= from_short && dec_ns <= kDieDecodes * all_ns && streams >= kDieStreamsShort));
   P.queue.resize(per_die ? n : 0);
   // queue order: descending cost, ties in creation order: a stable radix sort (11-bit digits) of

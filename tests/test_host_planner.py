@@ -310,6 +310,15 @@ def test_queue_per_die_starts_where_there_is_something_behind_the_dealt_items(li
     check_coverage(b, d)
 
 
+@pytest.mark.parametrize("D,n,q,per_die", [(64, 8, 1536, False), (64, 19, 800, False), (64, 20, 800, True), (128, 8, 1536, True), (128, 19, 800, True)])
+def test_queue_per_die_of_64_wide_heads_needs_more_streams(lib, D, n, q, per_die):
+    """Prompts on 4 kv-heads: 32 streams are enough where heads are 128 wide, 80 are needed where they are 64 wide."""
+    b = lengths_only(16, 4, D, [PREFILL] * n, [q] * n, [q] * n)
+    d = fill(b)
+    assert d["header"].n_items > 1408 and (d["queue"] is not None) == per_die
+    check_coverage(b, d)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D,n,lo,hi,decodes,per_die", [
     (32, 8, 128, 64, 20, 700, 0, True), (32, 4, 64, 60, 100, 900, 20, True), (24, 8, 128, 20, 500, 3000, 0, True), (8, 8, 128, 120, 50, 600, 5, True),
     (8, 1, 128, 170, 20, 500, 0, True), (32, 8, 128, 4, 1500, 2500, 0, True), (32, 8, 128, 3, 2500, 2500, 0, False), (8, 1, 128, 25, 1000, 2000, 0, False),
