@@ -2,8 +2,8 @@
 // address of a C function and what kinds of arguments it takes, turns Python objects into pointers and numbers, calls it with
 // the interpreter lock released, and returns its status.
 //
-// Through ctypes a call of the attention took 2.3 us of marshalling (the launch itself takes 2.5), the description of a step of four
-// requests 3.8; here they take 0.7 and 1.0.  Objects that are not met in such loops go to the Python functions that took all before.
+// Through ctypes the marshalling of an attention call took 2.1 us (the launch itself takes 2.5), that of the description of a step of four
+// requests 3.1; here they take 0.54 and 0.71.  Objects that are not met in such loops go to the Python functions that took all before.
 #if !defined(__x86_64__) || defined(__ILP32__) || defined(_WIN32)
 #error "arguments are passed as 64-bit integers, by the System V convention of x86-64"
 #endif

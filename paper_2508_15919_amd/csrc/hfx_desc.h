@@ -43,7 +43,7 @@ struct HfxHeader {
   uint32_t off_units;
   int32_t n_runs;               /* append runs: the new tokens of the step, cut at page boundaries */
   uint32_t off_runs;
-  uint32_t queue_classes;       /* HFX_QUEUE_CLASSES where the items themselves lie die by die (see `home`), else 1 */
+  uint32_t queue_classes;       /* HFX_QUEUE_CLASSES where the items themselves lie die by die (see `home`), else 1; kernels go by die_items */
   uint32_t deal_balanced;       /* the two dealt rounds pair large items with small ones (see the kernel) instead of running straight */
   uint32_t off_queue;           /* 0: queue position p is item p; else n_items item indices, by position */
   uint32_t die_items;           /* of the queue positions, the first die_items belong to dies, p to die p % HFX_QUEUE_CLASSES, and those behind to all */

@@ -248,7 +248,7 @@ struct Tickets {
 // meet on another, and the second round gives the workgroups with the largest items one more.  Here the
 // first round runs up and then down the queue -- with fewer items than workgroups, the CUs that stay with
 // one workgroup get the largest -- and the second runs down, both within the positions that are equal
-// modulo the number of classes.  (2500 tokens on 32/8 heads 69 -> 59 us, 4096 tokens 152 -> 138 us; nothing on queues of
+// modulo the number of classes.  (2500 tokens on 32/8 heads 66 -> 57 us, 4096 tokens 134 -> 126 us; nothing on queues of
 // many items.)
 // `mode` is set by the launch: the grid is HFX_PLAN_WGS (1), or more than half of that, one item each (2).
 __device__ __forceinline__ void deal_balanced(Tickets& t, int mode, int n_items) {
@@ -590,9 +590,9 @@ __device__ void decode_run(const KArgs& a, const HfxHeader* H, const HfxItem* __
 // matrix instructions are 1024: 1573 for a wavefront that has its SIMD to itself, 1980 and 2510 for the older and the younger of two
 // in a 4096-row chunk behind 61440 tokens, so that the matrix cores are busy 2 * 1024 of 2243 clocks there, 91 %.  The loop is 0.91 of the
 // workgroups' time in that step and 0.82 to 0.87 where tiles are shorter.  With the whole softmax behind the score instructions and one loop for
-// all stages the clocks were 2350, 2450 and 3050.  Times then and now, both in turn on one card: 4 prompt chunks of 2048 rows behind up to 12288
+// all stages the clocks were 2350, 2450 and 3050.  Times of the two loops, both in turn on one card: 4 prompt chunks of 2048 rows behind up to 12288
 // earlier tokens beside 32 decodes (0.96 TFLOP) 879 and 841 us; a 4096-row chunk behind 61440 tokens and 16 decodes 1020 and 943; a single prompt of 777
-// tokens 18.2 and 15.7.
+// tokens 18.2 and 15.7.  (With listed copies and the counters on lines of their own 797 to 837, 938 to 970 and 14.8 to 15.4 by the card.)
 // A value fragment takes the registers of the key fragment used up before it, and the other way round.
 // Tried with it: the synchronisation point behind the second value instruction instead of in front of the first (-1.5 to +1.5 %); a ring
 // of eight stages where a workgroup has its CU to itself (slower: nobody waits for a copy with four).

@@ -24,22 +24,20 @@ static const int kMaxSplits = 64;
 static const int kDecodeItemsPerWg = 4;    // decode partials are small (rows of D + 2 floats per q-head)
 // Which prefill-dominated steps have their items laid out die by die (see the queue order in plan_step), by items per
 // workgroup of the planning width and by the time of the step.  What it buys is HBM traffic: 0.6 instead of 1.06 GB on the
-// prefill-heavy mixed step.  It costs no time any more: 17 steps of one to four prompts in two to six rounds, classes over one queue
-// 0.97 to 1.02, the prefill-heavy step 813 and 815 us.  (While the counters were on one line it cost 40 to 80 us a step, 1.03 to 1.45 times, and the lines
-// were drawn by that; nothing is gained by moving them.  Steps of many prompts are under queue_per_die.)  With far more keys than the
-// last-level cache (256 MB) holds, each read by two items or more, a queue per die was the better one even then,
-// as far as the items are long (kMinItemNs, by the (row, key) pairs they work on): 105 chunks of 64 rows behind 8500 to 34009 on 64-wide
-// 24/8 heads 0.90.
+// prefill-heavy mixed step, in the same time (822 us, one queue 826).  The lines were drawn when the counters shared a cache line, which cost such a step 40 to
+// 80 us.  With the present counters, over one queue for all and, second, over the order table that queue_per_die would make of the same steps: 14 steps of one to six
+// prompts of the first kind 0.999 (0.985 to 1.02) and 1.002; 14 of the second, more than 1 GB of keys (the last-level cache holds 256 MB), each read by two items
+// or more, in long items (kMinItemNs, by the (row, key) pairs they work on), 1.049 (1.005 to 1.3) and 0.998 (105 chunks of 64 rows behind 8500 to 34009 on 64-wide 24/8 heads
+// 1586 us, 1631 and 1587); 14 of the third kind, below, 1.236 and 1.000.  So the order table would do as well in all three.
 static const int kClassRoundsMin = 4;
 static const double kClassStepNs = 800000.0;
 static const double kClassStreamBytes = 1e9;
 // Steps of requests with one row tile of few rows behind long contexts are another matter.  Where several head
 // blocks read the same keys, each on a die of its own, the step lasts as long as the blocks take to stream them apart
 // (apart_ns), unless the tiles keep the matrix cores busy for about as long (beside_ns): 134 chunks of 2 rows behind 5734 to
-// 22937 tokens on 24/8 heads 2775 us without classes, 1973 with; 97 of one row behind 12208, 1625 and 1253.  The ratio is
+// 22937 tokens on 24/8 heads 2422 us from one queue, 1950 with classes and with an order table; 97 of one row behind 12208, 1489, 1221 and 1224.  The ratio is
 // 1.9 with one busy wavefront of four, 1.65 with two, 1.3 with four, where two head blocks still find each other's keys in
-// the cache.  The gain held from three rounds and about 2100 keys an item on (90 steps, with the counters on one line); below that, queue_per_die
-// takes over.
+// the cache.  Below three rounds and about 2100 keys an item queue_per_die takes over.
 static const int kClassRoundsMinApart = 3;
 static const double kClassApart = 1.5;
 static const double kClassItemNsApart = 70000.0;
@@ -210,15 +208,16 @@ static double last_end(const std::vector<float>& cost, int copies, float scale, 
 // In short steps the cap is chosen by what it leads to: largest first, items go to where there is the least
 // work, an item alone on its CU runs at 1.74 times its rate, and every cut adds partials (64 KB a piece,
 // written and read: 26 ns) and the merge launch (4 us).  Not cutting at all is the common answer: whole tiles
-// fill the CUs (1500 tokens on 32/8 heads: 33.5 us cut at half a share, 27.6 whole; 2500 tokens 76 and 55; 4096 tokens 147 and
-// 123; 1000 behind 3000 beside 16 decodes 92 and 77).  Cuts pay where there are fewer tiles than CUs (128 tokens behind
-// 8000: 92 us whole, 36 in 4 pieces, 30 in 8, 42 in 9; 8 chunks of one row behind 4000: 58 whole, 33 in 4) and where a few tiles
-// outlast the rest (300 behind 5000 and 200 behind 6000: 73 and 61).  The estimate dates from a slower loop, so that the line lies
-// a little early: 8 chunks of one row behind 1000 take 19.1 in 3 pieces and 17.4 whole (20.6 and 21.6 with that loop).
+// fill the CUs (1500 tokens on 32/8 heads: 33.6 us cut at half a share, 27.8 whole; 2500 tokens 77 and 57; 4096 tokens 149 and
+// 126; 1000 behind 3000 beside 16 decodes 95 and 79).  Cuts pay where there are fewer tiles than CUs (128 tokens behind
+// 8000: 94 us whole, 36 in 4 pieces, 30 in 8, 42 in 9; 8 chunks of one row behind 4000: 57 whole, 33 in 4) and where a few tiles
+// outlast the rest (300 behind 5000 and 200 behind 6000: 83 and 63).  The estimate dates from a slower loop, so that the line lies
+// a little early: 8 chunks of one row behind 1000 take 18.2 in 3 pieces and 16.8 whole (20.6 and 21.6 with that loop).
 // Tiles of few rows in layouts of few q-heads per kv-head leave wavefronts without rows.  Where all such tiles start at
 // once, whole, they slow their neighbours on the CU the less; and no cut makes a step shorter than its keys take to
-// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 470 us whole, 493 in
-// three pieces each; 23 behind 8015 on 12/4 heads: 166 and 178; 42 behind 5321 on 8/8 heads of 64 92 and 114 in four.
+// stream from memory (stream_ns, once per kv-head).  36 chunks of 4 rows behind 17273 on 8/8 heads: 468 us whole, 489 in
+// three pieces each; 42 behind 5321 on 8/8 heads of 64 90 and 112 in four.  (Several head blocks that share their keys on a die are no longer bound by that stream:
+// 23 behind 8015 on 12/4 heads, 166 and 178 when they did not, take 141 whole and 131 in three pieces, which the estimate does not see.)
 // Long steps are cut by half a share of the step and then into whole rounds: a step of few, about equally
 // expensive items per workgroup lasts a whole number of items, so a partly filled last round is closed by
 // raising the cap by up to a half.
@@ -346,7 +345,7 @@ static int64_t cut_rows(const int32_t* kind, const int32_t* q_len, const int32_t
 // where the work itself asks for it: as many rows as half a share of the step, counted in visible
 // (row, key) pairs, cuts the tiles into, in whole rounds.  (A 4096-token chunk behind 61440 on one kv-head: 72 MB,
 // two rounds of equal pieces.  40 chunks of 40 rows behind 19960 tokens beside four of 2048, with the prefill loop before its whole
-// pairs: 85 MB and 1349 us by time, 64 MB by pairs, 43 MB and 1264 us so bounded; 1192 us now, 1157 uncut.)
+// pairs: 85 MB and 1349 us by time, 64 MB by pairs, 43 MB and 1264 us so bounded; 1186 us now, 1163 uncut.)
 static double cap_within_workspace(const int32_t* kind, const int32_t* q_len, const int32_t* ctx_len, int R, int mult, int D,
                                    int hpw, int rows_wg, double dec_ns, double pre_ns, int64_t dec_rows, double cap) {
   auto by_pairs = [&](int64_t p, int64_t r0, int64_t r1) {
@@ -567,8 +566,9 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
         proto.rq = q;
         // All items of a row tile cost the same and stay in this order, in which dealt positions go round the dies: with the kv-heads innermost, the head blocks
         // that read one kv-head's keys come 8 positions apart, on one die, where there are 8 kv-heads.  (24/8 heads: 36 chunks of 7 rows behind 550 to
-        // 760 tokens 47.5 us with the head blocks innermost, 28.3 so; 39 of 2 rows behind 5000 to 9000 310 and 207; 20 steps of a few rows on 24/8, 32/4 and 8/1 heads
-        // 1.09 times as fast on average, 40 of prompts 1.01, none slower than the runs of one side differ.)
+        // 760 tokens 46.4 us with the head blocks innermost, 28.0 so; 39 of 2 rows behind 5000 to 9000 464 and 261.  40 random steps of a few rows and of prompts on layouts
+        // with several head blocks 1.09 times as fast on average, 40 of one to three prompts, some beside decodes, 1.009, 0.97 to 1.05; one chunk of 698 behind
+        // 2749 beside 20 decodes is slower, 56 us and 60.)
         for (int hb = 0; hb < G / hpw; ++hb)
           for (int g = 0; g < Hkv; ++g) {
             int group = -1;
@@ -630,8 +630,8 @@ static const size_t kDieItems = HFX_PLAN_WGS * 11 / 4, kDieItemsShort = HFX_PLAN
 // A unit is at most this part of a die's share of the step: a longer one is cut into consecutive row tiles.  (2: 1.026 over the steps that 16 to 128 take 1.039 to
 // 1.044 over.)
 static const int kDieUnits = 32;
-// The share of a step's cost at the end of the queue that is handed out to all dies.  (3, 6, 12 and 25 %: 1.024, 1.023, 1.015 and 1.018 over 21 steps of
-// short prompts; the prefill-heavy mixed step the same within 1 %.)
+// The share of a step's cost at the end of the queue that is handed out to all dies.  (3, 6, 12 and 25 %: 1.075, 1.064, 1.067 and 1.061 over 21 steps of
+// short prompts; 384 of them 294.0, 293.6, 295.4 and 297.4 us; the prefill-heavy mixed step the same within 1 %.)
 static const double kSharedTail = 0.06;
 
 // `sorted`: the n items in descending cost, as keys of plan_step's sort (max_cost minus cost, index); P.stream_ns: time of the items of each stream
