@@ -119,9 +119,9 @@ def _serving() -> types.SimpleNamespace:
         def caller(function, kinds):
             return _hfxcall.Caller(ctypes.cast(function, ctypes.c_void_p).value, kinds, hfx_shape, _ptr, _as_int32)
         _calls = types.SimpleNamespace(
-            build=caller(lib.hfx_build_batch_desc, "SKAAAABBs"), attention=caller(lib.hfx_mixed_paged_attention, "SPPPPBPs"),
+            build=caller(lib.hfx_build_batch_desc, "SKAAAaBBs"), attention=caller(lib.hfx_mixed_paged_attention, "SPPPPBPs"),
             attention_static=caller(lib.hfx_mixed_paged_attention_static, "SPPPPPs"), gather=caller(lib.hfx_gather_kv, "SPPPiPPs"),
-            append=caller(lib.hfx_append_kv, "SPPPPPs"), copy_pages=caller(lib.hfx_copy_pages, "SPPiKAPPzs"))
+            append=caller(lib.hfx_append_kv, "SPPPPPs"), copy_pages=caller(lib.hfx_copy_pages, "SPPikaPPzs"))
     return _calls
 
 

@@ -218,20 +218,26 @@ hfx_status hfx_copy_pages(const hfx_shape* shape, const void* src_pool, void* ds
   static thread_local std::vector<int32_t> ids;
   mark.assign((size_t)dst_num_pages, 0);
   ids.resize(2 * (size_t)num_pairs);
+  int32_t* const from = ids.data();
+  int32_t* const to = from + num_pairs;
+  uint8_t* const marked = mark.data();
+  const uint32_t n_src = (uint32_t)shape->num_pages, n_dst = (uint32_t)dst_num_pages;
   for (int i = 0; i < num_pairs; ++i) {
-    const int32_t from = src_ids[i], to = dst_ids[i];
-    if (from < 0 || from >= shape->num_pages || to < 0 || to >= dst_num_pages) return HFX_ERR_PAGE_ID;
-    if (mark[(size_t)to]) return HFX_ERR_PAGES;
-    mark[(size_t)to] = 1;
-    ids[2 * (size_t)i] = from;
-    ids[2 * (size_t)i + 1] = to;
+    const int32_t s = src_ids[i], d = dst_ids[i];
+    if ((uint32_t)s >= n_src || (uint32_t)d >= n_dst) return HFX_ERR_PAGE_ID;
+    if (marked[d]) return HFX_ERR_PAGES;
+    marked[d] = 1;
+    from[i] = s;
+    to[i] = d;
   }
   if (src_pool == dst_pool)
-    for (int i = 0; i < num_pairs; ++i) {
-      const int32_t from = ids[2 * (size_t)i];
-      if (from < dst_num_pages && mark[(size_t)from]) return HFX_ERR_PAGES;
-    }
-  std::memcpy(host_stage, ids.data(), 8 * (size_t)num_pairs);
+    for (int i = 0; i < num_pairs; ++i)
+      if (from[i] < dst_num_pages && marked[from[i]]) return HFX_ERR_PAGES;
+  int32_t* stage = static_cast<int32_t*>(host_stage);
+  for (int i = 0; i < num_pairs; ++i) {
+    stage[2 * i] = from[i];
+    stage[2 * i + 1] = to[i];
+  }
   const unsigned units_per_page = (unsigned)(shape->num_kv_heads * 2 * HFX_PAGE * shape->head_dim * 2 / 16);
   if (hfx::copy_pages(host_stage, device_stage, num_pairs, units_per_page, src_pool, dst_pool, static_cast<hipStream_t>(stream)) != hipSuccess)
     return HFX_ERR_DEVICE;

@@ -20,6 +20,7 @@ enum { MAX_ARGS = 16, MAX_HELD = 8 };
 //  B  pointer, and behind it the object's nbytes        K  array of 32-bit integers; its length goes ahead of it
 //  A  array of 32-bit integers                          i  32-bit integer
 //  z  size                                              s  stream: None, a handle, or an object with cuda_stream
+//  k, a  as K and A, but never copied: lists that the library reads once, or checks again as it uses them
 typedef struct {
   PyObject_HEAD
   vectorcallfunc vectorcall;
@@ -33,7 +34,7 @@ typedef struct {
 
 static PyObject *s_data_ptr, *s_nbytes, *s_cuda_stream;
 
-// What a call holds on to until it is done: of each argument of kind S, K or A one thing, and caller_init sees to it that there are no more than MAX_HELD.
+// What a call holds on to until it is done: of each argument of kind S, K, A, k or a one thing, and caller_init sees to it that there are no more than MAX_HELD.
 typedef struct {
   Py_buffer views[MAX_HELD];
   void* copies[MAX_HELD];
@@ -45,9 +46,9 @@ static void release(Held* held) {
   while (held->n_copies > 0) PyMem_Free(held->copies[--held->n_copies]);
 }
 
-// Arrays of fewer bytes are copied while the interpreter lock is held: the library checks them and reads them again, and another thread
-// may write to the caller's in between.  Larger ones are the caller's to leave alone during the call.  (The copies of the five arrays of a step of four
-// requests take 0.03 us of 0.71, those of 40 with 3500 pages, 15 KB, 0.17 of 0.85.)
+// Arrays of K and A of fewer bytes are copied while the interpreter lock is held: the library checks them and reads them again, and another thread
+// may write to the caller's in between.  Larger ones are the caller's to leave alone during the call.  (The copies of the lengths of a step of four
+// requests take 0.03 us of 0.71.  Two lists of 1514 page ids, copied, took 1.2 of the 21 us of a page copy: k and a.)
 enum { COPY_BELOW = 1 << 14 };
 
 static int integer(PyObject* o, uint64_t* out) {
@@ -102,7 +103,7 @@ static int plain_int32(PyObject* o, Py_buffer* view) {
   return 0;
 }
 
-static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* address, uint64_t* length, int want_length) {
+static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* address, uint64_t* length, int want_length, int copied) {
   Py_buffer* view = &held->views[held->n];
   if (plain_int32(o, view)) {
     *length = (uint64_t)view->shape[0];
@@ -122,7 +123,7 @@ static int int32_array(const Caller* self, PyObject* o, Held* held, uint64_t* ad
     if (bad) return -1;
     *length = (uint64_t)n;
   }
-  if (view->len < COPY_BELOW) {
+  if (copied && view->len < COPY_BELOW) {
     void* copy = PyMem_Malloc((size_t)view->len);
     if (copy && view->len > 0) memcpy(copy, view->buf, (size_t)view->len);
     PyBuffer_Release(view);
@@ -172,16 +173,18 @@ static PyObject* call(PyObject* callable, PyObject* const* args, size_t nargsf, 
         if (!bad && o != Py_None) bad = attribute(o, s_nbytes, &a[n]) != 0;
         ++n;
         break;
-      case 'K': {
+      case 'K':
+      case 'k': {
         uint64_t length = 0;
-        bad = int32_array(self, o, &held, &a[n + 1], &length, 1) != 0;
+        bad = int32_array(self, o, &held, &a[n + 1], &length, 1, self->kinds[i] == 'K') != 0;
         a[n] = length;
         n += 2;
         break;
       }
-      case 'A': {
+      case 'A':
+      case 'a': {
         uint64_t length = 0;
-        bad = int32_array(self, o, &held, &a[n++], &length, 0) != 0;
+        bad = int32_array(self, o, &held, &a[n++], &length, 0, self->kinds[i] == 'A') != 0;
         break;
       }
       case 'i':
@@ -216,13 +219,13 @@ static int caller_init(PyObject* o, PyObject* args, PyObject* kwargs) {
   if (!PyArg_ParseTuple(args, "KsO!OO", &address, &kinds, &PyType_Type, &structure, &address_of, &as_int32)) return -1;
   int n = 0, words = 0, held = 0;
   for (; kinds[n]; ++n) {
-    if (n == MAX_ARGS || !strchr("SPBKAizs", kinds[n])) break;
-    words += kinds[n] == 'B' || kinds[n] == 'K' ? 2 : 1;
-    held += strchr("SKA", kinds[n]) != NULL;
+    if (n == MAX_ARGS || !strchr("SPBKAkaizs", kinds[n])) break;
+    words += kinds[n] == 'B' || kinds[n] == 'K' || kinds[n] == 'k' ? 2 : 1;
+    held += strchr("SKAka", kinds[n]) != NULL;
     self->kinds[n] = kinds[n];
   }
   if (kinds[n] || words > 12 || held > MAX_HELD || address == 0) {
-    PyErr_SetString(PyExc_ValueError, "kinds of at most 12 arguments out of SPBKAizs, at most 8 of them SKA, and an address");
+    PyErr_SetString(PyExc_ValueError, "kinds of at most 12 arguments out of SPBKAkaizs, at most 8 of them SKAka, and an address");
     return -1;
   }
   self->n_kinds = n;

@@ -1098,7 +1098,15 @@ hfx_status fill_blob(const hfx_shape* shape, Plan& P, const int32_t* bt_indptr, 
   for (int r = 0; r < R; ++r) {
     const HfxReq& q = P.reqs[(size_t)r];
     int32_t* dst = bt + q.bt_start;
-    std::memcpy(dst, bt_pages + bt_indptr[r], 4ull * (size_t)q.n_pages);
+    // (looked at again on the way: the caller's list may have changed since)
+    const int32_t* src = bt_pages + bt_indptr[r];
+    bool outside = false;
+    for (int i = 0; i < q.n_pages; ++i) {
+      const int32_t page = src[i];
+      outside |= (uint32_t)page >= (uint32_t)shape->num_pages;
+      dst[i] = page;
+    }
+    if (outside) return HFX_ERR_PAGE_ID;
     for (int i = q.n_pages; i < q.bt_len; ++i) dst[i] = dst[q.n_pages - 1];
   }
   put(h.off_bt + 4ull * (uint64_t)P.n_bt, nullptr, 0, h.off_items);
@@ -1117,7 +1125,7 @@ hfx_status fill_blob(const hfx_shape* shape, Plan& P, const int32_t* bt_indptr, 
   HfxRun* run = (HfxRun*)(base + h.off_runs);
   for (int r = 0; r < R; ++r) {
     const HfxReq& q = P.reqs[(size_t)r];
-    const int32_t* pages = bt_pages + bt_indptr[r];
+    const int32_t* pages = bt + q.bt_start;
     int32_t t = q.ctx_len - q.q_len;
     while (t < q.ctx_len) {
       const int32_t slot0 = t % HFX_PAGE;

@@ -77,7 +77,7 @@ def test_number_of_arguments(fill):
     with pytest.raises(TypeError):
         fill(shape, KIND, Q, CTX, INDPTR, PAGES, blob=ref)
     from paper_2508_15919_amd import _hfxcall
-    for kinds, address in (("SX", 1), ("S", 0), ("B" * 7, 1), ("P" * 17, 1), ("S" * 9, 1), ("SSSKKKAAA", 1), ("A" * 12, 1)):
+    for kinds, address in (("SX", 1), ("S", 0), ("B" * 7, 1), ("P" * 17, 1), ("S" * 9, 1), ("SSSKKKAAA", 1), ("A" * 12, 1), ("a" * 9, 1), ("k" * 7, 1)):
         with pytest.raises(ValueError):
             _hfxcall.Caller(address, kinds, hb.hfx_shape, hb._ptr, hb._as_int32)
     with pytest.raises(TypeError):
@@ -106,6 +106,21 @@ def test_validation_of_the_public_calls():
     assert e.value.code == hb.HFX_ERR_BUFSIZE
     with pytest.raises(AttributeError):
         hb.hfx_append_kv(shape, 16, 16, 16, ref, 16, stream="none")
+
+
+def test_lists_that_are_read_once_are_passed_in_place():
+    from paper_2508_15919_amd import _hfxcall
+    base = np.arange(5, dtype=np.int32)
+    seen = []
+
+    @ctypes.CFUNCTYPE(ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p, ctypes.c_void_p)
+    def look(length, first, second):
+        seen.append((length, first, second))
+        return 0
+
+    call = _hfxcall.Caller(ctypes.cast(look, ctypes.c_void_p).value, "ka", hb.hfx_shape, hb._ptr, hb._as_int32)
+    call(base, base)
+    assert seen == [(5, base.ctypes.data, base.ctypes.data)]
 
 
 @pytest.mark.parametrize("one", [lambda i: i, np.int64, np.int32, lambda i: np.array(i, np.int32), lambda i: torch.tensor(i)])

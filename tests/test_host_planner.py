@@ -732,6 +732,26 @@ def test_a_header_with_impossible_die_positions_is_refused(lib):
         assert lib.hfx_mixed_paged_attention(ctypes.byref(shape), 16, 16, bent.ctypes.data, 16, 16, ws, 16, None) == hb.HFX_ERR_DESC, wrong
 
 
+def test_page_ids_that_change_meanwhile_are_refused(lib):
+    """The ids that go into the descriptor are the ones that have been checked.  Here the list lies where the descriptor's header is written, so that it
+    changes between the two."""
+    shape = hb.make_shape(4, 2, 64, 16)
+    size = hb.hfx_batch_desc_sizes(shape, [0], [1], [200])[0]
+    host = np.zeros(size, np.uint8)
+    pages = host[:52].view(np.int32)
+    pages[:] = np.arange(13)
+    with pytest.raises(hb.HfxError) as e:
+        lib_fill(lib, shape, [0], [1], [200], [0, 13], pages, host)
+    assert e.value.code == hb.HFX_ERR_PAGE_ID
+
+
+def lib_fill(lib, shape, kind, q_len, ctx_len, indptr, pages, host):
+    a = [np.array(v, np.int32) for v in (kind, q_len, ctx_len, indptr)]
+    rc = lib.hfx_fill_batch_desc(ctypes.byref(shape), 1, *(v.ctypes.data for v in a), pages.ctypes.data, host.ctypes.data, host.nbytes)
+    if rc != hb.HFX_OK:
+        raise hb.HfxError(rc, "hfx_fill_batch_desc")
+
+
 def test_extra_reserved_pages_are_ignored(lib):
     b = synth.make_batch(4, 2, 64, [DECODE, PREFILL], [1, 20], [37, 50], 3, extra_pages_per_request=3)
     d = fill(b)
