@@ -1200,10 +1200,11 @@ __device__ void prefill_run(const KArgs& a, const HfxHeader* H, const HfxItem* _
       // burst in front of them they hold up the wavefront (a 4096-row chunk behind 61440 tokens 970 us, 950 so), and spread over
       // twice as many they land later, which chunks of few rows wait for (42 of 4 rows behind 5321 on 8/8 heads of 64 97.5 and 92.6,
       // 97 of one row behind 12208 on 24/8 heads 1294 and 1251; 90.7 and 1182 with one burst and the loop before).
-      // A wavefront without rows copies, in a loop of its own.  In chunks of few rows, where one wavefront of an item has all of them, the others' copies
-      // are what the item waits for: by way of the general form 30 chunks of 2 rows behind 2100 to 4100 on 64-wide 8/8 heads take 49.4 us and 48.0 so, 46 behind
-      // 1100 to 2200 36.8 and 35.1, 42 of 4 behind 5321 87.0 and 85.4; 16 of 2 behind 700 to 1250 on 8/8 heads of 128 19.5 and 20.0.
-      if (wave_end == 0 && end_st - g_st >= kPairsFrom && cs.asked == 0 && cs.count == g_st + RING - 1 + key_wave) {
+      // Where heads are 64 wide, a wavefront without rows copies in a loop of its own.  In chunks of few rows, where one wavefront of an item has all of them, the
+      // others' copies are what the item waits for: by way of the general form 30 chunks of 2 rows behind 2100 to 4100 on 8/8 heads take 49.4 us and 48.0 so, 46 behind
+      // 1100 to 2200 36.8 and 35.0, 42 of 4 behind 5321 87.0 and 85.4; prompts are the same within 1 %.  (128 wide, with twice the work a stage: 16 of 2 rows
+      // behind 700 to 1250 19.6 and 20.0, others the same.)
+      if (D == 64 && wave_end == 0 && end_st - g_st >= kPairsFrom && cs.asked == 0 && cs.count == g_st + RING - 1 + key_wave) {
         int stages = min(cs.listed - cs.count - (cs.left > 0 ? 2 : 0), (publish_st > g_st ? min(publish_st - 1, end_st - 1) : end_st - 1) - g_st + 1) & ~1;
         kt += max(stages, 0) * SK;
 #pragma unroll 1
