@@ -620,10 +620,10 @@ static hfx_status make_items(const hfx_shape* shape, int32_t R, const DecodeCut&
 // A share of 0.75 to 1.5 of the longest item and at least 160 streams 1.02 (0.97 to 1.07; 0.94 to 1.0 where decodes are more than a fifth of the
 // step).  Chunks of a few rows whose head blocks share keys gain most: 14 of them behind 1800 to 30000 on 24/8 and 12/4 heads 1.24 (1.08 to 1.32).
 //
-// Where the kv-heads are a multiple of 8, the dealt positions keep a stream on one die as it is, and the order has something to give only behind them.  167 such
-// steps, by items: a share of 1.5 and more from 1025 items on 0.996 times as fast (17 steps, 0.98 to 1.02), from 1408 on 1.024 (11, 0.99 to 1.06), 1536 1.02, 1664
-// 1.03; a smaller share from 1025 on 0.99, 1152 1.00, 1280 0.99, 1408 1.00 (60 in all, 0.93 to 1.05), from 1536 on 1.006 (15), 1664 1.013, 1792 and more 1.02
-// (40, 0.99 to 1.065).  With 1, 2 or 4 kv-heads all sizes gain: 1.03, 1.02, 1.00 and 1.03 from 1025, 1152, 1280 and 1408 items on (24 steps, 0.985 to 1.076).
+// Where the kv-heads are a multiple of 8, the dealt positions keep a stream on one die as it is, and the order has something to give only behind them.  Random
+// steps, by items: a share of 1.5 and more from 1025 items on 0.995 times as fast (17 steps, 0.98 to 1.02), from 1408 on 1.024 (11, 0.99 to 1.06), 1536 1.02, 1664
+// 1.03; a smaller share from 1025 on 0.993 (49, 0.93 to 1.05), 1408 0.996 (11), 1536 1.007 (15), 1664 1.013, 1792 and more 1.02
+// (40, 0.99 to 1.065).  With 1, 2 or 4 kv-heads all sizes gain: 1.02 from 1025 items on (18, 0.985 to 1.076), 1.03 from 1408 on.
 static const int64_t kDieStreams = 32, kDieStreams64 = 80, kDieStreamsShort = 160;
 static const double kDieShare = 1.5, kDieShareShort = 0.75, kDieDecodes = 0.2;
 static const size_t kDieItems = HFX_PLAN_WGS * 11 / 4, kDieItemsShort = HFX_PLAN_WGS * 3;
