@@ -1106,7 +1106,10 @@ hfx_status fill_blob(const hfx_shape* shape, Plan& P, const int32_t* bt_indptr, 
       outside |= (uint32_t)page >= (uint32_t)shape->num_pages;
       dst[i] = page;
     }
-    if (outside) return HFX_ERR_PAGE_ID;
+    if (outside) {
+      std::memset(base, 0, sizeof h);       // half a descriptor is none
+      return HFX_ERR_PAGE_ID;
+    }
     for (int i = q.n_pages; i < q.bt_len; ++i) dst[i] = dst[q.n_pages - 1];
   }
   put(h.off_bt + 4ull * (uint64_t)P.n_bt, nullptr, 0, h.off_items);

@@ -743,6 +743,7 @@ def test_page_ids_that_change_meanwhile_are_refused(lib):
     with pytest.raises(hb.HfxError) as e:
         lib_fill(lib, shape, [0], [1], [200], [0, 13], pages, host)
     assert e.value.code == hb.HFX_ERR_PAGE_ID
+    assert lib.hfx_mixed_paged_attention(ctypes.byref(shape), 16, 16, host.ctypes.data, 16, 16, 1 << 30, 16, None) == hb.HFX_ERR_DESC
 
 
 def lib_fill(lib, shape, kind, q_len, ctx_len, indptr, pages, host):
